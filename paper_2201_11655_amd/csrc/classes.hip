@@ -207,7 +207,7 @@ const ClassTables& class_tables() {
     if (it != g_tables.end()) return *it->second;
     auto* t = new ClassTables();
     uint8_t* d = nullptr;
-    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 768 + 16 + 16));
+    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 768 + 16 + 32));
     build_one<3>(d, t->host3, t->codes3);
     build_one<4>(d + 64, t->host4, t->codes4);
     t->t3 = d;
@@ -221,18 +221,20 @@ const ClassTables& class_tables() {
                ((p03 & 1u) << 9) | ((p03 >> 1) << 2) | ((p12 & 1u) << 7) | ((p12 >> 1) << 4) |
                ((p13 & 1u) << 6) | ((p13 >> 1) << 1) | ((p23 & 1u) << 3) | (p23 >> 1);
     };
-    std::vector<int> tree_classes, stars, paths;
+    std::vector<int> tree_classes, stars, paths, cycles;
     for (unsigned a = 1; a <= 3; a++)
         for (unsigned b = 1; b <= 3; b++)
             for (unsigned c = 1; c <= 3; c++) {
                 paths.push_back(t->host4[idx4(a, 0, 0, b, 0, c)]);   // path v0 - v1 - v2 - v3
                 stars.push_back(t->host4[idx4(a, 0, 0, b, c, 0)]);   // star centred at v1
+                for (unsigned e = 1; e <= 3; e++) cycles.push_back(t->host4[idx4(a, b, 0, 0, c, e)]);   // 4-cycle
             }
-    for (auto* v : {&stars, &paths}) {
+    for (auto* v : {&stars, &paths, &cycles}) {
         std::sort(v->begin(), v->end());
         v->erase(std::unique(v->begin(), v->end()), v->end());
     }
-    VDMC_REQUIRE(stars.size() == 10 && paths.size() == 15, VDMC_ERR_DEVICE, "expected 10 star and 15 path classes");
+    VDMC_REQUIRE(stars.size() == 10 && paths.size() == 15 && cycles.size() == 15, VDMC_ERR_DEVICE,
+                 "expected 10 star, 15 path and 15 4-cycle classes");
     for (size_t i = 0; i < stars.size(); i++) {
         star_of[stars[i]] = (uint8_t)i;
         star_cls.push_back((uint8_t)stars[i]);
@@ -240,6 +242,10 @@ const ClassTables& class_tables() {
     for (size_t i = 0; i < paths.size(); i++) {
         path_of[paths[i]] = (uint8_t)i;
         path_cls.push_back((uint8_t)paths[i]);
+    }
+    for (size_t i = 0; i < cycles.size(); i++) {   // the 4-cycle classes follow the path slots
+        path_of[cycles[i]] = (uint8_t)(paths.size() + i);
+        path_cls.push_back((uint8_t)cycles[i]);
     }
     tree_classes = stars;
     tree_classes.insert(tree_classes.end(), paths.begin(), paths.end());
@@ -256,16 +262,16 @@ const ClassTables& class_tables() {
     VDMC_HIP(hipMemcpy(d + 64 + 4096 + 256, slotcls.data(), 64, hipMemcpyHostToDevice));
     t->slot4 = d + 64 + 4096;
     t->slotcls = d + 64 + 4096 + 256;
-    // class -> star slot | path slot | tree slot, then slot -> class for stars and paths
+    // class -> star slot | path or 4-cycle slot | tree slot, then slot -> class for both
     std::vector<uint8_t> maps(star_of);
     maps.insert(maps.end(), path_of.begin(), path_of.end());
     maps.insert(maps.end(), slot.begin(), slot.end());
     star_cls.resize(16, 0);
-    path_cls.resize(16, 0);
+    path_cls.resize(32, 0);
     uint8_t* dm = d + 64 + 4096 + 256 + 64;
     VDMC_HIP(hipMemcpy(dm, maps.data(), 768, hipMemcpyHostToDevice));
     VDMC_HIP(hipMemcpy(dm + 768, star_cls.data(), 16, hipMemcpyHostToDevice));
-    VDMC_HIP(hipMemcpy(dm + 784, path_cls.data(), 16, hipMemcpyHostToDevice));
+    VDMC_HIP(hipMemcpy(dm + 784, path_cls.data(), 32, hipMemcpyHostToDevice));
     t->maps4 = dm;
     t->star_cls = dm + 768;
     t->path_cls = dm + 784;

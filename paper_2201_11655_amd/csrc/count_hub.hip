@@ -46,7 +46,8 @@ constexpr uint32_t DMAX = kHubMaxDegree;   // largest |N+(r)| (and largest degre
 constexpr uint32_t CW = DMAX / 16;         // words of a 2-bit code row over the slots
 constexpr uint32_t SHASH = 4096;           // slot hash entries (u16 slot + 1), load <= 1/2
 constexpr uint32_t SHORT = 64;             // slots whose row above r has at most this many entries: one wave each
-constexpr uint32_t NSTAR = 10, NPATH = 15, NTREE = kCompact4;
+constexpr uint32_t NSTAR = 10, NPC = 30, NTREE = kCompact4;   // star, path + 4-cycle, tree classes
+constexpr unsigned long long INV3 = 0xAAAAAAAAAAAAAAABull;      // 3 * INV3 = 1 mod 2^64
 constexpr uint32_t CH_HASH = 128;          // per-wave child hash (short slots)
 
 struct HubArgs {
@@ -60,17 +61,17 @@ struct HubArgs {
     unsigned* cursor;            // [0] root cursor, [1] long-slot tasks, [2] long-slot cursor
     const uint8_t* t3;
     const uint8_t* t4;
-    const uint8_t* maps;         // [0,256) class -> star slot, [256,512) class -> path slot,
-                                 // [512,768) class -> tree slot (0xFF = none)
+    const uint8_t* maps;         // [0,256) class -> star slot, [256,512) class -> path or 4-cycle
+                                 // slot, [512,768) class -> tree slot (0xFF = none)
     const uint8_t* star_cls;     // star slot -> class
-    const uint8_t* path_cls;     // path slot -> class
+    const uint8_t* path_cls;     // path or 4-cycle slot -> class
     const uint8_t* tree_cls;     // tree slot -> class
     unsigned long long* out3;
     unsigned long long* out4;
     unsigned long long* stats;
     int k3, k4;
     uint32_t rank_lo, rank_hi;   // only roots with rank in [rank_lo, rank_hi)
-    uint32_t* scratch;           // per workgroup: locoff | locnbr | nodes (u64) | groups | keys | heads
+    uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | keys | cnt
     size_t wg_words;
     uint32_t s2cap, tcap;
     uint2* tasks;                // long-slot tasks: (hub index, the slot's entry in r's row)
@@ -97,6 +98,32 @@ __device__ __forceinline__ void by_class(uint32_t cls, bool active, F&& f) {
         const unsigned long long same = __ballot(active && cls == k0) & m;
         if (lane_id() == leader) f(k0, (uint32_t)__popcll(same));
         m &= ~same;
+    }
+}
+
+// sum over the wave, in every lane
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);   // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane(x, 63);
+}
+
+// f(cls, sum of val) once per distinct class among the lanes with `active` (the whole wave calls it)
+template <class F>
+__device__ __forceinline__ void by_class_sum(uint32_t cls, uint32_t val, bool active, F&& f) {
+    unsigned long long m = __ballot(active);
+    while (m) {
+        const uint32_t leader = (uint32_t)(__ffsll((long long)m) - 1);
+        const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)cls, (int)leader);
+        const bool mine = active && cls == k0;
+        const uint32_t sum = wave_sum(mine ? val : 0u);
+        if (lane_id() == leader) f(k0, sum);
+        m &= ~__ballot(mine);
     }
 }
 
@@ -133,7 +160,7 @@ __device__ __forceinline__ void slot_insert(uint16_t* H, uint32_t x, uint32_t i)
 __device__ __forceinline__ uint32_t wave_task(uint32_t* ctr) {
     uint32_t t = 0;
     if (lane_id() == 0) t = atomicAdd(ctr, 1u);
-    return (uint32_t)__shfl((int)t, 0, 64);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
 }
 
 __device__ __forceinline__ uint32_t first_above(const uint32_t* adj, uint32_t lo, uint32_t hi, uint32_t r) {
@@ -169,19 +196,22 @@ __device__ uint32_t block_scan(uint32_t* a, uint32_t len, uint32_t* part) {
 
 // ----------------------------------------------------------------------------- LDS
 
-constexpr uint32_t U_WORDS = 35072;   // the phase-dependent region (137 KiB)
+constexpr uint32_t U_WORDS = 34000;   // the phase-dependent region (133 KiB)
 
 struct HubLds {
     uint32_t P[DMAX];                  // slots: (rank << 2) | arc bits r -> slot
     uint16_t locn[DMAX];               // local neighbours per slot
+    uint16_t ch1[DMAX], ch2[DMAX];     // depth-2 entries per slot with arc code 1, 2
     unsigned long long root3[kClasses3];
     unsigned long long root4[kClasses4];
     uint8_t t4[4096];
     uint8_t t3[64];
     uint8_t maps[768];
     uint32_t ctr[8];
-    uint32_t U[U_WORDS];
+    uint32_t seg[2];                   // first slot with arc code 2, 3 to r
+    alignas(16) uint32_t U[U_WORDS];
 };
+static_assert(sizeof(HubLds) + 16 <= 163840, "one workgroup's LDS");
 
 // the per-wave 2-bit code row over the slots from slot x's local list
 __device__ __forceinline__ void build_row(uint32_t* row, const uint32_t* locnbr, uint32_t base, uint32_t cnt) {
@@ -209,11 +239,14 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     const uint8_t* tree_of = L.maps + 512;
     uint32_t* S = A.scratch + (size_t)blockIdx.x * A.wg_words;
     uint32_t* locoff = S;                                        // DMAX + 2
-    uint32_t* locnbr = locoff + DMAX + 2;                        // s2cap (+ 1 to keep nodes 8-byte aligned)
-    unsigned long long* nodes = (unsigned long long*)(locnbr + A.s2cap + (A.s2cap & 1u));   // s2cap
-    uint32_t* groups = (uint32_t*)(nodes + A.s2cap);             // s2cap
-    uint32_t* keys = groups + A.s2cap;                           // tcap
-    uint32_t* heads = keys + A.tcap;                             // tcap
+    // rows: slot x has the words [locoff[x], locoff[x + 1]): its local entries from the
+    // front, its depth-2 entries (hash slot << 2 | code) from the back
+    uint32_t* locnbr = locoff + DMAX + 2;                        // s2cap (+ 1)
+    uint32_t* parents = locnbr + A.s2cap + (A.s2cap & 1u);       // s2cap: A(c) of every depth-2 vertex
+    uint32_t* poff = parents + A.s2cap;                          // s2cap: first parent of the j-th
+    uint32_t* cids = poff + A.s2cap;                             // s2cap: its hash slot, then its rank
+    uint32_t* keys = cids + A.s2cap;                             // tcap: rank + 1 per hash slot
+    uint32_t* cnt = keys + A.tcap;                               // tcap: parents of the hash slot's vertex
     unsigned long long shp[kShapes] = {0, 0, 0, 0, 0, 0};
 
     // The heaviest hub roots (the first A.split_roots of the queue) are each taken by
@@ -255,6 +288,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 n2 += (uint32_t)__popcll(__ballot(k == 2u));
             }
             uint32_t o[4] = {0u, 0u, n1, n1 + n2};
+            if (lane < 2) L.seg[lane] = n1 + (lane ? n2 : 0u);
             for (uint32_t q0 = 0; q0 < D; q0 += 64) {
                 const bool in = q0 + lane < D;
                 const uint32_t e = in ? A.adj[s0 + q0 + lane] : 0u, k = e & 3u;
@@ -274,7 +308,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         if (A.k4)
             for (uint32_t i = tid; i < TS; i += HT) {
                 keys[i] = 0u;
-                heads[i] = 0u;
+                cnt[i] = 0u;
             }
         __syncthreads();
         for (uint32_t i = tid; i < D; i += HT) {
@@ -298,8 +332,9 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             const uint32_t vx = L.P[x] >> 2, rx = L.P[x] & 3u;
             const uint32_t hi = A.off[vx + 1];
             const uint32_t base = locoff[x];
-            const uint32_t lo = hi - (locoff[x + 1] - base);
-            uint32_t nloc = 0;
+            const uint32_t end = locoff[x + 1];
+            const uint32_t lo = hi - (end - base);
+            uint32_t nloc = 0, nch = 0, nc1 = 0, nc2 = 0;
             if (own && A.k4 && hi - lo > SHORT && lane == 0) {
                 const uint32_t t = atomicAdd(&A.cursor[1], 1u);
                 if (t < A.task_cap) A.tasks[t] = make_uint2(hi_idx, L.P[x]);
@@ -329,25 +364,53 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         shp[1]++;
                     }
                 }
-                if (A.k4 && d2) {   // depth-2 entry (x, e) into e's bucket
-                    uint32_t h = (e * 2654435761u) >> (32u - tbits);
-                    for (;; h = (h + 1u) & (TS - 1u)) {
-                        const uint32_t k = atomicCAS(&keys[h], 0u, e + 1u);
-                        if (k == 0u) {
-                            groups[atomicAdd(&L.ctr[1], 1u)] = h;
-                            break;
+                if (A.k4) {   // depth-2 entry (x, e): e into the hash, the entry behind x's row
+                    const unsigned long long md = __ballot(d2);
+                    if (d2) {
+                        uint32_t h = (e * 2654435761u) >> (32u - tbits);
+                        for (;; h = (h + 1u) & (TS - 1u)) {
+                            const uint32_t k = atomicCAS(&keys[h], 0u, e + 1u);
+                            if (k == 0u) {
+                                cids[atomicAdd(&L.ctr[1], 1u)] = h;
+                                break;
+                            }
+                            if (k == e + 1u) break;
                         }
-                        if (k == e + 1u) break;
+                        atomicAdd(&cnt[h], 1u);
+                        locnbr[end - 1u - nch - (uint32_t)__popcll(md & ((1ull << lane) - 1ull))] = (h << 2) | ec;
                     }
-                    const uint32_t node = atomicAdd(&L.ctr[2], 1u);
-                    const uint32_t old = atomicExch(&heads[h], node + 1u);
-                    nodes[node] = ((unsigned long long)old << 32) | (x << 2) | ec;
+                    nch += (uint32_t)__popcll(md);
+                    nc1 += (uint32_t)__popcll(__ballot(d2 && ec == 1u));
+                    nc2 += (uint32_t)__popcll(__ballot(d2 && ec == 2u));
                 }
             }
-            if (lane == 0) L.locn[x] = (uint16_t)nloc;
+            if (lane == 0) {
+                L.locn[x] = (uint16_t)nloc;
+                L.ch1[x] = (uint16_t)nc1;
+                L.ch2[x] = (uint16_t)nc2;
+            }
         }
         __syncthreads();
         const uint32_t ngroups = L.ctr[1];
+        if (A.k4) {   // the parents of every depth-2 vertex, gathered: A(c_j) = parents[poff[j] .. poff[j + 1])
+            for (uint32_t j = tid; j <= ngroups; j += HT) poff[j] = j < ngroups ? cnt[cids[j]] : 0u;
+            __syncthreads();
+            block_scan(poff, ngroups + 1u, part);
+            for (uint32_t j = tid; j < ngroups; j += HT) {
+                const uint32_t h = cids[j];
+                cnt[h] = poff[j];
+                cids[j] = keys[h] - 1u;
+            }
+            __syncthreads();
+            for (uint32_t x = wid; x < D; x += NW) {
+                const uint32_t end = locoff[x + 1], m = end - locoff[x] - L.locn[x];
+                for (uint32_t i = lane; i < m; i += 64) {
+                    const uint32_t ent = locnbr[end - 1u - i];
+                    parents[atomicAdd(&cnt[ent >> 2], 1u)] = (x << 2) | (ent & 3u);
+                }
+            }
+            __syncthreads();
+        }
         // ---- phase C3: k = 3 (1,1): pairs a < b of slots, lanes over b
         if (A.k3) {
             uint32_t* rows = R3 + DMAX * kClasses3;   // per wave: one code row
@@ -381,125 +444,446 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 if (L.root3[i]) gadd(A.out3, A.perm, kClasses3, r, i, L.root3[i]);
         }
         if (!A.k4) continue;
+        const uint32_t seg2 = __builtin_amdgcn_readfirstlane(L.seg[0]), seg3 = __builtin_amdgcn_readfirstlane(L.seg[1]);
         __syncthreads();
-        // ---- phase C4: (3,0,0): a < b < c, lanes over c
-        uint32_t* R4 = L.U;                     // D x 10 star counters
-        uint32_t* rows4 = L.U + DMAX * NSTAR;   // per wave: BA, BB
-        for (uint32_t i = tid; i < D * NSTAR; i += HT) R4[i] = 0u;
-        __syncthreads();
-        for (;;) {
-            const uint32_t a = wave_task(&L.ctr[4]) * G + share;
-            if (a + 2 >= D) break;
-            uint32_t* BA = rows4 + wid * 2 * CW;
-            uint32_t* BB = BA + CW;
-            build_row(BA, locnbr, locoff[a], L.locn[a]);
-            const uint32_t va = L.P[a] >> 2, ra = L.P[a] & 3u;
-            for (uint32_t b = a + 1; b + 1 < D; b++) {
-                build_row(BB, locnbr, locoff[b], L.locn[b]);
-                const uint32_t vb = L.P[b] >> 2, rb = L.P[b] & 3u, ab = code_at(BA, b);
-                for (uint32_t c0 = b + 1; c0 < D; c0 += 64) {
-                    const uint32_t c = c0 + lane;
-                    const bool in = c < D;
-                    uint32_t cls = 0xFFu;
-                    if (in) cls = L.t4[motif_index4(ra, rb, L.P[c] & 3u, ab, code_at(BA, c), code_at(BB, c))];
-                    by_class(cls, in, [&](uint32_t k, uint32_t n) {
-                        atomicAdd(&L.root4[k], (unsigned long long)n);
-                        const uint32_t s = star_of[k];
-                        if (s < NSTAR) {
-                            atomicAdd(&R4[a * NSTAR + s], n);
-                            atomicAdd(&R4[b * NSTAR + s], n);
-                        } else {
-                            gadd(A.out4, A.perm, kClasses4, va, k, n);
-                            gadd(A.out4, A.perm, kClasses4, vb, k, n);
+        auto seg_at = [&](uint32_t k) -> uint32_t { return k < 2u ? 0u : (k == 2u ? seg2 : (k == 3u ? seg3 : D)); };
+        // ---- phase C4: (3,0,0): three slots.  A lane owns the slot a it credits; the pairs
+        // {b < c} of other slots come from the 2-bit code rows of b, 32 c's a word: the
+        // number of c's of one arc code to r (a run of slots) with codes ac and bc is a
+        // popcount of the rows' planes, so a group of sets that share r, a, b and the index
+        // costs one lane a few instructions.  Pairs whose b is adjacent to a are counted as
+        // if it were not, then moved to their index, one lane per adjacent pair (a, b).
+        // Every set is counted from each of its three slots; r takes a third of the sums,
+        // exactly, mod 2^64 (also when the tasks are shared by several workgroups).
+        {
+            const uint32_t W = (D + 31u) >> 5;
+            const bool inl = D * (NSTAR + 2u * (W | 1u)) <= U_WORDS;   // star counters in LDS
+            uint32_t* R4 = L.U;                                        // D x 10 star counters
+            uint2* X = (uint2*)(L.U + (inl ? D * NSTAR : 0u));         // D rows of Wb words, both planes
+            const uint32_t smax = (U_WORDS - (inl ? D * NSTAR : 0u)) / (2u * D);
+            const uint32_t Wb = (W | 1u) <= smax ? W : ((smax & 1u) ? smax : smax - 1u);
+            const uint32_t S1 = Wb | 1u;                               // odd stride: no bank conflicts
+            const uint32_t CB = D <= 256u ? 8u : (D <= 512u ? 16u : 32u);   // b's per task
+            const uint32_t nag = (D + 63u) >> 6;
+            if (inl)
+                for (uint32_t i = tid; i < D * NSTAR; i += HT) R4[i] = 0u;
+            // n sets of slot a with index code `code`
+            auto add_a = [&](uint32_t a, uint32_t cls, uint32_t n) {
+                const uint32_t s = star_of[cls];
+                if (inl && s < NSTAR) atomicAdd(&R4[a * NSTAR + s], n);
+                else gadd(A.out4, A.perm, kClasses4, L.P[a] >> 2, cls, (unsigned long long)(long long)(int32_t)n);
+            };
+            auto add_r = [&](uint32_t cls, uint32_t n) {
+                atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n * INV3);
+            };
+            // s[i][j] (all, bit 0, bit 1, both) -> sets by the codes 0..3 of both pairs
+            auto exact = [](uint32_t (&s)[16]) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    s[0 + j] += s[12 + j] - s[4 + j] - s[8 + j];
+                    s[4 + j] -= s[12 + j];
+                    s[8 + j] -= s[12 + j];
+                }
+#pragma unroll
+                for (int i = 0; i < 16; i += 4) {
+                    s[i] += s[i + 3] - s[i + 1] - s[i + 2];
+                    s[i + 1] -= s[i + 3];
+                    s[i + 2] -= s[i + 3];
+                }
+            };
+            // slots of the word w whose arc code to r is k
+            auto seg_word = [&](uint32_t k, uint32_t w) {
+                const uint32_t lo = seg_at(k), hi = seg_at(k + 1), b0 = w << 5;
+                uint32_t m = ~0u;
+                if (lo > b0) m &= lo - b0 < 32u ? ~0u << (lo - b0) : 0u;
+                if (hi < b0 + 32u) m &= hi > b0 ? ~(~0u << (hi - b0)) : 0u;
+                return m;
+            };
+            for (uint32_t w0 = 0; w0 < W; w0 += Wb) {
+                const uint32_t wn = min(Wb, W - w0);
+                __syncthreads();
+                for (uint32_t i = tid; i < D * S1; i += HT) X[i] = make_uint2(0u, 0u);
+                if (tid < 2) L.ctr[4 + tid] = 0u;
+                __syncthreads();
+                for (uint32_t x = wid; x < D; x += NW) {
+                    const uint32_t base = locoff[x], nl = L.locn[x];
+                    for (uint32_t i = lane; i < nl; i += 64) {
+                        const uint32_t e = locnbr[base + i], w = (e >> 7) - w0, bit = 1u << ((e >> 2) & 31u);
+                        if (w < wn) {
+                            uint32_t* p = &X[x * S1 + w].x;
+                            if (e & 1u) atomicOr(p, bit);
+                            if (e & 2u) atomicOr(p + 1, bit);
                         }
-                    });
-                    if (in) {
-                        const uint32_t s = star_of[cls];
-                        if (s < NSTAR) atomicAdd(&R4[c * NSTAR + s], 1u);
-                        else gadd(A.out4, A.perm, kClasses4, L.P[c] >> 2, cls, 1ull);
-                        shp[2]++;
                     }
                 }
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < D * NSTAR; i += HT) {
-            const uint32_t x = R4[i];
-            if (x) gadd(A.out4, A.perm, kClasses4, L.P[i / NSTAR] >> 2, A.star_cls[i % NSTAR], x);
-        }
-        __syncthreads();
-        // ---- phase D: (2,1,0): group c, parent x in A(c), lanes over the second slot y
-        uint32_t* R5 = L.U;                       // D x 15 path counters
-        uint32_t* rows5 = L.U + DMAX * NPATH;     // per wave: BC (codes of A(c) to c), BX
-        uint32_t* chist = rows5 + NW * 2 * CW;    // per wave: 16 path counters of c
-        for (uint32_t i = tid; i < D * NPATH; i += HT) R5[i] = 0u;
-        if (lane < 16) chist[wid * 16 + lane] = 0u;
-        __syncthreads();
-        for (;;) {
-            const uint32_t gi = wave_task(&L.ctr[5]);
-            if (gi >= ngroups) break;
-            const uint32_t h = groups[gi];
-            const uint32_t c = keys[h] - 1u;
-            if (c % G != share) continue;
-            uint32_t* BC = rows5 + wid * 2 * CW;
-            uint32_t* BX = BC + CW;
-            uint32_t* ch = chist + wid * 16;
-            for (uint32_t i = lane; i < CW; i += 64) BC[i] = 0u;
-            __threadfence_block();
-            if (lane == 0)
-                for (uint32_t nd = heads[h]; nd != 0u;) {
-                    const unsigned long long v = nodes[nd - 1u];
-                    const uint32_t x = ((uint32_t)v >> 2) & 0xFFFu, xc = (uint32_t)v & 3u;
-                    BC[x >> 4] |= xc << ((x & 15u) << 1);
-                    nd = (uint32_t)(v >> 32);
-                }
-            __threadfence_block();
-            for (uint32_t nd = heads[h]; nd != 0u;) {   // every lane walks the parent list
-                const unsigned long long v = nodes[nd - 1u];
-                const uint32_t x = ((uint32_t)v >> 2) & 0xFFFu, xc = (uint32_t)v & 3u;
-                nd = (uint32_t)(v >> 32);
-                build_row(BX, locnbr, locoff[x], L.locn[x]);
-                const uint32_t vx = L.P[x] >> 2, rx = L.P[x] & 3u;
-                for (uint32_t y0 = 0; y0 < D; y0 += 64) {
-                    const uint32_t y = y0 + lane;
-                    uint32_t cls = 0xFFu;
-                    bool in = y < D && y != x;
-                    if (in) {
-                        const uint32_t yc = code_at(BC, y);
-                        in = !(yc && y < x);   // c hangs under its lower-rank parent
-                        if (in) cls = L.t4[motif_index4(rx, L.P[y] & 3u, 0u, code_at(BX, y), xc, yc)];
-                    }
-                    by_class(cls, in, [&](uint32_t k, uint32_t n) {
-                        atomicAdd(&L.root4[k], (unsigned long long)n);
-                        const uint32_t s = path_of[k];
-                        if (s < NPATH) {
-                            atomicAdd(&R5[x * NPATH + s], n);
-                            ch[s] += n;
-                        } else {
-                            gadd(A.out4, A.perm, kClasses4, vx, k, n);
-                            gadd(A.out4, A.perm, kClasses4, c, k, n);
+                __syncthreads();
+                const uint32_t ntask = nag * ((min(D, (w0 + wn) << 5) + CB - 1u) / CB);
+                for (;;) {   // lanes over a, b's in turn
+                    const uint32_t t = wave_task(&L.ctr[4]) * G + share;
+                    if (t >= ntask) break;
+                    const uint32_t ch = t / nag, ag = t - ch * nag;
+                    const uint32_t a = ag * 64u + lane;
+                    const bool alive = a < D;
+                    const uint32_t ra = alive ? L.P[a] & 3u : 0u;
+                    for (uint32_t rb = 1; rb < 4; rb++) {
+                        const uint32_t blo = max(ch * CB, seg_at(rb)), bhi = min(ch * CB + CB, seg_at(rb + 1));
+                        if (blo >= bhi) continue;
+                        for (uint32_t rc = rb; rc < 4; rc++) {
+                            const uint32_t clo = max(seg_at(rc), blo + 1u), chi = seg_at(rc + 1);
+                            if (clo >= chi) continue;
+                            const uint32_t wlo = max(clo >> 5, w0), whi = min(((chi - 1u) >> 5) + 1u, w0 + wn);
+                            uint32_t s[16] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+                            for (uint32_t w = wlo; w < whi; w++) {
+                                const uint32_t sm = seg_word(rc, w);
+                                const uint2 aw = alive ? X[a * S1 + w - w0] : make_uint2(0u, 0u);
+                                const uint32_t a0 = aw.x, a1 = aw.y, a01 = a0 & a1;
+                                const uint32_t ae = alive ? ((a >> 5) == w ? ~(1u << (a & 31u)) : ~0u) : 0u;
+                                for (uint32_t b = blo; b < bhi; b++) {
+                                    if ((b >> 5) > w) break;
+                                    const uint32_t v = (b >> 5) == w ? sm & ~((2u << (b & 31u)) - 1u) : sm;
+                                    const uint2 bw = X[b * S1 + w - w0];
+                                    const uint32_t b0 = __builtin_amdgcn_readfirstlane(bw.x) & v;
+                                    const uint32_t b1 = __builtin_amdgcn_readfirstlane(bw.y) & v;
+                                    if (a != b) {
+                                        s[0] += __popc(ae & v);
+                                        s[4] += __popc(a0 & v);
+                                        s[8] += __popc(a1 & v);
+                                        s[12] += __popc(a01 & v);
+                                        if (b0 | b1) {
+                                            const uint32_t b01 = b0 & b1;
+                                            s[1] += __popc(ae & b0);
+                                            s[5] += __popc(a0 & b0);
+                                            s[9] += __popc(a1 & b0);
+                                            s[13] += __popc(a01 & b0);
+                                            s[2] += __popc(ae & b1);
+                                            s[6] += __popc(a0 & b1);
+                                            s[10] += __popc(a1 & b1);
+                                            s[14] += __popc(a01 & b1);
+                                            if (b01) {
+                                                s[3] += __popc(ae & b01);
+                                                s[7] += __popc(a0 & b01);
+                                                s[11] += __popc(a1 & b01);
+                                                s[15] += __popc(a01 & b01);
+                                            }
+                                        }
+                                    }
+                                }
+                            }
+                            shp[2] += s[0];
+                            exact(s);
+#pragma unroll
+                            for (uint32_t q = 0; q < 16; q++) {
+                                const uint32_t n = s[q];
+                                if (!__ballot(n != 0u)) continue;
+                                const uint32_t cls = n ? L.t4[motif_index4(ra, rb, rc, 0u, q >> 2, q & 3u)] : 0xFFu;
+                                if (n) add_a(a, cls, n);
+                                by_class_sum(cls, n, n != 0u, add_r);
+                            }
                         }
-                    });
-                    if (in) {
-                        const uint32_t s = path_of[cls];
-                        if (s < NPATH) atomicAdd(&R5[y * NPATH + s], 1u);
-                        else gadd(A.out4, A.perm, kClasses4, L.P[y] >> 2, cls, 1ull);
-                        shp[3]++;
+                    }
+                }
+                for (;;) {   // adjacent pairs (a, b): a fixed, lanes over b
+                    const uint32_t a = wave_task(&L.ctr[5]) * G + share;
+                    if (a >= D) break;
+                    const uint32_t nl = L.locn[a];
+                    if (nl == 0u) continue;
+                    const uint32_t base = locoff[a], ra = L.P[a] & 3u;
+                    for (uint32_t i0 = 0; i0 < nl; i0 += 64) {
+                        const bool on = i0 + lane < nl;
+                        const uint32_t ent = on ? locnbr[base + i0 + lane] : 0u;
+                        const uint32_t b = ent >> 2, ab = ent & 3u, rb = L.P[b] & 3u;
+                        for (uint32_t rc = 1; rc < 4; rc++) {
+                            const uint32_t clo = seg_at(rc), chi = seg_at(rc + 1);
+                            if (clo >= chi) continue;
+                            const uint32_t wlo = max(clo >> 5, w0), whi = min(((chi - 1u) >> 5) + 1u, w0 + wn);
+                            uint32_t s[16] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+                            for (uint32_t w = wlo; w < whi; w++) {
+                                uint32_t v = seg_word(rc, w);
+                                if ((a >> 5) == w) v &= ~(1u << (a & 31u));
+                                if (!on || (b >> 5) > w) v = 0u;
+                                else if ((b >> 5) == w) v &= ~((2u << (b & 31u)) - 1u);
+                                const uint2 aw = X[a * S1 + w - w0], bw = X[b * S1 + w - w0];
+                                const uint32_t a0 = __builtin_amdgcn_readfirstlane(aw.x);
+                                const uint32_t a1 = __builtin_amdgcn_readfirstlane(aw.y);
+                                const uint32_t b0 = bw.x & v, b1 = bw.y & v, b01 = b0 & b1;
+                                s[0] += __popc(v);
+                                s[1] += __popc(b0);
+                                s[2] += __popc(b1);
+                                s[3] += __popc(b01);
+                                if (a0 | a1) {
+                                    const uint32_t a01 = a0 & a1;
+                                    s[4] += __popc(a0 & v);
+                                    s[5] += __popc(a0 & b0);
+                                    s[6] += __popc(a0 & b1);
+                                    s[7] += __popc(a0 & b01);
+                                    s[8] += __popc(a1 & v);
+                                    s[9] += __popc(a1 & b0);
+                                    s[10] += __popc(a1 & b1);
+                                    s[11] += __popc(a1 & b01);
+                                    s[12] += __popc(a01 & v);
+                                    s[13] += __popc(a01 & b0);
+                                    s[14] += __popc(a01 & b1);
+                                    s[15] += __popc(a01 & b01);
+                                }
+                            }
+                            exact(s);
+#pragma unroll
+                            for (uint32_t q = 0; q < 16; q++) {
+                                const uint32_t n = s[q];
+                                if (!__ballot(n != 0u)) continue;
+                                const uint32_t k0 = n ? L.t4[motif_index4(ra, rb, rc, 0u, q >> 2, q & 3u)] : 0xFFu;
+                                const uint32_t k1 = n ? L.t4[motif_index4(ra, rb, rc, ab, q >> 2, q & 3u)] : 0xFFu;
+                                by_class_sum(k0, n, n != 0u, [&](uint32_t k, uint32_t m) {
+                                    add_a(a, k, 0u - m);
+                                    add_r(k, 0u - m);
+                                });
+                                by_class_sum(k1, n, n != 0u, [&](uint32_t k, uint32_t m) {
+                                    add_a(a, k, m);
+                                    add_r(k, m);
+                                });
+                            }
+                        }
                     }
                 }
             }
-            __threadfence_block();
-            if (lane < NPATH) {
-                const uint32_t n = ch[lane];
-                if (n) gadd(A.out4, A.perm, kClasses4, c, A.path_cls[lane], n);
-                ch[lane] = 0u;
-            }
-            __threadfence_block();
+            __syncthreads();
+            if (inl)
+                for (uint32_t i = tid; i < D * NSTAR; i += HT) {
+                    const uint32_t x = R4[i];
+                    if (x)
+                        gadd(A.out4, A.perm, kClasses4, L.P[i / NSTAR] >> 2, A.star_cls[i % NSTAR],
+                             (unsigned long long)(long long)(int32_t)x);
+                }
         }
         __syncthreads();
-        for (uint32_t i = tid; i < D * NPATH; i += HT) {
-            const uint32_t x = R5[i];
-            if (x) gadd(A.out4, A.perm, kClasses4, L.P[i / NPATH] >> 2, A.path_cls[i % NPATH], x);
+        // ---- phase D: (2,1,0): a depth-2 vertex c, a parent x of c and a second slot y.  The
+        // sets of one (x, c) are grouped by y's codes to r and x: the group sizes are
+        // properties of x (NX), the number of x's children by code is ch1, ch2, ch3.  A
+        // second parent y of c is counted in its group, then taken out again, and the set of
+        // both parents (one set, whichever hangs first: Lemma 3) is added under its own index.
+        {
+            const uint32_t W1 = ((D + 31u) >> 5) | 1u;
+            constexpr uint32_t FIX = 16 + 200 * NW + CW * NW;
+            const bool inl = D * (NPC + 5u) + FIX <= U_WORDS;                  // path and cycle counters in LDS
+            const bool inx = D * (NPC + 5u + 2u * W1) + FIX <= U_WORDS;        // and the code rows of all slots
+            uint32_t* SX = L.U;                            // [9] children of the slots of a code, by code
+            int32_t* CHS = (int32_t*)(L.U + 16) + wid * 200;   // per wave: class counters of c (or work space)
+            uint32_t* BX = L.U + 16 + 200 * NW + wid * CW;     // per wave: one code row
+            uint16_t* NX = (uint16_t*)(L.U + FIX);         // per slot: slots by (code to r, code to x) [9], ch3
+            uint32_t* R5 = L.U + FIX + D * 5u;             // D x 30 path and 4-cycle counters
+            uint2* X = (uint2*)(L.U + ((FIX + D * (NPC + 5u) + 1u) & ~1u));
+            const uint8_t* pc_of = path_of;
+            if (inl)
+                for (uint32_t i = tid; i < D * NPC; i += HT) R5[i] = 0u;
+            if (inx)
+                for (uint32_t i = tid; i < D * W1; i += HT) X[i] = make_uint2(0u, 0u);
+            if (tid < 16) SX[tid] = 0u;
+            if (tid < 2) L.ctr[4 + tid] = 0u;
+            for (uint32_t i = lane; i < 200; i += 64) CHS[i] = 0;
+            __syncthreads();
+            for (uint32_t x = tid; x < D; x += HT) {
+                const uint32_t n1 = L.ch1[x], n2 = L.ch2[x], q = ((L.P[x] & 3u) - 1u) * 3u;
+                const uint32_t n3 = locoff[x + 1] - locoff[x] - L.locn[x] - n1 - n2;
+                NX[x * 10 + 9] = (uint16_t)n3;
+                if (n1) atomicAdd(&SX[q], n1);
+                if (n2) atomicAdd(&SX[q + 1], n2);
+                if (n3) atomicAdd(&SX[q + 2], n3);
+            }
+            __syncthreads();
+            auto children = [&](uint32_t x, uint32_t k) -> uint32_t {
+                return k == 1u ? L.ch1[x] : (k == 2u ? L.ch2[x] : NX[x * 10 + 9]);
+            };
+            auto seg_size = [&](uint32_t k) { return seg_at(k + 1) - seg_at(k); };
+            // n (mod 2^32, signed) sets of class cls to slot x
+            auto add_x = [&](uint32_t x, uint32_t cls, uint32_t n) {
+                const uint32_t s = pc_of[cls];
+                if (inl && s < NPC) atomicAdd(&R5[x * NPC + s], n);
+                else gadd(A.out4, A.perm, kClasses4, L.P[x] >> 2, cls, (unsigned long long)(long long)(int32_t)n);
+            };
+            auto add_r = [&](uint32_t cls, uint32_t n) {
+                atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n);
+            };
+            // per slot x: its group sizes; its sets as a parent, and as the second slot of others' sets
+            for (;;) {
+                const uint32_t x = wave_task(&L.ctr[4]);
+                if (x >= D) break;
+                const bool own = x % G == share;
+                const uint32_t rx = L.P[x] & 3u, base = locoff[x], nl = L.locn[x];
+                uint32_t c9[9] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u}, l9[9] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+                for (uint32_t i0 = 0; i0 < nl; i0 += 64) {
+                    const bool on = i0 + lane < nl;
+                    const uint32_t ent = on ? locnbr[base + i0 + lane] : 0u;
+                    const uint32_t y = ent >> 2, k = ent & 3u, ry = L.P[y] & 3u;
+#pragma unroll
+                    for (uint32_t q = 0; q < 9; q++)
+                        c9[q] += (uint32_t)__popcll(__ballot(on && ry == q / 3u + 1u && k == q % 3u + 1u));
+                    if (inx && on) {
+                        uint32_t* p = &X[x * W1 + (y >> 5)].x;
+                        const uint32_t bit = 1u << (y & 31u);
+                        if (k & 1u) atomicOr(p, bit);
+                        if (k & 2u) atomicOr(p + 1, bit);
+                    }
+                    if (own)   // x as the second slot below its local neighbour y
+                        for (uint32_t xc = 1; xc < 4; xc++) {
+                            const uint32_t n = on ? children(y, xc) : 0u;
+                            if (!__ballot(n != 0u)) continue;
+                            const uint32_t cls = n ? L.t4[motif_index4(ry, rx, 0u, swap_arc_bits(k), xc, 0u)] : 0xFFu;
+                            by_class_sum(cls, n, n != 0u, [&](uint32_t kk, uint32_t m) { add_x(x, kk, m); });
+#pragma unroll
+                            for (uint32_t p = 0; p < 3; p++) {
+                                const uint32_t m = wave_sum(ry == p + 1u ? n : 0u);
+                                if (xc == 1u) l9[p * 3] += m;
+                                else if (xc == 2u) l9[p * 3 + 1] += m;
+                                else l9[p * 3 + 2] += m;
+                            }
+                        }
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < 9; q++)
+                    if (lane == q) {
+                        NX[x * 10 + q] = (uint16_t)c9[q];
+                        CHS[q] = (int32_t)c9[q];
+                        CHS[9 + q] = (int32_t)l9[q];
+                    }
+                __threadfence_block();
+                if (own && lane < 45) {
+                    uint32_t v, cls;
+                    if (lane < 36) {   // parent x, children of code xc, second slots of codes p (to r), k (to x)
+                        const uint32_t p = lane / 12u, k = lane % 12u / 3u, xc = lane % 3u + 1u;
+                        const uint32_t g = k ? (uint32_t)CHS[p * 3 + k - 1]
+                                             : seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u) -
+                                                   (uint32_t)(CHS[p * 3] + CHS[p * 3 + 1] + CHS[p * 3 + 2]);
+                        v = g * children(x, xc);
+                        if (v) {
+                            cls = L.t4[motif_index4(rx, p + 1u, 0u, k, xc, 0u)];
+                            add_x(x, cls, v);
+                            add_r(cls, v);
+                        }
+                    } else {   // second slot x, parents of code p that are not adjacent to x, children of code xc
+                        const uint32_t p = (lane - 36u) / 3u, xc = (lane - 36u) % 3u + 1u;
+                        v = SX[p * 3 + xc - 1u] - (p + 1u == rx ? children(x, xc) : 0u) -
+                            (uint32_t)CHS[9 + p * 3 + xc - 1u];
+                        if (v) add_x(x, L.t4[motif_index4(p + 1u, rx, 0u, 0u, xc, 0u)], v);
+                    }
+                }
+                __threadfence_block();
+            }
+            __syncthreads();
+            for (uint32_t i = lane; i < 200; i += 64) CHS[i] = 0;
+            __threadfence_block();
+            // arc code of (slot x, slot y) seen from x
+            auto code_xy = [&](uint32_t x, uint32_t y) -> uint32_t {
+                const uint2 w = X[x * W1 + (y >> 5)];
+                return ((w.x >> (y & 31u)) & 1u) | (((w.y >> (y & 31u)) & 1u) << 1);
+            };
+            // per depth-2 vertex c: a lane takes it alone when it has few parents, else the wave
+            const uint32_t lane_max = inx ? 8u : 1u;
+            for (;;) {
+                const uint32_t j = wave_task(&L.ctr[5]) * 64u + lane;
+                if (j - lane >= ngroups) break;
+                const bool on = j < ngroups;
+                const uint32_t c = on ? cids[j] : 0u;
+                const bool own = on && c % G == share;
+                const uint32_t p0 = own ? poff[j] : 0u, na = own ? poff[j + 1] - p0 : 0u;
+                shp[3] += (unsigned long long)na * (D - 1u) - (unsigned long long)na * (na - 1u) / 2u;
+                if (na > 0u && na <= lane_max) {
+                    unsigned long long* row = &A.out4[(size_t)A.perm[c] * kClasses4];
+                    for (uint32_t i = 0; i < na; i++) {
+                        const uint32_t ent = parents[p0 + i], x = ent >> 2, xc = ent & 3u, rx = L.P[x] & 3u;
+                        uint32_t g[12];
+#pragma unroll
+                        for (uint32_t p = 0; p < 3; p++) {
+                            const uint32_t n1 = NX[x * 10 + p * 3], n2 = NX[x * 10 + p * 3 + 1],
+                                           n3 = NX[x * 10 + p * 3 + 2];
+                            g[p * 4] = seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u) - n1 - n2 - n3;
+                            g[p * 4 + 1] = n1;
+                            g[p * 4 + 2] = n2;
+                            g[p * 4 + 3] = n3;
+                        }
+                        for (uint32_t i2 = 0; i2 < na; i2++) {
+                            if (i2 == i) continue;
+                            const uint32_t e2 = parents[p0 + i2], y = e2 >> 2, yc = e2 & 3u, ry = L.P[y] & 3u;
+                            const uint32_t xy = code_xy(x, y), at = (ry - 1u) * 4u + xy;
+#pragma unroll
+                            for (uint32_t q = 0; q < 12; q++) g[q] -= q == at ? 1u : 0u;
+                            const uint32_t k0 = L.t4[motif_index4(rx, ry, 0u, xy, xc, 0u)];
+                            add_x(x, k0, ~0u);
+                            add_x(y, k0, ~0u);
+                            add_r(k0, ~0u);
+                            if (i2 > i) {
+                                const uint32_t k1 = L.t4[motif_index4(rx, ry, 0u, xy, xc, yc)];
+                                add_x(x, k1, 1u);
+                                add_x(y, k1, 1u);
+                                add_r(k1, 1u);
+                                atomicAdd(&row[k1], 1ull);
+                            }
+                        }
+#pragma unroll
+                        for (uint32_t q = 0; q < 12; q++)
+                            if (g[q])
+                                atomicAdd(&row[L.t4[motif_index4(rx, q / 4u + 1u, 0u, q % 4u, xc, 0u)]],
+                                          (unsigned long long)g[q]);
+                    }
+                }
+                for (unsigned long long m = __ballot(na > lane_max); m; m &= m - 1ull) {
+                    const int src = __ffsll((long long)m) - 1;
+                    const uint32_t wc = (uint32_t)__builtin_amdgcn_readlane((int)c, src);
+                    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)p0, src);
+                    const uint32_t wna = (uint32_t)__builtin_amdgcn_readlane((int)na, src);
+                    for (uint32_t i = lane; i < wna; i += 64) {   // every parent's groups
+                        const uint32_t ent = parents[w0 + i], x = ent >> 2, xc = ent & 3u, rx = L.P[x] & 3u;
+                        for (uint32_t p = 0; p < 3; p++) {
+                            uint32_t rest = seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u);
+                            for (uint32_t k = 1; k < 4; k++) {
+                                const uint32_t n = NX[x * 10 + p * 3 + k - 1u];
+                                rest -= n;
+                                if (n) atomicAdd(&CHS[L.t4[motif_index4(rx, p + 1u, 0u, k, xc, 0u)]], (int32_t)n);
+                            }
+                            if (rest) atomicAdd(&CHS[L.t4[motif_index4(rx, p + 1u, 0u, 0u, xc, 0u)]], (int32_t)rest);
+                        }
+                    }
+                    for (uint32_t i = 0; i < wna; i++) {   // pairs of parents: y in turn, lanes over x
+                        const uint32_t e2 = parents[w0 + i], y = e2 >> 2, yc = e2 & 3u, ry = L.P[y] & 3u;
+                        const uint32_t nl = L.locn[y];
+                        if (nl) build_row(BX, locnbr, locoff[y], nl);
+                        for (uint32_t i0 = 0; i0 < wna; i0 += 64) {
+                            const uint32_t i1 = i0 + lane;
+                            const bool in = i1 < wna && i1 != i, both = in && i1 > i;
+                            const uint32_t ent = in ? parents[w0 + i1] : 0u, x = ent >> 2, xc = ent & 3u;
+                            const uint32_t rx = L.P[x] & 3u, xy = nl ? swap_arc_bits(code_at(BX, x)) : 0u;
+                            const uint32_t k0 = in ? L.t4[motif_index4(rx, ry, 0u, xy, xc, 0u)] : 0xFFu;
+                            by_class(k0, in, [&](uint32_t k, uint32_t n) {
+                                atomicAdd(&CHS[k], -(int32_t)n);
+                                add_x(y, k, 0u - n);
+                                add_r(k, 0u - n);
+                            });
+                            if (in) add_x(x, k0, ~0u);
+                            const uint32_t k1 = both ? L.t4[motif_index4(rx, ry, 0u, xy, xc, yc)] : 0xFFu;
+                            by_class(k1, both, [&](uint32_t k, uint32_t n) {
+                                atomicAdd(&CHS[k], (int32_t)n);
+                                add_x(y, k, n);
+                                add_r(k, n);
+                            });
+                            if (both) add_x(x, k1, 1u);
+                        }
+                    }
+                    __threadfence_block();
+                    for (uint32_t k = lane; k < kClasses4; k += 64) {
+                        const int32_t n = CHS[k];
+                        if (n) gadd(A.out4, A.perm, kClasses4, wc, k, (unsigned long long)(long long)n);
+                        CHS[k] = 0;
+                    }
+                    __threadfence_block();
+                }
+            }
+            __syncthreads();
+            if (inl)
+                for (uint32_t i = tid; i < D * NPC; i += HT) {
+                    const uint32_t x = R5[i];
+                    if (x)
+                        gadd(A.out4, A.perm, kClasses4, L.P[i / NPC] >> 2, A.path_cls[i % NPC],
+                             (unsigned long long)(long long)(int32_t)x);
+                }
         }
         __syncthreads();
         // ---- phase F: (1,2,0) and (1,1,1) below the slots with short rows, one wave each
@@ -623,6 +1007,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     }
     for (int s = 0; s < kShapes; s++) {
         unsigned long long x = shp[s];
+        if (s == 2) x *= INV3;   // (3,0,0) sets were seen from each of their three slots
         for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
         if (lane == 0 && x) atomicAdd(&A.stats[s], x);
     }

@@ -93,9 +93,9 @@ struct ClassTables {
     const uint8_t* t4;   // 4096 entries
     const uint8_t* slot4;     // 199 entries: class -> compact slot or 0xFF
     const uint8_t* slotcls;   // kCompact4 entries: compact slot -> class
-    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path slot (15), tree slot (25); 0xFF none
+    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), tree slot (25); 0xFF none
     const uint8_t* star_cls;  // 10 entries: star slot -> class
-    const uint8_t* path_cls;  // 15 entries: path slot -> class
+    const uint8_t* path_cls;  // 30 entries: path or 4-cycle slot -> class
     std::vector<uint8_t> host3, host4;
     std::vector<uint16_t> codes3, codes4;
 };
