@@ -207,7 +207,7 @@ const ClassTables& class_tables() {
     if (it != g_tables.end()) return *it->second;
     auto* t = new ClassTables();
     uint8_t* d = nullptr;
-    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 768 + 16 + 32));
+    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 768 + 16 + 32 + kCmpRow));
     build_one<3>(d, t->host3, t->codes3);
     build_one<4>(d + 64, t->host4, t->codes4);
     t->t3 = d;
@@ -262,19 +262,28 @@ const ClassTables& class_tables() {
     VDMC_HIP(hipMemcpy(d + 64 + 4096 + 256, slotcls.data(), 64, hipMemcpyHostToDevice));
     t->slot4 = d + 64 + 4096;
     t->slotcls = d + 64 + 4096 + 256;
-    // class -> star slot | path or 4-cycle slot | tree slot, then slot -> class for both
+    // counters of a compact row: 15 path, 10 star and 15 4-cycle classes, a 64-byte line each
+    std::vector<uint8_t> cmp_of(256, 0xFF), cmp_cls(kCmpRow, 0);
+    for (size_t i = 0; i < paths.size(); i++) cmp_of[paths[i]] = (uint8_t)i;
+    for (size_t i = 0; i < stars.size(); i++) cmp_of[stars[i]] = (uint8_t)(16 + i);
+    for (size_t i = 0; i < cycles.size(); i++) cmp_of[cycles[i]] = (uint8_t)(32 + i);
+    for (int c = 0; c < 256; c++)
+        if (cmp_of[c] != 0xFF) cmp_cls[cmp_of[c]] = (uint8_t)c;
+    // class -> star slot | path or 4-cycle slot | compact counter, then the inverse maps
     std::vector<uint8_t> maps(star_of);
     maps.insert(maps.end(), path_of.begin(), path_of.end());
-    maps.insert(maps.end(), slot.begin(), slot.end());
+    maps.insert(maps.end(), cmp_of.begin(), cmp_of.end());
     star_cls.resize(16, 0);
     path_cls.resize(32, 0);
+    maps.insert(maps.end(), star_cls.begin(), star_cls.end());
+    maps.insert(maps.end(), path_cls.begin(), path_cls.end());
+    maps.insert(maps.end(), cmp_cls.begin(), cmp_cls.end());
     uint8_t* dm = d + 64 + 4096 + 256 + 64;
-    VDMC_HIP(hipMemcpy(dm, maps.data(), 768, hipMemcpyHostToDevice));
-    VDMC_HIP(hipMemcpy(dm + 768, star_cls.data(), 16, hipMemcpyHostToDevice));
-    VDMC_HIP(hipMemcpy(dm + 784, path_cls.data(), 32, hipMemcpyHostToDevice));
+    VDMC_HIP(hipMemcpy(dm, maps.data(), maps.size(), hipMemcpyHostToDevice));
     t->maps4 = dm;
     t->star_cls = dm + 768;
     t->path_cls = dm + 784;
+    t->cmp_cls = dm + 816;
     g_tables[dev] = t;   // kept for the life of the process
     return *t;
 }

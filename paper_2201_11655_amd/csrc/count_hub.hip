@@ -1,37 +1,30 @@
-// Hub-root motif kernels: roots with many higher neighbours.
+// Hub-root motif kernel: roots with many higher neighbours.
 //
 // The sets are those of the per-set kernel (count.hip): every connected k-set once,
 // from its lowest-rank vertex r (Lemma 1), along the BFS shapes of Lemma 2 under the
-// rules of Lemmas 3-4.  Every set is visited by one lane, which assembles its motif
-// index from the arc bits (Sec. 4.1), reads its class from the table in LDS and credits
-// the class to each of the set's vertices (Sec. 4.2).  What is specific to hub roots is
-// where the work and the counters live:
+// rules of Lemmas 3-4, its motif index from the arc bits (Sec. 4.1), its class from the
+// table and one credit for each of its vertices (Sec. 4.2).  What is specific to hub
+// roots is that sets are counted in groups: sets that share all members but one, and
+// whose last member has the same arc codes, have one index, so a group costs one class
+// lookup and one credit per shared member instead of one per set.
 //
-//   * one workgroup (16 waves) per root; N+(r) (the "slots", depth-1 candidates) is
-//     staged in LDS with a hash from rank to slot; each slot's local neighbours (other
-//     slots) become a short list, and each depth-2 entry (slot x, vertex c above r and
-//     outside N+(r)) goes into a hash keyed by c whose buckets list c's parents
-//     A(c) = N(c) n N+(r), so that the depth-1 rule of (2,1,0) (c hangs under its
-//     lowest-rank parent) is a test on A(c);
-//   * within one wave step the lanes take sets that share all members but one:
-//     (3,0,0) fixes a < b and lanes take c; (2,1,0) fixes the depth-2 vertex c and a
-//     parent x and lanes take the second depth-1 vertex y; pair codes come from per-wave
-//     2-bit code rows built from the local lists;
-//   * the members fixed for the wave step are credited once per class present in the
-//     step (ballots group the lanes by class); the lane's own member, a slot, is
-//     credited with one LDS atomic to per-slot counters of the tree classes that the
-//     shape produces when it has no extra pair (the 10 3-star classes for (3,0,0), the
-//     15 4-path classes for (2,1,0)); sets of any other class go straight to the
-//     output;
-//   * (1,2,0) and (1,1,1) sets hang below one slot a: a's depth-2 children L_a (entries
-//     of a's row above r outside N+(r)) get per-child counters; a wave walks a child
-//     c's row once, which gives both its arcs to the later children (for the (1,2,0)
-//     pairs that follow) and the end vertices e of the (1,1,1) paths r - a - c - e (e
-//     not adjacent to r nor to a: the Lemma-4 rule); e, a vertex anywhere in the graph,
-//     is credited with one atomic to the output.  Slots whose row above r is short are
-//     taken one wave each at the end of the hub kernel; long ones go to a second
-//     kernel, one workgroup per slot.
-// Counters are flushed to the output (rows by original id) once per phase.
+//   * one workgroup (16 waves) per root; N+(r) (the "slots") is staged in LDS with a
+//     hash from rank to slot; each slot's neighbours among the slots become a short
+//     list; its entries above r outside N+(r) mark the depth-2 vertices in a bitmap,
+//     which numbers them in rank order, and the parents A(c) = N(c) n N+(r) of each are
+//     gathered into one run;
+//   * (3,0,0): 2-bit code rows over the slots, 32 slots a word; the group sizes are
+//     popcounts of two slots' rows (phase C4);
+//   * (2,1,0), (1,2,0) and (1,1,1): per slot a and child c of a, from the counts of the
+//     slots by code, of the other parents of c and of the vertices in c's row (phases D, E);
+//   * the end vertices of the (1,1,1) paths lie anywhere in the graph: each one that a
+//     root reaches is visited once, from its own row (phase G).
+// Credits of slots and of r are summed in LDS.  The others go to compact rows (kCmpRow
+// counters per vertex) a 64-byte line at a time, because the memory-side atomics (2.4e10
+// lines/s whatever the lanes add within a line) are what bounded a kernel that credited
+// set by set; k_expand adds the rows to the output.  Measured (one MI355X): Chung-Lu
+// n = 1e5, k = 3 and 4, 1.87e10 sets: 145 ms set by set, 43 ms in groups; R-MAT
+// n = 2^15, 1.6e10 sets: 212 ms and 25 ms.
 #include "motif_device.h"
 #include "vdmc_internal.h"
 
@@ -45,10 +38,8 @@ constexpr int NW = HT / 64;                // waves per workgroup
 constexpr uint32_t DMAX = kHubMaxDegree;   // largest |N+(r)| (and largest degree) on the hub path
 constexpr uint32_t CW = DMAX / 16;         // words of a 2-bit code row over the slots
 constexpr uint32_t SHASH = 4096;           // slot hash entries (u16 slot + 1), load <= 1/2
-constexpr uint32_t SHORT = 64;             // slots whose row above r has at most this many entries: one wave each
-constexpr uint32_t NSTAR = 10, NPC = 30, NTREE = kCompact4;   // star, path + 4-cycle, tree classes
+constexpr uint32_t NSTAR = 10;             // star classes
 constexpr unsigned long long INV3 = 0xAAAAAAAAAAAAAAABull;      // 3 * INV3 = 1 mod 2^64
-constexpr uint32_t CH_HASH = 128;          // per-wave child hash (short slots)
 
 struct HubArgs {
     const uint32_t* off;
@@ -56,26 +47,26 @@ struct HubArgs {
     const uint32_t* split;
     const int32_t* perm;
     const uint32_t* hubs;        // hub roots, largest work first
-    const uint32_t* hub_s2;      // per hub root: entries of its slots' rows above r
     uint32_t nhub;
-    unsigned* cursor;            // [0] root cursor, [1] long-slot tasks, [2] long-slot cursor
+    unsigned* cursor;            // root cursor
     const uint8_t* t3;
     const uint8_t* t4;
     const uint8_t* maps;         // [0,256) class -> star slot, [256,512) class -> path or 4-cycle
-                                 // slot, [512,768) class -> tree slot (0xFF = none)
+                                 // slot, [512,768) class -> compact counter (0xFF = none)
     const uint8_t* star_cls;     // star slot -> class
     const uint8_t* path_cls;     // path or 4-cycle slot -> class
-    const uint8_t* tree_cls;     // tree slot -> class
+    const uint8_t* cmp_cls;      // compact counter -> class
     unsigned long long* out3;
     unsigned long long* out4;
     unsigned long long* stats;
     int k3, k4;
     uint32_t rank_lo, rank_hi;   // only roots with rank in [rank_lo, rank_hi)
-    uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | keys | cnt
+    uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | pcount | bitmap
     size_t wg_words;
-    uint32_t s2cap, tcap;
-    uint2* tasks;                // long-slot tasks: (hub index, the slot's entry in r's row)
-    uint32_t task_cap;
+    uint32_t s2cap;
+    uint32_t n;                  // vertices
+    void* cmp;                   // compact rows (n x kCmpRow counters, zeroed), or nullptr
+    int cmp_wide;                // 64-bit counters instead of 32-bit
     uint32_t split_roots;        // the first split_roots hub roots (the heaviest) ...
     uint32_t shares;             // ... are each taken by this many workgroups (see k_hub)
 };
@@ -111,6 +102,48 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
     return (uint32_t)__builtin_amdgcn_readlane(x, 63);
+}
+
+// sum over the 16 lanes of a DPP row, in every one of them
+__device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);   // row_ror:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false);   // row_ror:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false);   // row_ror:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false);   // row_ror:1
+    return (uint32_t)x;
+}
+
+// n (signed) sets to counter s of vertex v's compact row, by the 16 lanes of a line (the whole
+// wave calls it): one request per line with a non-zero counter
+__device__ __forceinline__ void cmp_line(const HubArgs& A, uint32_t v, uint32_t s, uint32_t n) {
+    const bool any = ((__ballot(n != 0u) >> (lane_id() & 48u)) & 0xFFFFull) != 0ull;
+    if (!any) return;
+    const size_t at = (size_t)v * kCmpRow + s;
+    if (A.cmp == nullptr) {
+        if (n) gadd(A.out4, A.perm, kClasses4, v, A.cmp_cls[s], (unsigned long long)(long long)(int32_t)n);
+    } else if (A.cmp_wide) {
+        atomicAdd((unsigned long long*)A.cmp + at, (unsigned long long)(long long)(int32_t)n);
+    } else {
+        atomicAdd((uint32_t*)A.cmp + at, n);
+    }
+}
+
+// The depth-2 vertices of a root: bitmap B2 over ranks, P2[w] = how many lie before word w
+// (for words that hold one); index of vertex e among them, or ~0
+__device__ __forceinline__ uint32_t find2(const uint32_t* B2, const uint32_t* P2, uint32_t e) {
+    const uint32_t w = B2[e >> 5], bit = 1u << (e & 31u);
+    return (w & bit) ? P2[e >> 5] + (uint32_t)__popc(w & (bit - 1u)) : ~0u;
+}
+// B2 and P2 from the ascending list of the depth-2 vertices (every thread of the workgroup)
+__device__ __forceinline__ void index2(uint32_t* B2, uint32_t* P2, uint32_t nbw, const uint32_t* cids, uint32_t nc) {
+    for (uint32_t i = threadIdx.x; i < nbw; i += HT) B2[i] = 0u;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < nc; j += HT) {
+        const uint32_t c = cids[j];
+        atomicOr(&B2[c >> 5], 1u << (c & 31u));
+        if (j == 0u || (cids[j - 1u] >> 5) != (c >> 5)) P2[c >> 5] = j;
+    }
 }
 
 // f(cls, sum of val) once per distinct class among the lanes with `active` (the whole wave calls it)
@@ -155,6 +188,10 @@ __device__ __forceinline__ void slot_insert(uint16_t* H, uint32_t x, uint32_t i)
         }
     }
 }
+
+// bit of rank x in a filter of FILTER_BITS bits
+constexpr uint32_t FILTER_BITS = 16384;
+__device__ __forceinline__ uint32_t filter_bit(uint32_t x) { return (x * 0x9E3779B1u) >> 18; }
 
 // one dynamic task index per wave (LDS counter)
 __device__ __forceinline__ uint32_t wave_task(uint32_t* ctr) {
@@ -235,27 +272,31 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     for (uint32_t i = tid; i < 64; i += HT) L.t3[i] = A.t3[i];
     for (uint32_t i = tid; i < 768; i += HT) L.maps[i] = A.maps[i];
     const uint8_t* star_of = L.maps;
-    const uint8_t* path_of = L.maps + 256;
-    const uint8_t* tree_of = L.maps + 512;
+    const uint8_t* cmp_of = L.maps + 512;
     uint32_t* S = A.scratch + (size_t)blockIdx.x * A.wg_words;
     uint32_t* locoff = S;                                        // DMAX + 2
     // rows: slot x has the words [locoff[x], locoff[x + 1]): its local entries from the
-    // front, its depth-2 entries (hash slot << 2 | code) from the back
-    uint32_t* locnbr = locoff + DMAX + 2;                        // s2cap (+ 1)
-    uint32_t* parents = locnbr + A.s2cap + (A.s2cap & 1u);       // s2cap: A(c) of every depth-2 vertex
+    // front, its depth-2 entries from the back (rank, then index of the vertex, and code)
+    uint32_t* locnbr = locoff + DMAX + 2;                        // s2cap
+    uint32_t* parents = locnbr + A.s2cap;                        // s2cap: A(c) of every depth-2 vertex
     uint32_t* poff = parents + A.s2cap;                          // s2cap: first parent of the j-th
-    uint32_t* cids = poff + A.s2cap;                             // s2cap: its hash slot, then its rank
-    uint32_t* keys = cids + A.s2cap;                             // tcap: rank + 1 per hash slot
-    uint32_t* cnt = keys + A.tcap;                               // tcap: parents of the hash slot's vertex
+    uint32_t* cids = poff + A.s2cap;                             // s2cap: its rank (ascending)
+    // s2cap x 16 bytes: first an entry's place among its parents (one word each), then the
+    // parents of the j-th by the codes (to r, to c): nine 12-bit counts, five in the first
+    // word, four in the second, and above them the mask of the non-zero ones
+    ulonglong2* pcount = (ulonglong2*)(((uintptr_t)(cids + A.s2cap) + 15u) & ~(uintptr_t)15u);
+    uint32_t* place = (uint32_t*)pcount;
+    uint32_t* gbits = (uint32_t*)(pcount + A.s2cap);             // 2 x nbw: B2 and P2 when LDS has no room
+    const uint32_t nbw = (A.n + 31u) >> 5;
     unsigned long long shp[kShapes] = {0, 0, 0, 0, 0, 0};
 
     // The heaviest hub roots (the first A.split_roots of the queue) are each taken by
     // A.shares workgroups, so that no single root's workgroup is the critical path.  Each
-    // stages the whole root (its slot hash, local lists and depth-2 buckets live in its own
-    // scratch) and does the share of every phase's tasks that is its own: slots x with
-    // x % G == share (phases B-C4, F) and depth-2 vertices c with c % G == share (phase D,
-    // whose group order differs between workgroups).  Its counters are partial sums,
-    // flushed with atomics like a whole root's.  Later roots are taken whole (G = 1).
+    // stages the whole root (its lists live in its own scratch) and does the share of every
+    // phase's tasks that is its own: slots x with x % G == share and, in phase G, paths over
+    // depth-2 vertices c with c % G == share.  Its counters are partial sums (signed: a group
+    // and its correction may fall to different shares), flushed with atomics like a whole
+    // root's.  Later roots are taken whole (G = 1).
     const uint32_t split_tasks = A.split_roots * A.shares;
     for (;;) {
         __syncthreads();
@@ -270,9 +311,6 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         if (r < A.rank_lo || r >= A.rank_hi) continue;   // uniform over the workgroup
         const uint32_t s0 = A.split[r];
         const uint32_t D = A.off[r + 1] - s0;
-        uint32_t tbits = 6;
-        while ((1u << tbits) < 2u * A.hub_s2[hi_idx] + 64u) tbits++;
-        const uint32_t TS = 1u << tbits;
         // ---- phase A: stage the slots, the lengths of their rows above r, clear counters
         uint16_t* H = (uint16_t*)L.U;   // slot hash (phases A-B)
         // Slots ordered by their arc code to r, by rank within a code.  Any fixed order of
@@ -305,11 +343,6 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         for (uint32_t i = tid; i < kClasses3; i += HT) L.root3[i] = 0ull;
         for (uint32_t i = tid; i < kClasses4; i += HT) L.root4[i] = 0ull;
         if (tid < 8) L.ctr[tid] = 0u;
-        if (A.k4)
-            for (uint32_t i = tid; i < TS; i += HT) {
-                keys[i] = 0u;
-                cnt[i] = 0u;
-            }
         __syncthreads();
         for (uint32_t i = tid; i < D; i += HT) {
             const uint32_t x = L.P[i] >> 2;
@@ -324,6 +357,13 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         uint32_t* R3 = L.U + SHASH / 2 + HT;   // D x 13 k = 3 counters of the slots
         if (A.k3)
             for (uint32_t i = tid; i < D * kClasses3; i += HT) R3[i] = 0u;
+        // the depth-2 vertices in a bitmap over ranks, in LDS where it fits
+        const uint32_t used = SHASH / 2 + HT + (A.k3 ? D * kClasses3 : 0u);
+        uint32_t* B2 = used + 2u * nbw <= U_WORDS ? L.U + used : gbits;
+        uint32_t* P2 = B2 + nbw;
+        const bool kept = B2 == gbits;   // phases E and G find it there
+        if (A.k4)
+            for (uint32_t i = tid; i < nbw; i += HT) B2[i] = 0u;
         __syncthreads();
         for (;;) {
             const uint32_t x = wave_task(&L.ctr[0]);
@@ -335,10 +375,6 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             const uint32_t end = locoff[x + 1];
             const uint32_t lo = hi - (end - base);
             uint32_t nloc = 0, nch = 0, nc1 = 0, nc2 = 0;
-            if (own && A.k4 && hi - lo > SHORT && lane == 0) {
-                const uint32_t t = atomicAdd(&A.cursor[1], 1u);
-                if (t < A.task_cap) A.tasks[t] = make_uint2(hi_idx, L.P[x]);
-            }
             for (uint32_t q0 = lo; q0 < hi; q0 += 64) {
                 const uint32_t q = q0 + lane;
                 const bool in = q < hi;
@@ -364,20 +400,11 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         shp[1]++;
                     }
                 }
-                if (A.k4) {   // depth-2 entry (x, e): e into the hash, the entry behind x's row
+                if (A.k4) {   // depth-2 entry (x, e): e marked, the entry behind x's row
                     const unsigned long long md = __ballot(d2);
                     if (d2) {
-                        uint32_t h = (e * 2654435761u) >> (32u - tbits);
-                        for (;; h = (h + 1u) & (TS - 1u)) {
-                            const uint32_t k = atomicCAS(&keys[h], 0u, e + 1u);
-                            if (k == 0u) {
-                                cids[atomicAdd(&L.ctr[1], 1u)] = h;
-                                break;
-                            }
-                            if (k == e + 1u) break;
-                        }
-                        atomicAdd(&cnt[h], 1u);
-                        locnbr[end - 1u - nch - (uint32_t)__popcll(md & ((1ull << lane) - 1ull))] = (h << 2) | ec;
+                        atomicOr(&B2[e >> 5], 1u << (e & 31u));
+                        locnbr[end - 1u - nch - (uint32_t)__popcll(md & ((1ull << lane) - 1ull))] = (e << 2) | ec;
                     }
                     nch += (uint32_t)__popcll(md);
                     nc1 += (uint32_t)__popcll(__ballot(d2 && ec == 1u));
@@ -391,23 +418,55 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             }
         }
         __syncthreads();
-        const uint32_t ngroups = L.ctr[1];
-        if (A.k4) {   // the parents of every depth-2 vertex, gathered: A(c_j) = parents[poff[j] .. poff[j + 1])
-            for (uint32_t j = tid; j <= ngroups; j += HT) poff[j] = j < ngroups ? cnt[cids[j]] : 0u;
+        // the depth-2 vertices numbered in rank order (cids), their parents gathered:
+        // A(c_j) = parents[poff[j] .. poff[j + 1])
+        uint32_t ngroups = 0;
+        if (A.k4) {
+            for (uint32_t i = tid; i < nbw; i += HT) P2[i] = (uint32_t)__popc(B2[i]);
             __syncthreads();
-            block_scan(poff, ngroups + 1u, part);
-            for (uint32_t j = tid; j < ngroups; j += HT) {
-                const uint32_t h = cids[j];
-                cnt[h] = poff[j];
-                cids[j] = keys[h] - 1u;
+            ngroups = block_scan(P2, nbw, part);
+            for (uint32_t i = tid; i < nbw; i += HT) {
+                uint32_t at = P2[i];
+                for (uint32_t w = B2[i]; w; w &= w - 1u) cids[at++] = (i << 5) + (uint32_t)__ffs((int)w) - 1u;
             }
+            for (uint32_t j = tid; j <= ngroups; j += HT) poff[j] = 0u;
             __syncthreads();
             for (uint32_t x = wid; x < D; x += NW) {
                 const uint32_t end = locoff[x + 1], m = end - locoff[x] - L.locn[x];
                 for (uint32_t i = lane; i < m; i += 64) {
-                    const uint32_t ent = locnbr[end - 1u - i];
-                    parents[atomicAdd(&cnt[ent >> 2], 1u)] = (x << 2) | (ent & 3u);
+                    const uint32_t ent = locnbr[end - 1u - i], j = find2(B2, P2, ent >> 2);
+                    locnbr[end - 1u - i] = (j << 2) | (ent & 3u);
+                    place[end - 1u - i] = atomicAdd(&poff[j], 1u);
                 }
+            }
+            __syncthreads();
+            block_scan(poff, ngroups + 1u, part);
+            for (uint32_t x = wid; x < D; x += NW) {
+                const uint32_t end = locoff[x + 1], m = end - locoff[x] - L.locn[x];
+                for (uint32_t i = lane; i < m; i += 64) {
+                    const uint32_t ent = locnbr[end - 1u - i];
+                    parents[poff[ent >> 2] + place[end - 1u - i]] = (x << 2) | (ent & 3u);
+                }
+            }
+            __syncthreads();
+            // the parents of each depth-2 vertex counted by their codes to r and to it
+            for (uint32_t j0 = wid * 4u; j0 < ngroups; j0 += NW * 4u) {
+                const uint32_t j = j0 + (lane >> 4);
+                const uint32_t f0 = j < ngroups ? poff[j] : 0u, f1 = j < ngroups ? poff[j + 1] : 0u;
+                unsigned long long lo = 0, hi = 0;
+                for (uint32_t i = 0; __ballot(f0 + i < f1); i += 16u) {
+                    const uint32_t f = f0 + i + (lane & 15u);
+                    const uint32_t pe = f < f1 ? parents[f] : 0u;
+                    const uint32_t code = f < f1 ? ((L.P[pe >> 2] & 3u) - 1u) * 3u + (pe & 3u) - 1u : 9u;
+#pragma unroll
+                    for (uint32_t q = 0; q < 9; q++) {
+                        const unsigned long long n = __popcll((__ballot(code == q) >> (lane & 48u)) & 0xFFFFull);
+                        if (q < 5) lo += n << (12u * q);
+                        else hi += n << (12u * (q - 5u));
+                        if (n) hi |= 1ull << (48u + q);
+                    }
+                }
+                if ((lane & 15u) == 0u && j < ngroups) pcount[j] = make_ulonglong2(lo, hi);
             }
             __syncthreads();
         }
@@ -656,30 +715,17 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 }
         }
         __syncthreads();
-        // ---- phase D: (2,1,0): a depth-2 vertex c, a parent x of c and a second slot y.  The
-        // sets of one (x, c) are grouped by y's codes to r and x: the group sizes are
-        // properties of x (NX), the number of x's children by code is ch1, ch2, ch3.  A
-        // second parent y of c is counted in its group, then taken out again, and the set of
-        // both parents (one set, whichever hangs first: Lemma 3) is added under its own index.
+        // ---- phase D: per slot x, the other slots by their codes to r and to x (NX), and x's
+        // (2,1,0) sets as the second slot y: below every other slot x' and its children, by
+        // code, as if none were adjacent to y (the children that x and x' share are taken out
+        // in phase E).
+        const uint32_t nxw = (D * 5u + 1u) & ~1u;
+        uint16_t* NX = (uint16_t*)L.U;               // D x 10: [9] slots by codes, children of code 3
         {
-            const uint32_t W1 = ((D + 31u) >> 5) | 1u;
-            constexpr uint32_t FIX = 16 + 200 * NW + CW * NW;
-            const bool inl = D * (NPC + 5u) + FIX <= U_WORDS;                  // path and cycle counters in LDS
-            const bool inx = D * (NPC + 5u + 2u * W1) + FIX <= U_WORDS;        // and the code rows of all slots
-            uint32_t* SX = L.U;                            // [9] children of the slots of a code, by code
-            int32_t* CHS = (int32_t*)(L.U + 16) + wid * 200;   // per wave: class counters of c (or work space)
-            uint32_t* BX = L.U + 16 + 200 * NW + wid * CW;     // per wave: one code row
-            uint16_t* NX = (uint16_t*)(L.U + FIX);         // per slot: slots by (code to r, code to x) [9], ch3
-            uint32_t* R5 = L.U + FIX + D * 5u;             // D x 30 path and 4-cycle counters
-            uint2* X = (uint2*)(L.U + ((FIX + D * (NPC + 5u) + 1u) & ~1u));
-            const uint8_t* pc_of = path_of;
-            if (inl)
-                for (uint32_t i = tid; i < D * NPC; i += HT) R5[i] = 0u;
-            if (inx)
-                for (uint32_t i = tid; i < D * W1; i += HT) X[i] = make_uint2(0u, 0u);
+            uint32_t* SX = L.U + nxw;                // [9] children of the slots of a code, by code
+            uint32_t* CW18 = SX + 16 + wid * 20;     // per wave: 9 counts, 9 sums
             if (tid < 16) SX[tid] = 0u;
-            if (tid < 2) L.ctr[4 + tid] = 0u;
-            for (uint32_t i = lane; i < 200; i += 64) CHS[i] = 0;
+            if (tid == 0) L.ctr[4] = 0u;
             __syncthreads();
             for (uint32_t x = tid; x < D; x += HT) {
                 const uint32_t n1 = L.ch1[x], n2 = L.ch2[x], q = ((L.P[x] & 3u) - 1u) * 3u;
@@ -693,22 +739,12 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             auto children = [&](uint32_t x, uint32_t k) -> uint32_t {
                 return k == 1u ? L.ch1[x] : (k == 2u ? L.ch2[x] : NX[x * 10 + 9]);
             };
-            auto seg_size = [&](uint32_t k) { return seg_at(k + 1) - seg_at(k); };
-            // n (mod 2^32, signed) sets of class cls to slot x
-            auto add_x = [&](uint32_t x, uint32_t cls, uint32_t n) {
-                const uint32_t s = pc_of[cls];
-                if (inl && s < NPC) atomicAdd(&R5[x * NPC + s], n);
-                else gadd(A.out4, A.perm, kClasses4, L.P[x] >> 2, cls, (unsigned long long)(long long)(int32_t)n);
-            };
-            auto add_r = [&](uint32_t cls, uint32_t n) {
-                atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n);
-            };
-            // per slot x: its group sizes; its sets as a parent, and as the second slot of others' sets
             for (;;) {
                 const uint32_t x = wave_task(&L.ctr[4]);
                 if (x >= D) break;
                 const bool own = x % G == share;
                 const uint32_t rx = L.P[x] & 3u, base = locoff[x], nl = L.locn[x];
+                auto add_x = [&](uint32_t cls, uint32_t n) { gadd(A.out4, A.perm, kClasses4, L.P[x] >> 2, cls, n); };
                 uint32_t c9[9] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u}, l9[9] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
                 for (uint32_t i0 = 0; i0 < nl; i0 += 64) {
                     const bool on = i0 + lane < nl;
@@ -717,288 +753,326 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
 #pragma unroll
                     for (uint32_t q = 0; q < 9; q++)
                         c9[q] += (uint32_t)__popcll(__ballot(on && ry == q / 3u + 1u && k == q % 3u + 1u));
-                    if (inx && on) {
-                        uint32_t* p = &X[x * W1 + (y >> 5)].x;
-                        const uint32_t bit = 1u << (y & 31u);
-                        if (k & 1u) atomicOr(p, bit);
-                        if (k & 2u) atomicOr(p + 1, bit);
-                    }
                     if (own)   // x as the second slot below its local neighbour y
+#pragma unroll
                         for (uint32_t xc = 1; xc < 4; xc++) {
                             const uint32_t n = on ? children(y, xc) : 0u;
                             if (!__ballot(n != 0u)) continue;
                             const uint32_t cls = n ? L.t4[motif_index4(ry, rx, 0u, swap_arc_bits(k), xc, 0u)] : 0xFFu;
-                            by_class_sum(cls, n, n != 0u, [&](uint32_t kk, uint32_t m) { add_x(x, kk, m); });
+                            by_class_sum(cls, n, n != 0u, add_x);
 #pragma unroll
-                            for (uint32_t p = 0; p < 3; p++) {
-                                const uint32_t m = wave_sum(ry == p + 1u ? n : 0u);
-                                if (xc == 1u) l9[p * 3] += m;
-                                else if (xc == 2u) l9[p * 3 + 1] += m;
-                                else l9[p * 3 + 2] += m;
-                            }
+                            for (uint32_t p = 0; p < 3; p++) l9[p * 3 + xc - 1u] += wave_sum(ry == p + 1u ? n : 0u);
                         }
                 }
 #pragma unroll
                 for (uint32_t q = 0; q < 9; q++)
                     if (lane == q) {
                         NX[x * 10 + q] = (uint16_t)c9[q];
-                        CHS[q] = (int32_t)c9[q];
-                        CHS[9 + q] = (int32_t)l9[q];
+                        CW18[9 + q] = l9[q];
                     }
                 __threadfence_block();
-                if (own && lane < 45) {
-                    uint32_t v, cls;
-                    if (lane < 36) {   // parent x, children of code xc, second slots of codes p (to r), k (to x)
-                        const uint32_t p = lane / 12u, k = lane % 12u / 3u, xc = lane % 3u + 1u;
-                        const uint32_t g = k ? (uint32_t)CHS[p * 3 + k - 1]
-                                             : seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u) -
-                                                   (uint32_t)(CHS[p * 3] + CHS[p * 3 + 1] + CHS[p * 3 + 2]);
-                        v = g * children(x, xc);
-                        if (v) {
-                            cls = L.t4[motif_index4(rx, p + 1u, 0u, k, xc, 0u)];
-                            add_x(x, cls, v);
-                            add_r(cls, v);
-                        }
-                    } else {   // second slot x, parents of code p that are not adjacent to x, children of code xc
-                        const uint32_t p = (lane - 36u) / 3u, xc = (lane - 36u) % 3u + 1u;
-                        v = SX[p * 3 + xc - 1u] - (p + 1u == rx ? children(x, xc) : 0u) -
-                            (uint32_t)CHS[9 + p * 3 + xc - 1u];
-                        if (v) add_x(x, L.t4[motif_index4(p + 1u, rx, 0u, 0u, xc, 0u)], v);
-                    }
+                if (own && lane < 9u) {   // parents of code p + 1 that are not adjacent to x, children of code xc
+                    const uint32_t p = lane / 3u, xc = lane % 3u + 1u;
+                    const uint32_t v = SX[lane] - (p + 1u == rx ? children(x, xc) : 0u) - CW18[9 + lane];
+                    if (v) add_x(L.t4[motif_index4(p + 1u, rx, 0u, 0u, xc, 0u)], v);
                 }
                 __threadfence_block();
             }
-            __syncthreads();
-            for (uint32_t i = lane; i < 200; i += 64) CHS[i] = 0;
-            __threadfence_block();
-            // arc code of (slot x, slot y) seen from x
-            auto code_xy = [&](uint32_t x, uint32_t y) -> uint32_t {
-                const uint2 w = X[x * W1 + (y >> 5)];
-                return ((w.x >> (y & 31u)) & 1u) | (((w.y >> (y & 31u)) & 1u) << 1);
-            };
-            // per depth-2 vertex c: a lane takes it alone when it has few parents, else the wave
-            const uint32_t lane_max = inx ? 8u : 1u;
-            for (;;) {
-                const uint32_t j = wave_task(&L.ctr[5]) * 64u + lane;
-                if (j - lane >= ngroups) break;
-                const bool on = j < ngroups;
-                const uint32_t c = on ? cids[j] : 0u;
-                const bool own = on && c % G == share;
-                const uint32_t p0 = own ? poff[j] : 0u, na = own ? poff[j + 1] - p0 : 0u;
-                shp[3] += (unsigned long long)na * (D - 1u) - (unsigned long long)na * (na - 1u) / 2u;
-                if (na > 0u && na <= lane_max) {
-                    unsigned long long* row = &A.out4[(size_t)A.perm[c] * kClasses4];
-                    for (uint32_t i = 0; i < na; i++) {
-                        const uint32_t ent = parents[p0 + i], x = ent >> 2, xc = ent & 3u, rx = L.P[x] & 3u;
-                        uint32_t g[12];
-#pragma unroll
-                        for (uint32_t p = 0; p < 3; p++) {
-                            const uint32_t n1 = NX[x * 10 + p * 3], n2 = NX[x * 10 + p * 3 + 1],
-                                           n3 = NX[x * 10 + p * 3 + 2];
-                            g[p * 4] = seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u) - n1 - n2 - n3;
-                            g[p * 4 + 1] = n1;
-                            g[p * 4 + 2] = n2;
-                            g[p * 4 + 3] = n3;
-                        }
-                        for (uint32_t i2 = 0; i2 < na; i2++) {
-                            if (i2 == i) continue;
-                            const uint32_t e2 = parents[p0 + i2], y = e2 >> 2, yc = e2 & 3u, ry = L.P[y] & 3u;
-                            const uint32_t xy = code_xy(x, y), at = (ry - 1u) * 4u + xy;
-#pragma unroll
-                            for (uint32_t q = 0; q < 12; q++) g[q] -= q == at ? 1u : 0u;
-                            const uint32_t k0 = L.t4[motif_index4(rx, ry, 0u, xy, xc, 0u)];
-                            add_x(x, k0, ~0u);
-                            add_x(y, k0, ~0u);
-                            add_r(k0, ~0u);
-                            if (i2 > i) {
-                                const uint32_t k1 = L.t4[motif_index4(rx, ry, 0u, xy, xc, yc)];
-                                add_x(x, k1, 1u);
-                                add_x(y, k1, 1u);
-                                add_r(k1, 1u);
-                                atomicAdd(&row[k1], 1ull);
-                            }
-                        }
-#pragma unroll
-                        for (uint32_t q = 0; q < 12; q++)
-                            if (g[q])
-                                atomicAdd(&row[L.t4[motif_index4(rx, q / 4u + 1u, 0u, q % 4u, xc, 0u)]],
-                                          (unsigned long long)g[q]);
-                    }
-                }
-                for (unsigned long long m = __ballot(na > lane_max); m; m &= m - 1ull) {
-                    const int src = __ffsll((long long)m) - 1;
-                    const uint32_t wc = (uint32_t)__builtin_amdgcn_readlane((int)c, src);
-                    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)p0, src);
-                    const uint32_t wna = (uint32_t)__builtin_amdgcn_readlane((int)na, src);
-                    for (uint32_t i = lane; i < wna; i += 64) {   // every parent's groups
-                        const uint32_t ent = parents[w0 + i], x = ent >> 2, xc = ent & 3u, rx = L.P[x] & 3u;
-                        for (uint32_t p = 0; p < 3; p++) {
-                            uint32_t rest = seg_size(p + 1u) - (p + 1u == rx ? 1u : 0u);
-                            for (uint32_t k = 1; k < 4; k++) {
-                                const uint32_t n = NX[x * 10 + p * 3 + k - 1u];
-                                rest -= n;
-                                if (n) atomicAdd(&CHS[L.t4[motif_index4(rx, p + 1u, 0u, k, xc, 0u)]], (int32_t)n);
-                            }
-                            if (rest) atomicAdd(&CHS[L.t4[motif_index4(rx, p + 1u, 0u, 0u, xc, 0u)]], (int32_t)rest);
-                        }
-                    }
-                    for (uint32_t i = 0; i < wna; i++) {   // pairs of parents: y in turn, lanes over x
-                        const uint32_t e2 = parents[w0 + i], y = e2 >> 2, yc = e2 & 3u, ry = L.P[y] & 3u;
-                        const uint32_t nl = L.locn[y];
-                        if (nl) build_row(BX, locnbr, locoff[y], nl);
-                        for (uint32_t i0 = 0; i0 < wna; i0 += 64) {
-                            const uint32_t i1 = i0 + lane;
-                            const bool in = i1 < wna && i1 != i, both = in && i1 > i;
-                            const uint32_t ent = in ? parents[w0 + i1] : 0u, x = ent >> 2, xc = ent & 3u;
-                            const uint32_t rx = L.P[x] & 3u, xy = nl ? swap_arc_bits(code_at(BX, x)) : 0u;
-                            const uint32_t k0 = in ? L.t4[motif_index4(rx, ry, 0u, xy, xc, 0u)] : 0xFFu;
-                            by_class(k0, in, [&](uint32_t k, uint32_t n) {
-                                atomicAdd(&CHS[k], -(int32_t)n);
-                                add_x(y, k, 0u - n);
-                                add_r(k, 0u - n);
-                            });
-                            if (in) add_x(x, k0, ~0u);
-                            const uint32_t k1 = both ? L.t4[motif_index4(rx, ry, 0u, xy, xc, yc)] : 0xFFu;
-                            by_class(k1, both, [&](uint32_t k, uint32_t n) {
-                                atomicAdd(&CHS[k], (int32_t)n);
-                                add_x(y, k, n);
-                                add_r(k, n);
-                            });
-                            if (both) add_x(x, k1, 1u);
-                        }
-                    }
-                    __threadfence_block();
-                    for (uint32_t k = lane; k < kClasses4; k += 64) {
-                        const int32_t n = CHS[k];
-                        if (n) gadd(A.out4, A.perm, kClasses4, wc, k, (unsigned long long)(long long)n);
-                        CHS[k] = 0;
-                    }
-                    __threadfence_block();
-                }
-            }
-            __syncthreads();
-            if (inl)
-                for (uint32_t i = tid; i < D * NPC; i += HT) {
-                    const uint32_t x = R5[i];
-                    if (x)
-                        gadd(A.out4, A.perm, kClasses4, L.P[i / NPC] >> 2, A.path_cls[i % NPC],
-                             (unsigned long long)(long long)(int32_t)x);
-                }
         }
         __syncthreads();
-        // ---- phase F: (1,2,0) and (1,1,1) below the slots with short rows, one wave each
-        for (uint32_t i = tid; i < SHASH / 2; i += HT) L.U[i] = 0u;
-        __syncthreads();
-        for (uint32_t i = tid; i < D; i += HT) slot_insert(H, L.P[i] >> 2, i);
-        __syncthreads();
+        // ---- phase E: the sets below one slot a and one child c of a.  A wave takes a and marks
+        // its children in a bitmap over the depth-2 vertices; 16 lanes take a child c:
+        //   (2,1,0): a second slot of the group of its codes to r and a (NX), without the other
+        //     parents x of c; a pair of parents once, from the lower slot (Lemma 3's rule);
+        //   (1,2,0) and (1,1,1): c's row above r is walked, an e outside N(r) is another child
+        //     of a (the pair with its arcs) or the end of the path r - a - c - e (the Lemma-4
+        //     rule); the children of a that are not adjacent to c are a group by their code.
+        // The sets are counted by arc codes.  c's credits leave as whole 64-byte lines of the
+        // compact rows (a memory-side atomic costs the same for one counter as for a line of
+        // them); a's and r's are summed in LDS.
+        const uint32_t gl = lane & 15u;
         {
-            // per wave: child list (64), child hash (128: (rank + 1) << 6 | position), child
-            // codes to the current child (4 words), child counters (64 x 25), counters of a
-            constexpr uint32_t WW = 64 + CH_HASH + 4 + 64 * NTREE + kClasses4;
-            uint32_t* CL = L.U + SHASH / 2 + wid * WW;
-            uint32_t* CK = CL + 64;
-            uint32_t* CA = CK + CH_HASH;
-            uint32_t* CC = CA + 4;
-            uint32_t* AH = CC + 64 * NTREE;
+            constexpr uint32_t GW = 96;            // words per 16-lane group: 3 lines, 9 + 36 pair counts
+            constexpr uint32_t AW = 200;           // words per wave: a's classes
+            constexpr uint32_t FW = FILTER_BITS / 32;
+            constexpr uint32_t FIX = (HT / 16) * GW + NW * AW + NW * CW + SHASH / 2;
+            // a's children as a bitmap a plane over the depth-2 vertices (their arc codes), where
+            // LDS holds that for every wave beside B2 and P2; else as a filter over hashed ranks
+            // in front of a search of a's row (hubs with very many depth-2 vertices)
+            const uint32_t jw = (ngroups + 31u) >> 5;
+            const bool coded = nxw + FIX + 2u * nbw + 2u * NW * jw <= U_WORDS;
+            const uint32_t mw = coded ? 2u * jw : FW;               // words per wave
+            const bool in_lds = nxw + FIX + 2u * nbw + NW * mw <= U_WORDS;
+            uint32_t* GC = L.U + nxw + (tid >> 4) * GW;
+            uint32_t* AC = L.U + nxw + (HT / 16) * GW + wid * AW;
+            uint32_t* BX = L.U + nxw + (HT / 16) * GW + NW * AW + wid * CW;   // per wave: a's code row
+            uint16_t* H2 = (uint16_t*)(L.U + nxw + (HT / 16) * GW + NW * AW + NW * CW);
+            uint32_t* M0 = L.U + nxw + FIX + wid * mw;              // children with arc bit 0, or the filter
+            uint32_t* M1 = M0 + jw;                                 // children with arc bit 1
+            uint32_t* B2 = in_lds ? L.U + nxw + FIX + NW * mw : gbits;
+            uint32_t* P2 = B2 + nbw;
+            for (uint32_t i = nxw + tid; i < nxw + FIX; i += HT) L.U[i] = 0u;
+            for (uint32_t i = lane; i < mw; i += 64) M0[i] = 0u;
+            if (tid == 0) L.ctr[6] = 0u;
+            __syncthreads();
+            for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
+            if (in_lds || !kept) index2(B2, P2, nbw, cids, ngroups);
+            __syncthreads();
+            auto add_r = [&](uint32_t cls, uint32_t n) {
+                atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n);
+            };
+            auto add_a = [&](uint32_t cls, uint32_t n) { atomicAdd(&AC[cls], n); };
             for (;;) {
                 const uint32_t a = wave_task(&L.ctr[6]) * G + share;
                 if (a >= D) break;
-                const uint32_t len = locoff[a + 1] - locoff[a];
-                if (len == 0 || len > SHORT) continue;
-                const uint32_t va = L.P[a] >> 2, ra = L.P[a] & 3u;
-                const uint32_t hi = A.off[va + 1], lo = hi - len;
-                for (uint32_t i = lane; i < CH_HASH; i += 64) CK[i] = 0u;
-                for (uint32_t i = lane; i < kClasses4; i += 64) AH[i] = 0u;
-                for (uint32_t i = lane; i < 64 * NTREE; i += 64) CC[i] = 0u;
-                if (lane < 4) CA[lane] = 0u;
-                // children: entries of a's row above r outside N+(r)
-                const uint32_t q = lo + lane;
-                uint32_t e = 0, ec = 0;
-                bool chd = false;
-                if (q < hi) {
-                    e = A.adj[q] >> 2;
-                    ec = A.adj[q] & 3u;
-                    chd = slot_find(H, L.P, e) < 0;
+                const uint32_t end = locoff[a + 1], nloc = L.locn[a], m = end - locoff[a] - nloc;
+                if (m == 0u) continue;
+                const uint32_t ra = L.P[a] & 3u;
+                const uint32_t m1 = L.ch1[a], m2 = L.ch2[a], m3 = m - m1 - m2;
+                if (nloc) build_row(BX, locnbr, locoff[a], nloc);
+                if (lane < 6u) {   // (1,2,0) of a and r: pairs of children by code, as if not adjacent
+                    const uint32_t k = lane < 3u ? 1u : (lane < 5u ? 2u : 3u);
+                    const uint32_t l = lane < 3u ? lane + 1u : (lane < 5u ? lane - 1u : 3u);
+                    const uint32_t nk = k == 1u ? m1 : (k == 2u ? m2 : m3), nl = l == 1u ? m1 : (l == 2u ? m2 : m3);
+                    const uint32_t n = k == l ? nk * (nk - 1u) / 2u : nk * nl;
+                    if (n) {
+                        const uint32_t cls = L.t4[motif_index4(ra, 0u, 0u, k, l, 0u)];
+                        add_a(cls, n);
+                        add_r(cls, n);
+                    }
                 }
-                const unsigned long long mc = __ballot(chd);
-                const uint32_t m = (uint32_t)__popcll(mc);
-                __threadfence_block();
-                if (chd) {
-                    const uint32_t pos = (uint32_t)__popcll(mc & ((1ull << lane) - 1ull));
-                    CL[pos] = (e << 2) | ec;
-                    for (uint32_t h = (e * 2654435761u) >> 25;; h = (h + 1u) & (CH_HASH - 1u))
-                        if (atomicCAS(&CK[h], 0u, ((e + 1u) << 6) | pos) == 0u) break;
+                if (lane == 0u) shp[4] += (unsigned long long)m * (m - 1u) / 2u;
+                for (uint32_t i = lane; i < m; i += 64) {   // depth-2 entries of a's row: (j << 2) | code
+                    const uint32_t ent = locnbr[end - 1u - i], j = ent >> 2;
+                    if (coded) {
+                        if (ent & 1u) atomicOr(&M0[j >> 5], 1u << (j & 31u));
+                        if (ent & 2u) atomicOr(&M1[j >> 5], 1u << (j & 31u));
+                    } else {
+                        const uint32_t b = filter_bit(cids[j]);
+                        atomicOr(&M0[b >> 5], 1u << (b & 31u));
+                    }
                 }
                 __threadfence_block();
-                for (uint32_t i = 0; i < m; i++) {
-                    const uint32_t vc = CL[i] >> 2, ac = CL[i] & 3u;
-                    // walk c's row above r: arcs to later children, (1,1,1) end vertices
-                    const uint32_t chi = A.off[vc + 1];
-                    for (uint32_t t0 = first_above(A.adj, A.off[vc], chi, r); t0 < chi; t0 += 64) {
-                        const uint32_t t = t0 + lane;
-                        bool p111 = false;
-                        uint32_t cls = 0xFFu, ve = 0;
-                        if (t < chi) {
-                            ve = A.adj[t] >> 2;
-                            const uint32_t ce = A.adj[t] & 3u;
-                            int pos = -1;
-                            for (uint32_t h = (ve * 2654435761u) >> 25;; h = (h + 1u) & (CH_HASH - 1u)) {
-                                const uint32_t k = CK[h];
-                                if (k == 0u) break;
-                                if ((k >> 6) == ve + 1u) {
-                                    pos = (int)(k & 63u);
-                                    break;
-                                }
+                for (uint32_t i0 = 0; i0 < m; i0 += 4u) {
+                    const uint32_t i = i0 + (lane >> 4);
+                    const bool on = i < m;
+                    const uint32_t ent = on ? locnbr[end - 1u - i] : 0u, j = ent >> 2, ac = ent & 3u;
+                    const uint32_t c = cids[j];
+                    const uint32_t q1 = on ? A.off[c + 1] : 0u;
+                    const uint32_t f0 = poff[j], na = poff[j + 1] - f0;
+                    if (on && na > 1u)   // the other parents of c by codes, those above a in the high half
+                        for (uint32_t f = gl; f < na; f += 16u) {
+                            const uint32_t pe = parents[f0 + f], x = pe >> 2;
+                            if (x == a) continue;
+                            const uint32_t ax = nloc ? code_at(BX, x) : 0u;
+                            atomicAdd(&GC[57u + (((L.P[x] & 3u) - 1u) * 3u + (pe & 3u) - 1u) * 4u + ax],
+                                      x > a ? 0x10001u : 1u);
+                        }
+                    uint32_t e12 = 0, e3 = 0;   // e's outside N(r) by arc code (1 | 2 << 16, 3)
+                    for (uint32_t q = (on ? A.off[c] : 0u) + gl; q < q1; q += 16u) {
+                        const uint32_t ee = A.adj[q], e = ee >> 2, ce = ee & 3u;
+                        if (e <= r || slot_find(H2, L.P, e) >= 0) continue;
+                        if (ce == 3u) e3++;
+                        else e12 += ce == 1u ? 1u : 1u << 16;
+                        uint32_t ae = 0, j2 = 0;   // e another child of a: its code
+                        if (coded) {
+                            j2 = find2(B2, P2, e);
+                            if (j2 == ~0u) continue;
+                            ae = ((M0[j2 >> 5] >> (j2 & 31u)) & 1u) | (((M1[j2 >> 5] >> (j2 & 31u)) & 1u) << 1);
+                        } else {
+                            const uint32_t b = filter_bit(e);
+                            if (!((M0[b >> 5] >> (b & 31u)) & 1u)) continue;
+                            j2 = find2(B2, P2, e);
+                            if (j2 == ~0u) continue;
+                            uint32_t lo = 0, hi = m;
+                            while (lo + 1u < hi) {
+                                const uint32_t mid = (lo + hi) >> 1;
+                                if ((locnbr[end - 1u - mid] >> 2) <= j2) lo = mid; else hi = mid;
                             }
-                            if (pos >= 0) {
-                                if ((uint32_t)pos > i) atomicOr(&CA[pos >> 4], ce << ((pos & 15) << 1));
-                            } else if (slot_find(H, L.P, ve) < 0) {
-                                p111 = true;   // e above r, not adjacent to r nor to a
-                                cls = L.t4[motif_index4(ra, 0u, 0u, ac, 0u, ce)];
+                            const uint32_t ent2 = locnbr[end - 1u - lo];
+                            ae = (ent2 >> 2) == j2 ? ent2 & 3u : 0u;
+                        }
+                        if (ae) atomicAdd(&GC[48u + (ae - 1u) * 3u + ce - 1u], j2 > j ? 0x10001u : 1u);
+                    }
+                    e12 = row16_sum(e12);
+                    e3 = row16_sum(e3);
+                    __threadfence_block();
+                    auto add_c = [&](uint32_t cls, uint32_t n) {
+                        const uint32_t s = cmp_of[cls];
+                        if (s < kCmpRow) atomicAdd(&GC[s], n);
+                        else gadd(A.out4, A.perm, kClasses4, c, cls, (unsigned long long)(long long)(int32_t)n);
+                    };
+                    if (on && gl < 9u) {   // pairs of adjacent children: ae = gl / 3 + 1, ce = gl % 3 + 1
+                        const uint32_t n = GC[48u + gl] & 0xFFFFu, nu = GC[48u + gl] >> 16;
+                        const uint32_t ae = gl / 3u + 1u, ce = gl % 3u + 1u;
+                        if (n) {
+                            const uint32_t cls = L.t4[motif_index4(ra, 0u, 0u, ac, ae, ce)];
+                            add_c(cls, n);
+                            // c is no end of the paths r - a - e - c (phase G counts it as one)
+                            add_c(L.t4[motif_index4(ra, 0u, 0u, ae, 0u, swap_arc_bits(ce))], 0u - n);
+                            if (nu) {   // from the child of the lower rank: the pair, for a and r
+                                const uint32_t st = L.t4[motif_index4(ra, 0u, 0u, ac, ae, 0u)];
+                                add_a(cls, nu);
+                                add_r(cls, nu);
+                                add_a(st, 0u - nu);
+                                add_r(st, 0u - nu);
                             }
                         }
-                        by_class(cls, p111, [&](uint32_t k, uint32_t n) {
-                            atomicAdd(&L.root4[k], (unsigned long long)n);
-                            AH[k] += n;
-                            const uint32_t s = tree_of[k];
-                            if (s < NTREE) CC[i * NTREE + s] += n;
-                            else gadd(A.out4, A.perm, kClasses4, vc, k, n);
-                        });
-                        if (p111) {
-                            gadd(A.out4, A.perm, kClasses4, ve, cls, 1ull);
-                            shp[5]++;
+                    } else if (on && gl < 12u) {   // (1,1,1): ends of code k
+                        const uint32_t k = gl - 8u;
+                        const uint32_t n = (k == 3u ? e3 : (k == 1u ? e12 & 0xFFFFu : e12 >> 16)) -
+                                           (GC[47u + k] & 0xFFFFu) - (GC[50u + k] & 0xFFFFu) - (GC[53u + k] & 0xFFFFu);
+                        if (n) {
+                            const uint32_t cls = L.t4[motif_index4(ra, 0u, 0u, ac, 0u, k)];
+                            add_c(cls, n);
+                            add_a(cls, n);
+                            add_r(cls, n);
+                            shp[5] += (unsigned long long)(long long)(int32_t)n;
+                        }
+                    } else if (on && gl < 15u) {   // (1,2,0) with the children of code k not adjacent to c
+                        const uint32_t k = gl - 11u, s = 45u + 3u * k;
+                        const uint32_t n = (k == 1u ? m1 : (k == 2u ? m2 : m3)) - (k == ac ? 1u : 0u) -
+                                           (GC[s] & 0xFFFFu) - (GC[s + 1u] & 0xFFFFu) - (GC[s + 2u] & 0xFFFFu);
+                        if (n) add_c(L.t4[motif_index4(ra, 0u, 0u, ac, k, 0u)], n);
+                    }
+                    if (on && gl < 12u) {   // (2,1,0) under a: second slots by codes p + 1 to r and k to a
+                        const uint32_t p = gl >> 2, k = gl & 3u;
+                        uint32_t n;
+                        if (k) n = NX[a * 10 + p * 3 + k - 1u];
+                        else
+                            n = seg_at(p + 2u) - seg_at(p + 1u) - (p + 1u == ra ? 1u : 0u) - NX[a * 10 + p * 3] -
+                                NX[a * 10 + p * 3 + 1] - NX[a * 10 + p * 3 + 2];
+                        if (na > 1u)
+                            for (uint32_t xc = 0; xc < 3; xc++) n -= GC[57u + (p * 3u + xc) * 4u + k] & 0xFFFFu;
+                        if (n) {
+                            const uint32_t cls = L.t4[motif_index4(ra, p + 1u, 0u, k, ac, 0u)];
+                            add_c(cls, n);
+                            add_a(cls, n);
+                            add_r(cls, n);
+                            shp[3] += n;
                         }
                     }
+                    if (on && na > 1u)
+                        for (uint32_t q = gl; q < 36u; q += 16u) {   // pairs of parents (a, x)
+                            const uint32_t w = GC[57u + q], n = w & 0xFFFFu, nu = w >> 16;
+                            if (!n) continue;
+                            const uint32_t rx = q / 12u + 1u, xc = q % 12u / 4u + 1u, ax = q & 3u;
+                            const uint32_t cls = L.t4[motif_index4(ra, rx, 0u, ax, ac, xc)];
+                            add_a(cls, n);
+                            // a was counted as the second slot below x and c (phase D)
+                            add_a(L.t4[motif_index4(rx, ra, 0u, swap_arc_bits(ax), xc, 0u)], 0u - n);
+                            if (nu) {
+                                add_c(cls, nu);
+                                add_r(cls, nu);
+                                shp[3] += nu;
+                            }
+                        }
                     __threadfence_block();
-                    // (1,2,0): r - a - {c, c'} for the later children c'
-                    const uint32_t j = i + 1 + lane;
-                    const bool in = j < m;
-                    uint32_t cls = 0xFFu;
-                    if (in) cls = L.t4[motif_index4(ra, 0u, 0u, ac, CL[j] & 3u, code_at(CA, j))];
-                    by_class(cls, in, [&](uint32_t k, uint32_t n) {
-                        atomicAdd(&L.root4[k], (unsigned long long)n);
-                        AH[k] += n;
-                        const uint32_t s = tree_of[k];
-                        if (s < NTREE) CC[i * NTREE + s] += n;
-                        else gadd(A.out4, A.perm, kClasses4, vc, k, n);
-                    });
-                    if (in) {
-                        const uint32_t s = tree_of[cls];
-                        if (s < NTREE) atomicAdd(&CC[j * NTREE + s], 1u);
-                        else gadd(A.out4, A.perm, kClasses4, CL[j] >> 2, cls, 1ull);
-                        shp[4]++;
+#pragma unroll
+                    for (uint32_t ln = 0; ln < kCmpRow; ln += 16u) {   // c's counters, a line at a time
+                        const uint32_t n = GC[ln + gl];
+                        GC[ln + gl] = 0u;
+                        cmp_line(A, c, ln + gl, n);
                     }
-                    __threadfence_block();
-                    if (lane < 4) CA[lane] = 0u;
+                    for (uint32_t q = 48u + gl; q < 93u; q += 16u) GC[q] = 0u;
                     __threadfence_block();
                 }
-                for (uint32_t i = lane; i < m * NTREE; i += 64) {
-                    const uint32_t x = CC[i];
-                    if (x) gadd(A.out4, A.perm, kClasses4, CL[i / NTREE] >> 2, A.tree_cls[i % NTREE], x);
+                if (coded) {
+                    for (uint32_t i = lane; i < m; i += 64) {
+                        const uint32_t j = locnbr[end - 1u - i] >> 2;
+                        M0[j >> 5] = 0u;
+                        M1[j >> 5] = 0u;
+                    }
+                } else {
+                    for (uint32_t i = lane; i < FW; i += 64) M0[i] = 0u;
                 }
-                for (uint32_t i = lane; i < kClasses4; i += 64)
-                    if (AH[i]) gadd(A.out4, A.perm, kClasses4, va, i, AH[i]);
                 __threadfence_block();
+                for (uint32_t k = lane; k < kClasses4; k += 64) {
+                    const uint32_t n = AC[k];
+                    AC[k] = 0u;
+                    if (n) gadd(A.out4, A.perm, kClasses4, L.P[a] >> 2, k, (unsigned long long)(long long)(int32_t)n);
+                }
+                __threadfence_block();
+            }
+        }
+        __syncthreads();
+        // ---- phase G: the end vertices of the (1,1,1) paths, each once per root and window of
+        // ranks: marked in a bitmap from the rows of the depth-2 vertices, then 16 lanes per
+        // end e walk e's row: its depth-2 neighbours c and their parents (pcount, by codes) are
+        // its paths, parents adjacent to e included (phase E took those out).  Credited path by
+        // path instead, the ends alone would take a memory-side atomic per (1,1,1) set.
+        {
+            constexpr uint32_t GW = 16;    // words per 16-lane group: 16 path counters
+            constexpr uint32_t FIX = (HT / 16) * GW + NW * CW + SHASH / 2 + 32;
+            const bool in_lds = FIX + 2u * nbw + 4096u <= U_WORDS;
+            uint32_t* GC = L.U + (tid >> 4) * GW;
+            uint16_t* LST = (uint16_t*)(L.U + (HT / 16) * GW + wid * CW);   // per wave: 256 marked vertices
+            uint16_t* H2 = (uint16_t*)(L.U + (HT / 16) * GW + NW * CW);
+            uint32_t* KS = L.U + FIX - 32;   // path counter of the codes ((r -> a, a -> c) - 1) * 3 + (c -> e) - 1
+            uint32_t* B2 = in_lds ? L.U + FIX : gbits;
+            uint32_t* P2 = B2 + nbw;
+            uint32_t* BM = L.U + FIX + (in_lds ? 2u * nbw : 0u);
+            const uint32_t win = min(nbw, U_WORDS - (uint32_t)(BM - L.U));   // words of a window
+            for (uint32_t i = tid; i < FIX - 32; i += HT) L.U[i] = 0u;
+            if (tid < 27u) KS[tid] = cmp_of[L.t4[motif_index4(tid / 9u + 1u, 0u, 0u, tid % 9u / 3u + 1u, 0u, tid % 3u + 1u)]];
+            __syncthreads();
+            for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
+            if (in_lds || !kept) index2(B2, P2, nbw, cids, ngroups);
+            for (uint32_t w0 = (r + 1u) >> 5; w0 < nbw; w0 += win) {
+                const uint32_t wn = min(win, nbw - w0), e0 = w0 << 5;
+                __syncthreads();
+                for (uint32_t i = tid; i < wn; i += HT) BM[i] = 0u;
+                if (tid < 2) L.ctr[6 + tid] = 0u;
+                __syncthreads();
+                for (;;) {
+                    const uint32_t t = wave_task(&L.ctr[6]);
+                    if (t * 4u >= ngroups) break;
+                    const uint32_t j = t * 4u + (lane >> 4);
+                    const uint32_t c = j < ngroups ? cids[j] : 0u;
+                    const bool own = j < ngroups && c % G == share;
+                    const uint32_t q1 = own ? A.off[c + 1] : 0u;
+                    for (uint32_t q = (own ? A.off[c] : 0u) + gl; q < q1; q += 16u) {
+                        const uint32_t e = A.adj[q] >> 2, i = e - e0;
+                        if (e > r && i < (wn << 5) && slot_find(H2, L.P, e) < 0) atomicOr(&BM[i >> 5], 1u << (i & 31u));
+                    }
+                }
+                __syncthreads();
+                for (;;) {   // 256 ranks a wave
+                    const uint32_t b0 = wave_task(&L.ctr[7]) * 8u;
+                    if (b0 >= wn) break;
+                    uint32_t word = lane < 8u && b0 + lane < wn ? BM[b0 + lane] : 0u;
+                    uint32_t pos = 0, total = 0;
+                    for (uint32_t i = 0; i < 8; i++) {
+                        const uint32_t m = (uint32_t)__popc((uint32_t)__builtin_amdgcn_readlane((int)word, (int)i));
+                        pos += i < lane ? m : 0u;
+                        total += m;
+                    }
+                    for (; word; word &= word - 1u) LST[pos++] = (uint16_t)(lane * 32u + (uint32_t)__ffs((int)word) - 1u);
+                    __threadfence_block();
+                    for (uint32_t i0 = 0; i0 < total; i0 += 4u) {
+                        const uint32_t i = i0 + (lane >> 4);
+                        const bool on = i < total;
+                        const uint32_t e = e0 + (b0 << 5) + (on ? LST[i] : 0u);
+                        const uint32_t q1 = on ? A.off[e + 1] : 0u;
+                        for (uint32_t q = (on ? A.off[e] : 0u) + gl; q < q1; q += 16u) {
+                            const uint32_t ee = A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
+                            if (c <= r || (G > 1u && c % G != share)) continue;
+                            const uint32_t j = find2(B2, P2, c);
+                            if (j == ~0u) continue;
+                            const ulonglong2 pc = pcount[j];
+                            for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {
+                                const uint32_t s = (uint32_t)__ffs((int)mk) - 1u;
+                                const uint32_t n = (uint32_t)(s < 5u ? pc.x >> (12u * s) : pc.y >> (12u * (s - 5u))) & 0xFFFu;
+                                atomicAdd(&GC[KS[s * 3u + ce]], n);
+                            }
+                        }
+                        __threadfence_block();
+                        const uint32_t n = GC[gl];
+                        GC[gl] = 0u;
+                        cmp_line(A, e, gl, n);
+                        __threadfence_block();
+                    }
+                }
             }
         }
         __syncthreads();
@@ -1013,192 +1087,14 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     }
 }
 
-// ----------------------------------------------------------------------------- long slots
-
-// (1,2,0) and (1,1,1) sets below one slot a of a hub root r whose row above r is longer
-// than SHORT: one workgroup per task.  Children and their counters in LDS; membership
-// in N+(r) and in L_a by Bloom filters in front of binary searches of the sorted lists.
-constexpr uint32_t BLOOM_WORDS = 1024;      // 32768 bits
-constexpr uint32_t CTW = (NTREE + 1) / 2;   // u16 counter pairs per child (13 words)
-
-struct LongLds {
-    uint32_t P[DMAX];
-    uint32_t CL[DMAX];              // children of a, ascending rank: (rank << 2) | arc bits a -> child
-    uint32_t CC[DMAX * CTW];        // per child: 25 u16 tree-class counters in pairs
-    uint32_t CA[NW * CW];           // per wave: codes of the current child to the children
-    uint32_t bloomP[BLOOM_WORDS];
-    uint32_t bloomC[BLOOM_WORDS];
-    uint32_t root4[kClasses4];      // this task's credits of r
-    uint32_t ah[kClasses4];         // this task's credits of a
-    uint8_t t4[4096];
-    uint8_t tree_of[256];
-    uint32_t ctr[4];
-    uint32_t root;                  // root staged in P, or ~0
-};
-
-__device__ __forceinline__ uint32_t bloom_bit(uint32_t x) { return (x * 0x9E3779B1u) >> 17; }
-__device__ __forceinline__ bool bloom_has(const uint32_t* B, uint32_t x) {
-    const uint32_t b = bloom_bit(x);
-    return (B[b >> 5] >> (b & 31u)) & 1u;
-}
-// position of rank x in the sorted list Lst[0..n) of (rank << 2) | bits entries, or -1
-__device__ __forceinline__ int sorted_find(const uint32_t* Lst, uint32_t n, uint32_t x) {
-    uint32_t lo = 0, hi = n;
-    const uint32_t key = x << 2;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (Lst[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return (lo < n && (Lst[lo] >> 2) == x) ? (int)lo : -1;
-}
-
-__global__ __launch_bounds__(HT) void k_long_slots(HubArgs A) {
-    __shared__ LongLds L;
-    __shared__ uint32_t sTask, sM;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wid = wave_id();
-    for (uint32_t i = tid; i < 4096; i += HT) L.t4[i] = A.t4[i];
-    for (uint32_t i = tid; i < 256; i += HT) L.tree_of[i] = A.maps[512 + i];
-    if (tid == 0) L.root = 0xFFFFFFFFu;
-    const uint32_t ntask = min(A.cursor[1], A.task_cap);
-    // workgroups per task when there are fewer tasks than twice the workgroups (up to 8):
-    // each stages the task and walks the children i with i % G == share (the child list is
-    // a stable compaction of a's row, the same in every workgroup)
-    const uint32_t G = ntask >= 2u * gridDim.x ? 1u : min(8u, (2u * gridDim.x + ntask - 1u) / max(ntask, 1u));
-    unsigned long long shp[kShapes] = {0, 0, 0, 0, 0, 0};
-    auto cc_add = [&](uint32_t pos, uint32_t s, uint32_t n) {
-        atomicAdd(&L.CC[pos * CTW + (s >> 1)], n << ((s & 1u) << 4));
-    };
-    for (;;) {
-        __syncthreads();
-        if (tid == 0) sTask = atomicAdd(&A.cursor[2], 1u);
-        __syncthreads();
-        const uint32_t t = sTask / G, share = sTask - t * G;
-        if (t >= ntask) break;
-        const uint2 task = A.tasks[t];
-        const uint32_t r = A.hubs[task.x];
-        const uint32_t s0 = A.split[r], D = A.off[r + 1] - s0;
-        if (L.root != r) {   // stage N+(r) and its Bloom filter
-            for (uint32_t i = tid; i < BLOOM_WORDS; i += HT) L.bloomP[i] = 0u;
-            __syncthreads();
-            for (uint32_t i = tid; i < D; i += HT) {
-                const uint32_t e = A.adj[s0 + i];
-                L.P[i] = e;
-                const uint32_t b = bloom_bit(e >> 2);
-                atomicOr(&L.bloomP[b >> 5], 1u << (b & 31u));
-            }
-            __syncthreads();
-            if (tid == 0) L.root = r;
-        }
-        const uint32_t ea = task.y;   // the slot's entry in r's row
-        const uint32_t va = ea >> 2, ra = ea & 3u;
-        const uint32_t hi = A.off[va + 1], lo = first_above(A.adj, A.off[va], hi, r);
-        for (uint32_t i = tid; i < BLOOM_WORDS; i += HT) L.bloomC[i] = 0u;
-        for (uint32_t i = tid; i < kClasses4; i += HT) {
-            L.root4[i] = 0u;
-            L.ah[i] = 0u;
-        }
-        for (uint32_t i = tid; i < NW * CW; i += HT) L.CA[i] = 0u;
-        if (tid < 4) L.ctr[tid] = 0u;
-        __syncthreads();
-        // children in rank order (one wave compacts the row)
-        if (wid == 0) {
-            uint32_t m = 0;
-            for (uint32_t q0 = lo; q0 < hi; q0 += 64) {
-                const uint32_t q = q0 + lane;
-                bool chd = false;
-                uint32_t ent = 0;
-                if (q < hi) {
-                    ent = A.adj[q];
-                    const uint32_t e = ent >> 2;
-                    chd = !bloom_has(L.bloomP, e) || sorted_find(L.P, D, e) < 0;
-                }
-                const unsigned long long mc = __ballot(chd);
-                if (chd) {
-                    const uint32_t pos = m + (uint32_t)__popcll(mc & ((1ull << lane) - 1ull));
-                    L.CL[pos] = ent;
-                    const uint32_t b = bloom_bit(ent >> 2);
-                    atomicOr(&L.bloomC[b >> 5], 1u << (b & 31u));
-                }
-                m += (uint32_t)__popcll(mc);
-            }
-            if (lane == 0) sM = m;
-        }
-        __syncthreads();
-        const uint32_t m = sM;
-        for (uint32_t i = tid; i < m * CTW; i += HT) L.CC[i] = 0u;
-        __syncthreads();
-        uint32_t* CA = L.CA + wid * CW;
-        for (;;) {
-            const uint32_t i = wave_task(&L.ctr[0]) * G + share;
-            if (i >= m) break;
-            const uint32_t vc = L.CL[i] >> 2, ac = L.CL[i] & 3u;
-            const uint32_t chi = A.off[vc + 1];
-            for (uint32_t t0 = first_above(A.adj, A.off[vc], chi, r); t0 < chi; t0 += 64) {
-                const uint32_t tq = t0 + lane;
-                bool p111 = false;
-                uint32_t cls = 0xFFu, ve = 0;
-                if (tq < chi) {
-                    ve = A.adj[tq] >> 2;
-                    const uint32_t ce = A.adj[tq] & 3u;
-                    const int pos = bloom_has(L.bloomC, ve) ? sorted_find(L.CL, m, ve) : -1;
-                    if (pos >= 0) {
-                        if ((uint32_t)pos > i) atomicOr(&CA[pos >> 4], ce << ((pos & 15) << 1));
-                    } else if (!bloom_has(L.bloomP, ve) || sorted_find(L.P, D, ve) < 0) {
-                        p111 = true;   // e above r, not adjacent to r nor to a
-                        cls = L.t4[motif_index4(ra, 0u, 0u, ac, 0u, ce)];
-                    }
-                }
-                by_class(cls, p111, [&](uint32_t k, uint32_t n) {
-                    atomicAdd(&L.root4[k], n);
-                    atomicAdd(&L.ah[k], n);
-                    const uint32_t s = L.tree_of[k];
-                    if (s < NTREE) cc_add(i, s, n);
-                    else gadd(A.out4, A.perm, kClasses4, vc, k, n);
-                });
-                if (p111) {
-                    gadd(A.out4, A.perm, kClasses4, ve, cls, 1ull);
-                    shp[5]++;
-                }
-            }
-            __threadfence_block();
-            for (uint32_t j0 = i + 1; j0 < m; j0 += 64) {
-                const uint32_t j = j0 + lane;
-                const bool in = j < m;
-                uint32_t cls = 0xFFu;
-                if (in) cls = L.t4[motif_index4(ra, 0u, 0u, ac, L.CL[j] & 3u, code_at(CA, j))];
-                by_class(cls, in, [&](uint32_t k, uint32_t n) {
-                    atomicAdd(&L.root4[k], n);
-                    atomicAdd(&L.ah[k], n);
-                    const uint32_t s = L.tree_of[k];
-                    if (s < NTREE) cc_add(i, s, n);
-                    else gadd(A.out4, A.perm, kClasses4, vc, k, n);
-                });
-                if (in) {
-                    const uint32_t s = L.tree_of[cls];
-                    if (s < NTREE) cc_add(j, s, 1u);
-                    else gadd(A.out4, A.perm, kClasses4, L.CL[j] >> 2, cls, 1ull);
-                    shp[4]++;
-                }
-            }
-            __threadfence_block();
-            for (uint32_t w = lane; w < CW; w += 64) CA[w] = 0u;
-            __threadfence_block();
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < m * NTREE; i += HT) {
-            const uint32_t pos = i / NTREE, s = i - pos * NTREE;
-            const uint32_t x = (L.CC[pos * CTW + (s >> 1)] >> ((s & 1u) << 4)) & 0xFFFFu;
-            if (x) gadd(A.out4, A.perm, kClasses4, L.CL[pos] >> 2, A.tree_cls[s], x);
-        }
-        for (uint32_t i = tid; i < kClasses4; i += HT) {
-            if (L.root4[i]) gadd(A.out4, A.perm, kClasses4, r, i, L.root4[i]);
-            if (L.ah[i]) gadd(A.out4, A.perm, kClasses4, va, i, L.ah[i]);
-        }
-    }
-    for (int s = 0; s < kShapes; s++) {
-        unsigned long long x = shp[s];
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if (lane == 0 && x) atomicAdd(&A.stats[s], x);
+// the compact rows of the hub path added to the output (48 lanes per vertex; one writer per cell)
+__global__ __launch_bounds__(192) void k_expand(const void* cmp, int wide, int64_t n, const int32_t* __restrict__ perm,
+                                                const uint8_t* __restrict__ cmp_cls, unsigned long long* out4) {
+    const uint32_t s = threadIdx.x % kCmpRow, cls = cmp_cls[s];
+    for (int64_t v = blockIdx.x * 4ll + threadIdx.x / kCmpRow; v < n; v += gridDim.x * 4ll) {
+        const size_t at = (size_t)v * kCmpRow + s;
+        const unsigned long long x = wide ? ((const unsigned long long*)cmp)[at] : ((const uint32_t*)cmp)[at];
+        if (x) out4[(size_t)perm[v] * kClasses4 + cls] += x;
     }
 }
 
@@ -1249,22 +1145,6 @@ __global__ void k_root_work(const uint32_t* __restrict__ off, const uint32_t* __
     }
 }
 
-// per hub root (queue order): entries of its slots' rows above r, and |N+(r)|
-__global__ void k_hub_s2(const uint32_t* __restrict__ off, const uint32_t* __restrict__ adj,
-                         const uint32_t* __restrict__ split, const uint32_t* __restrict__ hubs, int64_t nhub,
-                         uint32_t* __restrict__ s2out, unsigned long long* __restrict__ dsum) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nhub; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t r = hubs[i];
-        uint32_t s2 = 0;
-        for (uint32_t t = split[r]; t < off[r + 1]; t++) {
-            const uint32_t a = adj[t] >> 2;
-            s2 += off[a + 1] - lower_bound_rank(adj, off[a], off[a + 1], r + 1);
-        }
-        s2out[i] = s2;
-        atomicAdd(dsum, (unsigned long long)(off[r + 1] - split[r]));
-    }
-}
-
 __global__ void k_split_bins(const uint32_t* __restrict__ roots, const uint32_t* __restrict__ is_hub,
                              const uint32_t* __restrict__ pos, int64_t nroots, uint32_t* __restrict__ light) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nroots; i += (int64_t)gridDim.x * blockDim.x)
@@ -1292,12 +1172,10 @@ int hub_workgroups() {
 }  // namespace
 
 void free_hub_scratch(vdmc_graph_s* g) {
-    if (!g->hub_scratch && !g->hub_tasks) return;
+    if (!g->hub_scratch) return;
     wait_graph(g);
     (void)hipFree(g->hub_scratch);
-    (void)hipFree(g->hub_tasks);
     g->hub_scratch = nullptr;
-    g->hub_tasks = nullptr;
     g->hub_scratch_bytes = 0;
 }
 
@@ -1307,10 +1185,8 @@ void free_hub(vdmc_graph_s* g) {
     (void)hipFree(g->light);
     (void)hipFree(g->hubs);
     (void)hipFree(g->hub_queue);
-    (void)hipFree(g->hub_s2);
     g->light = g->hubs = nullptr;
     g->hub_queue = nullptr;
-    g->hub_s2 = nullptr;
     g->hub_scratch_need = 0;
     g->nhub = g->nlight = 0;
     g->bins_hub_min = -1;
@@ -1320,15 +1196,8 @@ size_t hub_scratch_need(const vdmc_graph_s* g) { return g->nhub > 0 ? g->hub_scr
 
 void ensure_hub_scratch(vdmc_graph_s* g) {
     if (g->nhub == 0 || g->hub_scratch) return;
-    const size_t wg_bytes = g->hub_layout[0] * sizeof(uint32_t) * (size_t)hub_workgroups();
-    VDMC_HIP(hipMalloc(&g->hub_scratch, wg_bytes));
-    const hipError_t e = hipMalloc(&g->hub_tasks, (size_t)g->hub_task_cap * sizeof(uint2));
-    if (e != hipSuccess) {
-        (void)hipFree(g->hub_scratch);
-        g->hub_scratch = nullptr;
-        VDMC_HIP(e);
-    }
-    g->hub_scratch_bytes = wg_bytes + (size_t)g->hub_task_cap * sizeof(uint2);
+    VDMC_HIP(hipMalloc(&g->hub_scratch, g->hub_scratch_need));
+    g->hub_scratch_bytes = g->hub_scratch_need;
 }
 
 void ensure_edge_hash(vdmc_graph_s* g, hipStream_t st) {
@@ -1375,7 +1244,6 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     unsigned long long* d_max = (unsigned long long*)alloc(4 * sizeof(unsigned long long));
     VDMC_HIP(hipMemsetAsync(d_max, 0, 4 * sizeof(unsigned long long), st));
     unsigned* d_maxhi = (unsigned*)(d_max + 1);
-    unsigned long long* d_dsum = d_max + 2;
     int64_t nhub = 0, nlight = 0;
     std::vector<unsigned long long> hub_keys;   // sorted work keys of the hub roots (~work)
     unsigned long long max_s2 = 0;
@@ -1443,27 +1311,29 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     g->light_max_d = hub_ok ? std::min<int32_t>((int32_t)maxhi, hub_min - 1) : (int32_t)maxhi;
     VDMC_HIP(hipMalloc(&g->hub_queue, 64));
     if (nhub > 0) {
-        VDMC_HIP(hipMalloc(&g->hub_s2, nhub * sizeof(uint32_t)));
-        const unsigned hb = (unsigned)std::min<int64_t>((nhub + BT - 1) / BT, 65536);
-        hipLaunchKernelGGL(k_hub_s2, dim3(hb), dim3(BT), 0, st, g->off, g->adj, g->split, g->hubs, nhub, g->hub_s2,
-                           d_dsum);
-        VDMC_HIP(hipGetLastError());
-        unsigned long long dsum = 0;
-        VDMC_HIP(hipMemcpyAsync(&dsum, d_dsum, sizeof(dsum), hipMemcpyDeviceToHost, st));
-        VDMC_HIP(hipStreamSynchronize(st));
         const int wgs = hub_workgroups();
         const size_t s2cap = (size_t)max_s2 + 64;
-        size_t tcap = 64;
-        while (tcap < 2 * s2cap + 64) tcap <<= 1;
-        const size_t words = (DMAX + 2) + s2cap + (s2cap & 1) + 2 * s2cap + s2cap + 2 * tcap;
+        const size_t words = (DMAX + 2) + 8 * s2cap + 4 + 2 * (((size_t)g->n + 31) / 32);
         const size_t wg_words = (words + 63) & ~(size_t)63;
         g->hub_layout[0] = wg_words;
         g->hub_layout[1] = s2cap;
-        g->hub_layout[2] = tcap;
-        // long-slot tasks: at most one per (hub root, slot)
-        const size_t ntask = (size_t)std::max<unsigned long long>(dsum, 1ull);
-        g->hub_task_cap = (uint32_t)std::min<size_t>(ntask, 0xFFFFFFFFu);
-        g->hub_scratch_need = wg_words * sizeof(uint32_t) * (size_t)wgs + (size_t)g->hub_task_cap * sizeof(uint2);
+        // Workgroups (hub_layout[5]): one per compute unit, no more than there are roots and
+        // shares of roots.  Compact rows (hub_layout[6]: 0 none, 1 32-bit, 2 64-bit counters): a
+        // class of a vertex has at most 2 max_deg^3 paths or stars in a call, which 32 bits hold
+        // up to degree 1290.  Together they stay within the scratch of one workgroup per
+        // compute unit; graphs whose rows would take more than half of that go without.
+        const size_t wg_bytes = wg_words * sizeof(uint32_t), room = wg_bytes * (size_t)wgs;
+        const double dm = (double)g->max_deg;
+        const int wide = 2.0 * dm * dm * dm >= 4294967296.0 ? 1 : 0;
+        const size_t rows = (((size_t)g->n * kCmpRow * (wide ? 8 : 4)) + 255) & ~(size_t)255;
+        const bool use_rows = rows <= room / 2;
+        const size_t parts = (size_t)nhub + g->hub_layout[3] * (std::max<size_t>(1, g->hub_layout[4]) - 1);
+        size_t nwg = std::min<size_t>((size_t)wgs, parts);
+        if (use_rows) nwg = std::max<size_t>(1, std::min(nwg, (room - rows) / wg_bytes));
+        g->hub_layout[5] = nwg;
+        g->hub_layout[6] = use_rows ? 1 + wide : 0;
+        g->hub_layout[7] = use_rows ? rows : 0;
+        g->hub_scratch_need = g->hub_layout[7] + wg_bytes * nwg;
     }
     g->bins_hub_min = hub_min;
 }
@@ -1479,7 +1349,6 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.split = g->split;
     a.perm = g->perm;
     a.hubs = g->hubs;
-    a.hub_s2 = g->hub_s2;
     a.nhub = (uint32_t)g->nhub;
     a.cursor = g->hub_queue;
     a.t3 = t.t3;
@@ -1487,7 +1356,7 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.maps = t.maps4;
     a.star_cls = t.star_cls;
     a.path_cls = t.path_cls;
-    a.tree_cls = t.slotcls;
+    a.cmp_cls = t.cmp_cls;
     a.out3 = (unsigned long long*)out3;
     a.out4 = (unsigned long long*)out4;
     a.stats = g->stats;
@@ -1495,23 +1364,27 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.k4 = k4;
     a.rank_lo = rank_lo;
     a.rank_hi = rank_hi;
-    a.scratch = (uint32_t*)g->hub_scratch;
+    // the compact rows come first, then the workgroups' scratch
+    a.n = (uint32_t)g->n;
+    a.cmp = k4 && g->hub_layout[6] ? g->hub_scratch : nullptr;
+    a.cmp_wide = g->hub_layout[6] == 2;
+    a.scratch = (uint32_t*)((char*)g->hub_scratch + g->hub_layout[7]);
     a.wg_words = g->hub_layout[0];
     a.s2cap = (uint32_t)g->hub_layout[1];
-    a.tcap = (uint32_t)g->hub_layout[2];
-    a.tasks = (uint2*)g->hub_tasks;
-    a.task_cap = g->hub_task_cap;
-    const int wgs = hub_workgroups();
+    const unsigned wgs = (unsigned)g->hub_layout[5];
     a.split_roots = (uint32_t)g->hub_layout[3];   // the heaviest hub roots, shared (set at binning)
     a.shares = (uint32_t)std::max<size_t>(1, g->hub_layout[4]);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, g->hub_queue, 16);
+    if (a.cmp) launch_fill_u64((uint64_t*)a.cmp, g->hub_layout[7] / 8, 0, st);
     // around[0] and around[1] bracket the hub path, around[2] marks the end of k_hub
     if (around) VDMC_HIP(hipEventRecord(around[0], st));
     hipLaunchKernelGGL(k_hub, dim3(wgs), dim3(HT), 0, st, a);
     VDMC_HIP(hipGetLastError());
     if (around) VDMC_HIP(hipEventRecord(around[2], st));
-    if (k4) {
-        hipLaunchKernelGGL(k_long_slots, dim3(wgs), dim3(HT), 0, st, a);
+    if (a.cmp) {
+        const unsigned blocks = (unsigned)std::min<int64_t>((g->n + 3) / 4, 65536);
+        hipLaunchKernelGGL(k_expand, dim3(blocks), dim3(4 * kCmpRow), 0, st, a.cmp, a.cmp_wide, g->n, g->perm, a.cmp_cls,
+                           a.out4);
         VDMC_HIP(hipGetLastError());
     }
     if (around) VDMC_HIP(hipEventRecord(around[1], st));

@@ -87,15 +87,21 @@ inline int num_classes(int k) {
 constexpr int kCompact4 = 25;
 // the hub path takes graphs whose largest degree is at most this (slot and child lists in LDS)
 constexpr uint32_t kHubMaxDegree = 2048;
+// Compact rows: per vertex, kCmpRow counters of the most frequent 4-vertex classes, in three
+// 64-byte lines of 32-bit counters (paths, stars, 4-cycles), added to the output after the
+// kernels that use them.  A memory-side atomic instruction costs the same whether its lanes
+// add to one counter of a 64-byte line or to all of them (2.4e10 lines/s measured).
+constexpr uint32_t kCmpRow = 48;
 
 struct ClassTables {
     const uint8_t* t3;   // 64 entries
     const uint8_t* t4;   // 4096 entries
     const uint8_t* slot4;     // 199 entries: class -> compact slot or 0xFF
     const uint8_t* slotcls;   // kCompact4 entries: compact slot -> class
-    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), tree slot (25); 0xFF none
+    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), compact counter; 0xFF none
     const uint8_t* star_cls;  // 10 entries: star slot -> class
     const uint8_t* path_cls;  // 30 entries: path or 4-cycle slot -> class
+    const uint8_t* cmp_cls;   // kCmpRow entries: compact counter -> class
     std::vector<uint8_t> host3, host4;
     std::vector<uint16_t> codes3, codes4;
 };
@@ -149,11 +155,8 @@ struct vdmc_graph_s {
     // hub-path scratch (per workgroup slices), sized for this graph
     void* hub_scratch = nullptr;
     size_t hub_scratch_bytes = 0;
-    unsigned* hub_queue = nullptr;   // root cursor, long-slot task count and cursor
-    uint32_t* hub_s2 = nullptr;      // per hub root: entries of its slots' rows above it
-    void* hub_tasks = nullptr;       // long-slot tasks (hub index, slot)
-    uint32_t hub_task_cap = 0;
-    size_t hub_scratch_need = 0;     // bytes of hub_scratch + hub_tasks for the current bins
+    unsigned* hub_queue = nullptr;   // root cursor
+    size_t hub_scratch_need = 0;     // bytes of hub_scratch for the current bins
     unsigned long long* ehash = nullptr;   // edge hash: every pair of the graph, 2^ehash_bits slots
     uint32_t ehash_bits = 0;
     uint32_t* epid = nullptr;    // per edge-hash slot: output row of the pair (per-edge counts)
