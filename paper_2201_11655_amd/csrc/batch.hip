@@ -37,7 +37,8 @@ struct Plan {
     uint8_t* d_generic = nullptr;
     uint2* d_table = nullptr;
     unsigned long long* d_cursor = nullptr;
-    unsigned long long nentries = 0;
+    unsigned long long nentries = 0;   // pairs of the per-set kernel (behind the light tiers')
+    unsigned long long nlight[3] = {0, 0, 0};
     SmallGraph* d_small = nullptr;     // graphs counted whole by one workgroup
     std::vector<char> is_small;
     uint32_t nsmall = 0;
@@ -88,10 +89,9 @@ BatchKey key_of(const vdmc_graph* gs, int num, int k) {
 
 __global__ void k_fill_table(const uint32_t* const* lists, const unsigned long long* counts,
                              const unsigned long long* offsets, int num, uint2* table) {
-    const int gi = blockIdx.x;
-    if (gi >= num) return;
-    const uint32_t* l = lists[gi];
-    const unsigned long long n = counts[gi], o = offsets[gi];
+    const int gi = blockIdx.x % num, at = blockIdx.x;   // lists by tier, then graph
+    const uint32_t* l = lists[at];
+    const unsigned long long n = counts[at], o = offsets[at];
     for (unsigned long long i = threadIdx.x; i < n; i += blockDim.x) table[o + i] = make_uint2((unsigned)gi, l[i]);
 }
 
@@ -103,6 +103,7 @@ BatchArgs args_of(const Plan& p) {
     b.generic = p.d_generic;
     b.table = p.d_table;
     b.nentries = p.nentries;
+    for (int t = 0; t < 3; t++) b.nlight[t] = p.nlight[t];
     b.cursor = p.d_cursor;
     b.tile = p.cfg.tile;
     b.t3 = t.t3;
@@ -132,8 +133,9 @@ Plan* build_plan(const vdmc_graph* gs, int num, int k, uint64_t* const* outs, co
         std::vector<GraphView> views(num);
         std::vector<uint64_t> nvert(num);
         std::vector<uint8_t> generic(num, 0);
-        std::vector<const uint32_t*> lists(num);
-        std::vector<unsigned long long> counts(num), offsets(num);
+        // (graph, root) lists by tier, then graph
+        std::vector<const uint32_t*> lists(4 * (size_t)num);
+        std::vector<unsigned long long> counts(4 * (size_t)num), offsets(4 * (size_t)num);
         std::vector<uint32_t> small;
         unsigned long long total = 0;
         p->is_small.assign(num, 0);
@@ -153,12 +155,21 @@ Plan* build_plan(const vdmc_graph* gs, int num, int k, uint64_t* const* outs, co
                                  k == 4 ? (unsigned long long*)outs[i] : nullptr, g->stats, g->ehash,
                                  g->ehash_bits};
             nvert[i] = (uint64_t)g->n;
-            lists[i] = g->light;
-            counts[i] = p->is_small[i] ? 0ull : (unsigned long long)g->nlight;
-            offsets[i] = total;
-            total += counts[i];
+            const uint32_t* l = g->light;
+            for (int t = 0; t < 4; t++) {
+                lists[(size_t)t * num + i] = l;
+                counts[(size_t)t * num + i] = p->is_small[i] ? 0ull : (unsigned long long)g->ntier[t];
+                l += g->ntier[t];
+            }
         }
-        p->nentries = total;
+        for (int t = 0; t < 4; t++) {
+            const unsigned long long before = total;
+            for (int i = 0; i < num; i++) {
+                offsets[(size_t)t * num + i] = total;
+                total += counts[(size_t)t * num + i];
+            }
+            (t < 3 ? p->nlight[t] : p->nentries) = total - before;
+        }
         // largest work first (pairs x largest degree as the estimate), so that the last
         // workgroups to finish hold small graphs
         std::stable_sort(small.begin(), small.end(), [&](uint32_t a, uint32_t b) {
@@ -188,13 +199,15 @@ Plan* build_plan(const vdmc_graph* gs, int num, int k, uint64_t* const* outs, co
         VDMC_HIP(hipMemcpyAsync(p->d_generic, generic.data(), num, hipMemcpyHostToDevice, st));
         const uint32_t** d_lists = nullptr;
         unsigned long long *d_counts = nullptr, *d_offsets = nullptr;
-        VDMC_HIP(hipMalloc(&d_lists, sizeof(void*) * num));
-        VDMC_HIP(hipMalloc(&d_counts, sizeof(unsigned long long) * num));
-        VDMC_HIP(hipMalloc(&d_offsets, sizeof(unsigned long long) * num));
-        VDMC_HIP(hipMemcpyAsync(d_lists, lists.data(), sizeof(void*) * num, hipMemcpyHostToDevice, st));
-        VDMC_HIP(hipMemcpyAsync(d_counts, counts.data(), sizeof(unsigned long long) * num, hipMemcpyHostToDevice, st));
-        VDMC_HIP(hipMemcpyAsync(d_offsets, offsets.data(), sizeof(unsigned long long) * num, hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(k_fill_table, dim3(num), dim3(256), 0, st, d_lists, d_counts, d_offsets, num, p->d_table);
+        VDMC_HIP(hipMalloc(&d_lists, sizeof(void*) * lists.size()));
+        VDMC_HIP(hipMalloc(&d_counts, sizeof(unsigned long long) * counts.size()));
+        VDMC_HIP(hipMalloc(&d_offsets, sizeof(unsigned long long) * offsets.size()));
+        VDMC_HIP(hipMemcpyAsync(d_lists, lists.data(), sizeof(void*) * lists.size(), hipMemcpyHostToDevice, st));
+        VDMC_HIP(hipMemcpyAsync(d_counts, counts.data(), sizeof(unsigned long long) * counts.size(), hipMemcpyHostToDevice,
+                                st));
+        VDMC_HIP(hipMemcpyAsync(d_offsets, offsets.data(), sizeof(unsigned long long) * offsets.size(),
+                                hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(k_fill_table, dim3(4 * num), dim3(256), 0, st, d_lists, d_counts, d_offsets, num, p->d_table);
         VDMC_HIP(hipGetLastError());
         VDMC_HIP(hipStreamSynchronize(st));
         (void)hipFree(d_lists);

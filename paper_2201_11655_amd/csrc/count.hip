@@ -366,10 +366,7 @@ __global__ void k_batch_zero(BatchArgs b, int k3, int k4) {
     if (k4)
         for (size_t i = threadIdx.x; i < n * kClasses4; i += blockDim.x) g.out4[i] = 0;
     for (int i = threadIdx.x; i < kStatSlots; i += blockDim.x) g.stats[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *b.cursor = 0;
-        *b.gcursor = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x < 8) b.cursor[threadIdx.x] = 0;   // every cursor, the graph cursor too
 }
 
 __global__ void k_fill(unsigned long long* p, size_t n, unsigned long long v) {
@@ -396,12 +393,25 @@ void launch_batch(const BatchArgs& b, const SmallArgs* small, unsigned small_gri
         VDMC_REQUIRE(k3 != k4, VDMC_ERR_INVALID_ARG, "a batch counts one k");
         launch_small(*small, k3 ? 3 : 4, small_variant, small_grid, small_lds, st);
     }
+    const uint2* table = b.table;
+    for (int t = 0; t < 3; t++) {   // the light tiers' parts of the table, a cursor each
+        LightArgs l{};
+        l.graphs = b.graphs;
+        l.table = table;
+        l.nroots = (int64_t)b.nlight[t];
+        l.cursor = b.cursor + 2 + t;
+        l.tile = (unsigned)b.tile;
+        launch_light(l, t, k3, k4, st);
+        table += b.nlight[t];
+    }
     if (b.nentries == 0) return;
+    BatchArgs rest = b;
+    rest.table = table;
 #define VDMC_BATCH_LAUNCH(BS, STG)                                                                           \
     do {                                                                                                    \
-        if (k3 && k4) hipLaunchKernelGGL((k_count_batch<BS, STG, true, true>), dim3(grid), dim3(BS), 0, st, b); \
-        else if (k3) hipLaunchKernelGGL((k_count_batch<BS, STG, true, false>), dim3(grid), dim3(BS), 0, st, b); \
-        else hipLaunchKernelGGL((k_count_batch<BS, STG, false, true>), dim3(grid), dim3(BS), 0, st, b);         \
+        if (k3 && k4) hipLaunchKernelGGL((k_count_batch<BS, STG, true, true>), dim3(grid), dim3(BS), 0, st, rest); \
+        else if (k3) hipLaunchKernelGGL((k_count_batch<BS, STG, true, false>), dim3(grid), dim3(BS), 0, st, rest); \
+        else hipLaunchKernelGGL((k_count_batch<BS, STG, false, true>), dim3(grid), dim3(BS), 0, st, rest);         \
     } while (0)
     switch (variant) {
         case 0: VDMC_BATCH_LAUNCH(64, 256); break;
@@ -438,34 +448,49 @@ void launch_count(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out
         for (auto& e : g->ev) VDMC_HIP(hipEventCreate(&e));
     if (g->nlight > 0) {
         VDMC_HIP(hipEventRecord(g->ev[0], st));
-        Args a;
-        a.off = g->off;
-        a.adj = g->adj;
-        a.split = g->split;
-        a.perm = g->perm;
-        a.roots = g->light;
-        a.nroots = g->nlight;
-        a.t3 = t.t3;
-        a.t4 = t.t4;
-        a.out3 = (unsigned long long*)out3;
-        a.out4 = (unsigned long long*)out4;
-        a.stats = g->stats;
-        a.rank_lo = lo;
-        a.rank_hi = hi;
-        a.ehash = g->ehash;
-        a.ehash_bits = g->ehash_bits;
-        const int64_t blocks = g->nlight < 65536 ? g->nlight : 65536;
-        const dim3 grid((unsigned)blocks);
-        if (g->light_max_d <= 64) {   // every light root has at most 64 higher neighbours
-            if (k3 && k4) hipLaunchKernelGGL((k_count_roots<64, 64, true, true>), grid, dim3(64), 0, st, a);
-            else if (k3) hipLaunchKernelGGL((k_count_roots<64, 64, true, false>), grid, dim3(64), 0, st, a);
-            else hipLaunchKernelGGL((k_count_roots<64, 64, false, true>), grid, dim3(64), 0, st, a);
-        } else {
-            if (k3 && k4) hipLaunchKernelGGL((k_count_roots<kThreads, kStage, true, true>), grid, dim3(kThreads), 0, st, a);
-            else if (k3) hipLaunchKernelGGL((k_count_roots<kThreads, kStage, true, false>), grid, dim3(kThreads), 0, st, a);
-            else hipLaunchKernelGGL((k_count_roots<kThreads, kStage, false, true>), grid, dim3(kThreads), 0, st, a);
+        LightArgs l{};
+        l.gv = GraphView{g->off, g->adj, g->split, g->perm, (unsigned long long*)out3, (unsigned long long*)out4,
+                         g->stats, nullptr, 0};
+        l.rank_lo = lo;
+        l.rank_hi = hi;
+        l.roots = g->light;
+        // few roots in all: the first two tiers in one launch
+        const bool merge = g->ntier[0] + g->ntier[1] <= 1024;
+        for (int t = merge ? 1 : 0; t < 3; t++) {
+            l.nroots = merge && t == 1 ? g->ntier[0] + g->ntier[1] : g->ntier[t];
+            launch_light(l, t, k3, k4, st);
+            l.roots += l.nroots;
         }
-        VDMC_HIP(hipGetLastError());
+        if (g->ntier[3] > 0) {
+            Args a;
+            a.off = g->off;
+            a.adj = g->adj;
+            a.split = g->split;
+            a.perm = g->perm;
+            a.roots = l.roots;
+            a.nroots = g->ntier[3];
+            a.t3 = t.t3;
+            a.t4 = t.t4;
+            a.out3 = (unsigned long long*)out3;
+            a.out4 = (unsigned long long*)out4;
+            a.stats = g->stats;
+            a.rank_lo = lo;
+            a.rank_hi = hi;
+            a.ehash = g->ehash;
+            a.ehash_bits = g->ehash_bits;
+            const int64_t blocks = std::min<int64_t>(g->ntier[3], 65536);
+            const dim3 grid((unsigned)blocks);
+            if (g->light_max_d <= 64) {   // every light root has at most 64 higher neighbours
+                if (k3 && k4) hipLaunchKernelGGL((k_count_roots<64, 64, true, true>), grid, dim3(64), 0, st, a);
+                else if (k3) hipLaunchKernelGGL((k_count_roots<64, 64, true, false>), grid, dim3(64), 0, st, a);
+                else hipLaunchKernelGGL((k_count_roots<64, 64, false, true>), grid, dim3(64), 0, st, a);
+            } else {
+                if (k3 && k4) hipLaunchKernelGGL((k_count_roots<kThreads, kStage, true, true>), grid, dim3(kThreads), 0, st, a);
+                else if (k3) hipLaunchKernelGGL((k_count_roots<kThreads, kStage, true, false>), grid, dim3(kThreads), 0, st, a);
+                else hipLaunchKernelGGL((k_count_roots<kThreads, kStage, false, true>), grid, dim3(kThreads), 0, st, a);
+            }
+            VDMC_HIP(hipGetLastError());
+        }
         VDMC_HIP(hipEventRecord(g->ev[1], st));
         g->timed_light = true;
     }

@@ -1116,39 +1116,41 @@ __global__ void k_edge_hash(const uint32_t* __restrict__ off, const uint32_t* __
     }
 }
 
-// per root: hub or not and its work estimate (sort key); the largest slot-row scan and
-// the largest |N+(r)|
-__global__ void k_root_work(const uint32_t* __restrict__ off, const uint32_t* __restrict__ adj,
-                            const uint32_t* __restrict__ split, const uint32_t* __restrict__ roots, int64_t nroots,
-                            uint32_t hub_min, uint32_t hub_ok, uint32_t* __restrict__ is_hub,
-                            unsigned long long* __restrict__ wkey, unsigned long long* __restrict__ max_s2,
-                            unsigned* __restrict__ max_hi) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nroots; i += (int64_t)gridDim.x * blockDim.x) {
+// Per root, 16 lanes: the entries s2 of its slots' rows above it, its bin and sort key.  Hub
+// roots come first, largest estimated work first, then the light tiers.  tot: [0] largest s2
+// of a hub root, [1] largest |N+(r)| of all roots, [2..6] roots per bin (hubs, tiers 0..3).
+__global__ __launch_bounds__(256) void k_root_work(const uint32_t* __restrict__ off, const uint32_t* __restrict__ adj,
+                                                   const uint32_t* __restrict__ split,
+                                                   const uint32_t* __restrict__ roots, int64_t nroots,
+                                                   uint32_t hub_min, uint32_t hub_ok, uint32_t light_ok,
+                                                   unsigned long long* __restrict__ wkey,
+                                                   unsigned long long* __restrict__ tot) {
+    __shared__ unsigned long long sh[8];
+    if (threadIdx.x < 8) sh[threadIdx.x] = 0ull;
+    __syncthreads();
+    const uint32_t gl = threadIdx.x & 15u;
+    for (int64_t i = blockIdx.x * 16ll + threadIdx.x / 16; i < nroots; i += gridDim.x * 16ll) {
         const uint32_t r = roots[i];
         const uint32_t s = split[r], e = off[r + 1], d = e - s;
-        atomicMax(max_hi, d);
-        const bool hub = hub_ok && d >= hub_min && d <= DMAX;
-        is_hub[i] = hub ? 1u : 0u;
-        if (!hub) {
-            wkey[i] = ~0ull;
-            continue;
-        }
         unsigned long long s2 = 0;
-        for (uint32_t t = s; t < e; t++) {
+        for (uint32_t t = s + gl; t < e; t += 16u) {
             const uint32_t a = adj[t] >> 2;
             s2 += off[a + 1] - lower_bound_rank(adj, off[a], off[a + 1], r + 1);
         }
-        atomicMax(max_s2, s2);
+        for (int o = 8; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 64);
+        if (gl != 0u) continue;
+        int tier = light_ok ? light_tier(d, s2) : 3;
+        // hub path: from hub_min higher neighbours on, and roots too large for the light kernel
+        const bool hub = hub_ok && d <= DMAX && (d >= hub_min || (tier == 3 && d <= 32u));
         const unsigned long long dd = d;
-        const unsigned long long w = dd * (dd - 1) * (dd - 2) / 6 + s2 * dd + s2 + 1;
-        wkey[i] = ~w;   // ascending sort of ~w = largest work first; non-hubs (~0) last
+        wkey[i] = hub ? ~(dd * (dd - 1) * (dd - 2) / 100 + 150 * s2 + 4) : ~0ull - 3ull + (unsigned long long)tier;
+        atomicMax(&sh[1], dd);
+        if (hub) atomicMax(&sh[0], s2);
+        atomicAdd(&sh[hub ? 2 : 3 + tier], 1ull);
     }
-}
-
-__global__ void k_split_bins(const uint32_t* __restrict__ roots, const uint32_t* __restrict__ is_hub,
-                             const uint32_t* __restrict__ pos, int64_t nroots, uint32_t* __restrict__ light) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nroots; i += (int64_t)gridDim.x * blockDim.x)
-        if (!is_hub[i]) light[i - pos[i]] = roots[i];
+    __syncthreads();
+    if (threadIdx.x < 2) atomicMax(&tot[threadIdx.x], sh[threadIdx.x]);
+    else if (threadIdx.x < 7 && sh[threadIdx.x]) atomicAdd(&tot[threadIdx.x], sh[threadIdx.x]);
 }
 
 __global__ void k_zero_u32(unsigned* p, int n) {
@@ -1182,7 +1184,6 @@ void free_hub_scratch(vdmc_graph_s* g) {
 void free_hub(vdmc_graph_s* g) {
     wait_graph(g);
     free_hub_scratch(g);
-    (void)hipFree(g->light);
     (void)hipFree(g->hubs);
     (void)hipFree(g->hub_queue);
     g->light = g->hubs = nullptr;
@@ -1236,54 +1237,35 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     // the hub path needs every degree <= DMAX (a slot's children fit the LDS lists) and
     // ranks below 2^26 (per-wave child hash keys)
     const uint32_t hub_ok = (g->max_deg <= (int32_t)DMAX && g->n < ((int64_t)1 << 26)) ? 1u : 0u;
-    uint32_t* is_hub = (uint32_t*)alloc((nr + 1) * sizeof(uint32_t));
-    uint32_t* pos = (uint32_t*)alloc((nr + 1) * sizeof(uint32_t));
+    const uint32_t light_ok = g->max_deg < kLightMaxDegree ? 1u : 0u;
     unsigned long long* wkey = (unsigned long long*)alloc((nr + 1) * sizeof(unsigned long long));
     unsigned long long* wkey_s = (unsigned long long*)alloc((nr + 1) * sizeof(unsigned long long));
-    uint32_t* roots_s = (uint32_t*)alloc((nr + 1) * sizeof(uint32_t));
-    unsigned long long* d_max = (unsigned long long*)alloc(4 * sizeof(unsigned long long));
-    VDMC_HIP(hipMemsetAsync(d_max, 0, 4 * sizeof(unsigned long long), st));
-    unsigned* d_maxhi = (unsigned*)(d_max + 1);
-    int64_t nhub = 0, nlight = 0;
+    unsigned long long* d_tot = (unsigned long long*)alloc(8 * sizeof(unsigned long long));
+    unsigned long long tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int64_t nhub = 0;
     std::vector<unsigned long long> hub_keys;   // sorted work keys of the hub roots (~work)
-    unsigned long long max_s2 = 0;
-    unsigned maxhi = 0;
+    VDMC_HIP(hipMalloc(&g->hubs, (nr + 1) * sizeof(uint32_t)));
     if (nr > 0) {
-        unsigned blocks = (unsigned)std::min<int64_t>((nr + BT - 1) / BT, 65536);
-        hipLaunchKernelGGL(k_root_work, dim3(blocks), dim3(BT), 0, st, g->off, g->adj, g->split, g->roots, nr,
-                           (uint32_t)hub_min, hub_ok, is_hub, wkey, d_max, d_maxhi);
+        launch_fill_u64((uint64_t*)d_tot, 8, 0, st);
+        const unsigned blocks = (unsigned)std::min<int64_t>((nr + 15) / 16, 16384);
+        hipLaunchKernelGGL(k_root_work, dim3(blocks), dim3(256), 0, st, g->off, g->adj, g->split, g->roots, nr,
+                           (uint32_t)hub_min, hub_ok, light_ok, wkey, d_tot);
         VDMC_HIP(hipGetLastError());
-        VDMC_HIP(hipMemsetAsync(is_hub + nr, 0, sizeof(uint32_t), st));
-        size_t tb = 0;
-        int n1 = (int)(nr + 1);
-        VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, is_hub, pos, n1, st));
-        void* t1 = alloc(tb);
-        VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(t1, tb, is_hub, pos, n1, st));
-        uint32_t h = 0;
-        VDMC_HIP(hipMemcpyAsync(&h, pos + nr, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        VDMC_HIP(hipMemcpyAsync(&max_s2, d_max, sizeof(max_s2), hipMemcpyDeviceToHost, st));
-        VDMC_HIP(hipMemcpyAsync(&maxhi, d_maxhi, sizeof(maxhi), hipMemcpyDeviceToHost, st));
+        // hub roots by work, then the tiers, each in rank order
+        size_t sb = 0;
+        int ni = (int)nr;
+        VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sb, wkey, wkey_s, g->roots, g->hubs, ni, 0, 64, st));
+        void* t2 = alloc(sb);
+        VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(t2, sb, wkey, wkey_s, g->roots, g->hubs, ni, 0, 64, st));
+        VDMC_HIP(hipMemcpyAsync(tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost, st));
         VDMC_HIP(hipStreamSynchronize(st));
-        nhub = h;
-        nlight = nr - nhub;
-        VDMC_HIP(hipMalloc(&g->light, (nlight + 1) * sizeof(uint32_t)));
-        VDMC_HIP(hipMalloc(&g->hubs, (nhub + 1) * sizeof(uint32_t)));
-        if (nlight > 0)
-            hipLaunchKernelGGL(k_split_bins, dim3(blocks), dim3(BT), 0, st, g->roots, is_hub, pos, nr, g->light);
-        VDMC_HIP(hipGetLastError());
+        nhub = (int64_t)tot[2];
         if (nhub > 0) {
-            // sort all roots by work key (non-hubs carry ~0 and land at the end)
-            size_t sb = 0;
-            int ni = (int)nr;
-            VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sb, wkey, wkey_s, g->roots, roots_s, ni, 0, 64, st));
-            void* t2 = alloc(sb);
-            VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(t2, sb, wkey, wkey_s, g->roots, roots_s, ni, 0, 64, st));
-            VDMC_HIP(hipMemcpyAsync(g->hubs, roots_s, nhub * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
             hub_keys.resize((size_t)nhub);
             VDMC_HIP(hipMemcpyAsync(hub_keys.data(), wkey_s, nhub * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                                     st));
+            VDMC_HIP(hipStreamSynchronize(st));
         }
-        VDMC_HIP(hipStreamSynchronize(st));
         // Hub roots whose estimated work exceeds a fair share of the device (the total over
         // twice the workgroups) would each be the critical path on one workgroup: the
         // leading ones of the queue (largest first) are shared by G workgroups, G from the
@@ -1299,16 +1281,17 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
             g->hub_layout[3] = shares >= 2 ? h : 0;
             g->hub_layout[4] = shares >= 2 ? shares : 1;
         }
-    } else {
-        VDMC_HIP(hipMalloc(&g->light, sizeof(uint32_t)));
-        VDMC_HIP(hipMalloc(&g->hubs, sizeof(uint32_t)));
     }
+    const unsigned long long max_s2 = tot[0];
+    const int32_t maxhi = (int32_t)tot[1];
     g->nhub = nhub;
-    g->nlight = nlight;
+    g->light = g->hubs + nhub;
+    g->nlight = nr - nhub;
+    for (int t = 0; t < 4; t++) g->ntier[t] = (int64_t)tot[3 + t];
     g->max_scan2 = (int64_t)max_s2;
-    g->max_hi = (int32_t)maxhi;
+    g->max_hi = maxhi;
     // light roots: fewer than hub_min higher neighbours (every root when the hub path is off)
-    g->light_max_d = hub_ok ? std::min<int32_t>((int32_t)maxhi, hub_min - 1) : (int32_t)maxhi;
+    g->light_max_d = hub_ok ? std::min<int32_t>(maxhi, hub_min - 1) : maxhi;
     VDMC_HIP(hipMalloc(&g->hub_queue, 64));
     if (nhub > 0) {
         const int wgs = hub_workgroups();

@@ -145,8 +145,9 @@ struct vdmc_graph_s {
     // root bins (built at the first count after a change of the hub threshold)
     int hub_min = 32;            // roots with at least this many higher neighbours take the hub path
     int bins_hub_min = -1;
-    uint32_t* light = nullptr;   // roots handled by the per-set kernel
+    uint32_t* light = nullptr;   // the other roots, behind the hub roots (one allocation), by tier:
     int64_t nlight = 0;
+    int64_t ntier[4] = {0, 0, 0, 0};   // light-root kernel (three sizes), per-set kernel
     uint32_t* hubs = nullptr;    // roots handled by the hub kernel, largest work first
     int64_t nhub = 0;
     int64_t max_scan2 = 0;       // largest depth-2 scan over hub roots (scratch sizing)
@@ -240,13 +241,36 @@ struct GraphView {
     const unsigned long long* ehash = nullptr;   // edge hash if the graph has one (adjacency tests)
     uint32_t ehash_bits = 0;
 };
+// light-root kernel (count_light.hip): the roots of one graph, or a table over many
+struct LightArgs {
+    GraphView gv;                   // the graph of `roots`
+    const uint32_t* roots;          // roots of one graph, or nullptr: `table`
+    int64_t nroots;                 // entries of roots or table
+    uint32_t rank_lo, rank_hi;      // only roots with rank in [rank_lo, rank_hi) (roots)
+    const GraphView* graphs;        // device array (table)
+    const uint2* table;             // (graph, root) pairs
+    unsigned long long* cursor;     // work cursor, zeroed before the launch (table)
+    unsigned tile;                  // roots per cursor step (table)
+    const uint8_t* t3;
+    const uint8_t* t4;
+    const uint8_t* cmp_of;          // class -> compact counter or 0xFF
+    const uint8_t* cmp_cls;         // compact counter -> class
+};
+// Tier of a root with d higher neighbours whose rows hold s2 entries above it: the smallest
+// light-root kernel whose slot list and hash (three quarters full at most) hold it, 3 = none.
+__host__ __device__ inline int light_tier(uint32_t d, unsigned long long s2) {
+    return d > 32u || s2 + d > 3072u ? 3 : (s2 + d > 384u ? 2 : (d > 8u || s2 + d > 96u ? 1 : 0));
+}
+constexpr int32_t kLightMaxDegree = 1 << 20;   // its 32-bit counters of a root: 3072 entries x row length
+void launch_light(LightArgs a, int tier, int k3, int k4, hipStream_t st);
 // batched launch over many graphs (count.hip / batch.hip)
 struct BatchArgs {
     const GraphView* graphs;        // device array, one per graph
     const uint64_t* nvert;          // device array: n of every graph
     const uint2* table;             // device array of (graph, root) pairs
-    unsigned long long nentries;
-    unsigned long long* cursor;     // device work cursor, zeroed inside the launch
+    unsigned long long nentries;    // pairs of the per-set kernel, behind those of the light tiers
+    unsigned long long nlight[3];   // pairs of the light-root tiers, from the table's start
+    unsigned long long* cursor;     // device work cursors (8 words), zeroed inside the launch
     unsigned long long tile;        // roots taken per cursor step
     const uint8_t* t3;
     const uint8_t* t4;
