@@ -1002,7 +1002,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // its paths, parents adjacent to e included (phase E took those out).  Credited path by
         // path instead, the ends alone would take a memory-side atomic per (1,1,1) set.
         {
-            constexpr uint32_t GW = 16;    // words per 16-lane group: 16 path counters
+            constexpr uint32_t EB = 4;          // end vertices per group between two flushes
+            constexpr uint32_t GW = 16 * EB;    // words per 16-lane group: 16 path counters each
             constexpr uint32_t FIX = (HT / 16) * GW + NW * CW + SHASH / 2 + 32;
             const bool in_lds = FIX + 2u * nbw + 4096u <= U_WORDS;
             uint32_t* GC = L.U + (tid >> 4) * GW;
@@ -1014,7 +1015,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             uint32_t* BM = L.U + FIX + (in_lds ? 2u * nbw : 0u);
             const uint32_t win = min(nbw, U_WORDS - (uint32_t)(BM - L.U));   // words of a window
             for (uint32_t i = tid; i < FIX - 32; i += HT) L.U[i] = 0u;
-            if (tid < 27u) KS[tid] = cmp_of[L.t4[motif_index4(tid / 9u + 1u, 0u, 0u, tid % 9u / 3u + 1u, 0u, tid % 3u + 1u)]];
+            if (tid < 27u)
+                KS[tid] = cmp_of[L.t4[motif_index4(tid / 9u + 1u, 0u, 0u, tid % 9u / 3u + 1u, 0u, tid % 3u + 1u)]];
             __syncthreads();
             for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
             if (in_lds || !kept) index2(B2, P2, nbw, cids, ngroups);
@@ -1049,27 +1051,36 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                     }
                     for (; word; word &= word - 1u) LST[pos++] = (uint16_t)(lane * 32u + (uint32_t)__ffs((int)word) - 1u);
                     __threadfence_block();
-                    for (uint32_t i0 = 0; i0 < total; i0 += 4u) {
-                        const uint32_t i = i0 + (lane >> 4);
-                        const bool on = i < total;
-                        const uint32_t e = e0 + (b0 << 5) + (on ? LST[i] : 0u);
-                        const uint32_t q1 = on ? A.off[e + 1] : 0u;
-                        for (uint32_t q = (on ? A.off[e] : 0u) + gl; q < q1; q += 16u) {
-                            const uint32_t ee = A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
-                            if (c <= r || (G > 1u && c % G != share)) continue;
-                            const uint32_t j = find2(B2, P2, c);
-                            if (j == ~0u) continue;
-                            const ulonglong2 pc = pcount[j];
-                            for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {
-                                const uint32_t s = (uint32_t)__ffs((int)mk) - 1u;
-                                const uint32_t n = (uint32_t)(s < 5u ? pc.x >> (12u * s) : pc.y >> (12u * (s - 5u))) & 0xFFFu;
-                                atomicAdd(&GC[KS[s * 3u + ce]], n);
+                    // EB vertices a group, then their credits: vector memory operations finish in
+                    // order, so a load after an atomic waits for the atomic
+                    for (uint32_t i0 = 0; i0 < total; i0 += 4u * EB) {
+                        for (uint32_t eb = 0; eb < EB; eb++) {
+                            const uint32_t i = i0 + eb * 4u + (lane >> 4);
+                            const bool on = i < total;
+                            const uint32_t e = e0 + (b0 << 5) + (on ? LST[i] : 0u);
+                            const uint32_t q1 = on ? A.off[e + 1] : 0u;
+                            for (uint32_t q = (on ? A.off[e] : 0u) + gl; q < q1; q += 16u) {
+                                const uint32_t ee = A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
+                                if (c <= r || (G > 1u && c % G != share)) continue;
+                                const uint32_t j = find2(B2, P2, c);
+                                if (j == ~0u) continue;
+                                const ulonglong2 pc = pcount[j];
+                                for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {
+                                    const uint32_t s = (uint32_t)__ffs((int)mk) - 1u;
+                                    const unsigned long long f = s < 5u ? pc.x >> (12u * s) : pc.y >> (12u * (s - 5u));
+                                    const uint32_t n = (uint32_t)f & 0xFFFu;
+                                    atomicAdd(&GC[eb * 16u + KS[s * 3u + ce]], n);
+                                }
                             }
                         }
                         __threadfence_block();
-                        const uint32_t n = GC[gl];
-                        GC[gl] = 0u;
-                        cmp_line(A, e, gl, n);
+#pragma unroll
+                        for (uint32_t eb = 0; eb < EB; eb++) {
+                            const uint32_t i = i0 + eb * 4u + (lane >> 4);
+                            const uint32_t n = GC[eb * 16u + gl];
+                            GC[eb * 16u + gl] = 0u;
+                            cmp_line(A, e0 + (b0 << 5) + (i < total ? LST[i] : 0u), gl, n);
+                        }
                         __threadfence_block();
                     }
                 }
