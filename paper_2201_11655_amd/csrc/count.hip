@@ -29,19 +29,19 @@ constexpr int kThreads = 256;
 constexpr uint32_t kStage = 2048;   // entries of N+(r) staged in LDS (single-graph launch)
 
 struct Args {
-    const uint32_t* off;
-    const uint32_t* adj;
-    const uint32_t* split;
-    const int32_t* perm;
-    const uint32_t* roots;
+    gptr<const uint32_t> off;
+    gptr<const uint32_t> adj;
+    gptr<const uint32_t> split;
+    gptr<const int32_t> perm;
+    gptr<const uint32_t> roots;
     int64_t nroots;
     const uint8_t* t3;
     const uint8_t* t4;
-    unsigned long long* out3;   // n x 13, original ids
-    unsigned long long* out4;   // n x 199
-    unsigned long long* stats;  // kShapes
+    gptr<unsigned long long> out3;   // n x 13, original ids
+    gptr<unsigned long long> out4;   // n x 199
+    gptr<unsigned long long> stats;  // kShapes
     uint32_t rank_lo, rank_hi;  // only roots with rank in [rank_lo, rank_hi)
-    const unsigned long long* ehash;   // edge hash or nullptr
+    gptr<const unsigned long long> ehash;   // edge hash or nullptr
     uint32_t ehash_bits;
 };
 
@@ -64,7 +64,7 @@ __device__ __forceinline__ bool in_list(const uint32_t* P, uint32_t d, uint32_t 
 // One count of class cls to vertex v.  When every lane that gets here credits the same
 // (vertex, class) -- lanes that share a member of their sets, e.g. the centre of a star
 // -- one lane adds them all.
-__device__ __forceinline__ void credit(unsigned long long* out, const int32_t* perm, int C, uint32_t v,
+__device__ __forceinline__ void credit(gptr<unsigned long long> out, gptr<const int32_t> perm, int C, uint32_t v,
                                        uint32_t cls) {
     if (cls >= (uint32_t)C) return;   // 0xFF never credited
     const uint32_t fv = __builtin_amdgcn_readfirstlane(v), fc = __builtin_amdgcn_readfirstlane(cls);
@@ -72,9 +72,9 @@ __device__ __forceinline__ void credit(unsigned long long* out, const int32_t* p
     const unsigned long long same = __ballot(v == fv && cls == fc);
     if (same == act) {
         if ((threadIdx.x & 63u) == (uint32_t)(__ffsll((long long)act) - 1))
-            atomicAdd(&out[(size_t)perm[v] * C + cls], (unsigned long long)__popcll(act));
+            gadd64(&out[(size_t)perm[v] * C + cls], (unsigned long long)__popcll(act));
     } else {
-        atomicAdd(&out[(size_t)perm[v] * C + cls], 1ull);
+        gadd64(&out[(size_t)perm[v] * C + cls], 1ull);
     }
 }
 
@@ -89,10 +89,10 @@ struct GlobalSink {
         credit(gv.out4, gv.perm, kClasses4, v, cls);
     }
     __device__ __forceinline__ void root3(const GraphView& gv, uint32_t r, uint32_t cls, unsigned long long c) const {
-        atomicAdd(&gv.out3[(size_t)gv.perm[r] * kClasses3 + cls], c);
+        gadd64(&gv.out3[(size_t)gv.perm[r] * kClasses3 + cls], c);
     }
     __device__ __forceinline__ void root4(const GraphView& gv, uint32_t r, uint32_t cls, unsigned long long c) const {
-        atomicAdd(&gv.out4[(size_t)gv.perm[r] * kClasses4 + cls], c);
+        gadd64(&gv.out4[(size_t)gv.perm[r] * kClasses4 + cls], c);
     }
     __device__ __forceinline__ void set3(uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t) const {}
     __device__ __forceinline__ void set4(uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
@@ -103,10 +103,10 @@ struct GlobalSink {
 // vertex pair of a set that is joined in G_U gets one count of the set's class, in the
 // row the edge index gives it.  Vertex credits are dropped.
 struct EdgeSink {
-    const unsigned long long* table;   // the graph's edge hash
+    gptr<const unsigned long long> table;   // the graph's edge hash
     uint32_t bits;
-    const uint32_t* epid;              // slot -> output row of the pair
-    unsigned long long* out;           // pairs x C
+    gptr<const uint32_t> epid;              // slot -> output row of the pair
+    gptr<unsigned long long> out;           // pairs x C
     uint32_t C;
     __device__ __forceinline__ void c3(const GraphView&, uint32_t, uint32_t) const {}
     __device__ __forceinline__ void c4(const GraphView&, uint32_t, uint32_t) const {}
@@ -114,7 +114,7 @@ struct EdgeSink {
     __device__ __forceinline__ void root4(const GraphView&, uint32_t, uint32_t, unsigned long long) const {}
     __device__ __forceinline__ void pair(uint32_t u, uint32_t v, uint32_t cls) const {
         const uint32_t h = edge_find(table, bits, u, v);
-        if (h != 0xFFFFFFFFu) atomicAdd(&out[(size_t)epid[h] * C + cls], 1ull);
+        if (h != 0xFFFFFFFFu) gadd64(&out[(size_t)epid[h] * C + cls], 1ull);
     }
     // vertices v0..v2 / v0..v3 (v0 = the root) and the arc bits of their pairs
     __device__ __forceinline__ void set3(uint32_t cls, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t c01,
@@ -163,7 +163,7 @@ __device__ void process_root(const GraphView& gv, const uint8_t* t3, const uint8
     if (K4)
         for (uint32_t i = tid; i < kClasses4; i += BS) S.root4[i] = 0;
     __syncthreads();
-    const uint32_t* P = staged ? S.P : gv.adj + s;
+    const uint32_t* P = staged ? S.P : (const uint32_t*)(gv.adj + s);
 
     // ---- depth-1 shapes: pairs (i < j) of N+(r); k=4 extends each by l > j
     const uint64_t npairs = (uint64_t)d * (d - 1) / 2;
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(BS) void k_count_roots(Args a) {
         process_root<BS, STAGE, K3, K4>(gv, a.t3, a.t4, r, S, shape, GlobalSink());
     }
     for (int s = 0; s < kShapes; s++)
-        if (shape[s]) atomicAdd(&a.stats[s], shape[s]);
+        if (shape[s]) gadd64(&a.stats[s], shape[s]);
 }
 
 // Per-edge counts: every root with a non-empty higher neighbourhood, edges credited
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void k_count_edges(Args a, EdgeSink es) {
     for (int64_t ri = blockIdx.x; ri < a.nroots; ri += gridDim.x)
         process_root<kThreads, kStage, K3, K4>(gv, a.t3, a.t4, a.roots[ri], S, shape, es);
     for (int s = 0; s < kShapes; s++)
-        if (shape[s]) atomicAdd(&a.stats[s], shape[s]);
+        if (shape[s]) gadd64(&a.stats[s], shape[s]);
 }
 
 // Batched launch: a root table of (graph, root) pairs over many graphs, consumed in
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(BS) void k_count_batch(BatchArgs b) {
             if ((int)ent.x != cur_graph) {
                 if (cur_graph >= 0)
                     for (int s = 0; s < kShapes; s++)
-                        if (shape[s]) { atomicAdd(&b.graphs[cur_graph].stats[s], shape[s]); shape[s] = 0; }
+                        if (shape[s]) { gadd64(&b.graphs[cur_graph].stats[s], shape[s]); shape[s] = 0; }
                 cur_graph = (int)ent.x;
             }
             process_root<BS, STAGE, K3, K4>(b.graphs[ent.x], b.t3, b.t4, ent.y, S, shape, GlobalSink());
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(BS) void k_count_batch(BatchArgs b) {
     }
     if (cur_graph >= 0)
         for (int s = 0; s < kShapes; s++)
-            if (shape[s]) atomicAdd(&b.graphs[cur_graph].stats[s], shape[s]);
+            if (shape[s]) gadd64(&b.graphs[cur_graph].stats[s], shape[s]);
 }
 
 // zero every graph's shape counters and the outputs of the graphs counted by the root

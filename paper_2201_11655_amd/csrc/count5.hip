@@ -2,12 +2,12 @@
 // 5-vertex motifs as the next case of the same claims and data structure).
 //
 // What is counted is what k = 3, 4 count (Sec. 4.1-4.2): every connected 5-set S is
-// visited once, its index is read from the induced adjacency matrix (20 bits, first
+// counted once, its index is read from the induced adjacency matrix (20 bits, first
 // entry most significant), mapped to its isomorphism class (9364 weakly connected
 // classes) and credited to all five members.
 //
 // How each set is reached once (Lemma 1 and the BFS shapes of Lemmas 2-4, one level
-// further): S is visited from its lowest-rank vertex r only, along its BFS layering
+// further): S is reached from its lowest-rank vertex r only, along its BFS layering
 // from r: layer 1 = the members adjacent to r, layer i + 1 = the members adjacent to
 // layer i and to no earlier layer.  The layer sizes are the set's shape; five vertices
 // have eight: (4) (3,1) (2,2) (2,1,1) (1,3) (1,2,1) (1,1,2) (1,1,1,1), the 4-vertex
@@ -19,37 +19,26 @@
 // under an earlier parent (the rule of Lemma 4, generalised).  So the layering, the
 // parents and the choice order are all fixed by S, and each set is produced once.
 //
-// GPU mapping: the graph is held whole in LDS -- rank-space CSR, the rank -> id map
-// and a 1-bit adjacency matrix (every pair test is one LDS read; the arc bits of a
-// member with its parent come with the row entry, others are searched in the row).  A
-// work item is a root r with the first member a of its layer 1 (one per pair of G_U,
-// from its lower-rank end), cut for the heavy roots into K sub-items by the choice of
-// the third member; a lane runs a sub-item's whole search (three nested candidate
-// loops) and visits every set of it.  Lanes take items one at a time from the graph's
-// item cursor, so lanes with short items keep taking new ones.  Class ids come from a
-// 2^20-entry u16 table in device memory (2 MiB).  9364 classes per vertex do not fit in
-// LDS; the 27 single-arc tree classes, which hold most sets of a sparse digraph, have
-// per-vertex LDS counters (added to the output block when the part ends), and the other
-// classes are credited to the output block in device memory.  The last member of a set
-// is credited per set, the four fixed members per distinct signature of the last one in
-// their context (a 4-entry per-lane cache).  Over a graph in device memory (no LDS
-// counters) the first three members' credits are further added up per class over the
-// whole loop under one third member (an 8-entry per-lane cache of (class, count)).
+// Graphs up to kFiveSetsMaxN vertices (k_five_sets).  The first three members T of a set
+// fix the candidates C of the fourth: the rest of the third member's layer, then the next
+// layer under it.  The last two members are then
+//   * two of C: every pair of C once.  Pairs that are not adjacent and whose members have
+//     the same arc codes to T share their index, so they are counted as groups, from the
+//     number of candidates of each code; an adjacent pair is found from the row of either
+//     member and moved to its own index;
+//   * one y of C and a neighbour of y that is adjacent to no member of T.
+// A workgroup takes a pair {r, a} of first members (from the heaviest roots on) and a wave a
+// third member; the arc codes of r, of a and of the third member to all vertices lie in LDS
+// as bit planes, so that a pair test is one LDS read.  Credits are summed in an LDS hash of
+// (vertex, class), which leaves for the output when it fills: the triples of one pair credit
+// the same few thousand cells over and over, and a credit that goes to the output by itself
+// is a memory-side atomic.  What bounds it: issue and the latency of the class table's loads
+// (2 MiB, in L2).  See k_five_sets for the figures.
 //
-// Work split.  A graph is cut into P parts (P from its estimated work, sum of d^4 over
-// its vertices, so that the heaviest graphs of a batch spread over many compute units):
-// a part is a workgroup that loads the graph, zeroes its own output block -- the
-// caller's output for part 0, a private copy in scratch for the others -- and then
-// takes items from the graph's item cursor until none are left.  A block belongs to one
-// workgroup for the whole launch, so its credits are workgroup-scope atomics.  A second
-// launch adds the copies of each graph with P > 1 into its output.  Parts are claimed
-// heaviest graph first from a slot cursor; items of a graph are handed out in rank
-// order, the heavy roots first.
-// Graphs that LDS does not hold take the same search over the graph in device memory
-// (k_five_global): pair tests from the graph's edge hash, rows searched in place, one
-// item cursor for the whole grid and device-scope credits to the caller's output.
-// Visited sets are counted per shape (the graph's 8 counters) so that callers can
-// check that every set was visited: their sum is the number of connected 5-sets.
+// Larger graphs take the same search set by set over the graph in device memory
+// (k_five_global): pair tests from the graph's edge hash, rows searched in place.
+// Sets are counted per shape (the graph's 8 counters): their sum is the number of
+// connected 5-sets.
 #include <cmath>
 #include <map>
 
@@ -61,21 +50,16 @@
 namespace vdmc {
 namespace {
 
-constexpr size_t kFiveStaticLds = 14336;                       // the kernel's __shared__ bytes, rounded up
+constexpr int64_t kFiveSetsMaxN = 16384;                       // bit planes of 3 + members in LDS (24 KiB)
+constexpr int64_t kFiveSetsMaxPairs = (int64_t)1 << 24;        // item table of at most 128 MiB
+constexpr uint32_t kNone = 0xFFFFFFFFu;
 // LDS counter slots per vertex: the 27 classes of 5-sets whose induced subgraph is a tree
 // with single arcs (oriented paths, stars and forks without a reciprocal pair), which in a
-// sparse digraph hold most of the sets (~84% of the batch workload's credits); the other
-// classes are credited to the output block
+// sparse digraph hold most of the credits (~84% on G(n, p) graphs of mean degree 10)
 constexpr uint32_t kTreeSlots5 = 27;
+constexpr int64_t kDenseMaxN = 512;                            // graphs with such counters (55 KiB)
 constexpr uint32_t kClassPad = 9376;                           // 9364 classes, padded to 16 bytes
-constexpr int64_t kFiveMatMaxN = 16384;                        // device-memory graphs up to this get a bit matrix (32 MiB)
-constexpr size_t kFiveLdsBudget = 163840 - kFiveStaticLds;     // gfx950: 160 KiB of LDS per workgroup
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr int kPartsPerCu = 2;                                 // target parts per compute unit in a batch
 constexpr uint32_t kSplitDiv = 32;                             // sub-items of a root: d+ x deg / 32 (measured best of 2..128)
-constexpr uint32_t kMaxParts = 64;                             // parts of one graph
-constexpr size_t kBatchScratchBudget = size_t(8) << 30;       // private copies of one batched launch
-constexpr size_t kSingleScratchBudget = size_t(512) << 20;    // private copies of one graph's count
 
 // bit of the index of a 5-set for the entry (i, j), i != j: rows in order, the diagonal
 // skipped, entry (0,1) the most significant of the 20 (Sec. 4.1, Fig. 1)
@@ -88,57 +72,18 @@ __device__ __forceinline__ uint32_t pair_bits(uint32_t i, uint32_t t, uint32_t b
     return ((b & 1u) << shift5(i, t)) | ((b >> 1) << shift5(t, i));
 }
 
-struct FiveLds {
-    const uint32_t* off;
-    const uint32_t* adj;
-    const uint32_t* mat;    // n rows of W words, one adjacency bit per vertex
-    const uint32_t* perm;
-    uint32_t W;
-    __device__ __forceinline__ bool adjacent(uint32_t u, uint32_t v) const {
-        return (mat[u * W + (v >> 5)] >> (v & 31u)) & 1u;
-    }
-    // arc bits of (u, v) seen from u: bit 0 u -> v, bit 1 v -> u; 0 if not adjacent (a set
-    // bit is resolved by a search of u's row)
-    __device__ __forceinline__ uint32_t bits(uint32_t u, uint32_t v) const {
-        if (!adjacent(u, v)) return 0u;
-        uint32_t lo = off[u], hi = off[u + 1];
-        const uint32_t key = v << 2;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (adj[mid] < key) lo = mid + 1; else hi = mid;
-        }
-        return adj[lo] & 3u;
-    }
-    // first entry of u's row whose neighbour has rank above x
-    __device__ __forceinline__ uint32_t first_above(uint32_t u, uint32_t x) const {
-        uint32_t lo = off[u], hi = off[u + 1];
-        const uint32_t key = (x + 1u) << 2;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (adj[mid] < key) lo = mid + 1; else hi = mid;
-        }
-        return lo;
-    }
-};
-
-// The same interface over a graph in device memory, for graphs that LDS does not hold:
-// pair tests from a 1-bit adjacency matrix in device memory when the graph has one (one
-// cached load), else from the edge hash; arc bits of an adjacent pair from the edge hash
-// (one probe sequence); rows searched in place.
+// A graph in device memory: pair tests and arc bits from the edge hash (one probe
+// sequence), rows searched in place.
 struct FiveGlobal {
     const uint32_t* off;
     const uint32_t* adj;
     const uint32_t* perm;
     const unsigned long long* eh;
     uint32_t ebits;
-    const uint32_t* mat;   // n rows of W words, or nullptr
-    uint32_t W;
     __device__ __forceinline__ bool adjacent(uint32_t u, uint32_t v) const {
-        if (mat) return (mat[(size_t)u * W + (v >> 5)] >> (v & 31u)) & 1u;
         return edge_code(eh, ebits, u, v) != 0u;
     }
     __device__ __forceinline__ uint32_t bits(uint32_t u, uint32_t v) const {
-        if (mat && !((mat[(size_t)u * W + (v >> 5)] >> (v & 31u)) & 1u)) return 0u;
         return edge_code(eh, ebits, u, v);
     }
     __device__ __forceinline__ uint32_t first_above(uint32_t u, uint32_t x) const {
@@ -229,36 +174,12 @@ __device__ __forceinline__ uint32_t arc_of(const V& L, const Members& S, uint32_
     return L.bits(S[m], y);
 }
 
-// credits: workgroup scope to an output block that belongs to the calling workgroup (no
-// other workgroup touches it during the launch), device scope to an output all
-// workgroups share (kDev)
-template <bool kDev>
-__device__ __forceinline__ void bump(unsigned long long* p, unsigned long long v) {
-    if (kDev) __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Where a credit of v sets of class cls to vertex P (original id) goes.  GlobalSink: to
-// the output (device scope when kDev).  LdsSink: a class with an LDS counter slot (the
-// single-arc tree classes) to the workgroup's LDS counters, any other to its output
-// block.
-template <bool kDev>
+// a credit of v sets of class cls to vertex P (original id): one device-scope atomic
 struct GlobalSink {
-    static constexpr bool kClassCache = true;
     unsigned long long* out;
     __device__ __forceinline__ void add(uint32_t P, uint32_t cls, uint32_t v) const {
-        bump<kDev>(&out[(size_t)P * kClasses5 + cls], (unsigned long long)v);
-    }
-};
-struct LdsSink {
-    static constexpr bool kClassCache = false;
-    unsigned long long* out;
-    uint32_t* cnt;            // n x kTreeSlots5 (LDS), rows by original id
-    const uint8_t* slot_of;   // class -> counter slot or 0xFF (LDS)
-    __device__ __forceinline__ void add(uint32_t P, uint32_t cls, uint32_t v) const {
-        const uint32_t sl = slot_of[cls];
-        if (sl < kTreeSlots5) atomicAdd(&cnt[P * kTreeSlots5 + sl], v);
-        else bump<false>(&out[(size_t)P * kClasses5 + cls], (unsigned long long)v);
+        __hip_atomic_fetch_add(&out[(size_t)P * kClasses5 + cls], (unsigned long long)v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     }
 };
 
@@ -274,8 +195,7 @@ __device__ __forceinline__ void credit3(const Sk& sk, uint32_t P0, uint32_t P1, 
 // Per-lane cache of the classes credited to S[0], S[1], S[2] over one depth-2 loop (all
 // fourth members under one third member): entry = (count << 14) | class, 0 = empty; the
 // oldest entry makes room.  A count stays below 2^18: an entry about to pass it takes a
-// new slot instead.  Used where every credit is a memory-side atomic (GlobalSink); with
-// LDS counters the three credits are cheaper than the cache's registers.
+// new slot instead.
 struct ClassCache {
     uint32_t e0 = 0, e1 = 0, e2 = 0, e3 = 0, e4 = 0, e5 = 0, e6 = 0, e7 = 0, victim = 0;
     static __device__ __forceinline__ bool take(uint32_t& e, uint32_t cls, uint32_t v) {
@@ -326,8 +246,7 @@ __device__ __forceinline__ void credit_ctx(const Sk& sk, ClassCache& cc, uint32_
                                            uint32_t P3, uint32_t cls, uint32_t v) {
     if (v == 0u || cls >= (uint32_t)kClasses5) return;
     sk.add(P3, cls, v);
-    if constexpr (Sk::kClassCache) cc.add(cls, v, sk, P0, P1, P2);
-    else credit3(sk, P0, P1, P2, cls, v);
+    cc.add(cls, v, sk, P0, P1, P2);
 }
 
 // Per-lane cache of the last member's signatures in one context: entry = (count << 22) |
@@ -447,199 +366,10 @@ __device__ void five_item(const V& L, const uint16_t* __restrict__ table, const 
             add_shape(vis, base, same);
             add_shape(vis, base | 1u, opened);
         }
-        if constexpr (Sk::kClassCache) cc.flush_all(sk, P0, P1, P2);
+        cc.flush_all(sk, P0, P1, P2);
     }
 }
 
-
-struct FiveGraph {
-    const uint32_t* off;           // n + 1 (rank space)
-    const uint32_t* adj;           // entries: (nbr_rank << 2) | arc bits
-    const int32_t* perm;           // rank -> original id
-    unsigned long long* out;       // n x 9364, rows by original id (part 0)
-    size_t copies_off;             // first element of its (parts - 1) x n x 9364 private blocks in the
-                                   // call's copies (parts 1.., summed into out)
-    unsigned long long* stats;     // 8 shape counters
-    uint32_t n, entries;
-    uint32_t parts;
-};
-
-struct FiveArgs {
-    const FiveGraph* graphs;       // device array of num graphs, or nullptr: the graph `one`
-    FiveGraph one;
-    uint32_t num;
-    const uint2* slots;            // (graph, part) in claim order, or nullptr: (0, s)
-    uint32_t nslots;
-    unsigned* cursors;             // num item cursors (one per graph), then the slot cursor
-    unsigned long long* copies;    // private blocks of every graph's parts 1.., or nullptr
-    const uint16_t* table;         // code -> class id
-    const uint8_t* slot_of;        // class -> LDS counter slot or 0xFF (kClassPad entries)
-    const uint16_t* slot_cls;      // LDS counter slot -> class (kTreeSlots5 entries)
-    uint32_t split_div;            // sub-items of a root: ceil(d+ x deg / split_div), at most 64
-};
-
-__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// zeroes every graph's counters and item cursor and the slot cursor (before k_five)
-__global__ __launch_bounds__(256) void k_five_prep(FiveArgs A) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) A.cursors[A.num] = 0u;
-    if (i >= A.num) return;
-    const FiveGraph& G = A.graphs ? A.graphs[i] : A.one;
-    for (int s = 0; s < kStatSlots; s++) G.stats[s] = 0ull;
-    A.cursors[i] = 0u;
-}
-
-template <int BS>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_five(FiveArgs A) {
-    extern __shared__ uint32_t lds[];
-    __shared__ uint32_t s_slot;
-    __shared__ uint32_t part[BS];
-    __shared__ unsigned long long s_vis[8];   // sets visited per shape by this part
-    __shared__ uint8_t sSlotOf[kClassPad];
-    __shared__ uint16_t sSlotCls[32];
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t i = tid; i < (uint32_t)kClassPad; i += BS) sSlotOf[i] = A.slot_of[i];
-    if (tid < kTreeSlots5) sSlotCls[tid] = A.slot_cls[tid];
-    uint32_t loaded = kNone;
-    FiveGraph G{};
-    FiveLds L{};
-    uint32_t* sSplit = nullptr;
-    uint32_t* sHp = nullptr;
-    uint32_t* sCnt = nullptr;
-    for (;;) {
-        if (tid == 0) s_slot = atomicAdd(A.cursors + A.num, 1u);
-        __syncthreads();
-        const uint32_t slot = s_slot;
-        if (slot >= A.nslots) break;
-        const uint2 sl = A.slots ? A.slots[slot] : make_uint2(0u, slot);
-        if (sl.x != loaded) {   // the graph into LDS
-            G = A.graphs ? A.graphs[sl.x] : A.one;
-            const uint32_t n = G.n, E = G.entries, W = (n + 31u) >> 5;
-            uint32_t* sOff = lds;
-            sSplit = sOff + n + 1;
-            sHp = sSplit + n;
-            uint32_t* sPerm = sHp + n + 1;
-            uint32_t* sAdj = sPerm + n;
-            uint32_t* sMat = sAdj + E;
-            sCnt = sMat + n * W;   // n x kTreeSlots5 counters of the part, rows by original id
-            for (uint32_t i = tid; i < (n ? n + 1u : 0u); i += BS) sOff[i] = G.off[i];
-            for (uint32_t i = tid; i < n; i += BS) sPerm[i] = (uint32_t)G.perm[i];
-            for (uint32_t i = tid; i < E; i += BS) sAdj[i] = G.adj[i];
-            for (uint32_t i = tid; i < n * W; i += BS) sMat[i] = 0u;
-            __syncthreads();
-            for (uint32_t u = tid; u < n; u += BS) {
-                const uint32_t b = sOff[u], e = sOff[u + 1];
-                uint32_t split = e;
-                for (uint32_t x = b; x < e; x++) {
-                    const uint32_t a = sAdj[x], v = a >> 2;
-                    if (v > u && split == e) split = x;
-                    sMat[u * W + (v >> 5)] |= 1u << (v & 31u);   // row u is this thread's
-                }
-                sSplit[u] = split;
-                sHp[u] = (e - split) * item_split(e - split, e - b, A.split_div);
-            }
-            __syncthreads();
-            // exclusive prefix of the higher-neighbour counts: item i of the graph is the
-            // entry sSplit[r] + (i - sHp[r]) of the root r with sHp[r] <= i < sHp[r + 1]
-            const uint32_t per = (n + BS - 1) / BS;
-            const uint32_t lo = min(n, tid * per), hi = min(n, lo + per);
-            uint32_t s = 0;
-            for (uint32_t i = lo; i < hi; i++) s += sHp[i];
-            part[tid] = s;
-            __syncthreads();
-            for (uint32_t o = 1; o < (uint32_t)BS; o <<= 1) {
-                const uint32_t v = tid >= o ? part[tid - o] : 0u;
-                __syncthreads();
-                part[tid] += v;
-                __syncthreads();
-            }
-            uint32_t run = part[tid] - s;
-            for (uint32_t i = lo; i < hi; i++) {
-                const uint32_t x = sHp[i];
-                sHp[i] = run;
-                run += x;
-            }
-            if (tid == 0) sHp[n] = part[BS - 1];
-            L = FiveLds{sOff, sAdj, sMat, sPerm, W};
-            loaded = sl.x;
-        }
-        // this part's output block: the caller's output or a private copy; zeroed here
-        const size_t cells = (size_t)G.n * kClasses5;
-        unsigned long long* dst = sl.y == 0 ? G.out : A.copies + G.copies_off + (size_t)(sl.y - 1u) * cells;
-        if (((uintptr_t)dst & 15u) == 0) {   // 16-byte stores (9364 is even)
-            ulonglong2* o = reinterpret_cast<ulonglong2*>(dst);
-            for (size_t i = tid; i < cells / 2; i += BS) o[i] = make_ulonglong2(0ull, 0ull);
-        } else {
-            for (size_t i = tid; i < cells; i += BS) dst[i] = 0ull;
-        }
-        for (uint32_t i = tid; i < G.n * kTreeSlots5; i += BS) sCnt[i] = 0u;
-        if (tid < 8) s_vis[tid] = 0ull;
-        __syncthreads();
-        for (;;) {
-            const uint32_t i = atomicAdd(A.cursors + sl.x, 1u);   // items of the graph, shared by its parts
-            if (i >= sHp[G.n]) break;
-            uint32_t rlo = 0, rhi = G.n;   // root: last r with sHp[r] <= i
-            while (rhi - rlo > 1) {
-                const uint32_t mid = (rlo + rhi) >> 1;
-                if (sHp[mid] <= i) rlo = mid; else rhi = mid;
-            }
-            const uint32_t K = item_split(L.off[rlo + 1] - sSplit[rlo], L.off[rlo + 1] - L.off[rlo], A.split_div);
-            const uint32_t local = i - sHp[rlo];
-            five_item(L, A.table, LdsSink{dst, sCnt, sSlotOf}, rlo, sSplit[rlo] + local / K, local % K, K, s_vis);
-        }
-        __syncthreads();
-        // the part's LDS counters into its block (which only this workgroup writes)
-        for (uint32_t i = tid; i < G.n * kTreeSlots5; i += BS) {
-            const uint32_t x = sCnt[i];
-            if (!x) continue;
-            const uint32_t v = i / kTreeSlots5, sl2 = i - v * kTreeSlots5;
-            bump<false>(&dst[(size_t)v * kClasses5 + sSlotCls[sl2]], (unsigned long long)x);
-        }
-        if (tid < 8 && s_vis[tid]) atomicAdd(&G.stats[tid], s_vis[tid]);
-        __syncthreads();   // the part is done before the next claim rewrites s_slot
-    }
-}
-
-// out += the private copies of one graph (blockIdx.x strides over its cells)
-__device__ void five_reduce_one(const FiveGraph& G, const unsigned long long* copies) {
-    const size_t cells = (size_t)G.n * kClasses5;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (((uintptr_t)G.out & 15u) == 0) {   // copies are 256-byte aligned and cells is even
-        ulonglong2* o = reinterpret_cast<ulonglong2*>(G.out);
-        const ulonglong2* c = reinterpret_cast<const ulonglong2*>(copies);
-        const size_t h = cells / 2;
-        for (size_t i = t0; i < h; i += stride) {
-            ulonglong2 a = o[i];
-            for (uint32_t p = 0; p + 1 < G.parts; p++) {
-                const ulonglong2 b = c[p * h + i];
-                a.x += b.x;
-                a.y += b.y;
-            }
-            o[i] = a;
-        }
-    } else {
-        for (size_t i = t0; i < cells; i += stride) {
-            unsigned long long a = G.out[i];
-            for (uint32_t p = 0; p + 1 < G.parts; p++) a += copies[p * cells + i];
-            G.out[i] = a;
-        }
-    }
-}
-
-
-// out += the private copies, for every graph with more than one part (graphs strided
-// over blockIdx.y)
-__global__ __launch_bounds__(256) void k_five_reduce(FiveArgs A) {
-    for (uint32_t gi = blockIdx.y; gi < A.num; gi += gridDim.y) {
-        const FiveGraph& G = A.graphs ? A.graphs[gi] : A.one;
-        if (G.parts > 1) five_reduce_one(G, A.copies + G.copies_off);
-    }
-}
 
 // ----------------------------------------------------------------------------- graphs in device memory
 
@@ -686,10 +416,492 @@ __global__ __launch_bounds__(BS) void k_five_global(FiveGlobalArgs A) {
         const uint32_t r = lo, e = A.L.off[r + 1], sp = A.split[r];
         const uint32_t K = item_split(e - sp, e - A.L.off[r], A.split_div);
         const uint32_t local = (uint32_t)(i - A.hp[r]);
-        five_item(A.L, A.table, GlobalSink<true>{A.out}, r, sp + local / K, local % K, K, s_vis);
+        five_item(A.L, A.table, GlobalSink{A.out}, r, sp + local / K, local % K, K, s_vis);
     }
     __syncthreads();
     if (tid < 8 && s_vis[tid]) atomicAdd(&A.stats[tid], s_vis[tid]);
+}
+
+// ----------------------------------------------------------------------------- sets in groups
+
+struct SetsGraph {
+    gptr<const uint32_t> off;           // n + 1 (rank space)
+    gptr<const uint32_t> adj;           // entries: (nbr_rank << 2) | arc bits
+    gptr<const uint32_t> split;         // first entry above the row's vertex
+    gptr<const int32_t> perm;           // rank -> original id
+    gptr<unsigned long long> out;       // n x 9364, rows by original id
+    gptr<unsigned long long> stats;     // 8 shape counters
+    uint32_t n;
+    uint32_t first;                // items of the graphs before it in the table
+};
+
+struct SetsArgs {
+    const SetsGraph* graphs;       // device array, or nullptr: the graph `one`
+    SetsGraph one;
+    const uint2* items;            // per graph from its `first` on: (r, entry of a first layer-1 member in
+                                   // r's row); an item covers `step` members from there on, see item_step
+    const uint32_t* slots;         // graphs in the order workgroups take them, or nullptr: all `one`
+    uint32_t nslots;
+    unsigned* cursors;             // slot cursor, then per graph its item cursor and number of items
+    const uint16_t* table;         // code -> class id
+    const uint8_t* slot_of;        // class -> LDS counter slot or 0xFF (kClassPad entries)
+    const uint16_t* slot_cls;      // LDS counter slot -> class (kTreeSlots5 entries)
+    uint32_t words;                // words of a bit plane, of the largest graph
+    uint32_t dense;                // counters in LDS: the largest graph's vertices, or 0
+};
+
+// First layer-1 members of r in one item: about 100 third members, so that an item keeps a
+// workgroup busy and a heavy root still spreads over many.
+__device__ __forceinline__ uint32_t item_step(uint32_t dhi, uint32_t deg) { return max(1u, 96u / (dhi + deg)); }
+
+// the items of every graph, one workgroup each, in rank order; their number behind the graph's cursor
+constexpr int kItemThreads = 1024;
+__global__ __launch_bounds__(kItemThreads) void k_five_items(const SetsGraph* graphs, SetsGraph one, uint2* items,
+                                                             unsigned* cursors) {
+    __shared__ uint32_t part[kItemThreads];
+    const SetsGraph G = graphs ? graphs[blockIdx.x] : one;
+    const uint32_t tid = threadIdx.x, per = (G.n + kItemThreads - 1) / kItemThreads;
+    const uint32_t lo = min(G.n, tid * per), hi = min(G.n, lo + per);
+    uint32_t s = 0;
+    for (uint32_t r = lo; r < hi; r++) {
+        const uint32_t d = G.off[r + 1] - G.split[r], st = d ? item_step(d, G.off[r + 1] - G.off[r]) : 1u;
+        s += (d + st - 1u) / st;
+    }
+    part[tid] = s;
+    __syncthreads();
+    for (uint32_t o = 1; o < kItemThreads; o <<= 1) {
+        const uint32_t v = tid >= o ? part[tid - o] : 0u;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    uint32_t at = G.first + part[tid] - s;
+    for (uint32_t r = lo; r < hi; r++) {
+        const uint32_t t0 = G.split[r], t1 = G.off[r + 1];
+        if (t0 == t1) continue;
+        for (uint32_t t = t0, st = item_step(t1 - t0, t1 - G.off[r]); t < t1; t += st) items[at++] = make_uint2(r, t);
+    }
+    if (tid == kItemThreads - 1) cursors[2u + 2u * blockIdx.x] = part[tid];
+}
+
+// outputs, counters and item cursors of every graph to zero (blockIdx.y strides over the
+// graphs), the slot cursor too
+__global__ __launch_bounds__(256) void k_five_zero(SetsArgs A, uint32_t num) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) A.cursors[0] = 0u;
+    for (uint32_t g = blockIdx.y; g < num; g += gridDim.y) {
+        const SetsGraph& G = A.graphs ? A.graphs[g] : A.one;
+        const size_t cells = (size_t)G.n * kClasses5, stride = (size_t)gridDim.x * 256;
+        const size_t t0 = (size_t)blockIdx.x * 256 + threadIdx.x;
+        if (((uintptr_t)G.out.p & 15u) == 0) {   // 16-byte stores (9364 is even)
+            using u64x2 = unsigned long long __attribute__((ext_vector_type(2)));
+            const auto o = G.out.as<u64x2>();
+            for (size_t i = t0; i < cells / 2; i += stride) o[i] = u64x2{0ull, 0ull};
+        } else {
+            for (size_t i = t0; i < cells; i += stride) G.out[i] = 0ull;
+        }
+        if (blockIdx.x == 0 && threadIdx.x < kStatSlots) G.stats[threadIdx.x] = 0ull;
+        if (blockIdx.x == 0 && threadIdx.x == 0) A.cursors[1u + 2u * g] = 0u;
+    }
+}
+
+struct SetsWave {
+    uint32_t hist[64];     // candidates by signature (arc codes to r, a, the third member)
+    uint32_t sig[64];      // the signatures that occur ...
+    uint32_t cnt[64];      // ... and their candidates
+    uint32_t lone[192];    // (signature, arc code): last members below a candidate
+    uint32_t buf[64];      // candidates in hand: vertex | signature << 14 | phase << 20
+    uint32_t lo[64], hi[64];   // their rows
+    uint16_t kcls[192];    // classes of the sets that a neighbour of theirs alone completes, by arc code
+    uint16_t cls[256];     // class of two non-adjacent candidates by their signatures (up to 16 of them)
+    uint8_t idx[64];       // signature -> its place in sig
+};
+
+// a workgroup's credits: counters of the tree classes of every vertex (small graphs), a hash
+struct SetsCounters {
+    lptr<uint32_t> dense;  // n x kTreeSlots5 where `trees`
+    lptr<const uint8_t> slot_of;
+    lptr<uint32_t> key;    // hash: vertex << 14 | class, or kNone
+    lptr<uint32_t> val;
+    lptr<uint32_t> used;
+    uint32_t shift;        // 2^(32 - shift) cells
+    bool trees;
+};
+
+__device__ __forceinline__ uint32_t lds_add(lptr<uint32_t> p, uint32_t v) {
+    return __hip_atomic_fetch_add(p.p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// *p = want if it is `expect`; old: what it was
+__device__ __forceinline__ bool lds_cas(lptr<uint32_t> p, uint32_t expect, uint32_t want, uint32_t& old) {
+    old = expect;
+    return __hip_atomic_compare_exchange_strong(p.p, &old, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// credit cell (v, cls) += n: the LDS counter of a tree class, else through the hash; a full
+// neighbourhood of cells: to the output.  The hash's 32-bit sums carry into the output; a
+// dense counter cannot overflow (fewer than 2^32 5-sets hold a vertex of 512).
+struct SetsSink {
+    const SetsCounters L;
+    const SetsGraph G;
+    __device__ __forceinline__ gptr<unsigned long long> cell(uint32_t key) const {
+        return &G.out[(size_t)G.perm[key >> 14] * kClasses5 + (key & 0x3FFFu)];
+    }
+    __device__ __forceinline__ uint32_t find(uint32_t key) const {
+        const uint32_t mask = ~0u >> L.shift;
+        uint32_t h = (key * 2654435761u) >> L.shift;
+        for (int i = 0; i < 16; i++, h = (h + 1u) & mask) {
+            uint32_t k = L.key[h];
+            if (k == kNone) {
+                if (lds_cas(&L.key[h], kNone, key, k)) {
+                    lds_add(L.used, 1u);
+                    return h;
+                }
+            }
+            if (k == key) return h;
+        }
+        return kNone;
+    }
+    __device__ __forceinline__ uint32_t slot(uint32_t cls) const { return L.trees ? L.slot_of[cls] : 0xFFu; }
+    __device__ __forceinline__ void add(uint32_t v, uint32_t cls, uint32_t n) const {
+        const uint32_t sl = slot(cls);
+        if (sl < kTreeSlots5) {
+            lds_add(&L.dense[v * kTreeSlots5 + sl], n);
+            return;
+        }
+        const uint32_t key = (v << 14) | cls, h = find(key);
+        if (h == kNone) {
+            gadd64(cell(key), n);
+            return;
+        }
+        const uint32_t old = lds_add(&L.val[h], n);
+        if (old + n < old) gadd64(cell(key), 1ull << 32);
+    }
+    __device__ __forceinline__ void sub1(uint32_t v, uint32_t cls) const {
+        const uint32_t sl = slot(cls);
+        if (sl < kTreeSlots5) {
+            lds_add(&L.dense[v * kTreeSlots5 + sl], ~0u);
+            return;
+        }
+        const uint32_t key = (v << 14) | cls, h = find(key);
+        if (h == kNone) {
+            gadd64(cell(key), ~0ull);
+            return;
+        }
+        if (lds_add(&L.val[h], ~0u) == 0u) gadd64(cell(key), 0ull - (1ull << 32));
+    }
+};
+
+// arc code of a member with vertex z from the member's bit planes (both planes of a word side by side)
+__device__ __forceinline__ uint32_t plane_code(const uint2* P, uint32_t z) {
+    const uint2 w = P[z >> 5];
+    return ((w.x >> (z & 31u)) & 1u) | (((w.y >> (z & 31u)) & 1u) << 1);
+}
+
+// index bits of a member t = 3 or 4 with the codes sig to members 0, 1, 2
+__device__ __forceinline__ uint32_t sig_bits(uint32_t t, uint32_t sig) {
+    return pair_bits(0, t, sig & 3u) | pair_bits(1, t, (sig >> 2) & 3u) | pair_bits(2, t, sig >> 4);
+}
+
+__device__ __forceinline__ void wave_fence() {
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Every set whose first three members are r, a and y2 = the vertex of entry q (of r's row:
+// y2 shares a's layer; of a's row: y2 opens the next), by one wave.
+__device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& K, SetsWave& S, const uint16_t* __restrict__ table,
+                            const uint2* PR, const uint2* PA, uint2* PY, uint32_t W, uint32_t r, uint32_t a,
+                            uint32_t q, bool same, unsigned long long* vis) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t y2 = G.adj[q] >> 2;
+    const uint32_t ylo = G.off[y2], yhi = G.off[y2 + 1];
+    for (uint32_t i = lane; i < W; i += 64) PY[i] = make_uint2(0u, 0u);
+    S.hist[lane] = 0u;
+    for (uint32_t i = lane; i < 192u; i += 64) S.lone[i] = 0u;
+    wave_fence();
+    for (uint32_t i = ylo + lane; i < yhi; i += 64) {
+        const uint32_t e = G.adj[i], z = e >> 2, bit = 1u << (z & 31u);
+        if (e & 1u) atomicOr(&PY[z >> 5].x, bit);
+        if (e & 2u) atomicOr(&PY[z >> 5].y, bit);
+    }
+    wave_fence();
+    const uint32_t code3 = pair_bits(0, 1, plane_code(PR, a)) | pair_bits(0, 2, plane_code(PR, y2)) |
+                           pair_bits(1, 2, plane_code(PA, y2));
+    // rows that hold the candidates, one after the other: the rest of the third member's
+    // layer (phase 0), then the rows of a (if y2 shares its layer) and of y2 (phase 1)
+    const uint32_t l0 = (same ? G.off[r + 1] : G.off[a + 1]) - q - 1u;
+    const uint32_t l1 = same ? G.off[a + 1] - G.off[a] : 0u, l2 = yhi - ylo, len = l0 + l1 + l2;
+    // candidate i: its vertex, signature and phase as in S.buf, or kNone
+    auto candidate = [&](uint32_t i) -> uint32_t {
+        if (i >= len) return kNone;
+        const uint32_t ph = i >= l0 ? 1u : 0u;
+        const uint32_t at = i < l0 ? q + 1u + i : (i < l0 + l1 ? G.off[a] + i - l0 : ylo + i - l0 - l1);
+        const uint32_t z = G.adj[at] >> 2;
+        if (z <= r) return kNone;
+        const uint32_t cr = plane_code(PR, z), ca = plane_code(PA, z), cy = plane_code(PY, z);
+        if ((ph || !same) && cr) return kNone;             // adjacent to r: layer 1
+        if (i >= l0 + l1 && ca) return kNone;              // adjacent to a: hangs under a, or in y2's layer
+        return z | ((cr | (ca << 2) | (cy << 4)) << 14) | (ph << 20);
+    };
+    uint32_t c0 = 0, c1 = 0;
+    for (uint32_t i0 = 0; i0 < len; i0 += 64) {
+        const uint32_t c = candidate(i0 + lane);
+        if (c != kNone) atomicAdd(&S.hist[(c >> 14) & 63u], 1u);
+        c0 += (uint32_t)__popcll(__ballot(c != kNone && !(c >> 20)));
+        c1 += (uint32_t)__popcll(__ballot(c != kNone && (c >> 20)));
+    }
+    if (c0 + c1 == 0u) return;
+    wave_fence();
+    const uint32_t nh = S.hist[lane];
+    const unsigned long long occ = __ballot(nh != 0u);
+    const uint32_t D = (uint32_t)__popcll(occ), my = (uint32_t)__popcll(occ & ((1ull << lane) - 1ull));
+    if (nh) {
+        S.sig[my] = lane;
+        S.cnt[my] = nh;
+        S.idx[lane] = (uint8_t)my;
+    }
+    wave_fence();
+    // ---- pairs of candidates as if not adjacent: the three first members' credits
+    const bool small = D <= 16u;
+    for (uint32_t i = lane; i < D * D; i += 64) {
+        const uint32_t p = i / D, t = i - p * D;
+        if (t < p && !small) continue;
+        const uint32_t cls = table[code3 | sig_bits(3, S.sig[p]) | sig_bits(4, S.sig[t])];
+        if (small) S.cls[i] = (uint16_t)cls;
+        if (t < p) continue;
+        const uint32_t n = p == t ? S.cnt[p] * (S.cnt[p] - 1u) / 2u : S.cnt[p] * S.cnt[t];
+        if (n) {
+            K.add(r, cls, n);
+            K.add(a, cls, n);
+            K.add(y2, cls, n);
+        }
+    }
+    const uint32_t base = same ? 0u : 4u;
+    if (lane == 0) {
+        atomicAdd(&vis[base], (unsigned long long)c0 * (c0 - 1u) / 2u);
+        atomicAdd(&vis[base + 1u], (unsigned long long)c0 * c1);
+        atomicAdd(&vis[base + 2u], (unsigned long long)c1 * (c1 - 1u) / 2u);
+    }
+    wave_fence();
+    auto pair_class = [&](uint32_t s, uint32_t t) -> uint32_t {
+        return small ? S.cls[S.idx[s] * D + S.idx[t]] : table[code3 | sig_bits(3, s) | sig_bits(4, t)];
+    };
+    // ---- the candidates again, 64 in hand at a time
+    uint32_t lone0 = 0, lone1 = 0;
+    for (uint32_t i0 = 0; i0 < len; i0 += 64) {
+        const uint32_t c = candidate(i0 + lane);
+        const unsigned long long m = __ballot(c != kNone);
+        const uint32_t nb = (uint32_t)__popcll(m);
+        if (nb == 0u) continue;
+        if (c != kNone) {
+            const uint32_t y = c & 0x3FFFu, s = (c >> 14) & 63u, at = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            const uint32_t code4 = code3 | sig_bits(3, s);
+            S.buf[at] = c;
+            S.lo[at] = G.off[y];
+            S.hi[at] = G.off[y + 1];
+            for (uint32_t k = 0; k < 3; k++) S.kcls[at * 3u + k] = table[code4 | pair_bits(3, 4, k + 1u)];
+            // c with every other candidate, by signature, as if not adjacent
+            for (uint32_t t = 0; t < D; t++) {
+                const uint32_t st = S.sig[t], n = S.cnt[t] - (st == s ? 1u : 0u);
+                if (n) K.add(y, pair_class(s, st), n);
+            }
+        }
+        wave_fence();
+        // 8 lanes per candidate y: y's row above r
+        for (uint32_t b0 = 0; b0 < nb; b0 += 8) {
+            const uint32_t bi = b0 + (lane >> 3), gl = lane & 7u;
+            const bool on = bi < nb;
+            const uint32_t e = on ? S.buf[bi] : kNone;
+            const uint32_t y = e & 0x3FFFu, s = (e >> 14) & 63u;
+            const uint32_t code4 = code3 | sig_bits(3, s);
+            uint32_t n1 = 0, n2 = 0, n3 = 0;
+            const uint32_t hi = on ? S.hi[bi] : 0u;
+            for (uint32_t i = (on ? S.lo[bi] : 0u) + gl; i < hi; i += 8u) {
+                const uint32_t ent = G.adj[i], z = ent >> 2, k = ent & 3u;
+                if (z <= r) continue;
+                const uint32_t cr = plane_code(PR, z), ca = plane_code(PA, z), cy = plane_code(PY, z);
+                if (!(cr | ca | cy)) {   // adjacent to none of the first three: the last member
+                    n1 += k == 1u;
+                    n2 += k == 2u;
+                    n3 += k == 3u;
+                    K.add(z, S.kcls[bi * 3u + k - 1u], 1u);
+                    continue;
+                }
+                // a candidate too?  It comes after y2 where it shares y2's row of choice.
+                const bool in = same ? (cr ? z > y2 : true) : (cr ? false : (ca ? z > y2 : true));
+                if (!in || z == a) continue;
+                const uint32_t sz = cr | (ca << 2) | (cy << 4);
+                const uint32_t was = pair_class(s, sz), is = table[code4 | sig_bits(4, sz) | pair_bits(3, 4, k)];
+                K.add(y, is, 1u);
+                K.sub1(y, was);
+                if (y < z) {
+                    K.add(r, is, 1u);
+                    K.add(a, is, 1u);
+                    K.add(y2, is, 1u);
+                    K.sub1(r, was);
+                    K.sub1(a, was);
+                    K.sub1(y2, was);
+                }
+            }
+            for (int o = 1; o < 8; o <<= 1) {
+                n1 += (uint32_t)__shfl_xor((int)n1, o, 64);
+                n2 += (uint32_t)__shfl_xor((int)n2, o, 64);
+                n3 += (uint32_t)__shfl_xor((int)n3, o, 64);
+            }
+            if (on && gl < 3u) {
+                const uint32_t n = gl == 0u ? n1 : (gl == 1u ? n2 : n3);
+                if (n) {
+                    K.add(y, S.kcls[bi * 3u + gl], n);
+                    atomicAdd(&S.lone[S.idx[s] * 3u + gl], n);
+                    if (e >> 20) lone1 += n;
+                    else lone0 += n;
+                }
+            }
+        }
+        wave_fence();
+    }
+    for (uint32_t i = lane; i < D * 3u; i += 64) {
+        const uint32_t n = S.lone[i];
+        if (!n) continue;
+        const uint32_t cls = table[code3 | sig_bits(3, S.sig[i / 3u]) | pair_bits(3, 4, i % 3u + 1u)];
+        K.add(r, cls, n);
+        K.add(a, cls, n);
+        K.add(y2, cls, n);
+    }
+    if (lone0) atomicAdd(&vis[base + 1u], (unsigned long long)lone0);
+    if (lone1) atomicAdd(&vis[base + 3u], (unsigned long long)lone1);
+    wave_fence();
+}
+
+// Per workgroup of BS threads: LDS planes of r, and per wave of a and of the third member;
+// the tree counters (A.dense) and the hash of 2^hbits cells.
+template <int BS>
+__global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
+    constexpr uint32_t NWV = BS / 64;
+    extern __shared__ uint2 dyn[];
+    __shared__ SetsWave wv[NWV];
+    __shared__ unsigned long long vis[8];
+    __shared__ uint8_t sSlotOf[kClassPad];
+    __shared__ uint32_t sUsed, sNext, sTask;
+    const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u, hn = 1u << hbits;
+    uint2* PR = dyn;
+    uint2* PA = dyn + (1u + wid) * A.words;
+    uint2* PY = dyn + (1u + NWV + wid) * A.words;
+    uint32_t* key = (uint32_t*)(dyn + (1u + 2u * NWV) * A.words);
+    uint32_t* val = key + hn;
+    uint32_t* dense = val + hn;
+    const SetsCounters L{(lptr<uint32_t>)dense, (lptr<const uint8_t>)sSlotOf, (lptr<uint32_t>)key, (lptr<uint32_t>)val,
+                         (lptr<uint32_t>)&sUsed, 32u - hbits, A.dense != 0u};
+    for (uint32_t i = tid; i < hn; i += BS) {
+        key[i] = kNone;
+        val[i] = 0u;
+    }
+    if (A.dense) {
+        for (uint32_t i = tid; i < kClassPad / 4; i += BS) ((uint32_t*)sSlotOf)[i] = ((const uint32_t*)A.slot_of)[i];
+        for (uint32_t i = tid; i < A.dense * kTreeSlots5; i += BS) dense[i] = 0u;
+    }
+    if (tid < 8) vis[tid] = 0ull;
+    if (tid == 0) sUsed = 0u;
+    for (;;) {   // a slot: a graph's items until none are left
+        __syncthreads();
+        if (tid == 0) sNext = atomicAdd(&A.cursors[0], 1u);
+        __syncthreads();
+        const uint32_t slot = sNext;
+        if (slot >= A.nslots) break;
+        const uint32_t g = A.slots ? A.slots[slot] : 0u;
+        const SetsGraph G = A.graphs ? A.graphs[g] : A.one;
+        unsigned* cursor = &A.cursors[1u + 2u * g];
+        const uint32_t nitems = cursor[1], W = (G.n + 31u) >> 5;
+        const SetsSink K{L, G};
+        auto empty_hash = [&]() {
+            for (uint32_t i = tid; i < hn; i += BS) {
+                const uint32_t k = key[i], n = val[i];
+                if (k == kNone) continue;
+                if (n) gadd64(K.cell(k), n);
+                key[i] = kNone;
+                val[i] = 0u;
+            }
+            if (tid == 0) sUsed = 0u;
+            __syncthreads();
+        };
+        __syncthreads();
+        if (tid == 0) sNext = atomicAdd(cursor, 1u);
+        __syncthreads();
+        uint32_t cur_r = kNone, cur_a = kNone;
+        for (;;) {
+            const uint32_t item = sNext;
+            const bool full = sUsed > hn / 8u * 5u;
+            if (item >= nitems) break;
+            const uint2 it = A.items[G.first + item];
+            const uint32_t r = it.x, r1 = G.off[r + 1], deg = r1 - G.off[r];
+            const uint32_t t1 = min(r1, it.y + item_step(r1 - G.split[r], deg));
+            __syncthreads();   // sNext and sUsed are read
+            if (full) empty_hash();
+            if (r != cur_r)
+                for (uint32_t i = tid; i < W; i += BS) PR[i] = make_uint2(0u, 0u);
+            if (tid == 0) sTask = 0u;
+            __syncthreads();
+            if (r != cur_r)
+                for (uint32_t i = G.off[r] + tid; i < r1; i += BS) {
+                    const uint32_t e = G.adj[i], z = e >> 2, bit = 1u << (z & 31u);
+                    if (e & 1u) atomicOr(&PR[z >> 5].x, bit);
+                    if (e & 2u) atomicOr(&PR[z >> 5].y, bit);
+                }
+            cur_r = r;
+            if (tid == 0) sNext = atomicAdd(cursor, 1u);
+            __syncthreads();
+            // tasks: third members, for each a of the item the rest of r's row, then a's row
+            uint32_t t = it.y, base = 0, a = G.adj[t] >> 2, a0 = G.off[a], a1 = G.off[a + 1];
+            for (;;) {
+                uint32_t task = 0;
+                if (lane == 0) task = atomicAdd(&sTask, 1u);
+                task = (uint32_t)__builtin_amdgcn_readfirstlane((int)task);
+                while (t < t1 && task >= base + (r1 - t - 1u) + (a1 - a0)) {
+                    base += (r1 - t - 1u) + (a1 - a0);
+                    if (++t == t1) break;
+                    a = G.adj[t] >> 2;
+                    a0 = G.off[a];
+                    a1 = G.off[a + 1];
+                }
+                if (t >= t1) break;
+                const uint32_t nx = r1 - t - 1u, i = task - base;
+                const bool same = i < nx;
+                const uint32_t q = same ? t + 1u + i : a0 + i - nx;
+                if (!same) {
+                    const uint32_t z = G.adj[q] >> 2;
+                    if (z <= r || plane_code(PR, z)) continue;
+                }
+                if (a != cur_a) {   // this wave's planes of a
+                    cur_a = a;
+                    for (uint32_t x = lane; x < W; x += 64) PA[x] = make_uint2(0u, 0u);
+                    wave_fence();
+                    for (uint32_t x = a0 + lane; x < a1; x += 64) {
+                        const uint32_t e = G.adj[x], z = e >> 2, bit = 1u << (z & 31u);
+                        if (e & 1u) atomicOr(&PA[z >> 5].x, bit);
+                        if (e & 2u) atomicOr(&PA[z >> 5].y, bit);
+                    }
+                    wave_fence();
+                }
+                five_triple(G, K, wv[wid], A.table, PR, PA, PY, W, r, a, q, same, vis);
+            }
+            __syncthreads();
+        }
+        // the slot's counters to the graph's output
+        __syncthreads();
+        empty_hash();
+        if (A.dense)
+            for (uint32_t i = tid; i < G.n * kTreeSlots5; i += BS) {
+                const uint32_t n = dense[i];
+                if (!n) continue;
+                dense[i] = 0u;
+                const uint32_t v = i / kTreeSlots5;
+                gadd64(&G.out[(size_t)G.perm[v] * kClasses5 + A.slot_cls[i - v * kTreeSlots5]], n);
+            }
+        if (tid < 8) {
+            if (vis[tid]) gadd64(&G.stats[tid], vis[tid]);
+            vis[tid] = 0ull;
+        }
+    }
 }
 
 // Per-device LDS counter slots: the single-arc tree classes found from each class's
@@ -736,23 +948,6 @@ const FiveSlots& five_slots() {
     return g_slots.emplace(dev, fs).first->second;   // kept for the life of the process
 }
 
-// 1-bit adjacency matrix (rank space) of a graph counted in device memory: row u set by
-// thread u from its CSR row (zeroed before)
-__global__ __launch_bounds__(256) void k_five_mat(const uint32_t* off, const uint32_t* adj, uint32_t n, uint32_t W,
-                                                   uint32_t* mat) {
-    const uint32_t u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= n) return;
-    uint32_t* row = mat + (size_t)u * W;
-    for (uint32_t x = off[u]; x < off[u + 1]; x++) {
-        const uint32_t v = adj[x] >> 2;
-        row[v >> 5] |= 1u << (v & 31u);
-    }
-}
-
-// the matrices, kept with their graphs until free_five
-std::mutex g_mat_mu;
-std::map<const vdmc_graph_s*, uint32_t*> g_five_mat;
-
 int g_ncu = -1;
 int ncu() {
     if (g_ncu < 0) {
@@ -765,106 +960,74 @@ int ncu() {
     return g_ncu;
 }
 
-// Launches prep, the search and (when some graph has several parts) the reduction.
-void launch_five(const FiveArgs& a, size_t lds, uint32_t num_graphs, bool reduce, hipStream_t st) {
-    hipLaunchKernelGGL(k_five_prep, dim3((std::max<uint32_t>(num_graphs, 1) + 255) / 256), dim3(256), 0, st, a);
-    VDMC_HIP(hipGetLastError());
-    // 16 waves per compute unit (the register budget): one 1024-thread workgroup when the
-    // LDS admits one, two of 512 threads when it admits two or three, else four of 256
-    const int fit = std::max(1, (int)(163840 / (lds + kFiveStaticLds)));
-    const int bs = fit == 1 ? 1024 : (fit <= 3 ? 512 : 256);
-    const int per_cu = 1024 / bs;
-    void (*kern)(FiveArgs) = bs == 1024 ? k_five<1024> : (bs == 512 ? k_five<512> : k_five<256>);
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(a.nslots, (int64_t)ncu() * per_cu));
-    VDMC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(bs), lds, st, a);
-    VDMC_HIP(hipGetLastError());
-    if (reduce) {
-        hipLaunchKernelGGL(k_five_reduce, dim3(256, std::min<uint32_t>(std::max<uint32_t>(num_graphs, 1), 65535u)),
-                           dim3(256), 0, st, a);
-        VDMC_HIP(hipGetLastError());
+SetsGraph view_of(const vdmc_graph_s* g, uint64_t* out) {
+    return SetsGraph{g->off, g->adj, g->split, g->perm, (unsigned long long*)out, g->stats, (uint32_t)g->n, 0u};
+}
+
+// LDS of k_five_sets: the largest launch shape that fits.  dense_n: vertices with LDS counters of
+// the tree classes.  1024 threads where the bit planes of 16 waves leave room for a hash of 4096
+// cells, else 256.
+struct SetsShape {
+    int bs;
+    uint32_t hbits;
+    size_t lds;
+};
+SetsShape sets_shape(uint32_t words, uint32_t dense_n) {
+    const size_t dense = (size_t)dense_n * kTreeSlots5 * sizeof(uint32_t);
+    for (int bs : {1024, 256}) {
+        const size_t fixed = sizeof(SetsWave) * (bs / 64) + kClassPad + 256;
+        const size_t need = (size_t)(1 + 2 * (bs / 64)) * words * sizeof(uint2) + dense;
+        for (uint32_t hb : {13u, 12u}) {
+            const size_t lds = need + ((size_t)8 << hb);
+            if (fixed + lds <= 163840) return SetsShape{bs, hb, lds};
+        }
     }
+    throw Error{VDMC_ERR_DEVICE, "bit planes exceed one workgroup's LDS"};
 }
 
-// estimated work of a graph: sum over vertices of d^4 (d = degree in G_U)
-double work_estimate(const vdmc_graph_s* g) {
-    if (g->n == 0) return 0.0;
-    std::vector<uint32_t> off((size_t)g->n + 1);
-    VDMC_HIP(hipMemcpy(off.data(), g->off, off.size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
-    double w = 0.0;
-    for (int64_t v = 0; v < g->n; v++) {
-        const double d = (double)(off[v + 1] - off[v]);
-        w += d * d * d * d;
-    }
-    return w;
+// Zeroes the outputs and counters, then counts every graph's items.
+void launch_sets(SetsArgs a, uint32_t num, size_t cells, hipStream_t st) {
+    const unsigned zx = (unsigned)std::max<size_t>(1, std::min<size_t>((cells / num + 1023) / 1024, 16384 / num + 1));
+    hipLaunchKernelGGL(k_five_zero, dim3(zx, std::min<uint32_t>(num, 65535u)), dim3(256), 0, st, a, num);
+    VDMC_HIP(hipGetLastError());
+    if (a.nslots == 0) return;
+    const FiveSlots& fs = five_slots();
+    a.table = class_table5().table;
+    a.slot_of = fs.slot_of;
+    a.slot_cls = fs.slot_cls;
+    const SetsShape sh = sets_shape(a.words, a.dense);
+    void (*kern)(SetsArgs, uint32_t) = sh.bs == 1024 ? k_five_sets<1024> : k_five_sets<256>;
+    VDMC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds));
+    const unsigned grid = (unsigned)std::min<int64_t>(a.nslots, (int64_t)ncu() * (1024 / sh.bs));
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(sh.bs), sh.lds, st, a, sh.hbits);
+    VDMC_HIP(hipGetLastError());
 }
 
-size_t block_bytes(const vdmc_graph_s* g) { return (size_t)g->n * kClasses5 * sizeof(unsigned long long); }
-
-FiveGraph view_of(const vdmc_graph_s* g, uint64_t* out) {
-    FiveGraph v{};
-    v.off = g->off;
-    v.adj = g->adj;
-    v.perm = g->perm;
-    v.out = (unsigned long long*)out;
-    v.stats = g->stats;
-    v.n = (uint32_t)g->n;
-    v.entries = (uint32_t)(2 * g->pairs);
-    v.parts = 1;
-    return v;
-}
-
-// cached descriptors of batched 5-vertex launches, by (graphs, outputs).  Only the
-// read-only graph views and the slot order are kept; the cursors and the private copies
-// are taken from the stream-ordered pool for each call.
+// cached descriptors of batched 5-vertex launches, by (graphs, outputs): the graph views,
+// the item table and its cursor
 struct FivePlan {
     std::vector<vdmc_graph_s*> graphs;
     std::vector<uint64_t*> outs;
-    FiveGraph* d_graphs = nullptr;
-    uint2* d_slots = nullptr;
-    uint32_t nslots = 0;
-    size_t scratch = 0;   // bytes of private copies of parts 1..
-    bool reduce = false;
-    size_t lds = 0;
+    SetsGraph* d_graphs = nullptr;
+    uint2* d_items = nullptr;
+    uint32_t* d_slots = nullptr;
+    unsigned* d_cursors = nullptr;
+    uint32_t nslots = 0, words = 1, dense = 0;
+    size_t cells = 0;
     ~FivePlan() {
         (void)hipFree(d_graphs);
+        (void)hipFree(d_items);
         (void)hipFree(d_slots);
+        (void)hipFree(d_cursors);
     }
 };
 std::mutex g_five_mu;
 std::vector<FivePlan*> g_five_plans;
 
-// The private copies come from the device's default stream-ordered pool.  It keeps up to one
-// batched launch's budget after the frees, so repeated counts reuse the same pages instead
-// of mapping them anew; what lies above that goes back to the device at synchronisation.
-std::mutex g_pool_mu;
-uint64_t g_pool_set = 0;   // devices whose pool threshold is set (bit per device id < 64)
-void keep_scratch_pool() {
-    int dev = 0;
-    VDMC_HIP(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(g_pool_mu);
-    if (dev < 64 && (g_pool_set >> dev) & 1u) return;
-    hipMemPool_t pool;
-    VDMC_HIP(hipDeviceGetDefaultMemPool(&pool, dev));
-    uint64_t keep = kBatchScratchBudget + (size_t(256) << 20);
-    VDMC_HIP(hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep));
-    if (dev < 64) g_pool_set |= uint64_t(1) << dev;
-}
+// whether k_five_sets takes the graph
+bool takes_sets(const vdmc_graph_s* g) { return g->n <= kFiveSetsMaxN && g->pairs <= kFiveSetsMaxPairs; }
 
-}  // namespace
-
-size_t five_lds_bytes(int64_t n, int64_t entries) {
-    const int64_t W = (n + 31) / 32;
-    return (size_t)(4 * ((n + 1) + n + (n + 1) + n + entries + n * W + n * (int64_t)kTreeSlots5));
-}
-
-bool five_eligible(int64_t n, int64_t entries) {
-    return n <= kFiveMaxN && five_lds_bytes(n, entries) <= kFiveLdsBudget;
-}
-
-namespace {
-
-// 5-vertex counts of a graph that LDS does not hold: every workgroup of the grid takes
+// 5-vertex counts set by set over the graph in device memory: every workgroup of the grid takes
 // sub-items from one cursor and credits the caller's output with device-scope atomics.
 // Needs the graph's edge hash and its item prefix (both built at the first such count
 // and kept with the graph).
@@ -877,8 +1040,14 @@ void launch_count5_global(vdmc_graph_s* g, uint64_t* out, hipStream_t st) {
     ensure_edge_hash(g, st);
     if (!g->five_hp) {
         const uint32_t n = (uint32_t)g->n;
-        unsigned long long *cnt = nullptr, *hp = nullptr;
+        unsigned long long* hp = nullptr;
         VDMC_HIP(hipMalloc(&hp, sizeof(unsigned long long) * (n + 2)));   // prefix, then the item cursor
+        g->five_hp = hp;   // owned by the graph from here on; five_items 0: not filled yet
+        g->five_items = 0;
+    }
+    if (g->five_items == 0) {
+        const uint32_t n = (uint32_t)g->n;
+        unsigned long long *cnt = nullptr, *hp = g->five_hp;
         VDMC_HIP(hipMalloc(&cnt, sizeof(unsigned long long) * (n + 1)));
         struct Free {
             void* p;
@@ -890,38 +1059,17 @@ void launch_count5_global(vdmc_graph_s* g, uint64_t* out, hipStream_t st) {
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, cnt, hp, n + 1, st));
         void* tmp = nullptr;
         VDMC_HIP(hipMalloc(&tmp, tmp_bytes ? tmp_bytes : 16));
-        struct Free2 {
-            void* p;
-            ~Free2() { (void)hipFree(p); }
-        } ftmp{tmp};
+        Free ftmp{tmp};
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, cnt, hp, n + 1, st));
         unsigned long long total = 0;
         VDMC_HIP(hipMemcpyAsync(&total, hp + n, sizeof(total), hipMemcpyDeviceToHost, st));
         VDMC_HIP(hipStreamSynchronize(st));
-        g->five_hp = hp;
         g->five_items = total;
-    }
-    const uint32_t W = (uint32_t)((g->n + 31) / 32);
-    uint32_t* mat = nullptr;
-    if (g->n <= kFiveMatMaxN) {
-        std::lock_guard<std::mutex> lock(g_mat_mu);
-        auto it = g_five_mat.find(g);
-        if (it != g_five_mat.end()) {
-            mat = it->second;
-        } else {
-            const size_t words = ((size_t)g->n * W + 1) & ~(size_t)1;   // even: zeroed as u64
-            VDMC_HIP(hipMalloc(&mat, words * sizeof(uint32_t)));
-            launch_fill_u64(reinterpret_cast<uint64_t*>(mat), words / 2, 0, st);
-            hipLaunchKernelGGL(k_five_mat, dim3((uint32_t)((g->n + 255) / 256)), dim3(256), 0, st, g->off, g->adj,
-                               (uint32_t)g->n, W, mat);
-            VDMC_HIP(hipGetLastError());
-            g_five_mat[g] = mat;
-        }
     }
     unsigned long long* cursor = g->five_hp + g->n + 1;
     launch_fill_u64((uint64_t*)cursor, 1, 0, st);
     FiveGlobalArgs a{};
-    a.L = FiveGlobal{g->off, g->adj, reinterpret_cast<const uint32_t*>(g->perm), g->ehash, g->ehash_bits, mat, W};
+    a.L = FiveGlobal{g->off, g->adj, reinterpret_cast<const uint32_t*>(g->perm), g->ehash, g->ehash_bits};
     a.split = g->split;
     a.hp = g->five_hp;
     a.n = (uint32_t)g->n;
@@ -941,123 +1089,95 @@ void launch_count5_global(vdmc_graph_s* g, uint64_t* out, hipStream_t st) {
 
 void launch_count5(vdmc_graph_s* g, uint64_t* out, hipStream_t st) {
     g->timed_light = g->timed_hub = false;
-    if (!five_eligible(g->n, 2 * g->pairs)) {
+    if (!takes_sets(g)) {
         launch_count5_global(g, out, st);
         return;
     }
-    const ClassTable5& t = class_table5();
-    // parts: one per 32 items, at most two per compute unit, copies within the budget.  The
-    // cursors and the copies come from the stream-ordered pool and go back to it after the
-    // launches, so concurrent counts on other streams never share them.
-    const size_t bb = std::max<size_t>(block_bytes(g), 16);
-    const uint32_t by_items = std::max<uint32_t>(1u, (uint32_t)(g->pairs / 32));
-    const uint32_t by_mem = (uint32_t)std::min<size_t>(kMaxParts, 1 + kSingleScratchBudget / bb);
-    const uint32_t parts = std::max<uint32_t>(1u, std::min<uint32_t>({by_items, by_mem, (uint32_t)(2 * ncu())}));
-    const size_t bytes = 256 + (size_t)(parts - 1) * bb;
-    keep_scratch_pool();
-    void* buf = nullptr;
-    VDMC_HIP(hipMallocAsync(&buf, bytes, st));
-    FiveArgs a{};
-    a.graphs = nullptr;
+    SetsArgs a{};
     a.one = view_of(g, out);
-    a.one.copies_off = 0;
-    a.one.parts = parts;
-    a.num = 1;
-    a.slots = nullptr;
-    a.nslots = g->n > 0 ? parts : 0u;
-    a.cursors = static_cast<unsigned*>(buf);
-    a.copies = parts > 1 ? reinterpret_cast<unsigned long long*>(static_cast<char*>(buf) + 256) : nullptr;
-    a.table = t.table;
-    const FiveSlots& fs = five_slots();
-    a.slot_of = fs.slot_of;
-    a.slot_cls = fs.slot_cls;
-    a.split_div = kSplitDiv;
-    try {
-        launch_five(a, five_lds_bytes(g->n, 2 * g->pairs), 1, parts > 1, st);
-    } catch (...) {
-        (void)hipFreeAsync(buf, st);
-        throw;
+    // the item table (8 bytes per pair), then the cursors; kept with the graph
+    if (!g->five_tab) {
+        void* tab = nullptr;
+        VDMC_HIP(hipMalloc(&tab, sizeof(uint2) * (size_t)(g->pairs + 2)));
+        g->five_tab = tab;
     }
-    VDMC_HIP(hipFreeAsync(buf, st));
+    uint2* items = (uint2*)g->five_tab;
+    a.items = items;
+    a.cursors = reinterpret_cast<unsigned*>(items + g->pairs);
+    if (!g->five_tab_ready) {
+        hipLaunchKernelGGL(k_five_items, dim3(1), dim3(kItemThreads), 0, st, nullptr, a.one, items, a.cursors);
+        VDMC_HIP(hipGetLastError());
+        g->five_tab_ready = true;
+    }
+    a.nslots = (uint32_t)std::min<int64_t>((g->pairs + 3) / 4, (int64_t)ncu() * 4);
+    a.words = (uint32_t)std::max<int64_t>(1, (g->n + 31) / 32);
+    a.dense = g->n <= kDenseMaxN ? (uint32_t)g->n : 0u;
+    launch_sets(a, 1, (size_t)g->n * kClasses5, st);
 }
 
 void free_five(vdmc_graph_s* g) {
     (void)hipFree(g->five_hp);
+    (void)hipFree(g->five_tab);
     g->five_hp = nullptr;
+    g->five_tab = nullptr;
+    g->five_tab_ready = false;
     g->five_items = 0;
-    std::lock_guard<std::mutex> lock(g_mat_mu);
-    auto it = g_five_mat.find(g);
-    if (it != g_five_mat.end()) {
-        (void)hipFree(it->second);
-        g_five_mat.erase(it);
-    }
 }
 
-void count5_batch_lds(std::vector<vdmc_graph_s*>& gs, std::vector<uint64_t*>& outv, hipStream_t st) {
-    const int32_t num = (int32_t)gs.size();
-    if (num == 0) return;
-    uint64_t* const* outs = outv.data();
-    const ClassTable5& t = class_table5();
+// the graphs of one batched launch (all taken by k_five_sets)
+static void count5_batch_sets(const std::vector<vdmc_graph_s*>& gs, const std::vector<uint64_t*>& outs, hipStream_t st) {
+    if (gs.empty()) return;
     std::lock_guard<std::mutex> lock(g_five_mu);
     FivePlan* plan = nullptr;
     for (FivePlan* p : g_five_plans)
-        if (p->graphs == gs && std::equal(p->outs.begin(), p->outs.end(), outs)) {
+        if (p->graphs == gs && p->outs == outs) {
             plan = p;
             break;
         }
+    GraphUse use(gs, st);   // ordered after earlier work on these graphs
     if (!plan) {
         plan = new FivePlan();
         try {
             plan->graphs = gs;
-            plan->outs.assign(outs, outs + num);
-            std::vector<double> work(num);
+            plan->outs = outs;
+            // heaviest graphs first (pairs x squared largest degree as the estimate), so that
+            // the last workgroups hold small ones
+            std::vector<uint32_t> order(gs.size());
+            for (uint32_t i = 0; i < order.size(); i++) order[i] = i;
+            const auto work = [&](uint32_t i) { return (double)gs[i]->pairs * gs[i]->max_deg * gs[i]->max_deg; };
+            std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return work(x) > work(y); });
+            // slots: workgroups per graph by its share of the work, about two per compute unit
             double total = 0.0;
-            for (int i = 0; i < num; i++) {
-                work[i] = work_estimate(gs[i]);
-                total += work[i];
+            for (uint32_t i : order) total += work(i);
+            std::vector<SetsGraph> views;
+            std::vector<uint32_t> slots;
+            uint32_t nitems = 0;
+            int64_t max_n = 1;
+            for (uint32_t i : order) {
+                const double share = total > 0.0 ? work(i) / total * 2.0 * ncu() : 1.0;
+                const uint32_t parts = (uint32_t)std::max(1.0, std::min({std::ceil(share), 64.0, gs[i]->pairs / 16.0}));
+                for (uint32_t p = 0; p < parts; p++) slots.push_back((uint32_t)views.size());
+                views.push_back(view_of(gs[i], outs[i]));
+                views.back().first = nitems;
+                nitems += (uint32_t)gs[i]->pairs;
+                max_n = std::max(max_n, gs[i]->n);
+                plan->cells += (size_t)gs[i]->n * kClasses5;
             }
-            // parts per graph: about kPartsPerCu per compute unit over the batch, more for the
-            // heavy graphs; coarser while the private copies exceed the budget
-            std::vector<uint32_t> parts(num, 1);
-            double unit = total / std::max(1.0, (double)kPartsPerCu * ncu());
-            for (int round = 0; round < 32; round++) {
-                size_t scratch = 0;
-                for (int i = 0; i < num; i++) {
-                    const double want = unit > 0 ? std::ceil(work[i] / unit) : 1.0;
-                    parts[i] = (uint32_t)std::max(1.0, std::min<double>(kMaxParts, want));
-                    if (gs[i]->pairs < 64) parts[i] = 1;
-                    scratch += (size_t)(parts[i] - 1) * block_bytes(gs[i]);
-                }
-                if (scratch <= kBatchScratchBudget) break;
-                unit *= 1.5;
-            }
-            std::vector<int> order(num);
-            for (int i = 0; i < num; i++) order[i] = i;
-            std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
-            std::vector<FiveGraph> views(num);
-            std::vector<uint2> slots;
-            size_t scratch = 0;
-            for (int i = 0; i < num; i++) {
-                views[i] = view_of(gs[i], outs[i]);
-                views[i].parts = parts[i];
-                scratch += (size_t)(parts[i] - 1) * block_bytes(gs[i]);
-                plan->lds = std::max(plan->lds, five_lds_bytes(gs[i]->n, 2 * gs[i]->pairs));
-                plan->reduce |= parts[i] > 1;
-            }
-            for (int i : order)
-                for (uint32_t p = 0; p < parts[i]; p++) slots.push_back(make_uint2((unsigned)i, p));
             plan->nslots = (uint32_t)slots.size();
-            plan->scratch = scratch;
-            size_t at = 0;
-            for (int i = 0; i < num; i++) {
-                views[i].copies_off = at / sizeof(unsigned long long);
-                at += (size_t)(parts[i] - 1) * block_bytes(gs[i]);
-            }
-            VDMC_HIP(hipMalloc(&plan->d_graphs, sizeof(FiveGraph) * std::max(num, 1)));
-            VDMC_HIP(hipMalloc(&plan->d_slots, sizeof(uint2) * std::max<size_t>(slots.size(), 1)));
-            VDMC_HIP(hipMemcpy(plan->d_graphs, views.data(), sizeof(FiveGraph) * num, hipMemcpyHostToDevice));
-            if (!slots.empty())
-                VDMC_HIP(hipMemcpy(plan->d_slots, slots.data(), sizeof(uint2) * slots.size(), hipMemcpyHostToDevice));
+            plan->words = (uint32_t)((max_n + 31) / 32);
+            plan->dense = max_n <= kDenseMaxN ? (uint32_t)max_n : 0u;
+            VDMC_HIP(hipMalloc(&plan->d_graphs, sizeof(SetsGraph) * views.size()));
+            VDMC_HIP(hipMalloc(&plan->d_items, sizeof(uint2) * std::max<size_t>(nitems, 1)));
+            VDMC_HIP(hipMalloc(&plan->d_slots, sizeof(uint32_t) * slots.size()));
+            VDMC_HIP(hipMalloc(&plan->d_cursors, sizeof(unsigned) * (2 * views.size() + 2)));
+            VDMC_HIP(hipMemcpyAsync(plan->d_graphs, views.data(), sizeof(SetsGraph) * views.size(), hipMemcpyHostToDevice,
+                                    st));
+            VDMC_HIP(hipMemcpyAsync(plan->d_slots, slots.data(), sizeof(uint32_t) * slots.size(), hipMemcpyHostToDevice,
+                                    st));
+            hipLaunchKernelGGL(k_five_items, dim3((unsigned)views.size()), dim3(kItemThreads), 0, st, plan->d_graphs,
+                               SetsGraph{}, plan->d_items, plan->d_cursors);
+            VDMC_HIP(hipGetLastError());
+            VDMC_HIP(hipStreamSynchronize(st));   // the host arrays are read by the copies
         } catch (...) {
             delete plan;
             throw;
@@ -1068,67 +1188,56 @@ void count5_batch_lds(std::vector<vdmc_graph_s*>& gs, std::vector<uint64_t*>& ou
             g_five_plans.erase(g_five_plans.begin());
         }
     }
-    GraphUse use(plan->graphs, st);   // ordered after earlier work on these graphs
     for (auto* g : gs) g->timed_light = g->timed_hub = false;
-    FiveArgs a{};
+    SetsArgs a{};
     a.graphs = plan->d_graphs;
-    a.num = (uint32_t)num;
+    a.items = plan->d_items;
     a.slots = plan->d_slots;
     a.nslots = plan->nslots;
-    a.table = t.table;
-    const FiveSlots& fs = five_slots();
-    a.slot_of = fs.slot_of;
-    a.slot_cls = fs.slot_cls;
-    a.split_div = kSplitDiv;
-    // cursors and copies for this call only: concurrent counts of other batches on other
-    // streams never share them, and no cached plan holds copies between calls
-    const size_t head = (sizeof(unsigned) * ((size_t)num + 1) + 255) / 256 * 256;
-    keep_scratch_pool();
-    void* buf = nullptr;
-    VDMC_HIP(hipMallocAsync(&buf, head + plan->scratch, st));
-    a.cursors = static_cast<unsigned*>(buf);
-    a.copies = plan->scratch ? reinterpret_cast<unsigned long long*>(static_cast<char*>(buf) + head) : nullptr;
-    try {
-        launch_five(a, plan->lds, (uint32_t)num, plan->reduce, st);
-    } catch (...) {
-        (void)hipFreeAsync(buf, st);
-        throw;
-    }
-    VDMC_HIP(hipFreeAsync(buf, st));
+    a.cursors = plan->d_cursors;
+    a.words = plan->words;
+    a.dense = plan->dense;
+    launch_sets(a, (uint32_t)gs.size(), plan->cells, st);
 }
 
 void count5_batch(const vdmc_graph_s* const* gs_in, int32_t num, uint64_t* const* outs_in, hipStream_t st) {
-    // graphs that LDS holds go into one batched launch; the others are counted one by one
-    // in device memory after it
-    std::vector<vdmc_graph_s*> gs;
-    std::vector<uint64_t*> outv;
-    for (int i = 0; i < num; i++) {
-        vdmc_graph_s* g = const_cast<vdmc_graph_s*>(gs_in[i]);
-        if (five_eligible(g->n, 2 * g->pairs)) {
+    // graphs that k_five_sets takes go into batched launches (at most 2 GiB of items each);
+    // the others are counted one by one
+    for (const bool small : {true, false}) {   // with and without LDS counters
+        std::vector<vdmc_graph_s*> gs;
+        std::vector<uint64_t*> outs;
+        int64_t pairs = 0;
+        for (int i = 0; i < num; i++) {
+            vdmc_graph_s* g = const_cast<vdmc_graph_s*>(gs_in[i]);
+            if (!takes_sets(g) || (g->n <= kDenseMaxN) != small) continue;
+            if (pairs + g->pairs > kFiveSetsMaxPairs * 16) {
+                count5_batch_sets(gs, outs, st);
+                gs.clear();
+                outs.clear();
+                pairs = 0;
+            }
             gs.push_back(g);
-            outv.push_back(outs_in[i]);
+            outs.push_back(outs_in[i]);
+            pairs += g->pairs;
         }
+        count5_batch_sets(gs, outs, st);
     }
-    count5_batch_lds(gs, outv, st);
     for (int i = 0; i < num; i++) {
         vdmc_graph_s* g = const_cast<vdmc_graph_s*>(gs_in[i]);
-        if (!five_eligible(g->n, 2 * g->pairs)) {
-            GraphUse use(g, st);
-            launch_count5_global(g, outs_in[i], st);
-        }
+        if (takes_sets(g)) continue;
+        GraphUse use(g, st);
+        launch_count5_global(g, outs_in[i], st);
     }
 }
 
 void invalidate_five_plans(vdmc_graph_s* g) {
-    {
-        std::lock_guard<std::mutex> lock(g_five_mu);
-        for (auto it = g_five_plans.begin(); it != g_five_plans.end();) {
-            if (std::find((*it)->graphs.begin(), (*it)->graphs.end(), g) != (*it)->graphs.end()) {
-                delete *it;
-                it = g_five_plans.erase(it);
-            } else {
-                ++it;
-            }
+    std::lock_guard<std::mutex> lock(g_five_mu);
+    for (auto it = g_five_plans.begin(); it != g_five_plans.end();) {
+        if (std::find((*it)->graphs.begin(), (*it)->graphs.end(), g) != (*it)->graphs.end()) {
+            delete *it;
+            it = g_five_plans.erase(it);
+        } else {
+            ++it;
         }
     }
 }

@@ -129,22 +129,47 @@ __device__ __forceinline__ void cmp_line(const HubArgs& A, uint32_t v, uint32_t 
     }
 }
 
-// The depth-2 vertices of a root: bitmap B2 over ranks, P2[w] = how many lie before word w
-// (for words that hold one); index of vertex e among them, or ~0
-__device__ __forceinline__ uint32_t find2(const uint32_t* B2, const uint32_t* P2, uint32_t e) {
-    const uint32_t w = B2[e >> 5], bit = 1u << (e & 31u);
-    return (w & bit) ? P2[e >> 5] + (uint32_t)__popc(w & (bit - 1u)) : ~0u;
-}
-// B2 and P2 from the ascending list of the depth-2 vertices (every thread of the workgroup)
-__device__ __forceinline__ void index2(uint32_t* B2, uint32_t* P2, uint32_t nbw, const uint32_t* cids, uint32_t nc) {
-    for (uint32_t i = threadIdx.x; i < nbw; i += HT) B2[i] = 0u;
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < nc; j += HT) {
-        const uint32_t c = cids[j];
-        atomicOr(&B2[c >> 5], 1u << (c & 31u));
-        if (j == 0u || (cids[j - 1u] >> 5) != (c >> 5)) P2[c >> 5] = j;
+// The depth-2 vertices of a root: bitmap B over ranks, P[w] = how many lie before word w (for
+// words that hold one), in LDS or in the workgroup's scratch.
+struct Index2 {
+    bool in_lds;
+    lptr<uint32_t> lb, lp;
+    gptr<uint32_t> gb, gp;
+    __device__ __forceinline__ Index2(bool lds, uint32_t* l, uint32_t* g, uint32_t nbw)
+        : in_lds(lds), lb(l), lp(l + nbw), gb(g), gp(g + nbw) {}
+    __device__ __forceinline__ uint32_t word(uint32_t w) const { return in_lds ? lb[w] : gb[w]; }
+    __device__ __forceinline__ uint32_t before(uint32_t w) const { return in_lds ? lp[w] : gp[w]; }
+    __device__ __forceinline__ void mark(uint32_t e) const {
+        const uint32_t bit = 1u << (e & 31u);
+        if (in_lds) __hip_atomic_fetch_or((lb + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_fetch_or((gb + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-}
+    __device__ __forceinline__ void set_before(uint32_t w, uint32_t j) const {
+        if (in_lds) lp[w] = j;
+        else gp[w] = j;
+    }
+    __device__ __forceinline__ void clear(uint32_t nbw) const {
+        if (in_lds)
+            for (uint32_t i = threadIdx.x; i < nbw; i += HT) lb[i] = 0u;
+        else
+            for (uint32_t i = threadIdx.x; i < nbw; i += HT) gb[i] = 0u;
+    }
+    // index of vertex e among the depth-2 vertices, or ~0
+    __device__ __forceinline__ uint32_t find(uint32_t e) const {
+        const uint32_t w = word(e >> 5), bit = 1u << (e & 31u);
+        return (w & bit) ? before(e >> 5) + (uint32_t)__popc(w & (bit - 1u)) : ~0u;
+    }
+    // from the ascending list of the depth-2 vertices (every thread of the workgroup)
+    __device__ __forceinline__ void fill(uint32_t nbw, const uint32_t* cids, uint32_t nc) const {
+        clear(nbw);
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < nc; j += HT) {
+            const uint32_t c = cids[j];
+            mark(c);
+            if (j == 0u || (cids[j - 1u] >> 5) != (c >> 5)) set_before(c >> 5, j);
+        }
+    }
+};
 
 // f(cls, sum of val) once per distinct class among the lanes with `active` (the whole wave calls it)
 template <class F>
@@ -284,7 +309,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     // s2cap x 16 bytes: first an entry's place among its parents (one word each), then the
     // parents of the j-th by the codes (to r, to c): nine 12-bit counts, five in the first
     // word, four in the second, and above them the mask of the non-zero ones
-    ulonglong2* pcount = (ulonglong2*)(((uintptr_t)(cids + A.s2cap) + 15u) & ~(uintptr_t)15u);
+    ulonglong2* pcount = (ulonglong2*)(S + ((DMAX + 2 + 4 * (size_t)A.s2cap + 3) & ~(size_t)3));
     uint32_t* place = (uint32_t*)pcount;
     uint32_t* gbits = (uint32_t*)(pcount + A.s2cap);             // 2 x nbw: B2 and P2 when LDS has no room
     const uint32_t nbw = (A.n + 31u) >> 5;
@@ -359,11 +384,9 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             for (uint32_t i = tid; i < D * kClasses3; i += HT) R3[i] = 0u;
         // the depth-2 vertices in a bitmap over ranks, in LDS where it fits
         const uint32_t used = SHASH / 2 + HT + (A.k3 ? D * kClasses3 : 0u);
-        uint32_t* B2 = used + 2u * nbw <= U_WORDS ? L.U + used : gbits;
-        uint32_t* P2 = B2 + nbw;
-        const bool kept = B2 == gbits;   // phases E and G find it there
-        if (A.k4)
-            for (uint32_t i = tid; i < nbw; i += HT) B2[i] = 0u;
+        const bool kept = used + 2u * nbw > U_WORDS;   // in scratch: phases E and G find it there
+        const Index2 X2(!kept, L.U + used, gbits, nbw);
+        if (A.k4) X2.clear(nbw);
         __syncthreads();
         for (;;) {
             const uint32_t x = wave_task(&L.ctr[0]);
@@ -403,7 +426,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 if (A.k4) {   // depth-2 entry (x, e): e marked, the entry behind x's row
                     const unsigned long long md = __ballot(d2);
                     if (d2) {
-                        atomicOr(&B2[e >> 5], 1u << (e & 31u));
+                        X2.mark(e);
                         locnbr[end - 1u - nch - (uint32_t)__popcll(md & ((1ull << lane) - 1ull))] = (e << 2) | ec;
                     }
                     nch += (uint32_t)__popcll(md);
@@ -422,19 +445,19 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // A(c_j) = parents[poff[j] .. poff[j + 1])
         uint32_t ngroups = 0;
         if (A.k4) {
-            for (uint32_t i = tid; i < nbw; i += HT) P2[i] = (uint32_t)__popc(B2[i]);
+            for (uint32_t i = tid; i < nbw; i += HT) X2.set_before(i, (uint32_t)__popc(X2.word(i)));
             __syncthreads();
-            ngroups = block_scan(P2, nbw, part);
+            ngroups = kept ? block_scan(gbits + nbw, nbw, part) : block_scan(L.U + used + nbw, nbw, part);
             for (uint32_t i = tid; i < nbw; i += HT) {
-                uint32_t at = P2[i];
-                for (uint32_t w = B2[i]; w; w &= w - 1u) cids[at++] = (i << 5) + (uint32_t)__ffs((int)w) - 1u;
+                uint32_t at = X2.before(i);
+                for (uint32_t w = X2.word(i); w; w &= w - 1u) cids[at++] = (i << 5) + (uint32_t)__ffs((int)w) - 1u;
             }
             for (uint32_t j = tid; j <= ngroups; j += HT) poff[j] = 0u;
             __syncthreads();
             for (uint32_t x = wid; x < D; x += NW) {
                 const uint32_t end = locoff[x + 1], m = end - locoff[x] - L.locn[x];
                 for (uint32_t i = lane; i < m; i += 64) {
-                    const uint32_t ent = locnbr[end - 1u - i], j = find2(B2, P2, ent >> 2);
+                    const uint32_t ent = locnbr[end - 1u - i], j = X2.find(ent >> 2);
                     locnbr[end - 1u - i] = (j << 2) | (ent & 3u);
                     place[end - 1u - i] = atomicAdd(&poff[j], 1u);
                 }
@@ -809,14 +832,13 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             uint16_t* H2 = (uint16_t*)(L.U + nxw + (HT / 16) * GW + NW * AW + NW * CW);
             uint32_t* M0 = L.U + nxw + FIX + wid * mw;              // children with arc bit 0, or the filter
             uint32_t* M1 = M0 + jw;                                 // children with arc bit 1
-            uint32_t* B2 = in_lds ? L.U + nxw + FIX + NW * mw : gbits;
-            uint32_t* P2 = B2 + nbw;
+            const Index2 X2(in_lds, L.U + nxw + FIX + NW * mw, gbits, nbw);
             for (uint32_t i = nxw + tid; i < nxw + FIX; i += HT) L.U[i] = 0u;
             for (uint32_t i = lane; i < mw; i += 64) M0[i] = 0u;
             if (tid == 0) L.ctr[6] = 0u;
             __syncthreads();
             for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
-            if (in_lds || !kept) index2(B2, P2, nbw, cids, ngroups);
+            if (in_lds || !kept) X2.fill(nbw, cids, ngroups);
             __syncthreads();
             auto add_r = [&](uint32_t cls, uint32_t n) {
                 atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n);
@@ -876,13 +898,13 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         else e12 += ce == 1u ? 1u : 1u << 16;
                         uint32_t ae = 0, j2 = 0;   // e another child of a: its code
                         if (coded) {
-                            j2 = find2(B2, P2, e);
+                            j2 = X2.find(e);
                             if (j2 == ~0u) continue;
                             ae = ((M0[j2 >> 5] >> (j2 & 31u)) & 1u) | (((M1[j2 >> 5] >> (j2 & 31u)) & 1u) << 1);
                         } else {
                             const uint32_t b = filter_bit(e);
                             if (!((M0[b >> 5] >> (b & 31u)) & 1u)) continue;
-                            j2 = find2(B2, P2, e);
+                            j2 = X2.find(e);
                             if (j2 == ~0u) continue;
                             uint32_t lo = 0, hi = m;
                             while (lo + 1u < hi) {
@@ -1010,8 +1032,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             uint16_t* LST = (uint16_t*)(L.U + (HT / 16) * GW + wid * CW);   // per wave: 256 marked vertices
             uint16_t* H2 = (uint16_t*)(L.U + (HT / 16) * GW + NW * CW);
             uint32_t* KS = L.U + FIX - 32;   // path counter of the codes ((r -> a, a -> c) - 1) * 3 + (c -> e) - 1
-            uint32_t* B2 = in_lds ? L.U + FIX : gbits;
-            uint32_t* P2 = B2 + nbw;
+            const Index2 X2(in_lds, L.U + FIX, gbits, nbw);
             uint32_t* BM = L.U + FIX + (in_lds ? 2u * nbw : 0u);
             const uint32_t win = min(nbw, U_WORDS - (uint32_t)(BM - L.U));   // words of a window
             for (uint32_t i = tid; i < FIX - 32; i += HT) L.U[i] = 0u;
@@ -1019,7 +1040,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 KS[tid] = cmp_of[L.t4[motif_index4(tid / 9u + 1u, 0u, 0u, tid % 9u / 3u + 1u, 0u, tid % 3u + 1u)]];
             __syncthreads();
             for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
-            if (in_lds || !kept) index2(B2, P2, nbw, cids, ngroups);
+            if (in_lds || !kept) X2.fill(nbw, cids, ngroups);
             for (uint32_t w0 = (r + 1u) >> 5; w0 < nbw; w0 += win) {
                 const uint32_t wn = min(win, nbw - w0), e0 = w0 << 5;
                 __syncthreads();
@@ -1062,7 +1083,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                             for (uint32_t q = (on ? A.off[e] : 0u) + gl; q < q1; q += 16u) {
                                 const uint32_t ee = A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
                                 if (c <= r || (G > 1u && c % G != share)) continue;
-                                const uint32_t j = find2(B2, P2, c);
+                                const uint32_t j = X2.find(c);
                                 if (j == ~0u) continue;
                                 const ulonglong2 pc = pcount[j];
                                 for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {

@@ -43,9 +43,9 @@ struct LightLds {
 
 __device__ __forceinline__ uint32_t lhash(uint32_t x, uint32_t cap) { return (x * 2654435761u >> 16) & (cap - 1u); }
 
-__device__ __forceinline__ void ladd(unsigned long long* out, const int32_t* perm, uint32_t C, uint32_t v, uint32_t cls,
+__device__ __forceinline__ void ladd(gptr<unsigned long long> out, gptr<const int32_t> perm, uint32_t C, uint32_t v, uint32_t cls,
                                      unsigned long long n) {
-    atomicAdd(&out[(size_t)perm[v] * C + cls], n);
+    gadd64(&out[(size_t)perm[v] * C + cls], n);
 }
 
 // all threads of a root's group have arrived and see each other's LDS writes
@@ -201,7 +201,7 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
             const uint32_t a0 = S.X0[a], a1 = S.X1[a];
             const uint32_t all = d < 32u ? (1u << d) - 1u : ~0u;
             uint32_t run = 0xFFu, n = 0;
-            unsigned long long* row = &gv.out4[(size_t)gv.perm[c] * kClasses4];
+            gptr<unsigned long long> row = &gv.out4[(size_t)gv.perm[c] * kClasses4];
             for (uint32_t m = all & ~(1u << a) & ~((c0 | c1) & ((1u << a) - 1u)); m; m &= m - 1u) {
                 const uint32_t b = (uint32_t)__ffs((int)m) - 1u;
                 const uint32_t cls = t4[motif_index4(ra, S.P[b] & 3u, 0u, code(a0, a1, b), ac, code(c0, c1, b))];
@@ -211,7 +211,7 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                     if (n) {
                         add_a(a, run, n);
                         add_r(run, n);
-                        atomicAdd(&row[run], (unsigned long long)n);
+                        gadd64(&row[run], n);
                     }
                     run = cls;
                     n = 0;
@@ -221,7 +221,7 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
             if (n) {
                 add_a(a, run, n);
                 add_r(run, n);
-                atomicAdd(&row[run], (unsigned long long)n);
+                gadd64(&row[run], n);
             }
         }
         // ---- (1,2,0) of a and r: pairs of a's children by code, as if not adjacent
@@ -326,11 +326,11 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
 }
 
 // visited sets of the calling workgroup to a graph's shape counters, one atomic per wave and shape
-__device__ __forceinline__ void add_shapes(unsigned long long* stats, unsigned long long* shp) {
+__device__ __forceinline__ void add_shapes(gptr<unsigned long long> stats, unsigned long long* shp) {
     for (int s = 0; s < kShapes; s++) {
         unsigned long long x = shp[s];
         for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if ((threadIdx.x & 63u) == 0u && x) atomicAdd(&stats[s], x);
+        if ((threadIdx.x & 63u) == 0u && x) gadd64(&stats[s], x);
         shp[s] = 0;
     }
 }

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "vdmc_internal.h"
+
 namespace vdmc {
 
 // CSR entries are (neighbour_rank << 2) | arc bits, sorted ascending within a row.
@@ -12,9 +14,14 @@ namespace vdmc {
 
 __device__ __forceinline__ uint32_t swap_arc_bits(uint32_t c) { return ((c & 1u) << 1) | (c >> 1); }
 
+// *p += v at device scope
+__device__ __forceinline__ void gadd64(gptr<unsigned long long> p, unsigned long long v) {
+    __hip_atomic_fetch_add(p.p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // index of the first entry in [lo, hi) whose neighbour rank is >= x
-__device__ __forceinline__ uint32_t lower_bound_rank(const uint32_t* __restrict__ adj, uint32_t lo,
-                                                     uint32_t hi, uint32_t x) {
+template <class P>
+__device__ __forceinline__ uint32_t lower_bound_rank(P adj, uint32_t lo, uint32_t hi, uint32_t x) {
     const uint32_t key = x << 2;
     while (lo < hi) {
         uint32_t mid = (lo + hi) >> 1;
@@ -25,8 +32,8 @@ __device__ __forceinline__ uint32_t lower_bound_rank(const uint32_t* __restrict_
 
 // arc bits of the pair (u, v) seen from u; 0 when u and v are not adjacent.  Searches the
 // shorter of the two sorted rows (O(log min(deg u, deg v))).
-__device__ __forceinline__ uint32_t arc_bits(const uint32_t* __restrict__ off,
-                                             const uint32_t* __restrict__ adj, uint32_t u, uint32_t v) {
+template <class P>
+__device__ __forceinline__ uint32_t arc_bits(P off, P adj, uint32_t u, uint32_t v) {
     uint32_t lu = off[u], hu = off[u + 1], lv = off[v], hv = off[v + 1];
     bool from_u = (hu - lu) <= (hv - lv);
     uint32_t lo = from_u ? lu : lv, hi = from_u ? hu : hv, x = from_u ? v : u;
@@ -43,8 +50,8 @@ __device__ __forceinline__ uint32_t edge_slot(unsigned long long key, uint32_t b
     return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> (64u - bits));
 }
 // arc bits of (u, v) seen from u (0 if not adjacent), one probe sequence in the edge hash
-__device__ __forceinline__ uint32_t edge_code(const unsigned long long* __restrict__ table, uint32_t bits,
-                                              uint32_t u, uint32_t v) {
+template <class P>
+__device__ __forceinline__ uint32_t edge_code(P table, uint32_t bits, uint32_t u, uint32_t v) {
     const uint32_t lo = u < v ? u : v, hi = u < v ? v : u;
     const unsigned long long key = ((unsigned long long)lo << 32) | ((unsigned long long)hi << 2);
     const uint32_t mask = (1u << bits) - 1u;
@@ -55,32 +62,10 @@ __device__ __forceinline__ uint32_t edge_code(const unsigned long long* __restri
     }
 }
 
-// Fingerprint of an edge-hash key (never 0: 0 marks an empty slot).  A 16-bit table of
-// fingerprints at the same slots (4x smaller than the keys, so it stays cache-resident)
-// answers most lookups; the 64-bit key is read only when the fingerprint matches.
-__device__ __forceinline__ uint16_t edge_fp(unsigned long long key) {
-    const uint32_t f = (uint32_t)((key * 0xC2B2AE3D27D4EB4Full) >> 48);
-    return (uint16_t)(f ? f : 1u);
-}
-__device__ __forceinline__ uint32_t edge_code_fp(const uint16_t* __restrict__ fp, const unsigned long long* __restrict__ table,
-                                                 uint32_t bits, uint32_t u, uint32_t v) {
-    const uint32_t lo = u < v ? u : v, hi = u < v ? v : u;
-    const unsigned long long key = ((unsigned long long)lo << 32) | ((unsigned long long)hi << 2);
-    const uint16_t f = edge_fp(key);
-    const uint32_t mask = (1u << bits) - 1u;
-    for (uint32_t h = edge_slot(key, bits);; h = (h + 1u) & mask) {
-        const uint16_t g = fp[h];
-        if (g == 0) return 0u;
-        if (g != f) continue;
-        const unsigned long long s = table[h];
-        if ((s & ~3ull) == key) return u == lo ? (uint32_t)(s & 3u) : swap_arc_bits((uint32_t)(s & 3u));
-    }
-}
-
 // slot of the pair (u, v) in the edge hash, or 0xFFFFFFFF if the pair is not in the graph
 // (the probe stops at the first empty slot; the table is never full)
-__device__ __forceinline__ uint32_t edge_find(const unsigned long long* __restrict__ table, uint32_t bits,
-                                              uint32_t u, uint32_t v) {
+template <class P>
+__device__ __forceinline__ uint32_t edge_find(P table, uint32_t bits, uint32_t u, uint32_t v) {
     const uint32_t lo = u < v ? u : v, hi = u < v ? v : u;
     const unsigned long long key = ((unsigned long long)lo << 32) | ((unsigned long long)hi << 2);
     const uint32_t mask = (1u << bits) - 1u;

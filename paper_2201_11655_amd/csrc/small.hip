@@ -58,8 +58,8 @@ __device__ __forceinline__ uint32_t bit4(uint32_t code, uint32_t i, uint32_t j) 
 }
 
 // wg-scope atomic add on a graph's output (the block is owned by this workgroup)
-__device__ __forceinline__ void out_add(unsigned long long* p, unsigned long long v) {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+__device__ __forceinline__ void out_add(gptr<unsigned long long> p, unsigned long long v) {
+    __hip_atomic_fetch_add(p.p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // exclusive prefix sum of a[0..len) in place (LDS), returns the total; every thread of
@@ -162,8 +162,8 @@ struct SmallCredit {
     static constexpr uint32_t C = K == 3 ? (uint32_t)kClasses3 : (uint32_t)kClasses4;
     uint32_t* cnt;            // n x NC (LDS)
     const uint8_t* comp;      // k = 4: class -> counter slot or 0xFF (LDS)
-    const int32_t* perm;
-    unsigned long long* out;
+    gptr<const int32_t> perm;
+    gptr<unsigned long long> out;
     // slot of cls in the LDS counters, or NC when the class is credited to the output
     __device__ __forceinline__ uint32_t slot(uint32_t cls) const {
         if (K == 3) return cls;
@@ -290,10 +290,11 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         for (uint32_t i = tid; i < E; i += BS) sAdj[i] = (uint16_t)G.adj[i];
         for (uint32_t i = tid; i < n * W; i += BS) sBits[i] = 0u;
         for (uint32_t i = tid; i < n * NC; i += BS) sCnt[i] = 0u;
-        if (((uintptr_t)G.out & 15u) == 0) {   // 16-byte stores, then the odd last cell
+        if (((uintptr_t)G.out.p & 15u) == 0) {   // 16-byte stores, then the odd last cell
             const size_t cells = (size_t)n * C;
-            ulonglong2* o = reinterpret_cast<ulonglong2*>(G.out);
-            for (size_t i = tid; i < cells / 2; i += BS) o[i] = make_ulonglong2(0ull, 0ull);
+            using u64x2 = unsigned long long __attribute__((ext_vector_type(2)));
+            const auto o = G.out.as<u64x2>();
+            for (size_t i = tid; i < cells / 2; i += BS) o[i] = u64x2{0ull, 0ull};
             if ((cells & 1u) && tid == 0) G.out[cells - 1] = 0ull;
         } else {
             for (size_t i = tid; i < (size_t)n * C; i += BS) G.out[i] = 0ull;
@@ -550,11 +551,11 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         }
         if (lane_of() == 0) {
             if (K == 3) {
-                if (shp[0]) atomicAdd(&G.stats[0], shp[0]);
-                if (shp[1]) atomicAdd(&G.stats[1], shp[1]);
+                if (shp[0]) gadd64(&G.stats[0], shp[0]);
+                if (shp[1]) gadd64(&G.stats[1], shp[1]);
             } else {
                 for (int s = 0; s < 4; s++)
-                    if (shp[s]) atomicAdd(&G.stats[2 + s], shp[s]);
+                    if (shp[s]) gadd64(&G.stats[2 + s], shp[s]);
             }
         }
     }

@@ -171,8 +171,10 @@ struct vdmc_graph_s {
     // end of the last call's device work on this graph (every call's work is ordered after
     // the previous call's, whatever the streams)
     std::shared_ptr<vdmc::DoneEvent> last;
-    // 5-vertex counts in device memory (graphs that LDS does not hold): items before each
-    // root, then the item cursor; built at the first such count
+    // 5-vertex counts, built at the first one: the item table and its cursor, or (graphs above
+    // that kernel's size) items before each root, then the item cursor
+    void* five_tab = nullptr;
+    bool five_tab_ready = false;
     unsigned long long* five_hp = nullptr;
     unsigned long long five_items = 0;
 };
@@ -229,16 +231,45 @@ struct GraphUse {
 inline void wait_graph(vdmc_graph_s* g) {
     if (g->last) VDMC_HIP(hipEventSynchronize(g->last->e));
 }
+// Pointers kept in descriptors that kernels read from memory, and pointers to LDS kept in
+// structs: typed with their address space in device code.  As generic pointers they would be
+// accessed by flat instructions, which the LDS counter waits for too, so that each LDS read
+// after a memory-side atomic waits for the atomic (G(1000, 0.005), k = 3 and 4: 124 us with
+// flat atomics in k_light, see there for the figure without).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define VDMC_AS(n) __attribute__((address_space(n)))
+#else
+#define VDMC_AS(n)
+#endif
+template <class T, int AS>
+struct SpacePtr {
+    using P = T VDMC_AS(AS)*;
+    P p;
+    SpacePtr() = default;
+    __host__ __device__ SpacePtr(T* q) : p((P)q) {}
+#if defined(__HIP_DEVICE_COMPILE__)
+    __device__ SpacePtr(P q) : p(q) {}
+#endif
+    __host__ __device__ operator P() const { return p; }
+    template <class U>
+    __host__ __device__ SpacePtr<U, AS> as() const {
+        return SpacePtr<U, AS>((U VDMC_AS(AS)*)p);
+    }
+};
+template <class T>
+using gptr = SpacePtr<T, 1>;
+template <class T>
+using lptr = SpacePtr<T, 3>;
 // one graph as seen by the per-set kernels
 struct GraphView {
-    const uint32_t* off;
-    const uint32_t* adj;
-    const uint32_t* split;
-    const int32_t* perm;
-    unsigned long long* out3;
-    unsigned long long* out4;
-    unsigned long long* stats;
-    const unsigned long long* ehash = nullptr;   // edge hash if the graph has one (adjacency tests)
+    gptr<const uint32_t> off;
+    gptr<const uint32_t> adj;
+    gptr<const uint32_t> split;
+    gptr<const int32_t> perm;
+    gptr<unsigned long long> out3;
+    gptr<unsigned long long> out4;
+    gptr<unsigned long long> stats;
+    gptr<const unsigned long long> ehash = nullptr;   // edge hash if the graph has one (adjacency tests)
     uint32_t ehash_bits = 0;
 };
 // light-root kernel (count_light.hip): the roots of one graph, or a table over many
@@ -279,11 +310,11 @@ struct BatchArgs {
 };
 // Small graphs (small.hip): one workgroup counts a whole graph held in LDS.
 struct SmallGraph {
-    const uint32_t* off;        // n + 1 (rank space)
-    const uint32_t* adj;        // entries
-    const int32_t* perm;        // rank -> original id
-    unsigned long long* out;    // n x C, rows by original id
-    unsigned long long* stats;  // shape (visited-set) counters of the graph
+    gptr<const uint32_t> off;        // n + 1 (rank space)
+    gptr<const uint32_t> adj;        // entries
+    gptr<const int32_t> perm;        // rank -> original id
+    gptr<unsigned long long> out;    // n x C, rows by original id
+    gptr<unsigned long long> stats;  // shape (visited-set) counters of the graph
     uint32_t n, entries;
 };
 struct SmallArgs {
@@ -329,12 +360,8 @@ void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t strea
 void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t stream,
                 uint32_t rank_lo = 0, uint32_t rank_hi = 0xFFFFFFFFu, const hipEvent_t* around = nullptr);
 void free_hub(vdmc_graph_s* g);
-// 5-vertex motifs (count5.hip): graphs held whole in one workgroup's LDS, others in device memory
-constexpr int64_t kFiveMaxN = 512;
-size_t five_lds_bytes(int64_t n, int64_t entries);
-bool five_eligible(int64_t n, int64_t entries);
+// 5-vertex motifs (count5.hip)
 void launch_count5(vdmc_graph_s* g, uint64_t* out, hipStream_t stream);   // caller holds the graph (GraphUse)
-void count5_batch_lds(std::vector<vdmc_graph_s*>& gs, std::vector<uint64_t*>& outs, hipStream_t stream);
 void count5_batch(const vdmc_graph_s* const* gs, int32_t num, uint64_t* const* outs, hipStream_t stream);
 void invalidate_five_plans(vdmc_graph_s* g);
 void free_five(vdmc_graph_s* g);   // the graph's 5-vertex state; caller makes sure no count runs
