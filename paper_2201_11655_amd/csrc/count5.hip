@@ -58,7 +58,7 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 // sparse digraph hold most of the credits (~84% on G(n, p) graphs of mean degree 10)
 constexpr uint32_t kTreeSlots5 = 27;
 constexpr int64_t kDenseMaxN = 512;                            // graphs with such counters (55 KiB)
-constexpr uint32_t kClassPad = 9376;                           // 9364 classes, padded to 16 bytes
+constexpr uint32_t kTreeMark = 0x8000u;                        // in the marked class table: mark | slot for these classes
 constexpr uint32_t kSplitDiv = 32;                             // sub-items of a root: d+ x deg / 32 (measured best of 2..128)
 
 // bit of the index of a 5-set for the entry (i, j), i != j: rows in order, the diagonal
@@ -443,8 +443,7 @@ struct SetsArgs {
     const uint32_t* slots;         // graphs in the order workgroups take them, or nullptr: all `one`
     uint32_t nslots;
     unsigned* cursors;             // slot cursor, then per graph its item cursor and number of items
-    const uint16_t* table;         // code -> class id
-    const uint8_t* slot_of;        // class -> LDS counter slot or 0xFF (kClassPad entries)
+    const uint16_t* table;         // code -> class id, with LDS counters the marked table
     const uint16_t* slot_cls;      // LDS counter slot -> class (kTreeSlots5 entries)
     uint32_t words;                // words of a bit plane, of the largest graph
     uint32_t dense;                // counters in LDS: the largest graph's vertices, or 0
@@ -504,27 +503,25 @@ __global__ __launch_bounds__(256) void k_five_zero(SetsArgs A, uint32_t num) {
     }
 }
 
+// State of one wave (a triple of first members at a time).
 struct SetsWave {
     uint32_t hist[64];     // candidates by signature (arc codes to r, a, the third member)
-    uint32_t sig[64];      // the signatures that occur ...
-    uint32_t cnt[64];      // ... and their candidates
-    uint32_t lone[192];    // (signature, arc code): last members below a candidate
+    uint32_t lone[48];     // (signature's place, arc code): last members below a candidate (up to 16 signatures)
     uint32_t buf[64];      // candidates in hand: vertex | signature << 14 | phase << 20
     uint32_t lo[64], hi[64];   // their rows
-    uint16_t kcls[192];    // classes of the sets that a neighbour of theirs alone completes, by arc code
+    uint16_t kcls[3 * 64]; // classes of the sets that a neighbour of theirs alone completes, by arc code
     uint16_t cls[256];     // class of two non-adjacent candidates by their signatures (up to 16 of them)
+    uint8_t sig[64];       // the signatures that occur
     uint8_t idx[64];       // signature -> its place in sig
 };
 
 // a workgroup's credits: counters of the tree classes of every vertex (small graphs), a hash
 struct SetsCounters {
-    lptr<uint32_t> dense;  // n x kTreeSlots5 where `trees`
-    lptr<const uint8_t> slot_of;
+    lptr<uint32_t> dense;  // n x kTreeSlots5 (classes marked kTreeMark)
     lptr<uint32_t> key;    // hash: vertex << 14 | class, or kNone
     lptr<uint32_t> val;
     lptr<uint32_t> used;
     uint32_t shift;        // 2^(32 - shift) cells
-    bool trees;
 };
 
 __device__ __forceinline__ uint32_t lds_add(lptr<uint32_t> p, uint32_t v) {
@@ -561,11 +558,9 @@ struct SetsSink {
         }
         return kNone;
     }
-    __device__ __forceinline__ uint32_t slot(uint32_t cls) const { return L.trees ? L.slot_of[cls] : 0xFFu; }
     __device__ __forceinline__ void add(uint32_t v, uint32_t cls, uint32_t n) const {
-        const uint32_t sl = slot(cls);
-        if (sl < kTreeSlots5) {
-            lds_add(&L.dense[v * kTreeSlots5 + sl], n);
+        if (cls & kTreeMark) {
+            lds_add(&L.dense[v * kTreeSlots5 + (cls & 31u)], n);
             return;
         }
         const uint32_t key = (v << 14) | cls, h = find(key);
@@ -577,9 +572,8 @@ struct SetsSink {
         if (old + n < old) gadd64(cell(key), 1ull << 32);
     }
     __device__ __forceinline__ void sub1(uint32_t v, uint32_t cls) const {
-        const uint32_t sl = slot(cls);
-        if (sl < kTreeSlots5) {
-            lds_add(&L.dense[v * kTreeSlots5 + sl], ~0u);
+        if (cls & kTreeMark) {
+            lds_add(&L.dense[v * kTreeSlots5 + (cls & 31u)], ~0u);
             return;
         }
         const uint32_t key = (v << 14) | cls, h = find(key);
@@ -609,15 +603,16 @@ __device__ __forceinline__ void wave_fence() {
 
 // Every set whose first three members are r, a and y2 = the vertex of entry q (of r's row:
 // y2 shares a's layer; of a's row: y2 opens the next), by one wave.
-__device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& K, SetsWave& S, const uint16_t* __restrict__ table,
-                            const uint2* PR, const uint2* PA, uint2* PY, uint32_t W, uint32_t r, uint32_t a,
-                            uint32_t q, bool same, unsigned long long* vis) {
+__device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& K, SetsWave& S,
+                                            const uint16_t* __restrict__ table, const uint2* PR, const uint2* PA,
+                                            uint2* PY, uint32_t W, uint32_t r, uint32_t a, uint32_t q, bool same,
+                                            unsigned long long* vis) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t y2 = G.adj[q] >> 2;
     const uint32_t ylo = G.off[y2], yhi = G.off[y2 + 1];
     for (uint32_t i = lane; i < W; i += 64) PY[i] = make_uint2(0u, 0u);
     S.hist[lane] = 0u;
-    for (uint32_t i = lane; i < 192u; i += 64) S.lone[i] = 0u;
+    if (lane < 48u) S.lone[lane] = 0u;
     wave_fence();
     for (uint32_t i = ylo + lane; i < yhi; i += 64) {
         const uint32_t e = G.adj[i], z = e >> 2, bit = 1u << (z & 31u);
@@ -652,13 +647,13 @@ __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& 
     }
     if (c0 + c1 == 0u) return;
     wave_fence();
-    const uint32_t nh = S.hist[lane];
-    const unsigned long long occ = __ballot(nh != 0u);
-    const uint32_t D = (uint32_t)__popcll(occ), my = (uint32_t)__popcll(occ & ((1ull << lane) - 1ull));
-    if (nh) {
-        S.sig[my] = lane;
-        S.cnt[my] = nh;
-        S.idx[lane] = (uint8_t)my;
+    const bool in = S.hist[lane] != 0u;
+    const unsigned long long occ = __ballot(in);
+    const uint32_t D = (uint32_t)__popcll(occ);
+    if (in) {
+        const uint32_t at = (uint32_t)__popcll(occ & ((1ull << lane) - 1ull));
+        S.sig[at] = (uint8_t)lane;
+        S.idx[lane] = (uint8_t)at;
     }
     wave_fence();
     // ---- pairs of candidates as if not adjacent: the three first members' credits
@@ -669,7 +664,8 @@ __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& 
         const uint32_t cls = table[code3 | sig_bits(3, S.sig[p]) | sig_bits(4, S.sig[t])];
         if (small) S.cls[i] = (uint16_t)cls;
         if (t < p) continue;
-        const uint32_t n = p == t ? S.cnt[p] * (S.cnt[p] - 1u) / 2u : S.cnt[p] * S.cnt[t];
+        const uint32_t np = S.hist[S.sig[p]];
+        const uint32_t n = p == t ? np * (np - 1u) / 2u : np * S.hist[S.sig[t]];
         if (n) {
             K.add(r, cls, n);
             K.add(a, cls, n);
@@ -702,7 +698,7 @@ __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& 
             for (uint32_t k = 0; k < 3; k++) S.kcls[at * 3u + k] = table[code4 | pair_bits(3, 4, k + 1u)];
             // c with every other candidate, by signature, as if not adjacent
             for (uint32_t t = 0; t < D; t++) {
-                const uint32_t st = S.sig[t], n = S.cnt[t] - (st == s ? 1u : 0u);
+                const uint32_t st = S.sig[t], n = S.hist[st] - (st == s ? 1u : 0u);
                 if (n) K.add(y, pair_class(s, st), n);
             }
         }
@@ -752,7 +748,13 @@ __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& 
                 const uint32_t n = gl == 0u ? n1 : (gl == 1u ? n2 : n3);
                 if (n) {
                     K.add(y, S.kcls[bi * 3u + gl], n);
-                    atomicAdd(&S.lone[S.idx[s] * 3u + gl], n);
+                    if (small) {
+                        atomicAdd(&S.lone[S.idx[s] * 3u + gl], n);
+                    } else {
+                        K.add(r, S.kcls[bi * 3u + gl], n);
+                        K.add(a, S.kcls[bi * 3u + gl], n);
+                        K.add(y2, S.kcls[bi * 3u + gl], n);
+                    }
                     if (e >> 20) lone1 += n;
                     else lone0 += n;
                 }
@@ -760,7 +762,7 @@ __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& 
         }
         wave_fence();
     }
-    for (uint32_t i = lane; i < D * 3u; i += 64) {
+    for (uint32_t i = lane; small && i < D * 3u; i += 64) {
         const uint32_t n = S.lone[i];
         if (!n) continue;
         const uint32_t cls = table[code3 | sig_bits(3, S.sig[i / 3u]) | pair_bits(3, 4, i % 3u + 1u)];
@@ -781,7 +783,6 @@ __global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
     extern __shared__ uint2 dyn[];
     __shared__ SetsWave wv[NWV];
     __shared__ unsigned long long vis[8];
-    __shared__ uint8_t sSlotOf[kClassPad];
     __shared__ uint32_t sUsed, sNext, sTask;
     const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u, hn = 1u << hbits;
     uint2* PR = dyn;
@@ -790,16 +791,12 @@ __global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
     uint32_t* key = (uint32_t*)(dyn + (1u + 2u * NWV) * A.words);
     uint32_t* val = key + hn;
     uint32_t* dense = val + hn;
-    const SetsCounters L{(lptr<uint32_t>)dense, (lptr<const uint8_t>)sSlotOf, (lptr<uint32_t>)key, (lptr<uint32_t>)val,
-                         (lptr<uint32_t>)&sUsed, 32u - hbits, A.dense != 0u};
+    const SetsCounters L{dense, key, val, &sUsed, 32u - hbits};
     for (uint32_t i = tid; i < hn; i += BS) {
         key[i] = kNone;
         val[i] = 0u;
     }
-    if (A.dense) {
-        for (uint32_t i = tid; i < kClassPad / 4; i += BS) ((uint32_t*)sSlotOf)[i] = ((const uint32_t*)A.slot_of)[i];
-        for (uint32_t i = tid; i < A.dense * kTreeSlots5; i += BS) dense[i] = 0u;
-    }
+    for (uint32_t i = tid; i < A.dense * kTreeSlots5; i += BS) dense[i] = 0u;
     if (tid < 8) vis[tid] = 0ull;
     if (tid == 0) sUsed = 0u;
     for (;;) {   // a slot: a graph's items until none are left
@@ -904,10 +901,21 @@ __global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
     }
 }
 
-// Per-device LDS counter slots: the single-arc tree classes found from each class's
-// minimal index (four joined pairs, none reciprocal), in ascending class id.
+// code -> class id with the classes of LDS counters replaced by their mark and slot
+__global__ __launch_bounds__(256) void k_five_marks(const uint16_t* table, const uint16_t* slot_cls, uint16_t* marked) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    const uint16_t c = table[i];
+    uint16_t m = c;
+    for (uint32_t k = 0; k < kTreeSlots5; k++)
+        if (slot_cls[k] == c) m = (uint16_t)(kTreeMark | k);
+    marked[i] = m;
+}
+
+// Per device: the LDS counter slots, which are the single-arc tree classes found from each
+// class's minimal index (four joined pairs, none reciprocal), in ascending class id; the class
+// table with them marked (2 MiB).  Built at the first use, kept for the life of the process.
 struct FiveSlots {
-    uint8_t* slot_of = nullptr;    // kClassPad entries: class -> slot or 0xFF
+    uint16_t* marked = nullptr;    // 2^20 entries
     uint16_t* slot_cls = nullptr;  // 32 entries: slot -> class
 };
 std::mutex g_slots_mu;
@@ -919,7 +927,6 @@ const FiveSlots& five_slots() {
     std::lock_guard<std::mutex> lock(g_slots_mu);
     auto it = g_slots.find(dev);
     if (it != g_slots.end()) return it->second;
-    std::vector<uint8_t> slot_of(kClassPad, 0xFF);
     std::vector<uint16_t> slot_cls(32, 0);
     uint32_t k = 0;
     for (uint32_t c = 0; c < (uint32_t)kClasses5; c++) {
@@ -933,19 +940,23 @@ const FiveSlots& five_slots() {
             }
         if (joined == 4u && recip == 0u) {
             VDMC_REQUIRE(k < kTreeSlots5, VDMC_ERR_DEVICE, "more single-arc 5-vertex tree classes than slots");
-            slot_of[c] = (uint8_t)k;
-            slot_cls[k] = (uint16_t)c;
-            k++;
+            slot_cls[k++] = (uint16_t)c;
         }
     }
     VDMC_REQUIRE(k == kTreeSlots5, VDMC_ERR_DEVICE,
                  "expected 27 single-arc 5-vertex tree classes, found " + std::to_string(k));
     FiveSlots fs;
-    VDMC_HIP(hipMalloc(&fs.slot_of, kClassPad));
     VDMC_HIP(hipMalloc(&fs.slot_cls, 32 * sizeof(uint16_t)));
-    VDMC_HIP(hipMemcpy(fs.slot_of, slot_of.data(), kClassPad, hipMemcpyHostToDevice));
+    const hipError_t e = hipMalloc(&fs.marked, sizeof(uint16_t) << 20);
+    if (e != hipSuccess) {
+        (void)hipFree(fs.slot_cls);
+        VDMC_HIP(e);
+    }
     VDMC_HIP(hipMemcpy(fs.slot_cls, slot_cls.data(), 32 * sizeof(uint16_t), hipMemcpyHostToDevice));
-    return g_slots.emplace(dev, fs).first->second;   // kept for the life of the process
+    hipLaunchKernelGGL(k_five_marks, dim3((1u << 20) / 256), dim3(256), 0, 0, t.table, fs.slot_cls, fs.marked);
+    VDMC_HIP(hipGetLastError());
+    VDMC_HIP(hipStreamSynchronize(nullptr));
+    return g_slots.emplace(dev, fs).first->second;
 }
 
 int g_ncu = -1;
@@ -966,7 +977,9 @@ SetsGraph view_of(const vdmc_graph_s* g, uint64_t* out) {
 
 // LDS of k_five_sets: the largest launch shape that fits.  dense_n: vertices with LDS counters of
 // the tree classes.  1024 threads where the bit planes of 16 waves leave room for a hash of 4096
-// cells, else 256.
+// cells, else 256.  A hash of 8192 cells beside the counters of 512 vertices is why the state of
+// a wave is kept this small: 38.3 ms for 256 G(n, p) graphs of 20..500 vertices, 44.4 with 4096.
+// (Two triples of 32 lanes a wave, for the 25 or so candidates of a triple there: 51.3 ms.)
 struct SetsShape {
     int bs;
     uint32_t hbits;
@@ -975,7 +988,7 @@ struct SetsShape {
 SetsShape sets_shape(uint32_t words, uint32_t dense_n) {
     const size_t dense = (size_t)dense_n * kTreeSlots5 * sizeof(uint32_t);
     for (int bs : {1024, 256}) {
-        const size_t fixed = sizeof(SetsWave) * (bs / 64) + kClassPad + 256;
+        const size_t fixed = sizeof(SetsWave) * (bs / 64) + 256;
         const size_t need = (size_t)(1 + 2 * (bs / 64)) * words * sizeof(uint2) + dense;
         for (uint32_t hb : {13u, 12u}) {
             const size_t lds = need + ((size_t)8 << hb);
@@ -992,8 +1005,7 @@ void launch_sets(SetsArgs a, uint32_t num, size_t cells, hipStream_t st) {
     VDMC_HIP(hipGetLastError());
     if (a.nslots == 0) return;
     const FiveSlots& fs = five_slots();
-    a.table = class_table5().table;
-    a.slot_of = fs.slot_of;
+    a.table = a.dense ? fs.marked : class_table5().table;
     a.slot_cls = fs.slot_cls;
     const SetsShape sh = sets_shape(a.words, a.dense);
     void (*kern)(SetsArgs, uint32_t) = sh.bs == 1024 ? k_five_sets<1024> : k_five_sets<256>;
