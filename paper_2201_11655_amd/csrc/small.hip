@@ -2,38 +2,36 @@
 //
 // For graphs of a few hundred vertices (the batched workload, small served requests)
 // a per-root launch leaves most of a workgroup idle: a root of such a graph has a
-// handful of higher neighbours.  Here one workgroup takes a whole graph:
-//   * its rank-space CSR (16-bit row entries), a 1-bit adjacency matrix (so that almost
-//     every pair test is one LDS read; a set bit is resolved to its arc bits by a search
-//     of the LDS row) and per-vertex counters live in LDS;
-//   * the work of all roots is flattened into two item lists, so that threads never
-//     wait at per-root barriers:
-//       - pairs {a < b} of N+(r) for every root r: the k = 3 set (1,1) and the k = 4
-//         sets (3,0,0) that add a third higher neighbour c > b (Lemma 2);
-//       - depth-2 entries (r, a, c): a in N+(r), c in N(a), c > r, c not in N(r): the
-//         k = 3 set (1,2) and, for k = 4, the sets (2,1,0) (second depth-1 vertex b; c
-//         hangs under its lower-rank parent), (1,2,0) (a second child c' of a, each pair
-//         of children once) and
-//         (1,1,1) (an end vertex e of c's row, not adjacent to r or to a: the Lemma-4
-//         rule) (Lemmas 2-4);
-//   * every set is visited once by one lane: its index is assembled from the arc bits
-//     (Sec. 4.1), its class read from the table in LDS, and each of its k vertices
-//     credited (Sec. 4.2).  Credits go to LDS counters (k = 3: all 13 classes; k = 4:
-//     the 25 tree classes and the 12 single-arc 4-pair classes, which hold ~99.6% of the
-//     credits of sparse graphs), one LDS atomic per member and set; the other classes
-//     go straight to the graph's output with workgroup-scope atomics (the output block
-//     of a graph belongs to one workgroup for the whole launch; every such atomic is a
-//     memory-side operation, so they are kept rare), and there members that all lanes of
-//     a wave step share (the root, the depth-1 vertex of a run of depth-2 items, the
-//     loop's current vertex) are credited once per class present in the step, grouped
-//     by ballots;
-//   * in the k = 4 loops three members are fixed and the lane walks the fourth; a set
-//     whose fourth member has no arc to the fixed members other than the one the shape
-//     implies has its class fixed by that arc's code (a tree class): the fourth member
-//     is credited per set and the three fixed ones once per arc code after the loop.
+// handful of higher neighbours.  Here one workgroup takes a whole graph: its rank-space
+// CSR (16-bit row entries), a 1-bit adjacency matrix (almost every pair test is one LDS
+// read; a set bit is resolved to its arc bits by a search of the LDS row) and per-vertex
+// counters live in LDS.
+//
+// The sets are those of Lemmas 1-4, but most are not visited.  Of the sets of a root r,
+// those of three shapes are counted by arc codes as if their members had only the arcs
+// that the shape implies, and each set that has another arc is then corrected (its credits
+// moved from the tree class to its own):
+//   (3,0,0)  triples of N+(r), from the numbers of slots by code;
+//   (2,1,0)  a child c of a slot a with a second slot, from the children by code (the rule
+//            that c hangs under its lower-rank parent is part of the correction);
+//   (1,2,0)  pairs of children of a slot a.
+// The fourth, (1,1,1) (a path r - a - c - e), is visited: one credit for e, and for r, a and
+// c once per arc code.  Its walk of c's row finds what (2,1,0) and (1,2,0) have to correct
+// for c: the entries in N+(r) and those adjacent to a.  An adjacent pair of slots (a
+// triangle with r) is queued, and corrects the triples and the children of either.
+// In the 4096 graphs of the batched workload (20..500 vertices, mean out-degree 2..8)
+// there are 218 k sets a graph, of them 65 k paths, and 14 k corrections.
+//
+// k = 3 is the same: pairs of N+(r) and children by code, triangles corrected.
+//
+// Credits go to LDS counters (k = 3: all 13 classes; k = 4: the 25 tree classes and the 12
+// single-arc 4-pair classes, which hold ~99.6% of the credits of sparse graphs); the other
+// classes go straight to the graph's output with workgroup-scope atomics (the output block
+// of a graph belongs to one workgroup for the whole launch; every such atomic is a
+// memory-side operation, so they are kept rare).
 // The LDS counters are stored to the output once per graph (their classes never reach
 // the output otherwise).  u32 counters cannot overflow: a vertex of a graph with
-// n <= kSmallMaxN lies in fewer than 2^32 k-sets.
+// n <= kSmallMaxN lies in fewer than 2^32 k-sets, and a correction is arithmetic mod 2^32.
 #include "motif_device.h"
 #include "vdmc_internal.h"
 
@@ -162,7 +160,7 @@ struct SmallCredit {
     static constexpr uint32_t C = K == 3 ? (uint32_t)kClasses3 : (uint32_t)kClasses4;
     uint32_t* cnt;            // n x NC (LDS)
     const uint8_t* comp;      // k = 4: class -> counter slot or 0xFF (LDS)
-    gptr<const int32_t> perm;
+    const uint32_t* perm;     // rank -> original id (LDS)
     gptr<unsigned long long> out;
     // slot of cls in the LDS counters, or NC when the class is credited to the output
     __device__ __forceinline__ uint32_t slot(uint32_t cls) const {
@@ -177,52 +175,86 @@ struct SmallCredit {
     }
     // n sets of a class whose counter slot s (< NC) is already known
     __device__ __forceinline__ void add_s(uint32_t v, uint32_t s, uint32_t n) const { atomicAdd(&cnt[v * NC + s], n); }
-    // n sets of class cls credited to three members (nothing when n = 0)
-    __device__ __forceinline__ void add3(uint32_t u, uint32_t v, uint32_t w, uint32_t cls, uint32_t n) const {
-        if (!n) return;
-        add_n(u, cls, n);
-        add_n(v, cls, n);
-        add_n(w, cls, n);
-    }
-    // One set per active lane, of class cls, credited to the NS members in sv, which the
-    // lanes often share (the root, and the members fixed by the wave's loop position).
-    // A class with an LDS counter (every k = 3 class, the 37 slot classes of k = 4) is
-    // added lane by lane: an LDS atomic is cheap, and lanes that share a member and a
-    // class only meet in the LDS unit.  The other classes go to the output, where every
-    // atomic is a memory-side operation: a member common to all such lanes gets each of
-    // their classes once, with the lanes' count; a member that differs is added lane by
-    // lane.
-    template <int NS>
-    __device__ __forceinline__ void shared(uint32_t cls, const uint32_t (&sv)[NS], bool active) const {
-        const uint32_t s = active ? slot(cls) : NC;
-        if (active && s < NC)
-            for (int i = 0; i < NS; i++) atomicAdd(&cnt[sv[i] * NC + s], 1u);
-        if (K == 3) return;
-        const bool far = active && s >= NC;
-        const unsigned long long act = __ballot(far);
-        if (!act) return;
-        const int first = __ffsll((long long)act) - 1;
-        uint32_t common = 0;   // wave-uniform bit mask of the members all such lanes share
-        for (int i = 0; i < NS; i++)
-            if (__ballot(far && sv[i] != (uint32_t)__shfl((int)sv[i], first, 64)) == 0ull) common |= 1u << i;
-        if (common) {
-            unsigned long long m = act;
-            while (m) {
-                const uint32_t leader = (uint32_t)(__ffsll((long long)m) - 1);
-                const uint32_t k0 = (uint32_t)__shfl((int)cls, (int)leader, 64);
-                const unsigned long long grp = __ballot(far && cls == k0) & m;
-                if (lane_of() == leader)
-                    for (int i = 0; i < NS; i++)
-                        if ((common >> i) & 1u)
-                            out_add(&out[(size_t)perm[sv[i]] * C + k0], (unsigned long long)__popcll(grp));
-                m &= ~grp;
-            }
-        }
-        if (far)
-            for (int i = 0; i < NS; i++)
-                if (!((common >> i) & 1u)) out_add(&out[(size_t)perm[sv[i]] * C + cls], 1ull);
+    // one set: from the counter slot `was` to class `is`
+    __device__ __forceinline__ void move(uint32_t v, uint32_t was, uint32_t is) const {
+        add_s(v, was, ~0u);
+        add_n(v, is, 1u);
     }
 };
+
+// counter slots (k = 4) of tree classes, by two arc codes x, y in 1..3 at [4 x + y], for a
+// third code z in the byte z - 1
+struct SmallTrees {
+    uint32_t path[16];    // r - a - c - e: x = r to a, y = a to c, z = c to e
+    uint32_t path2[16];   // c - a - r - b: x = r to a, y = a to c, z = r to b
+    uint32_t starr[16];   // r with three slots
+    uint32_t stara[16];   // a with r (x: seen from r) and two children (y, z: seen from a)
+};
+__device__ __forceinline__ uint32_t byte_of(uint32_t w, uint32_t z) { return (w >> (8u * z - 8u)) & 0xFFu; }
+__device__ __forceinline__ uint32_t pick3(uint32_t k, uint32_t a, uint32_t b, uint32_t c) {
+    return k == 1u ? a : (k == 2u ? b : c);
+}
+// pairs of two codes k <= l of three, from the numbers by code
+__device__ __forceinline__ uint32_t pairs_of(uint32_t k, uint32_t l, uint32_t a, uint32_t b, uint32_t c) {
+    const uint32_t x = pick3(k, a, b, c);
+    return k == l ? x * (x - 1u) / 2u : x * pick3(l, a, b, c);
+}
+// i-th pair of codes k <= l
+__device__ __forceinline__ void code_pair(uint32_t i, uint32_t& k, uint32_t& l) {
+    k = i < 3u ? 1u : (i < 5u ? 2u : 3u);
+    l = i < 3u ? i + 1u : (i < 5u ? i - 1u : 3u);
+}
+// i-th triple of codes, two bits each, ascending
+__device__ __forceinline__ uint32_t code_triple(uint32_t i) {
+    constexpr unsigned long long t = 0x15ull | 0x25ull << 6 | 0x35ull << 12 | 0x29ull << 18 | 0x39ull << 24 |
+                                     0x3Dull << 30 | 0x2Aull << 36 | 0x3Aull << 42 | 0x3Eull << 48 | 0x3Full << 54;
+    return (uint32_t)(t >> (6u * i)) & 63u;
+}
+__device__ __forceinline__ uint32_t sum8(uint32_t v) {
+    v += (uint32_t)__shfl_xor((int)v, 1, 64);
+    v += (uint32_t)__shfl_xor((int)v, 2, 64);
+    v += (uint32_t)__shfl_xor((int)v, 4, 64);
+    return v;
+}
+__device__ __forceinline__ void small_fence() {
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The sets of r with the adjacent slots a < b, for lane i0 of step: triples (from the first of
+// their adjacent pairs) and children of one that are not adjacent to the other.
+__device__ __forceinline__ void fix_triangle(const SmallLds& L, const SmallCredit<4>& cr, const SmallTrees& F,
+                                             const uint8_t* table, uint32_t r, uint32_t a, uint32_t b, uint32_t i0,
+                                             uint32_t step) {
+    const uint32_t ra = L.code(r, a), rb = L.code(r, b), ab = L.code(a, b);
+    const uint32_t wr = F.starr[ra * 4u + rb];
+    for (uint32_t i = L.split[r] + i0; i < L.off[r + 1]; i += step) {
+        const uint32_t c = L.adj[i] >> 2, rc = L.adj[i] & 3u;
+        const bool xa = L.adjacent(a, c), xb = L.adjacent(b, c);
+        if (c == a || c == b || (xa && c < b) || (xb && c < a)) continue;
+        const uint32_t is = table[motif_index4(ra, rb, rc, ab, L.code_if(xa, a, c), L.code_if(xb, b, c))];
+        const uint32_t was = byte_of(wr, rc);
+        cr.move(r, was, is);
+        cr.move(a, was, is);
+        cr.move(b, was, is);
+        cr.move(c, was, is);
+    }
+    for (uint32_t side = 0; side < 2; side++) {
+        const uint32_t p = side ? b : a, q = side ? a : b, rp = side ? rb : ra, rq = side ? ra : rb;
+        const uint32_t pq = side ? swap_arc_bits(ab) : ab, lo = L.off[p];
+        for (uint32_t i = L.off[p + 1] - i0; (int32_t)i > (int32_t)lo; i -= step) {
+            const uint32_t c = L.adj[i - 1u] >> 2, pc = L.adj[i - 1u] & 3u;
+            if (c <= r) break;
+            if (L.adjacent(r, c) || L.adjacent(q, c)) continue;
+            const uint32_t is = table[motif_index4(rp, rq, 0u, pq, pc, 0u)];
+            const uint32_t was = byte_of(F.path2[rp * 4u + pc], rq);
+            cr.move(r, was, is);
+            cr.move(a, was, is);
+            cr.move(b, was, is);
+            cr.move(c, was, is);
+        }
+    }
+}
 
 template <int BS, int K>
 __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
@@ -233,6 +265,11 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
     __shared__ uint32_t sMask[8];   // k = 4: 256-bit mask of the single-arc 4-pair classes
     __shared__ uint32_t sPart[BS / 64];
     __shared__ uint32_t sGraph;
+    constexpr uint32_t kTriQueue = K == 4 ? 512 : 1;
+    __shared__ uint32_t sTri[kTriQueue];              // triangles (r, a, b), 10 bits each
+    __shared__ uint32_t sTriN;
+    __shared__ uint32_t sKids[K == 4 ? BS / 64 : 1][9];   // per wave: children of r's slots by both codes
+    __shared__ SmallTrees sTrees;
     constexpr uint32_t NC = SmallCredit<K>::NC;
     constexpr uint32_t C = SmallCredit<K>::C;
     const uint32_t tid = threadIdx.x;
@@ -265,6 +302,22 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
                     k++;
                 }
         }
+        if (tid < 64) {
+            const uint32_t x = (tid >> 2) & 3u, y = tid & 3u;
+            uint32_t w[4] = {0, 0, 0, 0};
+            for (uint32_t z = 1; tid < 16 && x && y && z < 4; z++) {
+                w[0] |= (uint32_t)sComp[sTable[motif_index4(x, 0u, 0u, y, 0u, z)]] << (8u * z - 8u);
+                w[1] |= (uint32_t)sComp[sTable[motif_index4(x, z, 0u, 0u, y, 0u)]] << (8u * z - 8u);
+                w[2] |= (uint32_t)sComp[sTable[motif_index4(x, y, z, 0u, 0u, 0u)]] << (8u * z - 8u);
+                w[3] |= (uint32_t)sComp[sTable[motif_index4(x, 0u, 0u, y, z, 0u)]] << (8u * z - 8u);
+            }
+            if (tid < 16) {
+                sTrees.path[tid] = w[0];
+                sTrees.path2[tid] = w[1];
+                sTrees.starr[tid] = w[2];
+                sTrees.stara[tid] = w[3];
+            }
+        }
     }
 
     for (uint32_t round = 0;; round++) {
@@ -279,14 +332,15 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         uint32_t* sOff = dyn;                 // n + 1
         uint32_t* sSplit = sOff + n + 1;      // n
         uint32_t* sPreD = sSplit + n;         // n + 1: upper entries before row r
-        uint32_t* sPre1 = sPreD + n + 1;      // n + 1: pair items before root r
-        uint32_t* sBits = sPre1 + n + 1;      // n * W
+        uint32_t* sPerm = sPreD + n + 1;      // n + 1: rank -> original id
+        uint32_t* sBits = sPerm + n + 1;      // n * W
         uint32_t* sCnt = sBits + n * W;       // n * NC
         uint32_t* sPre2 = sCnt + n * NC;      // E / 2 + 1: depth-2 candidates before each upper entry
         uint16_t* sAdj = reinterpret_cast<uint16_t*>(sPre2 + E / 2 + 1);   // E (u16)
         uint16_t* sRootOf = sAdj + E;         // E / 2 (u16): root of each upper entry
         // ---- stage the graph, clear bitmap, counters and the output block
         for (uint32_t i = tid; i <= n; i += BS) sOff[i] = G.off[i];
+        for (uint32_t i = tid; i < n; i += BS) sPerm[i] = (uint32_t)G.perm[i];
         for (uint32_t i = tid; i < E; i += BS) sAdj[i] = (uint16_t)G.adj[i];
         for (uint32_t i = tid; i < n * W; i += BS) sBits[i] = 0u;
         for (uint32_t i = tid; i < n * NC; i += BS) sCnt[i] = 0u;
@@ -299,6 +353,7 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         } else {
             for (size_t i = tid; i < (size_t)n * C; i += BS) G.out[i] = 0ull;
         }
+        if (tid == 0) sTriN = 0u;
         if (tid < (uint32_t)kShapes) G.stats[tid] = 0ull;   // this launch's visit counters of the graph
         __syncthreads();
         for (uint32_t r = tid; r < n; r += BS) {
@@ -310,227 +365,273 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
                 if (v > r && s == hi) s = t;
             }
             sSplit[r] = s;
-            const uint32_t d = hi - s;
-            sPreD[r] = d;
-            sPre1[r] = d * (d - 1u) / 2u;
+            sPreD[r] = hi - s;
         }
-        if (tid == 0) {
-            sPreD[n] = 0u;
-            sPre1[n] = 0u;
-        }
+        if (tid == 0) sPreD[n] = 0u;
         __syncthreads();
-        const uint32_t U = block_exclusive_scan<BS>(sPreD, n + 1, sPart);
-        const uint32_t N1 = block_exclusive_scan<BS>(sPre1, n + 1, sPart);
         const SmallLds L{sOff, sAdj, sSplit, sBits, W};
-        // candidates of each upper entry (r, a): entries of a's row above r
-        for (uint32_t r = tid; r < n; r += BS)
-            for (uint32_t t = sSplit[r]; t < sOff[r + 1]; t++) {
-                const uint32_t a = sAdj[t] >> 2;
-                sPre2[sPreD[r] + (t - sSplit[r])] = sOff[a + 1] - L.first_above(a, r);
-                sRootOf[sPreD[r] + (t - sSplit[r])] = (uint16_t)r;
-            }
-        if (tid == 0) sPre2[U] = 0u;
-        __syncthreads();
-        const uint32_t N2 = block_exclusive_scan<BS>(sPre2, U + 1, sPart);
-
-        const SmallCredit<K> cr{sCnt, sComp, G.perm, G.out};
-        unsigned long long shp[4] = {0, 0, 0, 0};
-        // ---- pairs {a < b} of N+(r): (1,1) / (3,0,0)
-        for (uint32_t q = tid; q < N1; q += BS) {
-            const uint32_t r = upper_idx(sPre1, n + 1, q);
-            const uint32_t idx = q - sPre1[r];
-            uint32_t j = (uint32_t)((1.0f + sqrtf(1.0f + 8.0f * (float)idx)) * 0.5f);
-            while (j * (j - 1u) / 2u > idx) j--;
-            while ((j + 1u) * j / 2u <= idx) j++;
-            const uint32_t i = idx - j * (j - 1u) / 2u;
-            const uint16_t* P = sAdj + sSplit[r];
-            const uint32_t d = sOff[r + 1] - sSplit[r];
-            const uint32_t a = P[i] >> 2, ra = P[i] & 3u, b = P[j] >> 2, rb = P[j] & 3u;
-            const uint32_t ab = L.code(a, b);
-            if (K == 3) {
-                const uint32_t cls = sTable[motif_index3(ra, rb, ab)];
-                const uint32_t sv[2] = {r, b};
-                cr.shared(cls, sv, true);
-                cr.add_n(a, cls, 1u);
-                shp[0]++;
-            } else {
-                // (3,0,0): r, a, b fixed, lanes' loops over c.  A set whose c is adjacent to
-                // neither a nor b has its class fixed by c's arc with r: those sets credit c
-                // one by one and r, a, b once per arc code after the loop.
-                const uint32_t p1 = sTable[motif_index4(ra, rb, 1u, ab, 0u, 0u)];
-                const uint32_t p2 = sTable[motif_index4(ra, rb, 2u, ab, 0u, 0u)];
-                const uint32_t p3 = sTable[motif_index4(ra, rb, 3u, ab, 0u, 0u)];
-                uint32_t np = 0;   // sets by arc code 1, 2, 3: 10-bit fields (every loop runs < 1024 times)
-                // software pipeline: the entry two candidates ahead and the bitmap words of
-                // the next one are read before this candidate's credits (LDS atomics, which
-                // later reads could not otherwise pass)
-                const uint32_t dm = d - 1u;
-                uint32_t e0 = P[min(j + 1u, dm)], e1 = P[min(j + 2u, dm)];
-                uint32_t wa0 = L.word(a, e0 >> 2), wb0 = L.word(b, e0 >> 2);
-                for (uint32_t l = j + 1; l < d; l++) {
-                    const uint32_t e2 = P[min(l + 2u, dm)];
-                    const uint32_t wa1 = L.word(a, e1 >> 2), wb1 = L.word(b, e1 >> 2);
-                    const uint32_t c = e0 >> 2, rc = e0 & 3u;
-                    const bool xa = SmallLds::bit(wa0, c), xb = SmallLds::bit(wb0, c);
-                    e0 = e1;
-                    e1 = e2;
-                    wa0 = wa1;
-                    wb0 = wb1;
-                    const uint32_t ac = L.code_if(xa, a, c), bc = L.code_if(xb, b, c);
-                    if (ac | bc) {
-                        const uint32_t cls = sTable[motif_index4(ra, rb, rc, ab, ac, bc)];
-                        const uint32_t sv[3] = {r, b, c};   // lanes share j, hence b and c
-                        cr.shared(cls, sv, true);
-                        cr.add_n(a, cls, 1u);
-                    } else {
-                        cr.add_n(c, rc == 1u ? p1 : (rc == 2u ? p2 : p3), 1u);
-                        np += 1u << (10u * rc - 10u);
-                    }
-                    shp[0]++;
+        uint32_t U = 0, N2 = 0;
+        if (K == 4) {
+            U = block_exclusive_scan<BS>(sPreD, n + 1, sPart);
+            // candidates of each upper entry (r, a): entries of a's row above r
+            for (uint32_t r = tid; r < n; r += BS)
+                for (uint32_t t = sSplit[r]; t < sOff[r + 1]; t++) {
+                    const uint32_t a = sAdj[t] >> 2;
+                    sPre2[sPreD[r] + (t - sSplit[r])] = sOff[a + 1] - L.first_above(a, r);
+                    sRootOf[sPreD[r] + (t - sSplit[r])] = (uint16_t)r;
                 }
-                cr.add3(r, a, b, p1, np & 1023u);
-                cr.add3(r, a, b, p2, (np >> 10) & 1023u);
-                cr.add3(r, a, b, p3, np >> 20);
-            }
+            if (tid == 0) sPre2[U] = 0u;
+            __syncthreads();
+            N2 = block_exclusive_scan<BS>(sPre2, U + 1, sPart);
         }
-        // ---- depth-2 entries (r, a, c)
-        for (uint32_t q = tid; q < N2; q += BS) {
-            const uint32_t u = upper_idx(sPre2, U + 1, q);
-            const uint32_t r = sRootOf[u];
-            const uint16_t* P = sAdj + sSplit[r];
-            const uint32_t d = sOff[r + 1] - sSplit[r];
-            const uint32_t ia = u - sPreD[r];
-            const uint32_t a = P[ia] >> 2, ra = P[ia] & 3u;
-            const uint32_t t0 = L.first_above(a, r), t = t0 + (q - sPre2[u]);
-            const uint32_t c = sAdj[t] >> 2, ac = sAdj[t] & 3u;
-            if (L.adjacent(r, c)) continue;   // c adjacent to r: depth 1, not 2
+
+        const SmallCredit<K> cr{sCnt, sComp, sPerm, G.out};
+        // visits of this thread: below 2^32 for every shape, as the CSR is in LDS (sum of d <= 2^14)
+        uint32_t shp[4] = {0, 0, 0, 0};
+        // ---- a root per wave, 8 lanes per slot: all that is counted by codes
+        for (uint32_t r = tid >> 6; r < n; r += BS / 64) {
+            const uint32_t lane = lane_of(), gl = lane & 7u, lo = sSplit[r], d = sOff[r + 1] - lo;
+            if (d == 0u) continue;
+            uint32_t m1 = 0, m2 = 0, m3 = 0;   // slots by code
+            for (uint32_t i = 0; i < d; i += 64) {
+                const uint32_t k = i + lane < d ? sAdj[lo + i + lane] & 3u : 0u;
+                m1 += (uint32_t)__popcll(__ballot(k == 1u));
+                m2 += (uint32_t)__popcll(__ballot(k == 2u));
+                m3 += (uint32_t)__popcll(__ballot(k == 3u));
+            }
+            uint32_t* T = sKids[K == 4 ? tid >> 6 : 0];
+            if (K == 4) {
+                if (lane < 9u) T[lane] = 0u;
+                small_fence();
+            }
+            for (uint32_t s0 = 0; s0 < d; s0 += 8) {
+                const bool on = s0 + (lane >> 3) < d;
+                const uint32_t ent = on ? sAdj[lo + s0 + (lane >> 3)] : 0u, a = ent >> 2, ra = ent & 3u;
+                // a's row above r, from its end
+                uint32_t h1 = 0, h2 = 0, h3 = 0;   // children by code
+                const uint32_t alo = on ? sOff[a] : 0u, ahi = on ? sOff[a + 1] : 0u;
+                for (uint32_t q = ahi; q > alo; q -= min(8u, q - alo)) {
+                    const uint32_t x = q - alo > gl ? sAdj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
+                    if (c > r) {
+                        if (!L.adjacent(r, c)) {
+                            h1 += k == 1u;
+                            h2 += k == 2u;
+                            h3 += k == 3u;
+                            if (K == 3) cr.add_s(c, sTable[motif_index3(ra, 0u, k)], 1u);
+                        } else if (c > a) {
+                            if (K == 3) {
+                                const uint32_t rc = L.code(r, c), is = sTable[motif_index3(ra, rc, k)];
+                                const uint32_t was = sTable[motif_index3(ra, rc, 0u)];
+                                cr.move(r, was, is);
+                                cr.move(a, was, is);
+                                cr.move(c, was, is);
+                            } else {
+                                const uint32_t at = atomicAdd(&sTriN, 1u);
+                                if (at < kTriQueue) sTri[at] = r | (a << 10) | (c << 20);
+                            }
+                        }
+                    }
+                    if (q - alo > 8u && (uint32_t)(sAdj[q - 8u] >> 2) <= r) break;
+                }
+                h1 = sum8(h1);
+                h2 = sum8(h2);
+                h3 = sum8(h3);
+                if (!on) continue;
+                const uint32_t h = h1 + h2 + h3;
+                const uint32_t o1 = m1 - (ra == 1u), o2 = m2 - (ra == 2u), o3 = m3 - (ra == 3u);   // the other slots
+                if (K == 3) {
+                    if (gl < 6u) {   // (1,1) of a; (1,2) of a and r
+                        const uint32_t k = gl % 3u + 1u, n = gl < 3u ? pick3(k, o1, o2, o3) : pick3(k, h1, h2, h3);
+                        const uint32_t cls = sTable[gl < 3u ? motif_index3(ra, k, 0u) : motif_index3(ra, 0u, k)];
+                        if (n) {
+                            cr.add_s(a, cls, n);
+                            if (gl >= 3u) cr.add_s(r, cls, n);
+                        }
+                    }
+                    if (gl == 0u) shp[1] += h;
+                    continue;
+                }
+                if (gl < 3u) atomicAdd(&T[(ra - 1u) * 3u + gl], pick3(gl + 1u, h1, h2, h3));
+                for (uint32_t t = gl; t < 24u; t += 8u) {
+                    uint32_t n, slot, k, l;
+                    if (t < 9u) {            // (2,1,0), a the parent
+                        k = t / 3u + 1u;
+                        l = t % 3u + 1u;
+                        n = pick3(k, h1, h2, h3) * pick3(l, o1, o2, o3);
+                        slot = byte_of(sTrees.path2[ra * 4u + k], l);
+                    } else if (t < 15u) {    // (3,0,0)
+                        code_pair(t - 9u, k, l);
+                        n = pairs_of(k, l, o1, o2, o3);
+                        slot = byte_of(sTrees.starr[ra * 4u + k], l);
+                    } else if (t < 21u) {    // (1,2,0): r too
+                        code_pair(t - 15u, k, l);
+                        n = pairs_of(k, l, h1, h2, h3);
+                        slot = byte_of(sTrees.stara[ra * 4u + k], l);
+                        if (n) cr.add_s(r, slot, n);
+                    } else {                 // (2,1,0), a the second slot: not with its own children
+                        k = t - 20u;
+                        n = 0u - pick3(k, h1, h2, h3);
+                        slot = byte_of(sTrees.path2[ra * 4u + k], ra);
+                    }
+                    if (n) cr.add_s(a, slot, n);
+                }
+                if (gl == 0u) {
+                    shp[1] += h * (d - 1u);
+                    shp[2] += h * (h - 1u) / 2u;
+                }
+                // the children: (2,1,0) and (1,2,0)
+                for (uint32_t q = h ? ahi : alo; q > alo; q -= min(8u, q - alo)) {
+                    const uint32_t x = q - alo > gl ? sAdj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
+                    if (c > r && !L.adjacent(r, c)) {
+                        const uint32_t w2 = sTrees.path2[ra * 4u + k], ws = sTrees.stara[ra * 4u + k];
+                        const uint32_t n1 = h1 - (k == 1u), n2 = h2 - (k == 2u), n3 = h3 - (k == 3u);
+                        if (o1) cr.add_s(c, w2 & 0xFFu, o1);
+                        if (o2) cr.add_s(c, (w2 >> 8) & 0xFFu, o2);
+                        if (o3) cr.add_s(c, w2 >> 16, o3);
+                        if (n1) cr.add_s(c, ws & 0xFFu, n1);
+                        if (n2) cr.add_s(c, (ws >> 8) & 0xFFu, n2);
+                        if (n3) cr.add_s(c, ws >> 16, n3);
+                    }
+                    if (q - alo > 8u && (uint32_t)(sAdj[q - 8u] >> 2) <= r) break;
+                }
+            }
             if (K == 3) {
-                const uint32_t cls = sTable[motif_index3(ra, 0u, ac)];
-                const uint32_t sv[2] = {r, a};
-                cr.shared(cls, sv, true);
-                cr.add_n(c, cls, 1u);
-                shp[1]++;
+                if (lane < 6u) {   // (1,1) of r
+                    uint32_t k, l;
+                    code_pair(lane, k, l);
+                    const uint32_t n = pairs_of(k, l, m1, m2, m3);
+                    if (n) cr.add_s(r, sTable[motif_index3(k, l, 0u)], n);
+                }
+                if (lane == 0u) shp[0] += d * (d - 1u) / 2u;
                 continue;
             }
-            // (2,1,0): a second depth-1 vertex b; c hangs under the lower-rank parent.  r, a,
-            // c are fixed for the lane's loop; a set whose b is adjacent to neither a nor c
-            // has its class fixed by b's arc with r: b is credited per set, r, a, c once per
-            // arc code after the loop.  The same holds below for (1,2,0) (c2 not adjacent to
-            // c: class by a's arc with c2) and for every (1,1,1) set (class by c's arc with e).
-            {
-                const uint32_t q1 = sTable[motif_index4(ra, 1u, 0u, 0u, ac, 0u)];
-                const uint32_t q2 = sTable[motif_index4(ra, 2u, 0u, 0u, ac, 0u)];
-                const uint32_t q3 = sTable[motif_index4(ra, 3u, 0u, 0u, ac, 0u)];
-                const uint32_t s1 = cr.slot(q1), s2 = cr.slot(q2), s3 = cr.slot(q3);   // 4-path classes: tree slots
-                uint32_t np = 0;   // sets by arc code 1, 2, 3: 10-bit fields (every loop runs < 1024 times)
-                // pipelined as the (3,0,0) loop; jb runs over r's row without a's entry ia
-                const uint32_t dm = d - 1u;
-                uint32_t jb = ia == 0u ? 1u : 0u;
-                uint32_t j1 = jb + 1u == ia ? jb + 2u : jb + 1u;
-                uint32_t e0 = P[min(jb, dm)], e1 = P[min(j1, dm)];
-                uint32_t wc0 = L.word(e0 >> 2, c), wa0 = L.word(a, e0 >> 2);
-                for (; jb < d; jb = j1, j1 = j1 + 1u == ia ? j1 + 2u : j1 + 1u) {
-                    const uint32_t j2 = j1 + 1u == ia ? j1 + 2u : j1 + 1u;
-                    const uint32_t e2 = P[min(j2, dm)];
-                    const uint32_t wc1 = L.word(e1 >> 2, c), wa1 = L.word(a, e1 >> 2);
-                    const uint32_t b = e0 >> 2, rb = e0 & 3u;
-                    const bool xbc = SmallLds::bit(wc0, c), xab = SmallLds::bit(wa0, b);
-                    e0 = e1;
-                    e1 = e2;
-                    wc0 = wc1;
-                    wa0 = wa1;
-                    if (xbc && jb < ia) continue;
-                    const uint32_t bc = L.code_if(xbc, b, c), ab = L.code_if(xab, a, b);
-                    if (ab | bc) {
-                        const uint32_t cls = sTable[motif_index4(ra, rb, 0u, ab, ac, bc)];
-                        const uint32_t sv[3] = {r, a, b};   // lanes share (r, a) and the loop position
-                        cr.shared(cls, sv, true);
-                        cr.add_n(c, cls, 1u);
-                    } else {
-                        cr.add_s(b, rb == 1u ? s1 : (rb == 2u ? s2 : s3), 1u);
-                        np += 1u << (10u * rb - 10u);
-                    }
-                    shp[1]++;
-                }
-                cr.add3(r, a, c, q1, np & 1023u);
-                cr.add3(r, a, c, q2, (np >> 10) & 1023u);
-                cr.add3(r, a, c, q3, np >> 20);
+            small_fence();
+            // (2,1,0) of the second slots (also with their own children, taken back above) and of r
+            for (uint32_t i = lane; i < d * 9u; i += 64) {
+                const uint32_t x = i % 9u, n = T[x], b = sAdj[lo + i / 9u];
+                if (n) cr.add_s(b >> 2, byte_of(sTrees.path2[x / 3u * 4u + x % 3u + 5u], b & 3u), n);
             }
-            // (1,2,0): a second child c2 of a, not adjacent to r.  Every pair {c, c2} of a's
-            // children is taken once, by the member from which the other lies less than half
-            // of a's row (above r) ahead, circularly: the lanes of one (r, a) then have equal
-            // loop lengths, (L - 1) / 2 or L / 2, instead of L - 1 down to 0.
-            {
-                const uint32_t u1 = sTable[motif_index4(ra, 0u, 0u, ac, 1u, 0u)];
-                const uint32_t u2 = sTable[motif_index4(ra, 0u, 0u, ac, 2u, 0u)];
-                const uint32_t u3 = sTable[motif_index4(ra, 0u, 0u, ac, 3u, 0u)];
-                const uint32_t s1 = cr.slot(u1), s2 = cr.slot(u2), s3 = cr.slot(u3);   // 3-star classes: tree slots
-                uint32_t np = 0;   // sets by arc code 1, 2, 3: 10-bit fields (every loop runs < 1024 times)
-                const uint32_t Lr = sOff[a + 1] - t0, pos = t - t0;
-                const uint32_t nd = (Lr - 1u) / 2u + ((Lr % 2u == 0u && pos < Lr / 2u) ? 1u : 0u);
-                // pipelined as the (3,0,0) loop over the circular positions pos + 1 .. pos + nd
-                const auto at = [&](uint32_t dl) {
-                    const uint32_t p2 = pos + dl < Lr ? pos + dl : pos + dl - Lr;
-                    return sAdj[t0 + (p2 < Lr ? p2 : 0u)];
-                };
-                uint32_t e0 = at(1u), e1 = at(2u);
-                uint32_t wr0 = L.word(r, e0 >> 2), wc0 = L.word(c, e0 >> 2);
-                for (uint32_t dlt = 1; dlt <= nd; dlt++) {
-                    const uint32_t e2 = at(dlt + 2u);
-                    const uint32_t wr1 = L.word(r, e1 >> 2), wc1 = L.word(c, e1 >> 2);
-                    const uint32_t c2 = e0 >> 2, ac2 = e0 & 3u;
-                    const bool xr = SmallLds::bit(wr0, c2), xc = SmallLds::bit(wc0, c2);
-                    e0 = e1;
-                    e1 = e2;
-                    wr0 = wr1;
-                    wc0 = wc1;
-                    if (xr) continue;
-                    const uint32_t cc2 = L.code_if(xc, c, c2);
-                    if (cc2) {
-                        const uint32_t cls = sTable[motif_index4(ra, 0u, 0u, ac, ac2, cc2)];
-                        const uint32_t sv[2] = {r, a};
-                        cr.shared(cls, sv, true);
-                        cr.add_n(c, cls, 1u);
-                        cr.add_n(c2, cls, 1u);
-                    } else {
-                        cr.add_s(c2, ac2 == 1u ? s1 : (ac2 == 2u ? s2 : s3), 1u);
-                        np += 1u << (10u * ac2 - 10u);
-                    }
-                    shp[2]++;
-                }
-                cr.add3(r, a, c, u1, np & 1023u);
-                cr.add3(r, a, c, u2, (np >> 10) & 1023u);
-                cr.add3(r, a, c, u3, np >> 20);
+            if (lane < 27u) {
+                const uint32_t x = lane / 3u, k = lane % 3u + 1u;
+                const uint32_t n = T[x] * (pick3(k, m1, m2, m3) - (x / 3u + 1u == k));
+                if (n) cr.add_s(r, byte_of(sTrees.path2[x / 3u * 4u + x % 3u + 5u], k), n);
+            } else if (lane < 37u) {   // (3,0,0) of r
+                const uint32_t t = code_triple(lane - 27u), k = t & 3u, l = (t >> 2) & 3u, q = t >> 4;
+                const uint32_t x = pick3(k, m1, m2, m3), y = pick3(l, m1, m2, m3), z = pick3(q, m1, m2, m3);
+                const uint32_t n = k == q ? x * (x - 1u) / 2u * (x - 2u) / 3u
+                                          : (k == l ? x * (x - 1u) / 2u * z : (l == q ? x * (y * (y - 1u) / 2u) : x * y * z));
+                if (n) cr.add_s(r, byte_of(sTrees.starr[k * 4u + l], q), n);
             }
-            // (1,1,1): path r - a - c - e, e not adjacent to r (nor equal to a) nor to a
-            {
-                const uint32_t w1 = sTable[motif_index4(ra, 0u, 0u, ac, 0u, 1u)];
-                const uint32_t w2 = sTable[motif_index4(ra, 0u, 0u, ac, 0u, 2u)];
-                const uint32_t w3 = sTable[motif_index4(ra, 0u, 0u, ac, 0u, 3u)];
-                const uint32_t s1 = cr.slot(w1), s2 = cr.slot(w2), s3 = cr.slot(w3);   // 4-path classes: tree slots
-                uint32_t np = 0;   // sets by arc code 1, 2, 3: 10-bit fields (every loop runs < 1024 times)
-                // pipelined as the (3,0,0) loop
-                const uint32_t tb = L.first_above(c, r), tend = sOff[c + 1];
-                const uint32_t tm = tend - 1u;   // read only when the row part is not empty
-                uint32_t e0 = tend > tb ? sAdj[tb] : 0u, e1 = tend > tb ? sAdj[min(tb + 1u, tm)] : 0u;
-                uint32_t wr0 = L.word(r, e0 >> 2), wa0 = L.word(a, e0 >> 2);
-                for (uint32_t te = tb; te < tend; te++) {
-                    const uint32_t e2 = sAdj[min(te + 2u, tm)];   // te < tend: in the row
-                    const uint32_t wr1 = L.word(r, e1 >> 2), wa1 = L.word(a, e1 >> 2);
-                    const uint32_t e = e0 >> 2, ce = e0 & 3u;
-                    const bool skip = SmallLds::bit(wr0, e) | SmallLds::bit(wa0, e);
-                    e0 = e1;
-                    e1 = e2;
-                    wr0 = wr1;
-                    wa0 = wa1;
-                    if (skip) continue;
-                    cr.add_s(e, ce == 1u ? s1 : (ce == 2u ? s2 : s3), 1u);
-                    np += 1u << (10u * ce - 10u);
-                    shp[3]++;
+            if (lane == 0u) shp[0] += d * (d - 1u) / 2u * (d - 2u) / 3u;
+            small_fence();
+        }
+        if constexpr (K == 4) {
+            // ---- depth-2 entries (r, a, c), a run of them per thread: the paths and what a row of
+            // c holds to correct.  Runs, not strides: the lanes of a wave then rarely share r and a.
+            const uint32_t per = (N2 + BS - 1) / BS, q0 = min(N2, tid * per), q1 = min(N2, q0 + per);
+            uint32_t u = q0 < q1 ? upper_idx(sPre2, U + 1, q0) : 0u, next = q0, r = 0, a = 0, ra = 0, t = 0;
+            for (uint32_t q = q0; q < q1; q++, t++) {
+                if (q == next) {   // the entry's first candidate in this run
+                    while (sPre2[u + 1] <= q) u++;
+                    next = sPre2[u + 1];
+                    r = sRootOf[u];
+                    const uint32_t ent = sAdj[sSplit[r] + u - sPreD[r]];
+                    a = ent >> 2;
+                    ra = ent & 3u;
+                    t = sOff[a + 1] - (next - q);
                 }
-                cr.add3(r, a, c, w1, np & 1023u);
-                cr.add3(r, a, c, w2, (np >> 10) & 1023u);
-                cr.add3(r, a, c, w3, np >> 20);
+                const uint32_t c = sAdj[t] >> 2, ac = sAdj[t] & 3u;
+                if (L.adjacent(r, c)) continue;   // c adjacent to r: depth 1, not 2
+                const uint32_t w = sTrees.path[ra * 4u + ac], clo = sOff[c];
+                uint32_t np = 0;   // paths by arc code 1, 2, 3: 10-bit fields (a row has < 1024 entries)
+                uint32_t hi = sOff[c + 1];
+                for (bool more = true; more && hi > clo;) {
+                    // up to 64 entries of c's row from its end.  Software pipeline: the entry two
+                    // ahead and the bitmap words of the next one are read before this entry's
+                    // credit (an LDS atomic, which later reads could not otherwise pass)
+                    const uint32_t len = min(64u, hi - clo), top = hi - 1u;
+                    unsigned long long odd = 0;   // entries with another arc
+                    uint32_t e0 = sAdj[top], e1 = sAdj[top - min(1u, len - 1u)];
+                    uint32_t wr0 = L.word(r, e0 >> 2), wa0 = L.word(a, e0 >> 2);
+                    uint32_t i = 0;
+                    for (; i < len; i++) {
+                        const uint32_t e2 = sAdj[top - min(i + 2u, len - 1u)];
+                        const uint32_t wr1 = L.word(r, e1 >> 2), wa1 = L.word(a, e1 >> 2);
+                        const uint32_t e = e0 >> 2, ce = e0 & 3u;
+                        if (e <= r) break;
+                        const bool x = (((wr0 | wa0) >> (e & 31u)) & 1u) != 0u;
+                        e0 = e1;
+                        e1 = e2;
+                        wr0 = wr1;
+                        wa0 = wa1;
+                        if (x) {
+                            if (e != a) odd |= 1ull << i;
+                        } else {
+                            cr.add_s(e, byte_of(w, ce), 1u);
+                            np += 1u << (10u * ce - 10u);
+                        }
+                    }
+                    more = i == len;
+                    for (; odd; odd &= odd - 1ull) {
+                        const uint32_t ent = sAdj[top - (uint32_t)(__ffsll((long long)odd) - 1)], e = ent >> 2, ce = ent & 3u;
+                        const bool xr = L.adjacent(r, e), xa = L.adjacent(a, e);
+                        const uint32_t ae = L.code_if(xa, a, e);
+                        if (xr) {   // (2,1,0) with the second slot e: from the lower parent of c
+                            const uint32_t re = L.code_if(true, r, e);
+                            const uint32_t was = byte_of(sTrees.path2[ra * 4u + ac], re);
+                            cr.add_s(r, was, ~0u);
+                            cr.add_s(a, was, ~0u);
+                            cr.add_s(e, was, ~0u);
+                            cr.add_s(c, was, ~0u);
+                            if (a < e) {
+                                const uint32_t is = sTable[motif_index4(ra, re, 0u, ae, ac, swap_arc_bits(ce))];
+                                cr.add_n(r, is, 1u);
+                                cr.add_n(a, is, 1u);
+                                cr.add_n(e, is, 1u);
+                                cr.add_n(c, is, 1u);
+                            } else {
+                                shp[1]--;
+                            }
+                        } else {    // (1,2,0) with the other child e of a: c here, e from its own row
+                            const uint32_t was = byte_of(sTrees.stara[ra * 4u + ac], ae);
+                            const uint32_t is = sTable[motif_index4(ra, 0u, 0u, ac, ae, ce)];
+                            cr.move(c, was, is);
+                            if (c < e) {
+                                cr.move(r, was, is);
+                                cr.move(a, was, is);
+                            }
+                        }
+                    }
+                    hi -= len;
+                }
+                for (uint32_t k = 0; k < 3; k++) {
+                    const uint32_t n = (np >> (10u * k)) & 1023u, s = (w >> (8u * k)) & 0xFFu;
+                    if (!n) continue;
+                    cr.add_s(r, s, n);
+                    cr.add_s(a, s, n);
+                    cr.add_s(c, s, n);
+                    shp[3] += n;
+                }
+            }
+            // ---- triangles, 8 lanes each: those of the queue, or, where it did not hold them all,
+            // the candidates again
+            __syncthreads();
+            const bool all = sTriN <= kTriQueue;
+            const uint32_t ntri = all ? sTriN : N2;
+            for (uint32_t i = tid >> 3; i < ntri; i += BS / 8) {
+                uint32_t tr, ta, tb;
+                if (all) {
+                    tr = sTri[i] & 1023u;
+                    ta = (sTri[i] >> 10) & 1023u;
+                    tb = sTri[i] >> 20;
+                } else {
+                    const uint32_t v = upper_idx(sPre2, U + 1, i);
+                    tr = sRootOf[v];
+                    ta = sAdj[sSplit[tr] + v - sPreD[tr]] >> 2;
+                    tb = sAdj[sOff[ta + 1] - (sPre2[v + 1] - i)] >> 2;
+                    if (tb < ta || !L.adjacent(tr, tb)) continue;
+                }
+                fix_triangle(L, cr, sTrees, sTable, tr, ta, tb, tid & 7u, 8u);
             }
         }
         __syncthreads();
@@ -541,22 +642,13 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
             if (!x) continue;
             const uint32_t v = i / NC, s = i - v * NC;
             const uint32_t cls = K == 3 ? s : sSlotCls[s];
-            G.out[(size_t)G.perm[v] * C + cls] = (unsigned long long)x;
+            G.out[(size_t)sPerm[v] * C + cls] = (unsigned long long)x;
         }
         // visited-set counters per shape: k = 3 -> (1,1), (1,2); k = 4 -> the four shapes
-        for (int s = 0; s < 4; s++) {
-            unsigned long long x = shp[s];
+        for (int s = 0; s < (K == 3 ? 2 : 4); s++) {
+            unsigned long long x = (unsigned long long)(long long)(int32_t)shp[s];
             for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-            shp[s] = x;
-        }
-        if (lane_of() == 0) {
-            if (K == 3) {
-                if (shp[0]) gadd64(&G.stats[0], shp[0]);
-                if (shp[1]) gadd64(&G.stats[1], shp[1]);
-            } else {
-                for (int s = 0; s < 4; s++)
-                    if (shp[s]) gadd64(&G.stats[2 + s], shp[s]);
-            }
+            if (lane_of() == 0 && x) gadd64(&G.stats[(K == 3 ? 0 : 2) + s], x);
         }
     }
 }
