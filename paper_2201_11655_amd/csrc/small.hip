@@ -160,7 +160,7 @@ struct SmallCredit {
     static constexpr uint32_t C = K == 3 ? (uint32_t)kClasses3 : (uint32_t)kClasses4;
     uint32_t* cnt;            // n x NC (LDS)
     const uint8_t* comp;      // k = 4: class -> counter slot or 0xFF (LDS)
-    const uint32_t* perm;     // rank -> original id (LDS)
+    const uint32_t* perm;     // rank -> original id in the low 10 bits (LDS)
     gptr<unsigned long long> out;
     // slot of cls in the LDS counters, or NC when the class is credited to the output
     __device__ __forceinline__ uint32_t slot(uint32_t cls) const {
@@ -171,7 +171,7 @@ struct SmallCredit {
     __device__ __forceinline__ void add_n(uint32_t v, uint32_t cls, uint32_t n) const {
         const uint32_t s = slot(cls);
         if (s < NC) atomicAdd(&cnt[v * NC + s], n);
-        else out_add(&out[(size_t)perm[v] * C + cls], (unsigned long long)n);
+        else out_add(&out[(size_t)(perm[v] & 1023u) * C + cls], (unsigned long long)n);
     }
     // n sets of a class whose counter slot s (< NC) is already known
     __device__ __forceinline__ void add_s(uint32_t v, uint32_t s, uint32_t n) const { atomicAdd(&cnt[v * NC + s], n); }
@@ -210,15 +210,27 @@ __device__ __forceinline__ uint32_t code_triple(uint32_t i) {
                                      0x3Dull << 30 | 0x2Aull << 36 | 0x3Aull << 42 | 0x3Eull << 48 | 0x3Full << 54;
     return (uint32_t)(t >> (6u * i)) & 63u;
 }
-__device__ __forceinline__ uint32_t sum8(uint32_t v) {
-    v += (uint32_t)__shfl_xor((int)v, 1, 64);
-    v += (uint32_t)__shfl_xor((int)v, 2, 64);
-    v += (uint32_t)__shfl_xor((int)v, 4, 64);
+// the value of a lane of the same 8, by a cross-lane move: the neighbour (0xB1), the other pair of
+// four (0x4E), the mirrored lane of eight (0x141)
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane8(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ unsigned long long lane8(unsigned long long v) {
+    return (unsigned long long)lane8<CTRL>((uint32_t)(v >> 32)) << 32 | lane8<CTRL>((uint32_t)v);
+}
+// sum over aligned groups of 8 lanes, in every lane
+template <class T>
+__device__ __forceinline__ T sum8(T v) {
+    v += lane8<0xB1>(v);
+    v += lane8<0x4E>(v);
+    v += lane8<0x141>(v);
     return v;
 }
-__device__ __forceinline__ void small_fence() {
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
+// 10-bit fields to 21-bit fields
+__device__ __forceinline__ unsigned long long wide3(uint32_t v) {
+    return (v & 1023u) | (unsigned long long)((v >> 10) & 1023u) << 21 | (unsigned long long)(v >> 20) << 42;
 }
 
 // The sets of r with the adjacent slots a < b, for lane i0 of step: triples (from the first of
@@ -268,7 +280,6 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
     constexpr uint32_t kTriQueue = K == 4 ? 512 : 1;
     __shared__ uint32_t sTri[kTriQueue];              // triangles (r, a, b), 10 bits each
     __shared__ uint32_t sTriN;
-    __shared__ uint32_t sKids[K == 4 ? BS / 64 : 1][9];   // per wave: children of r's slots by both codes
     __shared__ SmallTrees sTrees;
     constexpr uint32_t NC = SmallCredit<K>::NC;
     constexpr uint32_t C = SmallCredit<K>::C;
@@ -332,7 +343,7 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         uint32_t* sOff = dyn;                 // n + 1
         uint32_t* sSplit = sOff + n + 1;      // n
         uint32_t* sPreD = sSplit + n;         // n + 1: upper entries before row r
-        uint32_t* sPerm = sPreD + n + 1;      // n + 1: rank -> original id
+        uint32_t* sPerm = sPreD + n + 1;      // n + 1: rank -> original id | slots of code 1, 2 << 10, 20
         uint32_t* sBits = sPerm + n + 1;      // n * W
         uint32_t* sCnt = sBits + n * W;       // n * NC
         uint32_t* sPre2 = sCnt + n * NC;      // E / 2 + 1: depth-2 candidates before each upper entry
@@ -358,129 +369,118 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         __syncthreads();
         for (uint32_t r = tid; r < n; r += BS) {
             const uint32_t lo = sOff[r], hi = sOff[r + 1];
-            uint32_t s = hi;
+            uint32_t s = hi, m = sPerm[r];
             for (uint32_t t = lo; t < hi; t++) {
-                const uint32_t v = sAdj[t] >> 2;
+                const uint32_t v = sAdj[t] >> 2, k = sAdj[t] & 3u;
                 atomicOr(&sBits[r * W + (v >> 5)], 1u << (v & 31u));
                 if (v > r && s == hi) s = t;
+                if (v > r && k != 3u) m += 1u << (10u * k);
             }
+            sPerm[r] = m;
             sSplit[r] = s;
             sPreD[r] = hi - s;
         }
         if (tid == 0) sPreD[n] = 0u;
         __syncthreads();
         const SmallLds L{sOff, sAdj, sSplit, sBits, W};
-        uint32_t U = 0, N2 = 0;
-        if (K == 4) {
-            U = block_exclusive_scan<BS>(sPreD, n + 1, sPart);
-            // candidates of each upper entry (r, a): entries of a's row above r
-            for (uint32_t r = tid; r < n; r += BS)
-                for (uint32_t t = sSplit[r]; t < sOff[r + 1]; t++) {
-                    const uint32_t a = sAdj[t] >> 2;
-                    sPre2[sPreD[r] + (t - sSplit[r])] = sOff[a + 1] - L.first_above(a, r);
-                    sRootOf[sPreD[r] + (t - sSplit[r])] = (uint16_t)r;
-                }
-            if (tid == 0) sPre2[U] = 0u;
-            __syncthreads();
-            N2 = block_exclusive_scan<BS>(sPre2, U + 1, sPart);
-        }
+        const uint32_t U = block_exclusive_scan<BS>(sPreD, n + 1, sPart);
+        for (uint32_t r = tid; r < n; r += BS)
+            for (uint32_t t = sPreD[r]; t < sPreD[r] + sOff[r + 1] - sSplit[r]; t++) sRootOf[t] = (uint16_t)r;
+        __syncthreads();
 
         const SmallCredit<K> cr{sCnt, sComp, sPerm, G.out};
-        // visits of this thread: below 2^32 for every shape, as the CSR is in LDS (sum of d <= 2^14)
+        // visits of this thread: below 2^31 for every shape, as the CSR is in LDS (sum of d < 2^14)
         uint32_t shp[4] = {0, 0, 0, 0};
-        // ---- a root per wave, 8 lanes per slot: all that is counted by codes
-        for (uint32_t r = tid >> 6; r < n; r += BS / 64) {
-            const uint32_t lane = lane_of(), gl = lane & 7u, lo = sSplit[r], d = sOff[r + 1] - lo;
-            if (d == 0u) continue;
-            uint32_t m1 = 0, m2 = 0, m3 = 0;   // slots by code
-            for (uint32_t i = 0; i < d; i += 64) {
-                const uint32_t k = i + lane < d ? sAdj[lo + i + lane] & 3u : 0u;
-                m1 += (uint32_t)__popcll(__ballot(k == 1u));
-                m2 += (uint32_t)__popcll(__ballot(k == 2u));
-                m3 += (uint32_t)__popcll(__ballot(k == 3u));
-            }
-            uint32_t* T = sKids[K == 4 ? tid >> 6 : 0];
-            if (K == 4) {
-                if (lane < 9u) T[lane] = 0u;
-                small_fence();
-            }
-            for (uint32_t s0 = 0; s0 < d; s0 += 8) {
-                const bool on = s0 + (lane >> 3) < d;
-                const uint32_t ent = on ? sAdj[lo + s0 + (lane >> 3)] : 0u, a = ent >> 2, ra = ent & 3u;
-                // a's row above r, from its end
-                uint32_t h1 = 0, h2 = 0, h3 = 0;   // children by code
-                const uint32_t alo = on ? sOff[a] : 0u, ahi = on ? sOff[a + 1] : 0u;
-                for (uint32_t q = ahi; q > alo; q -= min(8u, q - alo)) {
-                    const uint32_t x = q - alo > gl ? sAdj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
-                    if (c > r) {
-                        if (!L.adjacent(r, c)) {
-                            h1 += k == 1u;
-                            h2 += k == 2u;
-                            h3 += k == 3u;
-                            if (K == 3) cr.add_s(c, sTable[motif_index3(ra, 0u, k)], 1u);
-                        } else if (c > a) {
-                            if (K == 3) {
-                                const uint32_t rc = L.code(r, c), is = sTable[motif_index3(ra, rc, k)];
-                                const uint32_t was = sTable[motif_index3(ra, rc, 0u)];
-                                cr.move(r, was, is);
-                                cr.move(a, was, is);
-                                cr.move(c, was, is);
-                            } else {
-                                const uint32_t at = atomicAdd(&sTriN, 1u);
-                                if (at < kTriQueue) sTri[at] = r | (a << 10) | (c << 20);
-                            }
+        const uint32_t gl = tid & 7u;
+        uint32_t pk, pl;   // pair of codes of this lane
+        code_pair(min(gl, 5u), pk, pl);
+        // ---- upper entries (r, a), 8 lanes each: all that is counted by codes
+        for (uint32_t u0 = 0; u0 < U; u0 += BS / 8) {
+            const uint32_t u = u0 + (tid >> 3);
+            const bool on = u < U;
+            const uint32_t r = on ? sRootOf[u] : 0u, lo = sSplit[r], d = sOff[r + 1] - lo, m = sPerm[r];
+            const uint32_t ent = on ? sAdj[lo + u - sPreD[r]] : 0u, a = ent >> 2, ra = ent & 3u;
+            // a's row above r, from its end
+            uint32_t h1 = 0, h2 = 0, h3 = 0;   // children by code
+            const uint32_t alo = on ? sOff[a] : 0u, ahi = on ? sOff[a + 1] : 0u;
+            for (uint32_t q = ahi; q > alo; q -= min(8u, q - alo)) {
+                const uint32_t x = q - alo > gl ? sAdj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
+                if (c > r) {
+                    if (!L.adjacent(r, c)) {
+                        h1 += k == 1u;
+                        h2 += k == 2u;
+                        h3 += k == 3u;
+                        if (K == 3) cr.add_s(c, sTable[motif_index3(ra, 0u, k)], 1u);
+                    } else if (c > a) {
+                        if (K == 3) {
+                            const uint32_t rc = L.code(r, c), is = sTable[motif_index3(ra, rc, k)];
+                            const uint32_t was = sTable[motif_index3(ra, rc, 0u)];
+                            cr.move(r, was, is);
+                            cr.move(a, was, is);
+                            cr.move(c, was, is);
+                        } else {
+                            const uint32_t at = atomicAdd(&sTriN, 1u);
+                            if (at < kTriQueue) sTri[at] = r | (a << 10) | (c << 20);
                         }
                     }
-                    if (q - alo > 8u && (uint32_t)(sAdj[q - 8u] >> 2) <= r) break;
                 }
-                h1 = sum8(h1);
-                h2 = sum8(h2);
-                h3 = sum8(h3);
-                if (!on) continue;
-                const uint32_t h = h1 + h2 + h3;
-                const uint32_t o1 = m1 - (ra == 1u), o2 = m2 - (ra == 2u), o3 = m3 - (ra == 3u);   // the other slots
-                if (K == 3) {
-                    if (gl < 6u) {   // (1,1) of a; (1,2) of a and r
-                        const uint32_t k = gl % 3u + 1u, n = gl < 3u ? pick3(k, o1, o2, o3) : pick3(k, h1, h2, h3);
-                        const uint32_t cls = sTable[gl < 3u ? motif_index3(ra, k, 0u) : motif_index3(ra, 0u, k)];
-                        if (n) {
-                            cr.add_s(a, cls, n);
-                            if (gl >= 3u) cr.add_s(r, cls, n);
-                        }
+                if (q - alo > 8u && (uint32_t)(sAdj[q - 8u] >> 2) <= r) break;
+            }
+            h1 = sum8(h1);
+            h2 = sum8(h2);
+            h3 = sum8(h3);
+            if (!on) continue;
+            const uint32_t m1 = (m >> 10) & 1023u, m2 = m >> 20, h = h1 + h2 + h3;
+            const uint32_t o1 = m1 - (ra == 1u), o2 = m2 - (ra == 2u), o3 = d - m1 - m2 - (ra == 3u);   // the other slots
+            if (K == 3) {
+                if (gl < 6u) {   // (1,1) of a; (1,2) of a and r
+                    const uint32_t k = gl % 3u + 1u, n = gl < 3u ? pick3(k, o1, o2, o3) : pick3(k, h1, h2, h3);
+                    const uint32_t cls = sTable[gl < 3u ? motif_index3(ra, k, 0u) : motif_index3(ra, 0u, k)];
+                    if (n) {
+                        cr.add_s(a, cls, n);
+                        if (gl >= 3u) cr.add_s(r, cls, n);
                     }
-                    if (gl == 0u) shp[1] += h;
-                    continue;
                 }
-                if (gl < 3u) atomicAdd(&T[(ra - 1u) * 3u + gl], pick3(gl + 1u, h1, h2, h3));
-                for (uint32_t t = gl; t < 24u; t += 8u) {
-                    uint32_t n, slot, k, l;
-                    if (t < 9u) {            // (2,1,0), a the parent
-                        k = t / 3u + 1u;
-                        l = t % 3u + 1u;
-                        n = pick3(k, h1, h2, h3) * pick3(l, o1, o2, o3);
-                        slot = byte_of(sTrees.path2[ra * 4u + k], l);
-                    } else if (t < 15u) {    // (3,0,0)
-                        code_pair(t - 9u, k, l);
-                        n = pairs_of(k, l, o1, o2, o3);
-                        slot = byte_of(sTrees.starr[ra * 4u + k], l);
-                    } else if (t < 21u) {    // (1,2,0): r too
-                        code_pair(t - 15u, k, l);
-                        n = pairs_of(k, l, h1, h2, h3);
-                        slot = byte_of(sTrees.stara[ra * 4u + k], l);
-                        if (n) cr.add_s(r, slot, n);
-                    } else {                 // (2,1,0), a the second slot: not with its own children
-                        k = t - 20u;
-                        n = 0u - pick3(k, h1, h2, h3);
-                        slot = byte_of(sTrees.path2[ra * 4u + k], ra);
+                if (gl == 0u) shp[1] += h;
+                continue;
+            }
+            {   // (3,0,0) of a; lanes 6 and 7: a part of the next
+                const bool star = gl < 6u;
+                const uint32_t k = star ? pk : 3u, l = star ? pl : gl - 4u;
+                const uint32_t n = star ? pairs_of(pk, pl, o1, o2, o3) : h3 * pick3(l, o1, o2, o3);
+                const uint32_t w = (star ? sTrees.starr : sTrees.path2)[ra * 4u + k];
+                if (n) {
+                    cr.add_s(a, byte_of(w, l), n);
+                    if (!star) cr.add_s(r, byte_of(w, l), n);
+                }
+            }
+            if (h) {
+                sPre2[u] = h1 | (h2 << 10) | (h3 << 20);
+                {   // (2,1,0) of a, the parent, and r; children of codes 1, 2 and the first of code 3
+                    const uint32_t k = gl / 3u + 1u, l = gl % 3u + 1u, n = gl < 7u ? pick3(k, h1, h2, h3) * pick3(l, o1, o2, o3) : 0u;
+                    const uint32_t slot = byte_of(sTrees.path2[ra * 4u + k], l);
+                    if (n) {
+                        cr.add_s(a, slot, n);
+                        cr.add_s(r, slot, n);
                     }
-                    if (n) cr.add_s(a, slot, n);
+                }
+                if (gl < 6u) {   // (1,2,0) of a and r
+                    const uint32_t n = pairs_of(pk, pl, h1, h2, h3), slot = byte_of(sTrees.stara[ra * 4u + pk], pl);
+                    if (n) {
+                        cr.add_s(a, slot, n);
+                        cr.add_s(r, slot, n);
+                    }
+                }
+                if (gl < 3u) {   // (2,1,0), a the second slot: not with its own children, counted below
+                    const uint32_t n = pick3(gl + 1u, h1, h2, h3);
+                    if (n) cr.add_s(a, byte_of(sTrees.path2[ra * 4u + gl + 1u], ra), 0u - n);
                 }
                 if (gl == 0u) {
                     shp[1] += h * (d - 1u);
                     shp[2] += h * (h - 1u) / 2u;
                 }
                 // the children: (2,1,0) and (1,2,0)
-                for (uint32_t q = h ? ahi : alo; q > alo; q -= min(8u, q - alo)) {
+                for (uint32_t q = ahi; q > alo; q -= min(8u, q - alo)) {
                     const uint32_t x = q - alo > gl ? sAdj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
                     if (c > r && !L.adjacent(r, c)) {
                         const uint32_t w2 = sTrees.path2[ra * 4u + k], ws = sTrees.stara[ra * 4u + k];
@@ -494,38 +494,63 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
                     }
                     if (q - alo > 8u && (uint32_t)(sAdj[q - 8u] >> 2) <= r) break;
                 }
+            } else {
+                sPre2[u] = 0u;
             }
+        }
+        __syncthreads();
+        // ---- roots, 8 lanes each: r's triples or pairs of slots; (2,1,0) of every slot as the second
+        // slot, with all children of r's slots (its own were taken back above)
+        for (uint32_t r = tid >> 3; r < n; r += BS / 8) {
+            const uint32_t lo = sSplit[r], d = sOff[r + 1] - lo, u0 = sPreD[r];
+            if (d == 0u) continue;
+            const uint32_t m1 = (sPerm[r] >> 10) & 1023u, m2 = sPerm[r] >> 20, m3 = d - m1 - m2;
             if (K == 3) {
-                if (lane < 6u) {   // (1,1) of r
-                    uint32_t k, l;
-                    code_pair(lane, k, l);
-                    const uint32_t n = pairs_of(k, l, m1, m2, m3);
-                    if (n) cr.add_s(r, sTable[motif_index3(k, l, 0u)], n);
-                }
-                if (lane == 0u) shp[0] += d * (d - 1u) / 2u;
+                const uint32_t n = gl < 6u ? pairs_of(pk, pl, m1, m2, m3) : 0u;
+                if (n) cr.add_s(r, sTable[motif_index3(pk, pl, 0u)], n);
+                if (gl == 0u) shp[0] += d * (d - 1u) / 2u;
                 continue;
             }
-            small_fence();
-            // (2,1,0) of the second slots (also with their own children, taken back above) and of r
-            for (uint32_t i = lane; i < d * 9u; i += 64) {
-                const uint32_t x = i % 9u, n = T[x], b = sAdj[lo + i / 9u];
-                if (n) cr.add_s(b >> 2, byte_of(sTrees.path2[x / 3u * 4u + x % 3u + 5u], b & 3u), n);
-            }
-            if (lane < 27u) {
-                const uint32_t x = lane / 3u, k = lane % 3u + 1u;
-                const uint32_t n = T[x] * (pick3(k, m1, m2, m3) - (x / 3u + 1u == k));
-                if (n) cr.add_s(r, byte_of(sTrees.path2[x / 3u * 4u + x % 3u + 5u], k), n);
-            } else if (lane < 37u) {   // (3,0,0) of r
-                const uint32_t t = code_triple(lane - 27u), k = t & 3u, l = (t >> 2) & 3u, q = t >> 4;
+            for (uint32_t i = gl; i < 10u; i += 8u) {
+                const uint32_t t = code_triple(i), k = t & 3u, l = (t >> 2) & 3u, q = t >> 4;
                 const uint32_t x = pick3(k, m1, m2, m3), y = pick3(l, m1, m2, m3), z = pick3(q, m1, m2, m3);
                 const uint32_t n = k == q ? x * (x - 1u) / 2u * (x - 2u) / 3u
                                           : (k == l ? x * (x - 1u) / 2u * z : (l == q ? x * (y * (y - 1u) / 2u) : x * y * z));
                 if (n) cr.add_s(r, byte_of(sTrees.starr[k * 4u + l], q), n);
             }
-            if (lane == 0u) shp[0] += d * (d - 1u) / 2u * (d - 2u) / 3u;
-            small_fence();
+            if (gl == 0u) shp[0] += d * (d - 1u) / 2u * (d - 2u) / 3u;
+            unsigned long long t1 = 0, t2 = 0, t3 = 0;   // children by code (21-bit fields), per code of their slot
+            for (uint32_t i = gl; i < d; i += 8u) {
+                const unsigned long long h = wide3(sPre2[u0 + i]);
+                const uint32_t x = sAdj[lo + i] & 3u;
+                t1 += x == 1u ? h : 0ull;
+                t2 += x == 2u ? h : 0ull;
+                t3 += x == 3u ? h : 0ull;
+            }
+            t1 = sum8(t1);
+            t2 = sum8(t2);
+            t3 = sum8(t3);
+            for (uint32_t i = gl; i < d; i += 8u) {
+                const uint32_t ent = sAdj[lo + i];
+                for (uint32_t x = 1; x < 4; x++) {
+                    const unsigned long long tx = x == 1u ? t1 : (x == 2u ? t2 : t3);
+                    for (uint32_t k = 1; k < 4; k++) {
+                        const uint32_t n = (uint32_t)(tx >> (21u * k - 21u)) & 0x1FFFFFu;
+                        if (n) cr.add_s(ent >> 2, byte_of(sTrees.path2[x * 4u + k], ent & 3u), n);
+                    }
+                }
+            }
         }
         if constexpr (K == 4) {
+            // candidates of each upper entry (r, a): entries of a's row above r
+            __syncthreads();
+            for (uint32_t u = tid; u < U; u += BS) {
+                const uint32_t r = sRootOf[u], a = sAdj[sSplit[r] + u - sPreD[r]] >> 2;
+                sPre2[u] = sOff[a + 1] - L.first_above(a, r);
+            }
+            if (tid == 0) sPre2[U] = 0u;
+            __syncthreads();
+            const uint32_t N2 = block_exclusive_scan<BS>(sPre2, U + 1, sPart);
             // ---- depth-2 entries (r, a, c), a run of them per thread: the paths and what a row of
             // c holds to correct.  Runs, not strides: the lanes of a wave then rarely share r and a.
             const uint32_t per = (N2 + BS - 1) / BS, q0 = min(N2, tid * per), q1 = min(N2, q0 + per);
@@ -642,7 +667,7 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
             if (!x) continue;
             const uint32_t v = i / NC, s = i - v * NC;
             const uint32_t cls = K == 3 ? s : sSlotCls[s];
-            G.out[(size_t)sPerm[v] * C + cls] = (unsigned long long)x;
+            G.out[(size_t)(sPerm[v] & 1023u) * C + cls] = (unsigned long long)x;
         }
         // visited-set counters per shape: k = 3 -> (1,1), (1,2); k = 4 -> the four shapes
         for (int s = 0; s < (K == 3 ? 2 : 4); s++) {
