@@ -114,6 +114,7 @@ struct SmallLds {
     const uint16_t* adj;   // entries (nbr_rank << 2) | arc bits; ranks below 1024 fit 16 bits
     const uint32_t* split;
     const uint32_t* bits;
+    const uint32_t* arcs;   // bit (u, v): arc u -> v; nullptr where LDS has no room for it
     uint32_t W;
     __device__ __forceinline__ bool adjacent(uint32_t u, uint32_t v) const {
         return (bits[u * W + (v >> 5)] >> (v & 31u)) & 1u;
@@ -124,6 +125,8 @@ struct SmallLds {
     // arc bits of (u, v) seen from u for a pair whose adjacency bit is already read
     __device__ __forceinline__ uint32_t code_if(bool is_adj, uint32_t u, uint32_t v) const {
         if (!is_adj) return 0u;
+        if (arcs)
+            return ((arcs[u * W + (v >> 5)] >> (v & 31u)) & 1u) | (((arcs[v * W + (u >> 5)] >> (u & 31u)) & 1u) << 1);
         uint32_t lo = off[u], hi = off[u + 1];
         const uint32_t key = v << 2;
         while (lo < hi) {
@@ -133,16 +136,7 @@ struct SmallLds {
         return adj[lo] & 3u;
     }
     // arc bits of (u, v) seen from u, 0 if not adjacent
-    __device__ __forceinline__ uint32_t code(uint32_t u, uint32_t v) const {
-        if (!adjacent(u, v)) return 0u;
-        uint32_t lo = off[u], hi = off[u + 1];
-        const uint32_t key = v << 2;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (adj[mid] < key) lo = mid + 1; else hi = mid;
-        }
-        return adj[lo] & 3u;
-    }
+    __device__ __forceinline__ uint32_t code(uint32_t u, uint32_t v) const { return code_if(adjacent(u, v), u, v); }
     __device__ __forceinline__ uint32_t first_above(uint32_t u, uint32_t x) const {
         uint32_t lo = off[u], hi = off[u + 1];
         const uint32_t key = (x + 1u) << 2;
@@ -156,29 +150,24 @@ struct SmallLds {
 
 template <int K>
 struct SmallCredit {
-    static constexpr uint32_t NC = K == 3 ? (uint32_t)kClasses3 : kSlots4;
     static constexpr uint32_t C = K == 3 ? (uint32_t)kClasses3 : (uint32_t)kClasses4;
-    uint32_t* cnt;            // n x NC (LDS)
-    const uint8_t* comp;      // k = 4: class -> counter slot or 0xFF (LDS)
+    uint32_t nc;              // counters of a vertex: the classes, or kSlots4 of them
+    uint32_t* cnt;            // n x nc (LDS)
+    const uint8_t* comp;      // class -> counter slot or 0xFF (LDS)
     const uint32_t* perm;     // rank -> original id in the low 10 bits (LDS)
     gptr<unsigned long long> out;
-    // slot of cls in the LDS counters, or NC when the class is credited to the output
-    __device__ __forceinline__ uint32_t slot(uint32_t cls) const {
-        if (K == 3) return cls;
-        const uint32_t s = comp[cls];
-        return s == 0xFFu ? NC : s;
+    // one set of class cls
+    __device__ __forceinline__ void add1(uint32_t v, uint32_t cls) const {
+        const uint32_t s = K == 3 ? cls : comp[cls];
+        if (K == 3 || s != 0xFFu) atomicAdd(&cnt[v * nc + s], 1u);
+        else out_add(&out[(size_t)(perm[v] & 1023u) * C + cls], 1ull);
     }
-    __device__ __forceinline__ void add_n(uint32_t v, uint32_t cls, uint32_t n) const {
-        const uint32_t s = slot(cls);
-        if (s < NC) atomicAdd(&cnt[v * NC + s], n);
-        else out_add(&out[(size_t)(perm[v] & 1023u) * C + cls], (unsigned long long)n);
-    }
-    // n sets of a class whose counter slot s (< NC) is already known
-    __device__ __forceinline__ void add_s(uint32_t v, uint32_t s, uint32_t n) const { atomicAdd(&cnt[v * NC + s], n); }
+    // n sets of the class of counter slot s
+    __device__ __forceinline__ void add_s(uint32_t v, uint32_t s, uint32_t n) const { atomicAdd(&cnt[v * nc + s], n); }
     // one set: from the counter slot `was` to class `is`
     __device__ __forceinline__ void move(uint32_t v, uint32_t was, uint32_t is) const {
         add_s(v, was, ~0u);
-        add_n(v, is, 1u);
+        add1(v, is);
     }
 };
 
@@ -269,26 +258,29 @@ __device__ __forceinline__ void fix_triangle(const SmallLds& L, const SmallCredi
 }
 
 template <int BS, int K>
-__global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
+__global__ __launch_bounds__(BS, 4) void k_small(SmallArgs A) {
     extern __shared__ uint32_t dyn[];
     __shared__ uint8_t sTable[K == 3 ? 64 : 4096];
     __shared__ uint8_t sComp[256];
+    __shared__ uint8_t sSame[K == 4 ? 256 : 1];        // class -> class
     __shared__ uint8_t sSlotCls[64];
     __shared__ uint32_t sMask[8];   // k = 4: 256-bit mask of the single-arc 4-pair classes
     __shared__ uint32_t sPart[BS / 64];
     __shared__ uint32_t sGraph;
-    constexpr uint32_t kTriQueue = K == 4 ? 512 : 1;
+    constexpr uint32_t kTriQueue = K == 4 ? 512 : 1;   // G(n, p) has about deg^3 / 6
     __shared__ uint32_t sTri[kTriQueue];              // triangles (r, a, b), 10 bits each
     __shared__ uint32_t sTriN;
-    __shared__ SmallTrees sTrees;
-    constexpr uint32_t NC = SmallCredit<K>::NC;
+    __shared__ SmallTrees sTreeSlots[2];               // with kSlots4 counters; with one per class
     constexpr uint32_t C = SmallCredit<K>::C;
     const uint32_t tid = threadIdx.x;
     for (uint32_t i = tid; i < (K == 3 ? 64u : 4096u); i += BS) sTable[i] = A.table[i];
     if (K == 4) {
         // counter slots: the tree classes' from the class tables, then the single-arc
         // 4-pair classes in ascending class id (each found from any of its codes)
-        for (uint32_t i = tid; i < 256u; i += BS) sComp[i] = A.comp_of[i];
+        for (uint32_t i = tid; i < 256u; i += BS) {
+            sComp[i] = A.comp_of[i];
+            sSame[i] = (uint8_t)i;
+        }
         for (uint32_t i = tid; i < (uint32_t)kCompact4; i += BS) sSlotCls[i] = A.comp_cls[i];
         if (tid < 8) sMask[tid] = 0u;
         __syncthreads();
@@ -315,18 +307,19 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         }
         if (tid < 64) {
             const uint32_t x = (tid >> 2) & 3u, y = tid & 3u;
-            uint32_t w[4] = {0, 0, 0, 0};
-            for (uint32_t z = 1; tid < 16 && x && y && z < 4; z++) {
-                w[0] |= (uint32_t)sComp[sTable[motif_index4(x, 0u, 0u, y, 0u, z)]] << (8u * z - 8u);
-                w[1] |= (uint32_t)sComp[sTable[motif_index4(x, z, 0u, 0u, y, 0u)]] << (8u * z - 8u);
-                w[2] |= (uint32_t)sComp[sTable[motif_index4(x, y, z, 0u, 0u, 0u)]] << (8u * z - 8u);
-                w[3] |= (uint32_t)sComp[sTable[motif_index4(x, 0u, 0u, y, z, 0u)]] << (8u * z - 8u);
-            }
-            if (tid < 16) {
-                sTrees.path[tid] = w[0];
-                sTrees.path2[tid] = w[1];
-                sTrees.starr[tid] = w[2];
-                sTrees.stara[tid] = w[3];
+            for (uint32_t f = 0; tid < 16 && f < 2; f++) {
+                const uint8_t* of = f ? sSame : sComp;
+                uint32_t w[4] = {0, 0, 0, 0};
+                for (uint32_t z = 1; x && y && z < 4; z++) {
+                    w[0] |= (uint32_t)of[sTable[motif_index4(x, 0u, 0u, y, 0u, z)]] << (8u * z - 8u);
+                    w[1] |= (uint32_t)of[sTable[motif_index4(x, z, 0u, 0u, y, 0u)]] << (8u * z - 8u);
+                    w[2] |= (uint32_t)of[sTable[motif_index4(x, y, z, 0u, 0u, 0u)]] << (8u * z - 8u);
+                    w[3] |= (uint32_t)of[sTable[motif_index4(x, 0u, 0u, y, z, 0u)]] << (8u * z - 8u);
+                }
+                sTreeSlots[f].path[tid] = w[0];
+                sTreeSlots[f].path2[tid] = w[1];
+                sTreeSlots[f].starr[tid] = w[2];
+                sTreeSlots[f].stara[tid] = w[3];
             }
         }
     }
@@ -345,17 +338,42 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         uint32_t* sPreD = sSplit + n;         // n + 1: upper entries before row r
         uint32_t* sPerm = sPreD + n + 1;      // n + 1: rank -> original id | slots of code 1, 2 << 10, 20
         uint32_t* sBits = sPerm + n + 1;      // n * W
-        uint32_t* sCnt = sBits + n * W;       // n * NC
-        uint32_t* sPre2 = sCnt + n * NC;      // E / 2 + 1: depth-2 candidates before each upper entry
+        uint32_t* sPre2 = sBits + n * W;      // E / 2 + 1: depth-2 candidates before each upper entry
         uint16_t* sAdj = reinterpret_cast<uint16_t*>(sPre2 + E / 2 + 1);   // E (u16)
         uint16_t* sRootOf = sAdj + E;         // E / 2 (u16): root of each upper entry
+        uint32_t* rest = sPre2 + E / 2 + 1 + (E + E / 2 + 1) / 2;
+        // With the LDS that is left: the arcs one way, which turn the search for a pair's codes
+        // into two reads; more of the triangle queue, whose overflow costs a search per
+        // candidate (600 us instead of 55 in the worst of the batched graphs); then counters of
+        // every class, which fit up to n = 160 or so, where a graph of 8 arcs a vertex is dense
+        // and the classes beyond kSlots4 are frequent.  4096 G(n, p) graphs: 2.70 ms with none of
+        // them, 2.05 with all.
+        uint32_t room = A.lds_words - (uint32_t)(rest - dyn) - n * (K == 3 ? C : kSlots4);
+        uint32_t* sArcs = nullptr;
+        if (K == 4 && room >= n * W) {
+            sArcs = rest;
+            rest += n * W;
+            room -= n * W;
+        }
+        uint32_t* sTri2 = rest;               // more of the queue
+        const uint32_t tri2 = K == 4 ? min(room, 1024u) : 0u;
+        rest += tri2;
+        room -= tri2;
+        const bool full = K == 3 || room >= n * (C - kSlots4);
+        const uint32_t NC = full ? C : kSlots4;
+        uint32_t* sCnt = rest;                // n * NC
+        const SmallTrees& sTrees = sTreeSlots[full ? 1 : 0];
         // ---- stage the graph, clear bitmap, counters and the output block
         for (uint32_t i = tid; i <= n; i += BS) sOff[i] = G.off[i];
         for (uint32_t i = tid; i < n; i += BS) sPerm[i] = (uint32_t)G.perm[i];
         for (uint32_t i = tid; i < E; i += BS) sAdj[i] = (uint16_t)G.adj[i];
-        for (uint32_t i = tid; i < n * W; i += BS) sBits[i] = 0u;
+        for (uint32_t i = tid; i < n * W; i += BS) {
+            sBits[i] = 0u;
+            if (sArcs) sArcs[i] = 0u;
+        }
         for (uint32_t i = tid; i < n * NC; i += BS) sCnt[i] = 0u;
-        if (((uintptr_t)G.out.p & 15u) == 0) {   // 16-byte stores, then the odd last cell
+        if (full) {   // every cell is stored at the end
+        } else if (((uintptr_t)G.out.p & 15u) == 0) {   // 16-byte stores, then the odd last cell
             const size_t cells = (size_t)n * C;
             using u64x2 = unsigned long long __attribute__((ext_vector_type(2)));
             const auto o = G.out.as<u64x2>();
@@ -373,6 +391,7 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
             for (uint32_t t = lo; t < hi; t++) {
                 const uint32_t v = sAdj[t] >> 2, k = sAdj[t] & 3u;
                 atomicOr(&sBits[r * W + (v >> 5)], 1u << (v & 31u));
+                if (sArcs && (k & 1u)) atomicOr(&sArcs[r * W + (v >> 5)], 1u << (v & 31u));
                 if (v > r && s == hi) s = t;
                 if (v > r && k != 3u) m += 1u << (10u * k);
             }
@@ -382,13 +401,13 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         }
         if (tid == 0) sPreD[n] = 0u;
         __syncthreads();
-        const SmallLds L{sOff, sAdj, sSplit, sBits, W};
+        const SmallLds L{sOff, sAdj, sSplit, sBits, sArcs, W};
         const uint32_t U = block_exclusive_scan<BS>(sPreD, n + 1, sPart);
         for (uint32_t r = tid; r < n; r += BS)
             for (uint32_t t = sPreD[r]; t < sPreD[r] + sOff[r + 1] - sSplit[r]; t++) sRootOf[t] = (uint16_t)r;
         __syncthreads();
 
-        const SmallCredit<K> cr{sCnt, sComp, sPerm, G.out};
+        const SmallCredit<K> cr{NC, sCnt, full ? sSame : sComp, sPerm, G.out};
         // visits of this thread: below 2^31 for every shape, as the CSR is in LDS (sum of d < 2^14)
         uint32_t shp[4] = {0, 0, 0, 0};
         const uint32_t gl = tid & 7u;
@@ -421,6 +440,7 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
                         } else {
                             const uint32_t at = atomicAdd(&sTriN, 1u);
                             if (at < kTriQueue) sTri[at] = r | (a << 10) | (c << 20);
+                            else if (at < kTriQueue + tri2) sTri2[at - kTriQueue] = r | (a << 10) | (c << 20);
                         }
                     }
                 }
@@ -610,10 +630,10 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
                             cr.add_s(c, was, ~0u);
                             if (a < e) {
                                 const uint32_t is = sTable[motif_index4(ra, re, 0u, ae, ac, swap_arc_bits(ce))];
-                                cr.add_n(r, is, 1u);
-                                cr.add_n(a, is, 1u);
-                                cr.add_n(e, is, 1u);
-                                cr.add_n(c, is, 1u);
+                                cr.add1(r, is);
+                                cr.add1(a, is);
+                                cr.add1(e, is);
+                                cr.add1(c, is);
                             } else {
                                 shp[1]--;
                             }
@@ -641,14 +661,15 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
             // ---- triangles, 8 lanes each: those of the queue, or, where it did not hold them all,
             // the candidates again
             __syncthreads();
-            const bool all = sTriN <= kTriQueue;
+            const bool all = sTriN <= kTriQueue + tri2;
             const uint32_t ntri = all ? sTriN : N2;
             for (uint32_t i = tid >> 3; i < ntri; i += BS / 8) {
                 uint32_t tr, ta, tb;
                 if (all) {
-                    tr = sTri[i] & 1023u;
-                    ta = (sTri[i] >> 10) & 1023u;
-                    tb = sTri[i] >> 20;
+                    const uint32_t x = i < kTriQueue ? sTri[i] : sTri2[i - kTriQueue];
+                    tr = x & 1023u;
+                    ta = (x >> 10) & 1023u;
+                    tb = x >> 20;
                 } else {
                     const uint32_t v = upper_idx(sPre2, U + 1, i);
                     tr = sRootOf[v];
@@ -664,9 +685,9 @@ __global__ __launch_bounds__(BS) void k_small(SmallArgs A) {
         // LDS-counted class never reaches the output otherwise, so its cells are stored.
         for (uint32_t i = tid; i < n * NC; i += BS) {
             const uint32_t x = sCnt[i];
-            if (!x) continue;
+            if (!x && !full) continue;
             const uint32_t v = i / NC, s = i - v * NC;
-            const uint32_t cls = K == 3 ? s : sSlotCls[s];
+            const uint32_t cls = full ? s : sSlotCls[s];
             G.out[(size_t)(sPerm[v] & 1023u) * C + cls] = (unsigned long long)x;
         }
         // visited-set counters per shape: k = 3 -> (1,1), (1,2); k = 4 -> the four shapes
@@ -694,11 +715,17 @@ bool small_eligible(int64_t n, int64_t entries, int k) {
 
 int small_threads(int variant) { return variant <= 0 ? 256 : (variant == 1 ? 512 : 1024); }
 
-void launch_small(const SmallArgs& a, int k, int variant, unsigned grid, size_t lds, hipStream_t st) {
+void launch_small(SmallArgs a, int k, int variant, unsigned grid, size_t lds, hipStream_t st) {
     void (*kern)(SmallArgs) = nullptr;
     const int bs = small_threads(variant);
     if (k == 3) kern = bs == 256 ? k_small<256, 3> : (bs == 512 ? k_small<512, 3> : k_small<1024, 3>);
     else kern = bs == 256 ? k_small<256, 4> : (bs == 512 ? k_small<512, 4> : k_small<1024, 4>);
+    // all the LDS that the workgroups which a CU holds (16 waves by registers) leave each other
+    if (k == 4) {
+        const size_t fit = std::max<size_t>(1, std::min<size_t>(163840 / (lds + 9216), (size_t)(1024 / bs)));
+        lds = std::max(lds, (163840 / fit - 9216) & ~(size_t)15);
+    }
+    a.lds_words = (uint32_t)(lds / sizeof(uint32_t));
     VDMC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(bs), lds, st, a);
     VDMC_HIP(hipGetLastError());

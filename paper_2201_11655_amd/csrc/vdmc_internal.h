@@ -325,13 +325,14 @@ struct SmallArgs {
     const uint8_t* table;       // code -> class id for the launch's k
     const uint8_t* comp_of;     // class -> tree slot or 0xFF (256 entries)
     const uint8_t* comp_cls;    // tree slot -> class
+    uint32_t lds_words;         // dynamic LDS of a workgroup (set by launch_small)
 };
 constexpr int64_t kSmallMaxN = 1024;            // u32 LDS counters cannot overflow below this
 constexpr size_t kSmallLdsBudget = 163840 - 9216;   // dynamic LDS of one workgroup (gfx950: 160 KiB per CU)
 size_t small_lds_bytes(int64_t n, int64_t entries, int k);
 bool small_eligible(int64_t n, int64_t entries, int k);
 int small_threads(int variant);
-void launch_small(const SmallArgs& a, int k, int variant, unsigned grid, size_t lds, hipStream_t stream);
+void launch_small(SmallArgs a, int k, int variant, unsigned grid, size_t lds, hipStream_t stream);
 constexpr int kBatchVariants = 3;   // 64, 128, 256 threads per root
 struct TuneChoice {
     int small_variant = 2;   // threads per workgroup of the whole-graph kernel: 256, 512, 1024
