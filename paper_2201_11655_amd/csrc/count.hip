@@ -506,6 +506,11 @@ void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {
     if (g->pairs == 0) return;
     launch_fill_u64(out, (size_t)g->pairs * C, 0, st);
     if (g->nroots == 0) return;
+    if (g->ework) {   // up to kEdgeSetsMaxN vertices, and memory for it
+        launch_edge_sets(g, k, out, st);
+        g->timed_light = g->timed_hub = false;
+        return;
+    }
     Args a;
     a.off = g->off;
     a.adj = g->adj;

@@ -3,8 +3,18 @@
 //
 // Output rows are the vertex pairs {lo < hi} joined in G_U, in ascending (lo, hi) order
 // of original ids (vdmc_edge_list).  The edge index maps every pair's slot in the
-// graph's edge hash to its row, so the per-set kernel finds a pair's row with one probe
-// sequence.  Every root goes through the per-set kernel (count.hip, EdgeSink).
+// graph's edge hash to its row, and every CSR entry to the row of its pair.
+//
+// k_edge_sets counts a root r's sets by its upper entries (r, a), a wave each, as small.hip
+// does for vertices: by arc codes as if the members had only the arcs that the shape implies,
+// and then each set that has another arc is corrected.  The pair (r, a) takes the part of
+// the slot a there, (a, c) that of the child c, (c, e) that of the end vertex of a path; a
+// further pair gets only the corrected sets.  The arcs of r and of a are two bit planes in LDS
+// (2 n bytes a workgroup), so that testing an entry of c's row costs two LDS reads.
+// What bounds it: the memory-side atomics on the pairs (a, c) and (c, e) (2.4e10 a second);
+// the pair (r, a) is summed in LDS.  Power-law graph of 3001 vertices, 20 k pairs, 25 M sets,
+// k = 4: 0.55 ms a call, 16.1 with the per-set kernel (count.hip, EdgeSink), which remains for
+// graphs of more vertices than the bit planes hold (kEdgeSetsMaxN).
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
@@ -66,6 +76,364 @@ __global__ void k_slot_rows(const uint32_t* __restrict__ off, const uint32_t* __
     }
 }
 
+// every CSR entry -> the output row of its pair, every upper entry -> its root; a wave per row
+__global__ __launch_bounds__(ET) void k_entry_rows(gptr<const uint32_t> off, gptr<const uint32_t> split,
+                                                   gptr<const uint32_t> adj, int64_t n, gptr<const uint32_t> uoff,
+                                                   gptr<const unsigned long long> table, uint32_t bits,
+                                                   gptr<const uint32_t> epid, gptr<uint32_t> eid,
+                                                   gptr<uint32_t> root_of) {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (int64_t u = blockIdx.x * (int64_t)(ET / 64) + (threadIdx.x >> 6); u < n; u += (int64_t)gridDim.x * (ET / 64)) {
+        const uint32_t s = split[u];
+        for (uint32_t t = off[u] + lane; t < off[u + 1]; t += 64) {
+            const uint32_t h = edge_find(table, bits, (uint32_t)u, adj[t] >> 2);
+            eid[t] = h != 0xFFFFFFFFu ? epid[h] : 0u;
+            if (t >= s) root_of[uoff[u] + (t - s)] = (uint32_t)u;
+        }
+    }
+}
+
+constexpr uint32_t kRootRow = 12;   // per root: children of its slots by both codes (9), its slots by code (3)
+
+struct EdgeArgs {
+    gptr<const uint32_t> off, adj, split;
+    gptr<const uint32_t> eid;      // CSR entry -> output row
+    gptr<const uint32_t> root_of;  // upper entry -> r
+    gptr<const uint32_t> uoff;     // r -> its first upper entry
+    gptr<uint32_t> kids;           // upper entry (r, a) -> children of a by code
+    gptr<uint32_t> rows;           // r -> kRootRow
+    gptr<const unsigned long long> table;
+    gptr<const uint32_t> epid;
+    uint32_t bits, words, n, pairs;
+    const uint8_t* tab;            // code -> class
+    gptr<unsigned long long> out;
+    gptr<unsigned long long> stats;
+};
+
+__device__ __forceinline__ uint32_t esum8(uint32_t v) {
+    v += (uint32_t)__shfl_xor((int)v, 1, 64);
+    v += (uint32_t)__shfl_xor((int)v, 2, 64);
+    v += (uint32_t)__shfl_xor((int)v, 4, 64);
+    return v;
+}
+
+// children of a by code for every upper entry (r, a), 8 lanes each: entries of a's row above r
+// that are not adjacent to r
+__global__ __launch_bounds__(ET) void k_edge_kids(EdgeArgs A) {
+    const uint32_t gl = threadIdx.x & 7u;
+    const uint32_t step = gridDim.x * (ET / 8);
+    for (uint32_t u0 = blockIdx.x * (ET / 8); u0 < A.pairs; u0 += step) {
+        const uint32_t u = u0 + (threadIdx.x >> 3);
+        const bool on = u < A.pairs;
+        uint32_t h1 = 0, h2 = 0, h3 = 0;
+        if (on) {
+            const uint32_t r = A.root_of[u], a = A.adj[A.split[r] + (u - A.uoff[r])] >> 2, alo = A.off[a];
+            for (uint32_t q = A.off[a + 1]; q > alo; q -= min(8u, q - alo)) {
+                const uint32_t x = q - alo > gl ? A.adj[q - 1u - gl] : 0u, c = x >> 2, k = x & 3u;
+                if (c > r && edge_find(A.table, A.bits, r, c) == 0xFFFFFFFFu) {
+                    h1 += k == 1u;
+                    h2 += k == 2u;
+                    h3 += k == 3u;
+                }
+                if (q - alo > 8u && (A.adj[q - 8u] >> 2) <= r) break;
+            }
+        }
+        h1 = esum8(h1);
+        h2 = esum8(h2);
+        h3 = esum8(h3);
+        if (on && gl < 3u) A.kids[(size_t)3 * u + gl] = gl == 0u ? h1 : (gl == 1u ? h2 : h3);
+    }
+}
+
+// per root, a wave: children of all slots by both codes, slots by code; the visits of the shapes
+// that these fix
+template <bool K4>
+__global__ __launch_bounds__(ET) void k_edge_roots(EdgeArgs A) {
+    const uint32_t lane = threadIdx.x & 63u;
+    unsigned long long v0 = 0, v1 = 0;
+    for (uint32_t r = blockIdx.x * (ET / 64) + (threadIdx.x >> 6); r < A.n; r += gridDim.x * (ET / 64)) {
+        const uint32_t lo = A.split[r], d = A.off[r + 1] - lo, u = A.uoff[r];
+        if (d == 0u) continue;
+        uint32_t t[kRootRow] = {0};
+        for (uint32_t i = lane; i < d; i += 64) {
+            const uint32_t x = A.adj[lo + i] & 3u;
+            for (uint32_t c = 1; c < 4; c++)
+                for (uint32_t k = 0; k < 3; k++) t[(c - 1) * 3 + k] += x == c ? A.kids[(size_t)3 * (u + i) + k] : 0u;
+            for (uint32_t c = 1; c < 4; c++) t[8 + c] += x == c;
+        }
+        uint32_t all = 0;
+        for (uint32_t k = 0; k < kRootRow; k++) {
+            for (int o = 1; o < 64; o <<= 1) t[k] += (uint32_t)__shfl_xor((int)t[k], o, 64);
+            if (k < 9) all += t[k];
+            if (lane == 0) A.rows[(size_t)r * kRootRow + k] = t[k];
+        }
+        const unsigned long long dd = d;
+        v0 += K4 ? (dd * (dd - 1) / 2 * (dd - 2)) / 3 : dd * (dd - 1) / 2;
+        v1 += K4 ? all * (dd - 1) : (unsigned long long)all;
+    }
+    if (lane == 0 && v0) gadd64(&A.stats[K4 ? 2 : 0], v0);
+    if (lane == 0 && v1) gadd64(&A.stats[K4 ? 3 : 1], v1);
+}
+
+__device__ __forceinline__ uint32_t epick(uint32_t k, const uint32_t (&v)[3]) {
+    return k == 1u ? v[0] : (k == 2u ? v[1] : v[2]);
+}
+__device__ __forceinline__ unsigned long long epairs(uint32_t k, uint32_t l, const uint32_t (&v)[3]) {
+    const unsigned long long x = epick(k, v);
+    return k == l ? x * (x - 1u) / 2u : x * epick(l, v);
+}
+__device__ __forceinline__ void epair(uint32_t i, uint32_t& k, uint32_t& l) {
+    k = i < 3u ? 1u : (i < 5u ? 2u : 3u);
+    l = i < 3u ? i + 1u : (i < 5u ? i - 1u : 3u);
+}
+__device__ __forceinline__ uint32_t plane_bits(const uint2* p, uint32_t v) {
+    const uint2 w = p[v >> 5];
+    return ((w.x >> (v & 31u)) & 1u) | (((w.y >> (v & 31u)) & 1u) << 1);
+}
+__device__ __forceinline__ void plane_set(uint2* p, uint32_t ent) {
+    const uint32_t v = ent >> 2, bit = 1u << (v & 31u);
+    if (ent & 1u) atomicOr(&p[v >> 5].x, bit);
+    if (ent & 2u) atomicOr(&p[v >> 5].y, bit);
+}
+__device__ __forceinline__ void edge_fence() {
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A wave per upper entry (r, a), from the roots of the largest degrees on.
+template <bool K4>
+__global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
+    constexpr uint32_t C = K4 ? (uint32_t)kClasses4 : (uint32_t)kClasses3;
+    constexpr uint32_t NWV = ET / 64;
+    constexpr unsigned long long kLess = ~0ull;   // one set less
+    extern __shared__ uint2 dyn[];
+    __shared__ unsigned long long rows[NWV][K4 ? 3 : 1][C];   // classes of (r, a); of a triangle's (r, b), (a, b)
+    __shared__ uint8_t tab[K4 ? 4096 : 64];
+    const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u, gl = tid & 7u;
+    uint2* PR = dyn + wid * 2u * A.words;   // arcs of r to its slots
+    uint2* PA = PR + A.words;               // arcs of a to the vertices above r
+    unsigned long long(&RA)[C] = rows[wid][0];
+    for (uint32_t i = tid; i < (K4 ? 4096u : 64u); i += ET) tab[i] = A.tab[i];
+    __syncthreads();
+    auto add = [&](uint32_t row, uint32_t cls, unsigned long long n) { gadd64(&A.out[(size_t)row * C + cls], n); };
+    auto move = [&](uint32_t row, uint32_t was, uint32_t is) {
+        add(row, was, kLess);
+        add(row, is, 1ull);
+    };
+    auto lmove = [&](unsigned long long* row, uint32_t was, uint32_t is) {
+        atomicAdd(&row[was], kLess);
+        atomicAdd(&row[is], 1ull);
+    };
+    auto row_of = [&](uint32_t x, uint32_t y) { return A.epid[edge_find(A.table, A.bits, x, y)]; };
+    auto idx4 = [&](uint32_t p01, uint32_t p02, uint32_t p03, uint32_t p12, uint32_t p13, uint32_t p23) -> uint32_t {
+        return tab[motif_index4(p01, p02, p03, p12, p13, p23)];
+    };
+    unsigned long long v1 = 0, v2 = 0, v3 = 0;   // (2,1,0) less, (1,2,0), (1,1,1)
+    for (uint32_t u = blockIdx.x * NWV + wid; u < A.pairs; u += gridDim.x * NWV) {
+        const uint32_t r = A.root_of[u], lo = A.split[r], rend = A.off[r + 1], t = lo + (u - A.uoff[r]);
+        const uint32_t ent = A.adj[t], a = ent >> 2, ra = ent & 3u, alo = A.off[a], aend = A.off[a + 1];
+        for (uint32_t i = lane; i < A.words; i += 64) PR[i] = PA[i] = make_uint2(0u, 0u);
+        for (uint32_t i = lane; i < C * (K4 ? 3u : 1u); i += 64) RA[i] = 0ull;
+        edge_fence();
+        for (uint32_t i = lo + lane; i < rend; i += 64) plane_set(PR, A.adj[i]);
+        uint32_t abeg = aend;   // a's first entry above r
+        for (bool more = true; more && abeg > alo;) {
+            const uint32_t x = lane < abeg - alo ? A.adj[abeg - 1u - lane] : 0u;
+            const bool in = (x >> 2) > r;
+            if (in) plane_set(PA, x);
+            const uint32_t cnt = (uint32_t)__popcll(__ballot(in));
+            abeg -= cnt;
+            more = cnt == 64u;
+        }
+        edge_fence();
+        // ---- (r, a): sets by code
+        const gptr<const uint32_t> T = &A.rows[(size_t)r * kRootRow];
+        const uint32_t h[3] = {A.kids[(size_t)3 * u], A.kids[(size_t)3 * u + 1u], A.kids[(size_t)3 * u + 2u]};
+        const uint32_t o[3] = {T[9] - (ra == 1u), T[10] - (ra == 2u), T[11] - (ra == 3u)};
+        if (lane < (K4 ? 30u : 6u)) {
+            unsigned long long n;
+            uint32_t cls, k, l;
+            if (!K4) {
+                k = lane % 3u + 1u;
+                n = lane < 3u ? epick(k, o) : epick(k, h);
+                cls = tab[lane < 3u ? motif_index3(ra, k, 0u) : motif_index3(ra, 0u, k)];
+            } else if (lane < 9u) {    // (2,1,0), a the parent
+                k = lane / 3u + 1u;
+                l = lane % 3u + 1u;
+                n = (unsigned long long)epick(k, h) * epick(l, o);
+                cls = idx4(ra, l, 0u, 0u, k, 0u);
+            } else if (lane < 15u) {   // (3,0,0)
+                epair(lane - 9u, k, l);
+                n = epairs(k, l, o);
+                cls = idx4(ra, k, l, 0u, 0u, 0u);
+            } else if (lane < 21u) {   // (1,2,0)
+                epair(lane - 15u, k, l);
+                n = epairs(k, l, h);
+                cls = idx4(ra, 0u, 0u, k, l, 0u);
+            } else {                   // (2,1,0), a the second slot
+                k = (lane - 21u) / 3u + 1u;
+                l = (lane - 21u) % 3u + 1u;
+                n = T[lane - 21u] - (k == ra ? epick(l, h) : 0u);
+                cls = idx4(k, ra, 0u, 0u, l, 0u);
+            }
+            if (n) atomicAdd(&RA[cls], n);
+        }
+        if (K4 && lane == 0) {
+            const unsigned long long x = (unsigned long long)h[0] + h[1] + h[2];
+            v2 += x * (x - 1u) / 2u;
+        }
+        // ---- a's row above r: children c, 8 lanes each; for k = 3 a lane per entry
+        if (!K4) {
+            for (uint32_t i = abeg + lane; i < aend; i += 64) {
+                const uint32_t x = A.adj[i], c = x >> 2, ac = x & 3u, rc = plane_bits(PR, c);
+                if (!rc) {
+                    add(A.eid[i], tab[motif_index3(ra, 0u, ac)], 1ull);
+                } else if (c > a) {
+                    const uint32_t was = tab[motif_index3(ra, rc, 0u)], is = tab[motif_index3(ra, rc, ac)];
+                    lmove(RA, was, is);
+                    move(row_of(r, c), was, is);
+                    add(A.eid[i], is, 1ull);
+                }
+            }
+        } else {
+            for (uint32_t i0 = abeg; i0 < aend; i0 += 8) {
+                const uint32_t i = i0 + (lane >> 3);
+                const uint32_t x = i < aend ? A.adj[i] : 0u, c = x >> 2, ac = x & 3u;
+                const bool on = i < aend && !plane_bits(PR, c);
+                const uint32_t eac = on ? A.eid[i] : 0u, clo = on ? A.off[c] : 0u;
+                uint32_t e1 = 0, e2 = 0, e3 = 0;   // paths by their last arc
+                for (uint32_t q = on ? A.off[c + 1] : 0u; q > clo; q -= min(8u, q - clo)) {
+                    const bool in = gl < q - clo;
+                    const uint32_t y = in ? A.adj[q - 1u - gl] : 0u, ece = in ? A.eid[q - 1u - gl] : 0u;
+                    const uint32_t e = y >> 2, ce = y & 3u;
+                    if (e > r && e != a) {
+                        const uint32_t re = plane_bits(PR, e), ae = plane_bits(PA, e);
+                        if (re) {          // (2,1,0) with the second slot e: from the lower parent of c
+                            const uint32_t was = idx4(ra, re, 0u, 0u, ac, 0u), ere = row_of(r, e);
+                            atomicAdd(&RA[was], kLess);
+                            add(ere, was, kLess);
+                            add(eac, was, kLess);
+                            if (a < e) {
+                                const uint32_t is = idx4(ra, re, 0u, ae, ac, swap_arc_bits(ce));
+                                atomicAdd(&RA[is], 1ull);
+                                add(ere, is, 1ull);
+                                add(eac, is, 1ull);
+                                add(ece, is, 1ull);
+                                if (ae) add(row_of(a, e), is, 1ull);
+                            } else {
+                                v1--;
+                            }
+                        } else if (ae) {   // (1,2,0) with the other child e
+                            const uint32_t was = idx4(ra, 0u, 0u, ac, ae, 0u), is = idx4(ra, 0u, 0u, ac, ae, ce);
+                            move(eac, was, is);
+                            if (c < e) {
+                                lmove(RA, was, is);
+                                add(ece, is, 1ull);
+                            }
+                        } else {           // path
+                            add(ece, idx4(ra, 0u, 0u, ac, 0u, ce), 1ull);
+                            e1 += ce == 1u;
+                            e2 += ce == 2u;
+                            e3 += ce == 3u;
+                        }
+                    }
+                    if (q - clo > 8u && (A.adj[q - 8u] >> 2) <= r) break;
+                }
+                const uint32_t ne[3] = {esum8(e1), esum8(e2), esum8(e3)};
+                if (!on) continue;
+                // (a, c): 3 classes each of (2,1,0), (1,2,0) and (1,1,1)
+                for (uint32_t j = gl; j < 9u; j += 8u) {
+                    const uint32_t k = j % 3u + 1u;
+                    const uint32_t n = j < 3u ? epick(k, o) : (j < 6u ? epick(k, h) - (k == ac) : epick(k, ne));
+                    const uint32_t cls = j < 3u ? idx4(ra, k, 0u, 0u, ac, 0u)
+                                                : (j < 6u ? idx4(ra, 0u, 0u, ac, k, 0u) : idx4(ra, 0u, 0u, ac, 0u, k));
+                    if (n) {
+                        add(eac, cls, n);
+                        if (j >= 6u) {
+                            atomicAdd(&RA[cls], (unsigned long long)n);
+                            v3 += n;
+                        }
+                    }
+                }
+            }
+            // ---- triangles (r, a, b), a < b: triples of slots from the first of their adjacent pairs,
+            // and children of one of a, b that are not adjacent to the other
+            unsigned long long* RB = rows[wid][K4 ? 1 : 0];
+            unsigned long long* AB = rows[wid][K4 ? 2 : 0];
+            for (uint32_t i0 = abeg; i0 < aend; i0 += 64) {
+                const uint32_t x = i0 + lane < aend ? A.adj[i0 + lane] : 0u;
+                unsigned long long todo = __ballot((x >> 2) > a && plane_bits(PR, x >> 2));
+                for (; todo; todo &= todo - 1ull) {
+                    const int src = __ffsll((long long)todo) - 1;
+                    const uint32_t y = (uint32_t)__shfl((int)x, src, 64), b = y >> 2, ab = y & 3u;
+                    const uint32_t rb = plane_bits(PR, b);
+                    edge_fence();
+                    for (uint32_t j = lo + lane; j < rend; j += 64) {
+                        const uint32_t z = A.adj[j], c = z >> 2, rc = z & 3u;
+                        if (c == a || c == b) continue;
+                        const uint32_t xa = plane_bits(PA, c);
+                        if (xa && c < b) continue;
+                        const uint32_t xb = edge_code(A.table, A.bits, b, c);
+                        if (xb && c < a) continue;
+                        const uint32_t was = idx4(ra, rb, rc, 0u, 0u, 0u), is = idx4(ra, rb, rc, ab, xa, xb);
+                        lmove(RA, was, is);
+                        lmove(RB, was, is);
+                        move(A.eid[j], was, is);
+                        atomicAdd(&AB[is], 1ull);
+                        if (xa) add(row_of(a, c), is, 1ull);
+                        if (xb) add(row_of(b, c), is, 1ull);
+                    }
+                    for (uint32_t j = abeg + lane; j < aend; j += 64) {
+                        const uint32_t z = A.adj[j], c = z >> 2, ac = z & 3u;
+                        if (plane_bits(PR, c) || edge_code(A.table, A.bits, b, c)) continue;
+                        const uint32_t was = idx4(ra, rb, 0u, 0u, ac, 0u), is = idx4(ra, rb, 0u, ab, ac, 0u);
+                        lmove(RA, was, is);
+                        lmove(RB, was, is);
+                        move(A.eid[j], was, is);
+                        atomicAdd(&AB[is], 1ull);
+                    }
+                    const uint32_t blo = A.off[b];
+                    for (uint32_t j = A.off[b + 1]; j > blo; j -= min(64u, j - blo)) {
+                        const uint32_t z = j - blo > lane ? A.adj[j - 1u - lane] : 0u, c = z >> 2, bc = z & 3u;
+                        if (c > r && !plane_bits(PR, c) && !plane_bits(PA, c)) {
+                            const uint32_t was = idx4(rb, ra, 0u, 0u, bc, 0u);
+                            const uint32_t is = idx4(rb, ra, 0u, swap_arc_bits(ab), bc, 0u);
+                            lmove(RA, was, is);
+                            lmove(RB, was, is);
+                            move(A.eid[j - 1u - lane], was, is);
+                            atomicAdd(&AB[is], 1ull);
+                        }
+                        if (j - blo > 64u && (A.adj[j - 64u] >> 2) <= r) break;
+                    }
+                    edge_fence();
+                    const uint32_t erb = row_of(r, b), eab = A.eid[i0 + (uint32_t)src];
+                    for (uint32_t k = lane; k < C; k += 64) {
+                        if (RB[k]) add(erb, k, RB[k]);
+                        if (AB[k]) add(eab, k, AB[k]);
+                        RB[k] = AB[k] = 0ull;
+                    }
+                    edge_fence();
+                }
+            }
+        }
+        edge_fence();
+        const uint32_t era = A.eid[t];
+        for (uint32_t k = lane; k < C; k += 64)
+            if (RA[k]) add(era, k, RA[k]);
+        edge_fence();
+    }
+    if (!K4) return;
+    for (int o = 1; o < 64; o <<= 1) {
+        v1 += __shfl_xor(v1, o, 64);
+        v2 += __shfl_xor(v2, o, 64);
+        v3 += __shfl_xor(v3, o, 64);
+    }
+    if (lane < 3u) {
+        const unsigned long long n = lane == 0u ? v1 : (lane == 1u ? v2 : v3);
+        if (n) gadd64(&A.stats[3u + lane], n);
+    }
+}
+
 }  // namespace
 
 void ensure_edge_index(vdmc_graph_s* g, hipStream_t st) {
@@ -90,9 +458,17 @@ void ensure_edge_index(vdmc_graph_s* g, hipStream_t st) {
     VDMC_HIP(hipMalloc(&epid, ((size_t)1 << g->ehash_bits) * sizeof(uint32_t)));
     VDMC_HIP(hipMalloc(&elo, std::max<int64_t>(P, 1) * sizeof(int32_t)));
     VDMC_HIP(hipMalloc(&ehi, std::max<int64_t>(P, 1) * sizeof(int32_t)));
+    // CSR entry -> row, upper entry -> root, and the scratch of k_edge_sets
+    uint32_t* work = nullptr;
+    const size_t words = (size_t)6 * P + (1 + kRootRow) * (n + 1);
+    if (n <= kEdgeSetsMaxN && hipMalloc(&work, words * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();   // the per-set kernel needs none of it
+        work = nullptr;
+    }
     g->epid = epid;   // owned by the graph from here on
     g->elo = elo;
     g->ehi = ehi;
+    g->ework = work;
     if (n == 0 || P == 0) return;
     uint32_t* cnt = (uint32_t*)alloc((n + 1) * sizeof(uint32_t));
     uint32_t* uoff = (uint32_t*)alloc((n + 1) * sizeof(uint32_t));
@@ -115,8 +491,45 @@ void ensure_edge_index(vdmc_graph_s* g, hipStream_t st) {
     hipLaunchKernelGGL(k_rows, dim3(blocks_of(P)), dim3(ET), 0, st, keys_s, vals_s, P, row_of, elo, ehi);
     hipLaunchKernelGGL(k_slot_rows, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff, row_of,
                        g->ehash, g->ehash_bits, epid);
+    if (work) {
+        VDMC_HIP(hipMemcpyAsync(work + 6 * P, uoff, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+        hipLaunchKernelGGL(k_entry_rows, dim3(blocks_of(n * 64)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff,
+                           g->ehash, g->ehash_bits, epid, work, work + 2 * P);
+    }
     VDMC_HIP(hipGetLastError());
     VDMC_HIP(hipStreamSynchronize(st));
+}
+
+void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {
+    const ClassTables& t = class_tables();
+    const int64_t n = g->n, P = g->pairs;
+    EdgeArgs a;
+    a.off = g->off;
+    a.adj = g->adj;
+    a.split = g->split;
+    a.eid = g->ework;
+    a.root_of = g->ework + 2 * P;
+    a.kids = g->ework + 3 * P;
+    a.uoff = g->ework + 6 * P;
+    a.rows = g->ework + 6 * P + n + 1;
+    a.table = g->ehash;
+    a.epid = g->epid;
+    a.bits = g->ehash_bits;
+    a.words = (uint32_t)((n + 31) / 32);
+    a.n = (uint32_t)n;
+    a.pairs = (uint32_t)P;
+    a.tab = k == 3 ? t.t3 : t.t4;
+    a.out = (unsigned long long*)out;
+    a.stats = g->stats;
+    const size_t lds = (size_t)(ET / 64) * 2 * a.words * sizeof(uint2);
+    const unsigned blocks = (unsigned)std::min<int64_t>((P + ET / 64 - 1) / (ET / 64), 8192);
+    hipLaunchKernelGGL(k_edge_kids, dim3(blocks_of(P * 8)), dim3(ET), 0, st, a);
+    void (*kern)(EdgeArgs) = k == 3 ? k_edge_sets<false> : k_edge_sets<true>;
+    VDMC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (k == 3) hipLaunchKernelGGL((k_edge_roots<false>), dim3(blocks_of(n * 64)), dim3(ET), 0, st, a);
+    else hipLaunchKernelGGL((k_edge_roots<true>), dim3(blocks_of(n * 64)), dim3(ET), 0, st, a);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(ET), lds, st, a);
+    VDMC_HIP(hipGetLastError());
 }
 
 }  // namespace vdmc

@@ -352,12 +352,14 @@ static void free_graph_arrays(vdmc_graph_s* g) {
     (void)hipFree(g->utmp);
     (void)hipFree(g->ehash);
     (void)hipFree(g->epid);
+    (void)hipFree(g->ework);
     (void)hipFree(g->elo);
     (void)hipFree(g->ehi);
     g->utmp = nullptr;
     g->ehash = nullptr;
     g->ehash_bits = 0;
     g->epid = nullptr;
+    g->ework = nullptr;
     g->elo = g->ehi = nullptr;
     (void)hipFree(g->off);
     (void)hipFree(g->adj);

@@ -161,6 +161,7 @@ struct vdmc_graph_s {
     unsigned long long* ehash = nullptr;   // edge hash: every pair of the graph, 2^ehash_bits slots
     uint32_t ehash_bits = 0;
     uint32_t* epid = nullptr;    // per edge-hash slot: output row of the pair (per-edge counts)
+    uint32_t* ework = nullptr;   // CSR entry -> row, scratch of k_edge_sets (up to kEdgeSetsMaxN vertices)
     int32_t* elo = nullptr;      // per output row: the pair's endpoints (original ids, lo < hi)
     int32_t* ehi = nullptr;
     size_t hub_layout[16] = {0};
@@ -357,6 +358,8 @@ void ensure_hub_scratch(vdmc_graph_s* g);                 // caller holds g->mu
 void free_hub_scratch(vdmc_graph_s* g);                   // caller holds g->mu; waits for the graph's work
 void ensure_edge_hash(vdmc_graph_s* g, hipStream_t stream);    // count_hub.hip
 void ensure_edge_index(vdmc_graph_s* g, hipStream_t stream);   // edges.hip
+constexpr int64_t kEdgeSetsMaxN = 65536;   // bit planes of four waves in one workgroup's LDS
+void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // edges.hip
 void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // count.hip
 void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t stream,
                 uint32_t rank_lo = 0, uint32_t rank_hi = 0xFFFFFFFFu, const hipEvent_t* around = nullptr);
