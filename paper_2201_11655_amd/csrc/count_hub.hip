@@ -1216,8 +1216,7 @@ void free_hub_scratch(vdmc_graph_s* g) {
 void free_hub(vdmc_graph_s* g) {
     wait_graph(g);
     free_hub_scratch(g);
-    (void)hipFree(g->hubs);
-    (void)hipFree(g->hub_queue);
+    (void)hipFree(g->hub_queue);   // and hubs
     g->light = g->hubs = nullptr;
     g->hub_queue = nullptr;
     g->hub_scratch_need = 0;
@@ -1253,30 +1252,19 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     if (g->bins_hub_min == hub_min) return;
     free_hub(g);   // waits for running work on the old bins
     const int64_t nr = g->nroots;
-    std::vector<void*> tmp;
-    auto alloc = [&](size_t bytes) {
-        void* p = nullptr;
-        VDMC_HIP(hipMalloc(&p, bytes ? bytes : 16));
-        tmp.push_back(p);
-        return p;
-    };
-    struct Free {
-        std::vector<void*>& v;
-        ~Free() {
-            for (void* p : v) (void)hipFree(p);
-        }
-    } guard{tmp};
+    DeviceTemps tmp((size_t)nr * 40 + (1u << 20));
     // the hub path needs every degree <= DMAX (a slot's children fit the LDS lists) and
     // ranks below 2^26 (per-wave child hash keys)
     const uint32_t hub_ok = (g->max_deg <= (int32_t)DMAX && g->n < ((int64_t)1 << 26)) ? 1u : 0u;
     const uint32_t light_ok = g->max_deg < kLightMaxDegree ? 1u : 0u;
-    unsigned long long* wkey = (unsigned long long*)alloc((nr + 1) * sizeof(unsigned long long));
-    unsigned long long* wkey_s = (unsigned long long*)alloc((nr + 1) * sizeof(unsigned long long));
-    unsigned long long* d_tot = (unsigned long long*)alloc(8 * sizeof(unsigned long long));
+    unsigned long long* wkey = tmp.alloc<unsigned long long>(nr + 1);
+    unsigned long long* wkey_s = tmp.alloc<unsigned long long>(nr + 1);
+    unsigned long long* d_tot = tmp.alloc<unsigned long long>(8);
     unsigned long long tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t nhub = 0;
     std::vector<unsigned long long> hub_keys;   // sorted work keys of the hub roots (~work)
-    VDMC_HIP(hipMalloc(&g->hubs, (nr + 1) * sizeof(uint32_t)));
+    VDMC_HIP(hipMalloc(&g->hub_queue, 64 + (nr + 1) * sizeof(uint32_t)));   // the cursors, then the binned roots
+    g->hubs = (uint32_t*)g->hub_queue + 16;
     if (nr > 0) {
         launch_fill_u64((uint64_t*)d_tot, 8, 0, st);
         const unsigned blocks = (unsigned)std::min<int64_t>((nr + 15) / 16, 16384);
@@ -1287,7 +1275,7 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
         size_t sb = 0;
         int ni = (int)nr;
         VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sb, wkey, wkey_s, g->roots, g->hubs, ni, 0, 64, st));
-        void* t2 = alloc(sb);
+        void* t2 = tmp.alloc<uint8_t>(sb);
         VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(t2, sb, wkey, wkey_s, g->roots, g->hubs, ni, 0, 64, st));
         VDMC_HIP(hipMemcpyAsync(tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost, st));
         VDMC_HIP(hipStreamSynchronize(st));
@@ -1324,7 +1312,6 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     g->max_hi = maxhi;
     // light roots: fewer than hub_min higher neighbours (every root when the hub path is off)
     g->light_max_d = hub_ok ? std::min<int32_t>(maxhi, hub_min - 1) : maxhi;
-    VDMC_HIP(hipMalloc(&g->hub_queue, 64));
     if (nhub > 0) {
         const int wgs = hub_workgroups();
         const size_t s2cap = (size_t)max_s2 + 64;

@@ -154,6 +154,12 @@ __global__ void k_split(const uint32_t* __restrict__ off, const uint32_t* __rest
     }
 }
 
+// one or two words to where the host reads them
+__global__ void k_copy2(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b, uint32_t* __restrict__ to) {
+    to[0] = *a;
+    if (b) to[1] = *b;
+}
+
 __global__ void k_compact_roots(const uint32_t* __restrict__ has_hi, const uint32_t* __restrict__ pos,
                                 int64_t n, uint32_t* __restrict__ roots) {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n;
@@ -161,23 +167,8 @@ __global__ void k_compact_roots(const uint32_t* __restrict__ has_hi, const uint3
         if (has_hi[r]) roots[pos[r]] = (uint32_t)r;
 }
 
-// RAII list of temporaries freed at scope exit
-struct Temps {
-    std::vector<void*> ptrs;
-    template <class T>
-    T* alloc(size_t count) {
-        void* p = nullptr;
-        VDMC_HIP(hipMalloc(&p, count * sizeof(T) + 16));
-        ptrs.push_back(p);
-        return static_cast<T*>(p);
-    }
-    ~Temps() {
-        for (void* p : ptrs) (void)hipFree(p);
-    }
-};
-
 template <class F>
-void* cub_temp(Temps& t, F&& query) {
+void* cub_temp(DeviceTemps& t, F&& query) {
     size_t bytes = 0;
     VDMC_HIP(query(nullptr, bytes));
     return t.alloc<uint8_t>(bytes ? bytes : 1);
@@ -194,7 +185,7 @@ static void build_graph(int64_t n, int64_t m, const int32_t* src, const int32_t*
     VDMC_HIP(hipGetDevice(&g->device));
     g->n = n;
     g->undirected = (flags & VDMC_UNDIRECTED) != 0;
-    Temps t;
+    DeviceTemps t((size_t)m * 96 + (size_t)n * 64 + (2u << 20));
     const int32_t* d_src = src;
     const int32_t* d_dst = dst;
     if (!(flags & VDMC_INPUT_ON_DEVICE) && m > 0) {
@@ -206,18 +197,28 @@ static void build_graph(int64_t n, int64_t m, const int32_t* src, const int32_t*
         d_dst = d;
     }
     // graph arrays that always exist
-    VDMC_HIP(hipMalloc(&g->off, (n + 1) * sizeof(uint32_t)));
-    VDMC_HIP(hipMalloc(&g->split, (n > 0 ? n : 1) * sizeof(uint32_t)));
-    VDMC_HIP(hipMalloc(&g->perm, (n > 0 ? n : 1) * sizeof(int32_t)));
-    VDMC_HIP(hipMalloc(&g->stats, kStatSlots * sizeof(unsigned long long)));
+    const size_t col = ((size_t)(n + 1) * sizeof(uint32_t) + 255) & ~(size_t)255;
+    VDMC_HIP(hipMalloc(&g->base, 4 * col + kStatSlots * sizeof(unsigned long long)));
+    g->off = (uint32_t*)g->base;
+    g->split = (uint32_t*)((char*)g->base + col);
+    g->perm = (int32_t*)((char*)g->base + 2 * col);
+    g->roots = (uint32_t*)((char*)g->base + 3 * col);
+    g->stats = (unsigned long long*)((char*)g->base + 4 * col);
     VDMC_HIP(hipMemsetAsync(g->stats, 0, kStatSlots * sizeof(unsigned long long), st));
 
-    int* d_bad = t.alloc<int>(1);
-    unsigned long long* d_arcs = t.alloc<unsigned long long>(1);
-    unsigned* d_maxdeg = t.alloc<unsigned>(1);
-    VDMC_HIP(hipMemsetAsync(d_bad, 0, sizeof(int), st));
-    VDMC_HIP(hipMemsetAsync(d_arcs, 0, sizeof(unsigned long long), st));
-    VDMC_HIP(hipMemsetAsync(d_maxdeg, 0, sizeof(unsigned), st));
+    // what the host has to know, read in one copy at each of the two points where it does
+    struct Found {
+        unsigned long long arcs;
+        unsigned maxdeg;
+        int bad;
+        uint32_t pairs[2];   // the last pair's position, and whether it is one
+        uint32_t roots;
+    } found = {};
+    Found* d_found = t.alloc<Found>(1);
+    VDMC_HIP(hipMemsetAsync(d_found, 0, sizeof(Found), st));
+    int* d_bad = &d_found->bad;
+    unsigned long long* d_arcs = &d_found->arcs;
+    unsigned* d_maxdeg = &d_found->maxdeg;
 
     // ---- 1. merge arcs into undirected pairs with arc bits
     int64_t np = 0;
@@ -246,14 +247,11 @@ static void build_graph(int64_t n, int64_t m, const int32_t* src, const int32_t*
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, sb, head, hpos, mi, st));
         void* stmp = t.alloc<uint8_t>(sb ? sb : 1);
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(stmp, sb, head, hpos, mi, st));
-        uint32_t last[2] = {0, 0};
-        VDMC_HIP(hipMemcpyAsync(&last[0], hpos + (m - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        VDMC_HIP(hipMemcpyAsync(&last[1], head + (m - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        int bad = 0;
-        VDMC_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, st));
+        hipLaunchKernelGGL(k_copy2, dim3(1), dim3(1), 0, st, hpos + (m - 1), head + (m - 1), d_found->pairs);
+        VDMC_HIP(hipMemcpyAsync(&found, d_found, sizeof(Found), hipMemcpyDeviceToHost, st));
         VDMC_HIP(hipStreamSynchronize(st));
-        VDMC_REQUIRE(!bad, VDMC_ERR_INVALID_ARG, "arc endpoint outside [0, n)");
-        np = (int64_t)last[0] + last[1];
+        VDMC_REQUIRE(!found.bad, VDMC_ERR_INVALID_ARG, "arc endpoint outside [0, n)");
+        np = (int64_t)found.pairs[0] + found.pairs[1];
         pkey = t.alloc<uint64_t>(np > 0 ? np : 1);
         pcode = t.alloc<uint32_t>(np > 0 ? np : 1);
         hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(np)), dim3(kThreads), 0, st, pcode, np, 0u);
@@ -326,24 +324,15 @@ static void build_graph(int64_t n, int64_t m, const int32_t* src, const int32_t*
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, sb, has_hi, pos, ni, st));
         void* stmp = t.alloc<uint8_t>(sb ? sb : 1);
         VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(stmp, sb, has_hi, pos, ni, st));
-        uint32_t nr = 0;
-        VDMC_HIP(hipMemcpyAsync(&nr, pos + n, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        VDMC_HIP(hipStreamSynchronize(st));
-        g->nroots = nr;
-        VDMC_HIP(hipMalloc(&g->roots, (nr > 0 ? nr : 1) * sizeof(uint32_t)));
-        if (nr > 0)
-            hipLaunchKernelGGL(k_compact_roots, dim3(blocks_for(n)), dim3(kThreads), 0, st, has_hi, pos, n, g->roots);
+        hipLaunchKernelGGL(k_compact_roots, dim3(blocks_for(n)), dim3(kThreads), 0, st, has_hi, pos, n, g->roots);
+        hipLaunchKernelGGL(k_copy2, dim3(1), dim3(1), 0, st, pos + n, nullptr, &d_found->roots);
         VDMC_HIP(hipGetLastError());
-    } else {
-        VDMC_HIP(hipMalloc(&g->roots, sizeof(uint32_t)));
     }
-    unsigned long long arcs = 0;
-    unsigned maxdeg = 0;
-    VDMC_HIP(hipMemcpyAsync(&arcs, d_arcs, sizeof(arcs), hipMemcpyDeviceToHost, st));
-    VDMC_HIP(hipMemcpyAsync(&maxdeg, d_maxdeg, sizeof(maxdeg), hipMemcpyDeviceToHost, st));
+    VDMC_HIP(hipMemcpyAsync(&found, d_found, sizeof(Found), hipMemcpyDeviceToHost, st));
     VDMC_HIP(hipStreamSynchronize(st));
-    g->arcs = (int64_t)arcs;
-    g->max_deg = (int32_t)maxdeg;
+    g->nroots = found.roots;
+    g->arcs = (int64_t)found.arcs;
+    g->max_deg = (int32_t)found.maxdeg;
 }
 
 static void free_graph_arrays(vdmc_graph_s* g) {
@@ -361,12 +350,9 @@ static void free_graph_arrays(vdmc_graph_s* g) {
     g->epid = nullptr;
     g->ework = nullptr;
     g->elo = g->ehi = nullptr;
-    (void)hipFree(g->off);
+    (void)hipFree(g->base);   // off, split, perm, roots, stats
     (void)hipFree(g->adj);
-    (void)hipFree(g->split);
-    (void)hipFree(g->perm);
-    (void)hipFree(g->roots);
-    (void)hipFree(g->stats);
+    g->base = nullptr;
     for (auto& e : g->ev)
         if (e) {
             (void)hipEventDestroy(e);

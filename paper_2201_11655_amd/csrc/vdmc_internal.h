@@ -117,6 +117,38 @@ const ClassTable5& class_table5();   // for the current device
 
 // ----------------------------------------------------------------------------- graph
 
+// Temporary device memory for the length of a scope.  Pieces of a first block of `first` bytes (at
+// most 64 MiB), then blocks of their own: an allocation and its release cost 10 to 20 us each, which is
+// most of the time of building a small graph.
+struct DeviceTemps {
+    std::vector<void*> blocks;
+    char* at = nullptr;
+    size_t left = 0, first;
+    explicit DeviceTemps(size_t bytes) : first(std::min<size_t>(bytes, (size_t)64 << 20)) {}
+    DeviceTemps(const DeviceTemps&) = delete;
+    DeviceTemps& operator=(const DeviceTemps&) = delete;
+    template <class T>
+    T* alloc(size_t count) {
+        const size_t bytes = (count * sizeof(T) + 16 + 255) & ~(size_t)255;
+        if (bytes > left) {
+            const bool shared = blocks.empty() && bytes <= first;
+            void* p = nullptr;
+            VDMC_HIP(hipMalloc(&p, shared ? first : bytes));
+            blocks.push_back(p);
+            if (!shared) return static_cast<T*>(p);
+            at = (char*)p;
+            left = first;
+        }
+        T* p = (T*)at;
+        at += bytes;
+        left -= bytes;
+        return p;
+    }
+    ~DeviceTemps() {
+        for (void* p : blocks) (void)hipFree(p);
+    }
+};
+
 struct DeviceScratch {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -133,6 +165,7 @@ struct vdmc_graph_s {
     int32_t max_deg = 0;
     bool undirected = false;     // built with VDMC_UNDIRECTED: every pair has both arc bits
     uint64_t* utmp = nullptr;    // directed-class scratch of the undirected counts (n x 199)
+    void* base = nullptr;        // one allocation: off, split, perm, roots, stats
     uint32_t* off = nullptr;     // n + 1 row offsets (rank space)
     uint32_t* adj = nullptr;     // 2 * pairs entries: (nbr_rank << 2) | arc bits
     uint32_t* split = nullptr;   // n: index of the first entry with nbr_rank > row
