@@ -875,13 +875,21 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                     }
                 }
                 __threadfence_block();
+                // The loads of the next children are issued before this one's atomics: entry, then
+                // vertex and parents, row, first 16 entries of it, each where the one before has
+                // arrived (vector memory operations finish in order, so a load after an atomic
+                // waits for it)
+                const auto entry = [&](uint32_t i) { return i < m ? locnbr[end - 1u - i] : 0u; };
+                uint32_t ent = entry(lane >> 4), ent1 = entry(4u + (lane >> 4));
+                uint32_t c = cids[ent >> 2], f0 = poff[ent >> 2], f1 = poff[(ent >> 2) + 1u];
+                uint32_t q0 = A.off[c] + gl, q1 = (lane >> 4) < m ? A.off[c + 1] : 0u;
+                uint32_t x0 = q0 < q1 ? A.adj[q0] : 0u;
                 for (uint32_t i0 = 0; i0 < m; i0 += 4u) {
                     const uint32_t i = i0 + (lane >> 4);
                     const bool on = i < m;
-                    const uint32_t ent = on ? locnbr[end - 1u - i] : 0u, j = ent >> 2, ac = ent & 3u;
-                    const uint32_t c = cids[j];
-                    const uint32_t q1 = on ? A.off[c + 1] : 0u;
-                    const uint32_t f0 = poff[j], na = poff[j + 1] - f0;
+                    const uint32_t j = ent >> 2, ac = ent & 3u, na = f1 - f0;
+                    const uint32_t cn = cids[ent1 >> 2], f0n = poff[ent1 >> 2], f1n = poff[(ent1 >> 2) + 1u];
+                    const uint32_t ent2 = entry(i + 8u);
                     if (on && na > 1u)   // the other parents of c by codes, those above a in the high half
                         for (uint32_t f = gl; f < na; f += 16u) {
                             const uint32_t pe = parents[f0 + f], x = pe >> 2;
@@ -890,9 +898,10 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                             atomicAdd(&GC[57u + (((L.P[x] & 3u) - 1u) * 3u + (pe & 3u) - 1u) * 4u + ax],
                                       x > a ? 0x10001u : 1u);
                         }
+                    const uint32_t q0n = A.off[cn] + gl, q1n = i + 4u < m ? A.off[cn + 1] : 0u;
                     uint32_t e12 = 0, e3 = 0;   // e's outside N(r) by arc code (1 | 2 << 16, 3)
-                    for (uint32_t q = (on ? A.off[c] : 0u) + gl; q < q1; q += 16u) {
-                        const uint32_t ee = A.adj[q], e = ee >> 2, ce = ee & 3u;
+                    for (uint32_t q = q0; q < q1; q += 16u) {
+                        const uint32_t ee = q == q0 ? x0 : A.adj[q], e = ee >> 2, ce = ee & 3u;
                         if (e <= r || slot_find(H2, L.P, e) >= 0) continue;
                         if (ce == 3u) e3++;
                         else e12 += ce == 1u ? 1u : 1u << 16;
@@ -916,6 +925,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         }
                         if (ae) atomicAdd(&GC[48u + (ae - 1u) * 3u + ce - 1u], j2 > j ? 0x10001u : 1u);
                     }
+                    const uint32_t x0n = q0n < q1n ? A.adj[q0n] : 0u;
                     e12 = row16_sum(e12);
                     e3 = row16_sum(e3);
                     __threadfence_block();
@@ -998,6 +1008,14 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                     }
                     for (uint32_t q = 48u + gl; q < 93u; q += 16u) GC[q] = 0u;
                     __threadfence_block();
+                    ent = ent1;
+                    ent1 = ent2;
+                    c = cn;
+                    f0 = f0n;
+                    f1 = f1n;
+                    q0 = q0n;
+                    q1 = q1n;
+                    x0 = x0n;
                 }
                 if (coded) {
                     for (uint32_t i = lane; i < m; i += 64) {
