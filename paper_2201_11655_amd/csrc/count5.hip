@@ -596,11 +596,6 @@ __device__ __forceinline__ uint32_t sig_bits(uint32_t t, uint32_t sig) {
     return pair_bits(0, t, sig & 3u) | pair_bits(1, t, (sig >> 2) & 3u) | pair_bits(2, t, sig >> 4);
 }
 
-__device__ __forceinline__ void wave_fence() {
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Every set whose first three members are r, a and y2 = the vertex of entry q (of r's row:
 // y2 shares a's layer; of a's row: y2 opens the next), by one wave.
 __device__ __forceinline__ void five_triple(const SetsGraph& G, const SetsSink& K, SetsWave& S,

@@ -53,9 +53,8 @@ template <int BS>
 __device__ __forceinline__ void group_sync() {
     if (BS > 64) {
         __syncthreads();
-    } else {   // one wave: its LDS operations complete in order
-        __threadfence_block();
-        __builtin_amdgcn_wave_barrier();
+    } else {
+        wave_fence();
     }
 }
 

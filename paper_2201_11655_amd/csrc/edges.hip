@@ -195,11 +195,6 @@ __device__ __forceinline__ void plane_set(uint2* p, uint32_t ent) {
     if (ent & 1u) atomicOr(&p[v >> 5].x, bit);
     if (ent & 2u) atomicOr(&p[v >> 5].y, bit);
 }
-__device__ __forceinline__ void edge_fence() {
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
-}
-
 // A wave per upper entry (r, a), from the roots of the largest degrees on.
 template <bool K4>
 __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
@@ -234,7 +229,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
         const uint32_t ent = A.adj[t], a = ent >> 2, ra = ent & 3u, alo = A.off[a], aend = A.off[a + 1];
         for (uint32_t i = lane; i < A.words; i += 64) PR[i] = PA[i] = make_uint2(0u, 0u);
         for (uint32_t i = lane; i < C * (K4 ? 3u : 1u); i += 64) RA[i] = 0ull;
-        edge_fence();
+        wave_fence();
         for (uint32_t i = lo + lane; i < rend; i += 64) plane_set(PR, A.adj[i]);
         uint32_t abeg = aend;   // a's first entry above r
         for (bool more = true; more && abeg > alo;) {
@@ -245,7 +240,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
             abeg -= cnt;
             more = cnt == 64u;
         }
-        edge_fence();
+        wave_fence();
         // ---- (r, a): sets by code
         const gptr<const uint32_t> T = &A.rows[(size_t)r * kRootRow];
         const uint32_t h[3] = {A.kids[(size_t)3 * u], A.kids[(size_t)3 * u + 1u], A.kids[(size_t)3 * u + 2u]};
@@ -367,7 +362,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
                     const int src = __ffsll((long long)todo) - 1;
                     const uint32_t y = (uint32_t)__shfl((int)x, src, 64), b = y >> 2, ab = y & 3u;
                     const uint32_t rb = plane_bits(PR, b);
-                    edge_fence();
+                    wave_fence();
                     for (uint32_t j = lo + lane; j < rend; j += 64) {
                         const uint32_t z = A.adj[j], c = z >> 2, rc = z & 3u;
                         if (c == a || c == b) continue;
@@ -405,22 +400,22 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
                         }
                         if (j - blo > 64u && (A.adj[j - 64u] >> 2) <= r) break;
                     }
-                    edge_fence();
+                    wave_fence();
                     const uint32_t erb = row_of(r, b), eab = A.eid[i0 + (uint32_t)src];
                     for (uint32_t k = lane; k < C; k += 64) {
                         if (RB[k]) add(erb, k, RB[k]);
                         if (AB[k]) add(eab, k, AB[k]);
                         RB[k] = AB[k] = 0ull;
                     }
-                    edge_fence();
+                    wave_fence();
                 }
             }
         }
-        edge_fence();
+        wave_fence();
         const uint32_t era = A.eid[t];
         for (uint32_t k = lane; k < C; k += 64)
             if (RA[k]) add(era, k, RA[k]);
-        edge_fence();
+        wave_fence();
     }
     if (!K4) return;
     for (int o = 1; o < 64; o <<= 1) {

@@ -44,6 +44,13 @@ __device__ __forceinline__ uint32_t arc_bits(P off, P adj, uint32_t u, uint32_t 
     return from_u ? (e & 3u) : swap_arc_bits(e & 3u);
 }
 
+// Orders a wave's LDS operations before and after it for the compiler.  A wave's LDS operations
+// complete in order, so that its lanes see each other's without a wait.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Edge hash: one 64-bit slot per vertex pair {lo < hi} of the graph, holding
 // (lo << 32) | (hi << 2) | arc bits seen from lo; 0 = empty; linear probing.
 __device__ __forceinline__ uint32_t edge_slot(unsigned long long key, uint32_t bits) {
