@@ -1092,14 +1092,18 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                     __threadfence_block();
                     // EB vertices a group, then their credits: vector memory operations finish in
                     // order, so a load after an atomic waits for the atomic
+                    // (and the first loads of the next vertex come before this one's parents)
+                    const uint32_t eg = e0 + (b0 << 5);
+                    const auto end_at = [&](uint32_t i) { return eg + (i < total ? LST[i] : 0u); };
+                    uint32_t q0 = A.off[end_at(lane >> 4)] + gl;
+                    uint32_t q1 = (lane >> 4) < total ? A.off[end_at(lane >> 4) + 1u] : 0u;
+                    uint32_t x0 = q0 < q1 ? A.adj[q0] : 0u;
                     for (uint32_t i0 = 0; i0 < total; i0 += 4u * EB) {
                         for (uint32_t eb = 0; eb < EB; eb++) {
-                            const uint32_t i = i0 + eb * 4u + (lane >> 4);
-                            const bool on = i < total;
-                            const uint32_t e = e0 + (b0 << 5) + (on ? LST[i] : 0u);
-                            const uint32_t q1 = on ? A.off[e + 1] : 0u;
-                            for (uint32_t q = (on ? A.off[e] : 0u) + gl; q < q1; q += 16u) {
-                                const uint32_t ee = A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
+                            const uint32_t in = i0 + (eb + 1u) * 4u + (lane >> 4), en = end_at(in);
+                            const uint32_t q0n = A.off[en] + gl, q1n = in < total ? A.off[en + 1u] : 0u;
+                            for (uint32_t q = q0; q < q1; q += 16u) {
+                                const uint32_t ee = q == q0 ? x0 : A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
                                 if (c <= r || (G > 1u && c % G != share)) continue;
                                 const uint32_t j = X2.find(c);
                                 if (j == ~0u) continue;
@@ -1111,6 +1115,9 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                                     atomicAdd(&GC[eb * 16u + KS[s * 3u + ce]], n);
                                 }
                             }
+                            q0 = q0n;
+                            q1 = q1n;
+                            x0 = q0 < q1 ? A.adj[q0] : 0u;
                         }
                         __threadfence_block();
 #pragma unroll
