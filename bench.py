@@ -14,7 +14,7 @@ motifs), ``serve`` (the serving workload alone at its full pool).  There, one st
 device graph build + one count call.
 
 Every count is checked: column sums are multiples of k and equal k x the number of sets
-the kernels visited one by one (the per-shape visit counters); batched = per-graph,
+the kernels counted per shape (added up apart from the credits); batched = per-graph,
 served = alone.  Bit-exact parity with the oracle is the test suite's job.
 
 Prints ONE JSON line.  ``--gpus N`` with N > 1 exits with a message: this build runs on
@@ -51,8 +51,8 @@ WORKLOADS = {
     "chunglu_u": "the Chung-Lu graph with arc directions ignored; undirected 4-vertex motifs (6 classes)",
     "serve": "serving: pool of resident ER and Chung-Lu graphs (even/odd), n log-uniform, mean out-degree "
              "U[2,10], k in {3,4} 50/50, Poisson arrivals at 0.5x and 0.8x the measured capacity",
-    "chunglu5000_k5": "5-vertex motifs of one Chung-Lu graph too large for LDS (n = 5000, the chunglu recipe "
-                      "scaled down: ~50k arcs, max degree 141), counted in device memory",
+    "chunglu5000_k5": "5-vertex motifs of one Chung-Lu graph (n = 5000, the chunglu recipe "
+                      "scaled down: ~50k arcs, max degree 141)",
     "batch256_k5": "5-vertex motifs (9364 classes): the first 256 graphs of the batch4096 recipe (directed "
                    "G(n,p), n ~ U{20..500}, mean out-degree ~ U[2,8], graph i seeded (3,i)); one batched "
                    "launch (graphs cut into parts by estimated work) vs 256 per-graph launches",
@@ -83,8 +83,9 @@ _CS = "paper_2201_11655_amd/csrc/"
 COUNTER_SOURCES = {
     "batch4096": [_CS + "small.hip", _CS + "count.hip", _CS + "batch.hip", _CS + "motif_device.h",
                   _CS + "vdmc_internal.h"],
-    "chunglu": [_CS + "count.hip", _CS + "count_hub.hip", _CS + "motif_device.h", _CS + "vdmc_internal.h"],
-    "batch256_k5": [_CS + "count5.hip", _CS + "vdmc_internal.h"],
+    "chunglu": [_CS + "count.hip", _CS + "count_light.hip", _CS + "count_hub.hip", _CS + "motif_device.h",
+                _CS + "vdmc_internal.h"],
+    "batch256_k5": [_CS + "count5.hip", _CS + "motif_device.h", _CS + "vdmc_internal.h"],
     "chunglu5000_k5": [_CS + "count5.hip", _CS + "motif_device.h", _CS + "vdmc_internal.h"],
 }
 COUNTER_SOURCES["rmat22"] = COUNTER_SOURCES["chunglu"]
@@ -250,7 +251,7 @@ def bench_batch(args, torch, gg, v):
         assert (col % 4 == 0).all(), "column sums must be multiples of 4"
         T4 = int(col.sum()) // 4
         visited = sum(visited_sets(v, G, 4) for G in Gs)
-        assert visited == T4, f"sets visited one by one ({visited}) != sets counted ({T4})"
+        assert visited == T4, f"sets per shape ({visited}) != sets counted ({T4})"
         ref = [o.clone() for o in outs]
         if args.no_per_graph:
             return _batch_result(args, graphs, Gs, T4, visited, ms_batch, dev_ms, choice, None, None, None), graphs
@@ -335,7 +336,7 @@ def bench_batch5(args, torch, gg, v):
             for key, val in v.shape_counts5(G).items():
                 shapes[key] = shapes.get(key, 0) + val
         visited = sum(shapes.values())
-        assert visited == T5, f"sets visited one by one ({visited}) != sets counted ({T5})"
+        assert visited == T5, f"sets per shape ({visited}) != sets counted ({T5})"
         per_graph, same = None, None
         if not args.no_per_graph:
             ref = [o.clone() for o in outs]
@@ -363,7 +364,7 @@ def bench_batch5(args, torch, gg, v):
                    "sets_visited": visited, "shapes_visited": shapes},
         "batched": {"sets_per_s": T5 / (ms_batch * 1e-3), "ms": ms_batch, "device_ms": dev_ms},
         "per_graph": per_graph, "batched_equals_per_graph": same,
-        "roofline": roofline("batch256_k5", T5, dev_ms, "k_five (layered search) + k_five_prep + k_five_reduce",
+        "roofline": roofline("batch256_k5", T5, dev_ms, "k_five_sets (layered search) + k_five_zero",
                              out_bytes + csr_bytes, ops_per_set=MODEL_OPS_PER_SET5),
     }
     return result, graphs
@@ -394,7 +395,7 @@ def bench_graph5(args, torch, gg, v):
     assert (col % 5 == 0).all()
     T5 = int(col.sum()) // 5
     shapes = v.shape_counts5(G)
-    assert sum(shapes.values()) == T5, "sets visited one by one != sets counted"
+    assert sum(shapes.values()) == T5, "sets per shape != sets counted"
     log(f"[bench] {args.steps} steps: {ms:.1f} ms/step, T5={T5}")
     result = {
         "metric": "connected 5-vertex subgraphs counted/s (bit-exact)", "value": T5 / (ms * 1e-3),
@@ -402,7 +403,7 @@ def bench_graph5(args, torch, gg, v):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "u64", "data": "synthetic",
         "config": {"workload": WORKLOADS["chunglu5000_k5"], "n": g.n, "arcs": G.arcs, "pairs": G.pairs,
                    "max_degree": G.max_deg, "sets5": T5, "shapes_visited": shapes},
-        "roofline": roofline("chunglu5000_k5", T5, dev_ms, "k_five_global (layered search in device memory)",
+        "roofline": roofline("chunglu5000_k5", T5, dev_ms, "k_five_sets (layered search) + k_five_zero",
                              4.0 * (g.n + 1) + 8.0 * G.pairs + 8.0 * g.n * v.num_classes(5),
                              ops_per_set=MODEL_OPS_PER_SET5),
     }
@@ -553,13 +554,13 @@ def bench_graph(args, torch, gg, v):
     assert (c4 % 4 == 0).all()
     T4 = int(c4.sum()) // 4
     if not undirected:
-        assert visited_sets(v, G, 4) == T4, "k=4 sets visited one by one != sets counted"
+        assert visited_sets(v, G, 4) == T4, "k=4 sets per shape != sets counted"
     T3 = 0
     if not only4:
         c3 = out3.sum(dim=0).cpu().numpy().view(np.uint64)
         assert (c3 % 3 == 0).all()
         T3 = int(c3.sum()) // 3
-        assert visited_sets(v, G, 3) == T3, "k=3 sets visited one by one != sets counted"
+        assert visited_sets(v, G, 3) == T3, "k=3 sets per shape != sets counted"
     # kernel times (HIP events the library records on the stream): one record per timed step,
     # or one per root range of each step for the ranged count
     timed = kt_steps[-(len(kt_steps) * args.steps // (args.steps + (args.warmup if only4 else 0))):]
@@ -580,7 +581,7 @@ def bench_graph(args, torch, gg, v):
     }
     if hub:
         result["roofline"] = roofline(args.workload, T4 + T3, hub + (light or 0.0),
-                                      "hub path (k_hub + k_long_slots) + per-root kernel",
+                                      "hub path (k_hub + k_expand) + light-root and per-set kernels",
                                       csr_bytes + 8.0 * g.n * (13 + 199))
     if not args.no_cpu_baseline:
         log("[bench] cpu baseline ...")

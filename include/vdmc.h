@@ -156,8 +156,10 @@ vdmc_status vdmc_count_undirected(vdmc_graph g, int32_t k, uint64_t* out, void* 
  *   vdmc_count_edges: out is a DEVICE buffer of pairs * vdmc_num_classes(k) uint64,
  *     written, not accumulated.  Asynchronous on `stream`, except that the first call on
  *     a graph builds the edge index (an edge hash of 2^ceil(log2(4 pairs)) 8-byte slots
- *     plus a 4-byte row per slot, kept with the graph) and synchronises `stream`.  Every
- *     root goes through the per-set kernel, which credits the joined pairs of each set.
+ *     plus a 4-byte row per slot; up to 65536 vertices also 24 bytes per pair and 52 per
+ *     vertex, if there is memory for them; kept with the graph) and synchronises
+ *     `stream`.  Graphs with the latter count sets in groups, a wave per pair; others
+ *     go through the per-set kernel, which credits the joined pairs of each set.
  */
 vdmc_status vdmc_edge_list(vdmc_graph g, int32_t* lo, int32_t* hi);
 vdmc_status vdmc_count_edges(vdmc_graph g, int32_t k, uint64_t* out, void* stream);
@@ -169,30 +171,27 @@ vdmc_status vdmc_free_graph(vdmc_graph g);
 /*
  * Per-vertex k-motif counts (Sec. 4.2): out is a caller-owned DEVICE buffer of
  * n * vdmc_num_classes(k) uint64, fully overwritten (zeroed first, inside the call).
- * Every connected k-set is visited exactly once, from its lowest-rank vertex (Lemma 1)
- * along the BFS shapes of Lemma 2 under the rules of Lemmas 3-4: one lane assembles
- * its index (Sec. 4.1), looks up its class and credits the class to its k vertices
- * (vdmc_shape_counts reports the sets visited per shape).
- * k in {3, 4, 5}, other k INVALID_ARG.  k = 5 (n x 9364 output; n < 229,338): a graph
- * held whole in one workgroup's LDS -- n <= 512 and 4 (4n + 2 + 2 pairs + n ceil(n/32))
- * bytes of CSR, id map and 1-bit adjacency matrix within 159744 -- is counted there;
- * any other is counted in device memory, which at its first 5-vertex count builds the
- * graph's edge hash (2^ceil(log2(4 pairs)) 8-byte slots), an (n + 2) x 8-byte item
- * table and, for n <= 16384, a 1-bit adjacency matrix (n x ceil(n/32) x 4 bytes, at
- * most 32 MiB), kept with the graph and synchronising `stream` once.  Its sets are visited
- * along the eight BFS layer shapes of five vertices (vdmc_profile_counters).  An LDS
- * count of a graph with at least 64 pairs splits it into up to 64 parts whose extra
- * private n x 9364 blocks (at most 512 MiB) and item cursors are taken from the
- * device's default stream-ordered pool (hipMallocAsync on `stream`) and returned to it
- * after the launches; the library raises that pool's release threshold to 8.25 GiB so
- * that repeated counts reuse the pages (other users of the default pool keep that
- * much too).  A graph
+ * Every connected k-set is counted exactly once, from its lowest-rank vertex (Lemma 1)
+ * along the BFS shapes of Lemma 2 under the rules of Lemmas 3-4, and its class (Sec. 4.1)
+ * credited to its k vertices.  Sets that share all but one member and whose last members
+ * have the same arc codes to the others share an index and are counted together
+ * (vdmc_shape_counts reports the sets per shape).
+ * k in {3, 4, 5}, other k INVALID_ARG.  k = 5 (n x 9364 output; n < 229,338): along the
+ * eight BFS layer shapes of five vertices (vdmc_profile_counters).  Graphs of at most
+ * 16384 vertices and 2^24 pairs count sets in groups; their first 5-vertex count builds an
+ * item table of 8 (pairs + 2) bytes.  Larger ones go set by set, and their first 5-vertex
+ * count builds the graph's edge hash (2^ceil(log2(4 pairs)) 8-byte slots) and an
+ * (n + 2) x 8-byte item table, synchronising `stream` once.  Both are kept with the
+ * graph.  The first 5-vertex count on a device builds 4 MiB of class tables.  A graph
  * with n < k gives an all-zero matrix.  Asynchronous on `stream`; `out` must not be in use by
  * another call.  The first count on a graph (and the first after a change of its hub
  * threshold) bins its roots and synchronises `stream`; the hub path's scratch is
  * allocated then and kept with the graph.  Roots with at most 2048 higher neighbours
  * in graphs whose largest degree is at most 2048 (and n < 2^26) can take the hub
- * path; every other root is counted by the per-root kernel.
+ * path; of the others, those with at most 32 higher neighbours and 3072 entries in
+ * their rows above the root (and degrees below 2^20) take the light-root kernel, the
+ * rest the per-set kernel.  Roots below the hub threshold that the light-root kernel
+ * does not hold take the hub path where the graph allows it.
  */
 vdmc_status vdmc_count(vdmc_graph g, int32_t k, uint64_t* out, void* stream);
 
@@ -212,8 +211,8 @@ vdmc_status vdmc_count_range(vdmc_graph g, int32_t k, uint64_t* out, int64_t ran
                              uint32_t flags, void* stream);
 
 /* Hub threshold of a graph: roots with at least min_higher higher-rank neighbours
- * (|N+(r)|, the depth-1 candidates of Lemma 2) are counted by the hub path, the others by
- * the per-root kernel; both enumerate the same sets (Lemma 1 makes roots independent),
+ * (|N+(r)|, the depth-1 candidates of Lemma 2) are counted by the hub path, the others as
+ * vdmc_count says; all count the same sets (Lemma 1 makes roots independent),
  * so the counts do not depend on the threshold.  The default is 32.  A change takes
  * effect at the next count; the root bins and any cached batched launch of the graph
  * are rebuilt.  min_higher in [1, 2^30] (1: every root with work takes the hub path),
@@ -224,23 +223,23 @@ vdmc_status vdmc_set_hub_threshold(vdmc_graph g, int32_t min_higher);
  * each root's neighbourhood feeds both. */
 vdmc_status vdmc_count34(vdmc_graph g, uint64_t* out3, uint64_t* out4, void* stream);
 
-/* Sets visited one by one by the last count on this graph (host; waits for it), per BFS
- * shape in the order k=3: (1,1), (1,2); k=4: (3,0,0), (2,1,0), (1,2,0), (1,1,1).  Every
- * visit is one set whose index was assembled, class looked up and vertices credited, so
- * the k=4 entries add up to the number of 4-sets.  shape_counts: 6 entries. */
+/* Sets counted by the last count on this graph (host; waits for it), per BFS shape in the
+ * order k=3: (1,1), (1,2); k=4: (3,0,0), (2,1,0), (1,2,0), (1,1,1).  The kernels add them
+ * up where they find the sets, in groups or one by one, and apart from the credits: the
+ * k=4 entries add up to the number of 4-sets.  shape_counts: 6 entries. */
 vdmc_status vdmc_shape_counts(vdmc_graph g, uint64_t* shape_counts);
 
 /* The graph's counters of the last count (host; waits for it): after k = 3, 4 entries
  * 0-5 are the shape counts above, 6-7 are zero; after k = 5 the 8 entries are the sets
- * visited per BFS layer shape of five vertices, in the order (4) (3,1) (2,2) (2,1,1)
+ * counted per BFS layer shape of five vertices, in the order (4) (3,1) (2,2) (2,1,1)
  * (1,3) (1,2,1) (1,1,2) (1,1,1,1) (layer sizes from the root outwards), adding up to
  * the number of connected 5-sets.  Copies min(n, 8) entries. */
 vdmc_status vdmc_profile_counters(vdmc_graph g, uint64_t* counters, int32_t n);
 
 /* Device time of the kernels of the last count call on this graph, from events recorded
  * on the count's stream around the launches (host; waits for those events):
- * ms_out[0] the per-root kernel over the light roots, ms_out[1] the hub path (the hub
- * kernel, then for k = 4 the long-slot kernel), ms_out[2] the hub kernel alone; -1 for a
+ * ms_out[0] the light-root and per-set kernels, ms_out[1] the hub path (the hub kernel,
+ * then for k = 4 its compact rows added to the output), ms_out[2] the hub kernel alone; -1 for a
  * part that the call did not launch.  ms_out: n floats, caller-owned; the first
  * min(n, 3) are written. */
 vdmc_status vdmc_kernel_times(vdmc_graph g, float* ms_out, int32_t n);
@@ -251,10 +250,9 @@ vdmc_status vdmc_kernel_times(vdmc_graph g, float* ms_out, int32_t n);
  * persistent launch whose work tiles come from a device-side cursor; the launch is
  * captured in a HIP graph the first time a batch signature (same graphs, same
  * outputs, same k) is seen and replayed afterwards.  Asynchronous on `stream`.
- * k = 5: every graph must satisfy vdmc_count_supported (else UNSUPPORTED).  The graphs
- * that LDS holds are counted by one launch (graphs cut into parts with private blocks,
- * summed afterwards: at most 8 GiB per call, from the default stream-ordered pool as
- * for vdmc_count), the others one by one in device memory after it; not captured.
+ * k = 5: every graph must satisfy vdmc_count_supported (else UNSUPPORTED).  Graphs of at
+ * most 16384 vertices and 2^24 pairs are counted by one launch (those up to 512 vertices and the
+ * rest by one each), larger ones one by one after it; not captured.
  */
 vdmc_status vdmc_count_batch(const vdmc_graph* gs, int32_t num, int32_t k,
                              uint64_t* const* outs, void* stream);

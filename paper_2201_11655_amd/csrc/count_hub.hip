@@ -410,7 +410,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 }
                 const bool local = in && sl >= 0, d2 = in && sl < 0;
                 const unsigned long long ml = __ballot(local);
-                if (local) locnbr[base + nloc + (uint32_t)__popcll(ml & ((1ull << lane) - 1ull))] = ((uint32_t)sl << 2) | ec;
+                if (local)
+                    locnbr[base + nloc + (uint32_t)__popcll(ml & ((1ull << lane) - 1ull))] = ((uint32_t)sl << 2) | ec;
                 nloc += (uint32_t)__popcll(ml);
                 if (A.k3) {   // (1,2): r - x - e
                     const uint32_t cls = L.t3[motif_index3(rx, 0u, ec)];
@@ -1088,7 +1089,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         pos += i < lane ? m : 0u;
                         total += m;
                     }
-                    for (; word; word &= word - 1u) LST[pos++] = (uint16_t)(lane * 32u + (uint32_t)__ffs((int)word) - 1u);
+                    for (; word; word &= word - 1u)
+                        LST[pos++] = (uint16_t)(lane * 32u + (uint32_t)__ffs((int)word) - 1u);
                     __threadfence_block();
                     // EB vertices a group, then their credits: vector memory operations finish in
                     // order, so a load after an atomic waits for the atomic
@@ -1103,7 +1105,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                             const uint32_t in = i0 + (eb + 1u) * 4u + (lane >> 4), en = end_at(in);
                             const uint32_t q0n = A.off[en] + gl, q1n = in < total ? A.off[en + 1u] : 0u;
                             for (uint32_t q = q0; q < q1; q += 16u) {
-                                const uint32_t ee = q == q0 ? x0 : A.adj[q], c = ee >> 2, ce = swap_arc_bits(ee & 3u) - 1u;
+                                const uint32_t ee = q == q0 ? x0 : A.adj[q], c = ee >> 2;
+                                const uint32_t ce = swap_arc_bits(ee & 3u) - 1u;
                                 if (c <= r || (G > 1u && c % G != share)) continue;
                                 const uint32_t j = X2.find(c);
                                 if (j == ~0u) continue;
@@ -1410,7 +1413,8 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     if (around) VDMC_HIP(hipEventRecord(around[2], st));
     if (a.cmp) {
         const unsigned blocks = (unsigned)std::min<int64_t>((g->n + 3) / 4, 65536);
-        hipLaunchKernelGGL(k_expand, dim3(blocks), dim3(4 * kCmpRow), 0, st, a.cmp, a.cmp_wide, g->n, g->perm, a.cmp_cls,
+        hipLaunchKernelGGL(k_expand, dim3(blocks), dim3(4 * kCmpRow), 0, st, a.cmp, a.cmp_wide, g->n, g->perm,
+                           a.cmp_cls,
                            a.out4);
         VDMC_HIP(hipGetLastError());
     }

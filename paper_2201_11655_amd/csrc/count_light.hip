@@ -12,8 +12,8 @@
 //   * the slots' and r's credits are summed in LDS; a depth-2 vertex takes one memory-side
 //     atomic per class and parent, an end vertex of (1,1,1) one per set.
 // What bounds it: the latency of the few dependent loads per root at small sizes, the
-// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 587 us in the
-// per-set kernel, see k_light below for the figures here.
+// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 116 us, 587 in the per-set
+// kernel; G(150, 0.027), k = 4: 55 us a call, 258 with the per-set kernel.
 //
 // A root's depth-2 entries must fit the hash; three sizes are built (light_tier), chosen by
 // the number of slots and of entries in their rows above r.  Larger roots take the hub path
@@ -43,8 +43,8 @@ struct LightLds {
 
 __device__ __forceinline__ uint32_t lhash(uint32_t x, uint32_t cap) { return (x * 2654435761u >> 16) & (cap - 1u); }
 
-__device__ __forceinline__ void ladd(gptr<unsigned long long> out, gptr<const int32_t> perm, uint32_t C, uint32_t v, uint32_t cls,
-                                     unsigned long long n) {
+__device__ __forceinline__ void ladd(gptr<unsigned long long> out, gptr<const int32_t> perm, uint32_t C, uint32_t v,
+                                     uint32_t cls, unsigned long long n) {
     gadd64(&out[(size_t)perm[v] * C + cls], n);
 }
 

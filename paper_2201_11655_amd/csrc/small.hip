@@ -20,7 +20,9 @@
 // for c: the entries in N+(r) and those adjacent to a.  An adjacent pair of slots (a
 // triangle with r) is queued, and corrects the triples and the children of either.
 // In the 4096 graphs of the batched workload (20..500 vertices, mean out-degree 2..8)
-// there are 218 k sets a graph, of them 65 k paths, and 14 k corrections.
+// there are 218 k sets a graph, of them 65 k paths, and 14 k corrections: 2.05 ms a call,
+// 4.75 with every set visited.  What bounds it: the LDS of the path walk, three reads and an
+// atomic per row entry, with one workgroup a CU (128 registers, 16 waves).
 //
 // k = 3 is the same: pairs of N+(r) and children by code, triangles corrected.
 //
@@ -451,7 +453,8 @@ __global__ __launch_bounds__(BS, 4) void k_small(SmallArgs A) {
             h3 = sum8(h3);
             if (!on) continue;
             const uint32_t m1 = (m >> 10) & 1023u, m2 = m >> 20, h = h1 + h2 + h3;
-            const uint32_t o1 = m1 - (ra == 1u), o2 = m2 - (ra == 2u), o3 = d - m1 - m2 - (ra == 3u);   // the other slots
+            // the other slots
+            const uint32_t o1 = m1 - (ra == 1u), o2 = m2 - (ra == 2u), o3 = d - m1 - m2 - (ra == 3u);
             if (K == 3) {
                 if (gl < 6u) {   // (1,1) of a; (1,2) of a and r
                     const uint32_t k = gl % 3u + 1u, n = gl < 3u ? pick3(k, o1, o2, o3) : pick3(k, h1, h2, h3);
@@ -477,7 +480,8 @@ __global__ __launch_bounds__(BS, 4) void k_small(SmallArgs A) {
             if (h) {
                 sPre2[u] = h1 | (h2 << 10) | (h3 << 20);
                 {   // (2,1,0) of a, the parent, and r; children of codes 1, 2 and the first of code 3
-                    const uint32_t k = gl / 3u + 1u, l = gl % 3u + 1u, n = gl < 7u ? pick3(k, h1, h2, h3) * pick3(l, o1, o2, o3) : 0u;
+                    const uint32_t k = gl / 3u + 1u, l = gl % 3u + 1u;
+                    const uint32_t n = gl < 7u ? pick3(k, h1, h2, h3) * pick3(l, o1, o2, o3) : 0u;
                     const uint32_t slot = byte_of(sTrees.path2[ra * 4u + k], l);
                     if (n) {
                         cr.add_s(a, slot, n);
@@ -534,8 +538,10 @@ __global__ __launch_bounds__(BS, 4) void k_small(SmallArgs A) {
             for (uint32_t i = gl; i < 10u; i += 8u) {
                 const uint32_t t = code_triple(i), k = t & 3u, l = (t >> 2) & 3u, q = t >> 4;
                 const uint32_t x = pick3(k, m1, m2, m3), y = pick3(l, m1, m2, m3), z = pick3(q, m1, m2, m3);
-                const uint32_t n = k == q ? x * (x - 1u) / 2u * (x - 2u) / 3u
-                                          : (k == l ? x * (x - 1u) / 2u * z : (l == q ? x * (y * (y - 1u) / 2u) : x * y * z));
+                uint32_t n = x * y * z;
+                if (k == q) n = x * (x - 1u) / 2u * (x - 2u) / 3u;
+                else if (k == l) n = x * (x - 1u) / 2u * z;
+                else if (l == q) n = x * (y * (y - 1u) / 2u);
                 if (n) cr.add_s(r, byte_of(sTrees.starr[k * 4u + l], q), n);
             }
             if (gl == 0u) shp[0] += d * (d - 1u) / 2u * (d - 2u) / 3u;
@@ -618,7 +624,8 @@ __global__ __launch_bounds__(BS, 4) void k_small(SmallArgs A) {
                     }
                     more = i == len;
                     for (; odd; odd &= odd - 1ull) {
-                        const uint32_t ent = sAdj[top - (uint32_t)(__ffsll((long long)odd) - 1)], e = ent >> 2, ce = ent & 3u;
+                        const uint32_t ent = sAdj[top - (uint32_t)(__ffsll((long long)odd) - 1)];
+                        const uint32_t e = ent >> 2, ce = ent & 3u;
                         const bool xr = L.adjacent(r, e), xa = L.adjacent(a, e);
                         const uint32_t ae = L.code_if(xa, a, e);
                         if (xr) {   // (2,1,0) with the second slot e: from the lower parent of c

@@ -98,7 +98,8 @@ struct ClassTables {
     const uint8_t* t4;   // 4096 entries
     const uint8_t* slot4;     // 199 entries: class -> compact slot or 0xFF
     const uint8_t* slotcls;   // kCompact4 entries: compact slot -> class
-    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), compact counter; 0xFF none
+    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), compact
+                              // counter; 0xFF none
     const uint8_t* star_cls;  // 10 entries: star slot -> class
     const uint8_t* path_cls;  // 30 entries: path or 4-cycle slot -> class
     const uint8_t* cmp_cls;   // kCmpRow entries: compact counter -> class
@@ -268,8 +269,8 @@ inline void wait_graph(vdmc_graph_s* g) {
 // Pointers kept in descriptors that kernels read from memory, and pointers to LDS kept in
 // structs: typed with their address space in device code.  As generic pointers they would be
 // accessed by flat instructions, which the LDS counter waits for too, so that each LDS read
-// after a memory-side atomic waits for the atomic (G(1000, 0.005), k = 3 and 4: 124 us with
-// flat atomics in k_light, see there for the figure without).
+// after a memory-side atomic waits for the atomic (k_five_sets, 256 G(n, p) graphs: 143 ms a
+// call with flat credits, 47 without).
 #if defined(__HIP_DEVICE_COMPILE__)
 #define VDMC_AS(n) __attribute__((address_space(n)))
 #else

@@ -319,7 +319,7 @@ SHAPES5 = ("(4)", "(3,1)", "(2,2)", "(2,1,1)", "(1,3)", "(1,2,1)", "(1,1,2)", "(
 
 
 def shape_counts5(g: Graph) -> dict:
-    """Sets visited per BFS layer shape by the last 5-vertex count on g."""
+    """Sets counted per BFS layer shape by the last 5-vertex count on g."""
     return {s: int(v) for s, v in zip(SHAPES5, profile_counters(g))}
 
 
@@ -331,7 +331,7 @@ def profile_counters(g: Graph) -> np.ndarray:
 
 
 def kernel_times(g: Graph) -> tuple:
-    """(per-set kernel ms, hub path ms, hub kernel alone ms) of the last count call on g;
+    """(light-root and per-set kernels ms, hub path ms, hub kernel alone ms) of the last count call on g;
     -1 for a part that was not launched."""
     out = np.zeros(3, np.float32)
     _check(load().vdmc_kernel_times(g.handle, _np_ptr(out), 3))
