@@ -12,8 +12,8 @@
 //   * the slots' and r's credits are summed in LDS; a depth-2 vertex takes one memory-side
 //     atomic per class and parent, an end vertex of (1,1,1) one per set.
 // What bounds it: the latency of the few dependent loads per root at small sizes, the
-// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 116 us, 587 in the per-set
-// kernel; G(150, 0.027), k = 4: 55 us a call, 258 with the per-set kernel.
+// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 126 us a call, 665 with the per-set
+// kernel; G(150, 0.027), k = 4: 45 us, 258.
 //
 // A root's depth-2 entries must fit the hash; three sizes are built (light_tier), chosen by
 // the number of slots and of entries in their rows above r.  Larger roots take the hub path
@@ -29,6 +29,7 @@ constexpr uint32_t kSlotMark = 0x80000000u;
 template <uint32_t DM, uint32_t CAP>
 struct LightLds {
     uint32_t P[DM];                 // slots: (rank << 2) | arc bits r -> slot
+    uint32_t PP[DM];                // their original ids
     uint32_t X0[DM], X1[DM];        // arc bits of a slot to the slots, a plane each
     uint32_t CH[DM][3];             // depth-2 entries of a slot by code
     uint32_t SC[DM][kCmpRow];       // compact counters of a slot (k = 4)
@@ -43,9 +44,11 @@ struct LightLds {
 
 __device__ __forceinline__ uint32_t lhash(uint32_t x, uint32_t cap) { return (x * 2654435761u >> 16) & (cap - 1u); }
 
-__device__ __forceinline__ void ladd(gptr<unsigned long long> out, gptr<const int32_t> perm, uint32_t C, uint32_t v,
-                                     uint32_t cls, unsigned long long n) {
-    gadd64(&out[(size_t)perm[v] * C + cls], n);
+// n sets of class cls to the vertex of original id v.  Ids are read before the atomics of a phase:
+// vector memory operations finish in order, so a load after an atomic waits for it.
+__device__ __forceinline__ void ladd(gptr<unsigned long long> out, uint32_t C, uint32_t v, uint32_t cls,
+                                     unsigned long long n) {
+    gadd64(&out[(size_t)v * C + cls], n);
 }
 
 // all threads of a root's group have arrived and see each other's LDS writes
@@ -71,8 +74,10 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                            const uint8_t* cmp_cls, uint32_t r, LightLds<DM, CAP>& S, unsigned long long* shp) {
     const uint32_t tid = threadIdx.x % BS;
     const uint32_t s = gv.split[r], d = min(gv.off[r + 1] - s, DM);
+    const uint32_t pr = gv.perm[r];
     for (uint32_t i = tid; i < d; i += BS) {
         S.P[i] = gv.adj[s + i];
+        S.PP[i] = gv.perm[S.P[i] >> 2];
         S.X0[i] = S.X1[i] = 0u;
         for (int k = 0; k < 3; k++) S.CH[i][k] = 0u;
     }
@@ -100,10 +105,14 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
     // ---- rows of the slots, from the end: arcs among the slots, depth-2 entries
     for (uint32_t a = tid >> 4; a < d; a += BS / 16) {
         const uint32_t va = S.P[a] >> 2, ra = S.P[a] & 3u, lo = gv.off[va];
-        for (uint32_t hi = gv.off[va + 1]; hi > lo; hi -= min(16u, hi - lo)) {
-            const uint32_t q = hi - 1u - (tid & 15u);
+        uint32_t hi = gv.off[va + 1], next = (tid & 15u) < hi - lo ? gv.adj[hi - 1u - (tid & 15u)] : 0u;
+        for (; hi > lo; hi -= min(16u, hi - lo)) {
             const bool in = (tid & 15u) < hi - lo;
-            const uint32_t ent = in ? gv.adj[q] : 0u, e = ent >> 2, c = ent & 3u;
+            const uint32_t ent = next, e = ent >> 2, c = ent & 3u;
+            const uint32_t pe = K3 && e > r ? gv.perm[e] : 0u;
+            const bool more = hi - lo > 16u;
+            next = (tid & 15u) + 16u < hi - lo ? gv.adj[hi - 17u - (tid & 15u)] : 0u;
+            const uint32_t first = more ? gv.adj[hi - 16u] >> 2 : 0u;
             if (in && e > r) {
                 uint32_t h = lhash(e + 1u, CAP);
                 bool slot = false;
@@ -134,12 +143,11 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                         const uint32_t cls = t3[motif_index3(ra, 0u, c)];
                         atomicAdd(&S.R3[cls], 1u);
                         atomicAdd(&S.S3[a][cls], 1u);
-                        ladd(gv.out3, gv.perm, kClasses3, e, cls, 1ull);
+                        ladd(gv.out3, kClasses3, pe, cls, 1ull);
                         shp[1]++;
                     }
                 }
             }
-            const uint32_t first = hi - lo > 16u ? gv.adj[hi - 16u] >> 2 : 0u;
             if (first <= r) break;   // the rest of the row is not above r
         }
     }
@@ -149,7 +157,7 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
     auto add_a = [&](uint32_t a, uint32_t cls, uint32_t n) {
         const uint32_t c = cmp_of[cls];
         if (c < kCmpRow) atomicAdd(&S.SC[a][c], n);
-        else ladd(gv.out4, gv.perm, kClasses4, S.P[a] >> 2, cls, (unsigned long long)(long long)(int32_t)n);
+        else ladd(gv.out4, kClasses4, S.PP[a], cls, (unsigned long long)(long long)(int32_t)n);
     };
     auto add_r = [&](uint32_t cls, uint32_t n) { atomicAdd(&S.R4[cls], n); };
     // ---- pairs a < b of slots: (1,1), (3,0,0)
@@ -236,17 +244,26 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
             }
         }
         // ---- (1,2,0) and (1,1,1) of every depth-2 entry (a, c), 8 lanes each: c's row above r
+        // (the next entry's row is loaded before this one's credits)
+        const uint32_t gl = tid & 7u;
+        const auto child = [&](uint32_t i) { return i < n2 ? S.K[S.CL[i] >> 7] - 1u : 0u; };
+        uint32_t c = child(tid >> 3), lo = gv.off[c], hi0 = (tid >> 3) < n2 ? gv.off[c + 1] : 0u, pc = gv.perm[c];
+        uint32_t x0 = hi0 > lo + gl ? gv.adj[hi0 - 1u - gl] : 0u;
         for (uint32_t i0 = 0; i0 < n2; i0 += BS / 8) {
-            const uint32_t i = i0 + (tid >> 3), gl = tid & 7u;
+            const uint32_t i = i0 + (tid >> 3);
             const bool on = i < n2;
-            const uint32_t ent = on ? S.CL[i] : 0u, a = (ent >> 2) & 31u, ac = ent & 3u;
-            const uint32_t c = on ? S.K[ent >> 7] - 1u : 0u, ra = S.P[a] & 3u;
+            const uint32_t ent = on ? S.CL[i] : 0u, a = (ent >> 2) & 31u, ac = ent & 3u, ra = S.P[a] & 3u;
+            const uint32_t cn = child(i + BS / 8), lon = gv.off[cn], hin = i + BS / 8 < n2 ? gv.off[cn + 1] : 0u;
+            const uint32_t pcn = gv.perm[cn];
+            uint32_t x0n = 0;
             uint32_t e1 = 0, e2 = 0, e3 = 0;   // ends of paths by arc code
             uint32_t j1 = 0, j2 = 0, j3 = 0;   // children of a adjacent to c, by their code
-            const uint32_t lo = on ? gv.off[c] : 0u;
-            for (uint32_t hi = on ? gv.off[c + 1] : 0u; hi > lo; hi -= min(8u, hi - lo)) {
+            for (uint32_t hi = hi0; hi > lo; hi -= min(8u, hi - lo)) {
                 const bool in = gl < hi - lo;
-                const uint32_t ee = in ? gv.adj[hi - 1u - gl] : 0u, e = ee >> 2, ce = ee & 3u;
+                const uint32_t ee = hi == hi0 ? x0 : (in ? gv.adj[hi - 1u - gl] : 0u), e = ee >> 2, ce = ee & 3u;
+                const uint32_t pe = e > r ? gv.perm[e] : 0u;
+                const uint32_t first = hi - lo > 8u ? gv.adj[hi - 8u] >> 2 : 0u;
+                if (hi == hi0) x0n = hin > lon + gl ? gv.adj[hin - 1u - gl] : 0u;
                 if (in && e > r) {
                     uint32_t h = lhash(e + 1u, CAP), k;
                     for (;; h = (h + 1u) & (CAP - 1u)) {
@@ -257,7 +274,7 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                         const uint32_t ae = k ? code(S.A0[h], S.A1[h], a) : 0u;
                         if (ae) {   // e is another child of a
                             const uint32_t cls = t4[motif_index4(ra, 0u, 0u, ac, ae, ce)];
-                            ladd(gv.out4, gv.perm, kClasses4, c, cls, 1ull);
+                            ladd(gv.out4, kClasses4, pc, cls, 1ull);
                             j1 += ae == 1u;
                             j2 += ae == 2u;
                             j3 += ae == 3u;
@@ -269,14 +286,13 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                                 add_r(st, ~0u);
                             }
                         } else {    // path r - a - c - e
-                            ladd(gv.out4, gv.perm, kClasses4, e, t4[motif_index4(ra, 0u, 0u, ac, 0u, ce)], 1ull);
+                            ladd(gv.out4, kClasses4, pe, t4[motif_index4(ra, 0u, 0u, ac, 0u, ce)], 1ull);
                             e1 += ce == 1u;
                             e2 += ce == 2u;
                             e3 += ce == 3u;
                         }
                     }
                 }
-                const uint32_t first = hi - lo > 8u ? gv.adj[hi - 8u] >> 2 : 0u;
                 if (first <= r) break;
             }
             e1 = sum8(e1);
@@ -293,33 +309,38 @@ __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t
                         const uint32_t cls = t4[motif_index4(ra, 0u, 0u, ac, 0u, k + 1u)];
                         add_a(a, cls, n);
                         add_r(cls, n);
-                        ladd(gv.out4, gv.perm, kClasses4, c, cls, n);
+                        ladd(gv.out4, kClasses4, pc, cls, n);
                         shp[5] += n;
                     }
                 } else {   // the children of a that are not adjacent to c, by code
                     const uint32_t n = S.CH[a][k] - (k + 1u == ac ? 1u : 0u) -
                                        (k == 2u ? j3 : (k == 0u ? j1 : j2));
-                    if (n) ladd(gv.out4, gv.perm, kClasses4, c, t4[motif_index4(ra, 0u, 0u, ac, k + 1u, 0u)], n);
+                    if (n) ladd(gv.out4, kClasses4, pc, t4[motif_index4(ra, 0u, 0u, ac, k + 1u, 0u)], n);
                 }
             }
+            c = cn;
+            lo = lon;
+            hi0 = hin;
+            pc = pcn;
+            x0 = x0n;
         }
     }
     group_sync<BS>();
     if (K4) {
         for (uint32_t i = tid; i < d * kCmpRow; i += BS) {
             const uint32_t n = (&S.SC[0][0])[i];
-            if (n) ladd(gv.out4, gv.perm, kClasses4, S.P[i / kCmpRow] >> 2, cmp_cls[i % kCmpRow], n);
+            if (n) ladd(gv.out4, kClasses4, S.PP[i / kCmpRow], cmp_cls[i % kCmpRow], n);
         }
         for (uint32_t i = tid; i < (uint32_t)kClasses4; i += BS)
-            if (S.R4[i]) ladd(gv.out4, gv.perm, kClasses4, r, i, S.R4[i]);
+            if (S.R4[i]) ladd(gv.out4, kClasses4, pr, i, S.R4[i]);
     }
     if (K3) {
         for (uint32_t i = tid; i < d * kClasses3; i += BS) {
             const uint32_t n = (&S.S3[0][0])[i];
-            if (n) ladd(gv.out3, gv.perm, kClasses3, S.P[i / kClasses3] >> 2, i % kClasses3, n);
+            if (n) ladd(gv.out3, kClasses3, S.PP[i / kClasses3], i % kClasses3, n);
         }
         for (uint32_t i = tid; i < (uint32_t)kClasses3; i += BS)
-            if (S.R3[i]) ladd(gv.out3, gv.perm, kClasses3, r, i, S.R3[i]);
+            if (S.R3[i]) ladd(gv.out3, kClasses3, pr, i, S.R3[i]);
     }
     group_sync<BS>();
 }
@@ -342,12 +363,14 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
     __shared__ uint32_t t4w[K4 ? 1024 : 1];
     __shared__ uint8_t t3[64];
     __shared__ uint8_t cmp_of[256];
+    __shared__ uint8_t cmp_cls[kCmpRow];
     __shared__ unsigned long long next;
     const uint8_t* t4 = (const uint8_t*)t4w;
     if (K4)
         for (uint32_t i = threadIdx.x; i < 1024u; i += BS * WPB) t4w[i] = ((const uint32_t*)A.t4)[i];
     for (uint32_t i = threadIdx.x; i < 64u; i += BS * WPB) t3[i] = A.t3[i];
     for (uint32_t i = threadIdx.x; i < 256u; i += BS * WPB) cmp_of[i] = A.cmp_of[i];
+    if (threadIdx.x < kCmpRow) cmp_cls[threadIdx.x] = A.cmp_cls[threadIdx.x];
     __syncthreads();
     const uint32_t group = threadIdx.x / BS;
     LightLds<DM, CAP>& S = lds[group];
@@ -356,7 +379,7 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
         for (int64_t i = (int64_t)blockIdx.x * WPB + group; i < A.nroots; i += (int64_t)gridDim.x * WPB) {
             const uint32_t r = A.roots[i];
             if (r < A.rank_lo || r >= A.rank_hi) continue;   // uniform over the group
-            light_root<BS, DM, CAP, K3, K4>(A.gv, t3, t4, cmp_of, A.cmp_cls, r, S, shp);
+            light_root<BS, DM, CAP, K3, K4>(A.gv, t3, t4, cmp_of, cmp_cls, r, S, shp);
         }
         add_shapes(A.gv.stats, shp);
         return;
@@ -381,7 +404,7 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
                 if (cur >= 0) add_shapes(A.graphs[cur].stats, shp);
                 cur = (int)ent.x;
             }
-            light_root<BS, DM, CAP, K3, K4>(A.graphs[ent.x], t3, t4, cmp_of, A.cmp_cls, ent.y, S, shp);
+            light_root<BS, DM, CAP, K3, K4>(A.graphs[ent.x], t3, t4, cmp_of, cmp_cls, ent.y, S, shp);
         }
     }
     if (cur >= 0) add_shapes(A.graphs[cur].stats, shp);
