@@ -394,15 +394,16 @@ void launch_batch(const BatchArgs& b, const SmallArgs* small, unsigned small_gri
         launch_small(*small, k3 ? 3 : 4, small_variant, small_grid, small_lds, st);
     }
     const uint2* table = b.table;
-    for (int t = 0; t < 3; t++) {   // the light tiers' parts of the table, a cursor each
+    for (int t = k4 ? 0 : 2; t < 3; t++) {   // the light tiers' parts, a cursor each; k = 3 alone: all three
+        const unsigned long long nt = k4 ? b.nlight[t] : b.nlight[0] + b.nlight[1] + b.nlight[2];
         LightArgs l{};
         l.graphs = b.graphs;
         l.table = table;
-        l.nroots = (int64_t)b.nlight[t];
+        l.nroots = (int64_t)nt;
         l.cursor = b.cursor + 2 + t;
         l.tile = (unsigned)b.tile;
         launch_light(l, t, k3, k4, st);
-        table += b.nlight[t];
+        table += nt;
     }
     if (b.nentries == 0) return;
     BatchArgs rest = b;
@@ -456,8 +457,9 @@ void launch_count(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out
         l.roots = g->light;
         // few roots in all: the first two tiers in one launch
         const bool merge = g->ntier[0] + g->ntier[1] <= 1024;
-        for (int t = merge ? 1 : 0; t < 3; t++) {
-            l.nroots = merge && t == 1 ? g->ntier[0] + g->ntier[1] : g->ntier[t];
+        for (int t = !k4 ? 2 : (merge ? 1 : 0); t < 3; t++) {   // k = 3 alone: all three
+            l.nroots = !k4 ? g->ntier[0] + g->ntier[1] + g->ntier[2]
+                           : (merge && t == 1 ? g->ntier[0] + g->ntier[1] : g->ntier[t]);
             launch_light(l, t, k3, k4, st);
             l.roots += l.nroots;
         }

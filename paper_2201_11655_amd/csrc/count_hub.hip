@@ -59,7 +59,7 @@ struct HubArgs {
     unsigned long long* out3;
     unsigned long long* out4;
     unsigned long long* stats;
-    int k3, k4;
+    int k3;
     uint32_t rank_lo, rank_hi;   // only roots with rank in [rank_lo, rank_hi)
     uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | pcount | bitmap
     size_t wg_words;
@@ -289,13 +289,16 @@ __device__ __forceinline__ void build_row(uint32_t* row, const uint32_t* locnbr,
 
 // ----------------------------------------------------------------------------- hub kernel
 
+// K4 = false (k = 3 alone): phases A, B and C3 only.  A kernel of its own (54 registers), as
+// the other's spill, which a launch of some 40 us feels: R-MAT 2^10, five ranges, 271 -> 250 us.
+template <bool K4>
 __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     __shared__ HubLds L;
     __shared__ uint32_t sRoot;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wid = wave_id();
-    for (uint32_t i = tid; i < 4096; i += HT) L.t4[i] = A.t4[i];
+    for (uint32_t i = tid; K4 && i < 4096; i += HT) L.t4[i] = A.t4[i];
     for (uint32_t i = tid; i < 64; i += HT) L.t3[i] = A.t3[i];
-    for (uint32_t i = tid; i < 768; i += HT) L.maps[i] = A.maps[i];
+    for (uint32_t i = tid; K4 && i < 768; i += HT) L.maps[i] = A.maps[i];
     const uint8_t* star_of = L.maps;
     const uint8_t* cmp_of = L.maps + 512;
     uint32_t* S = A.scratch + (size_t)blockIdx.x * A.wg_words;
@@ -366,7 +369,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         }
         for (uint32_t i = tid; i < SHASH / 2; i += HT) L.U[i] = 0u;
         for (uint32_t i = tid; i < kClasses3; i += HT) L.root3[i] = 0ull;
-        for (uint32_t i = tid; i < kClasses4; i += HT) L.root4[i] = 0ull;
+        for (uint32_t i = tid; K4 && i < kClasses4; i += HT) L.root4[i] = 0ull;
         if (tid < 8) L.ctr[tid] = 0u;
         __syncthreads();
         for (uint32_t i = tid; i < D; i += HT) {
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         const uint32_t used = SHASH / 2 + HT + (A.k3 ? D * kClasses3 : 0u);
         const bool kept = used + 2u * nbw > U_WORDS;   // in scratch: phases E and G find it there
         const Index2 X2(!kept, L.U + used, gbits, nbw);
-        if (A.k4) X2.clear(nbw);
+        if (K4) X2.clear(nbw);
         __syncthreads();
         for (;;) {
             const uint32_t x = wave_task(&L.ctr[0]);
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         shp[1]++;
                     }
                 }
-                if (A.k4) {   // depth-2 entry (x, e): e marked, the entry behind x's row
+                if (K4) {   // depth-2 entry (x, e): e marked, the entry behind x's row
                     const unsigned long long md = __ballot(d2);
                     if (d2) {
                         X2.mark(e);
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // the depth-2 vertices numbered in rank order (cids), their parents gathered:
         // A(c_j) = parents[poff[j] .. poff[j + 1])
         uint32_t ngroups = 0;
-        if (A.k4) {
+        if (K4) {
             for (uint32_t i = tid; i < nbw; i += HT) X2.set_before(i, (uint32_t)__popc(X2.word(i)));
             __syncthreads();
             ngroups = kept ? block_scan(gbits + nbw, nbw, part) : block_scan(L.U + used + nbw, nbw, part);
@@ -526,7 +529,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             for (uint32_t i = tid; i < kClasses3; i += HT)
                 if (L.root3[i]) gadd(A.out3, A.perm, kClasses3, r, i, L.root3[i]);
         }
-        if (!A.k4) continue;
+        if (!K4) continue;
         const uint32_t seg2 = __builtin_amdgcn_readfirstlane(L.seg[0]), seg3 = __builtin_amdgcn_readfirstlane(L.seg[1]);
         __syncthreads();
         auto seg_at = [&](uint32_t k) -> uint32_t { return k < 2u ? 0u : (k == 2u ? seg2 : (k == 3u ? seg3 : D)); };
@@ -1161,6 +1164,7 @@ __global__ __launch_bounds__(192) void k_expand(const void* cmp, int wide, int64
 // ----------------------------------------------------------------------------- binning
 
 constexpr int BT = 256;
+constexpr double kShareWork3 = 1e6;   // in the unit of the hub queue's key
 
 // every pair {u < v} into the edge hash, one thread per row (entries from split[u] on)
 __global__ void k_edge_hash(const uint32_t* __restrict__ off, const uint32_t* __restrict__ split,
@@ -1328,6 +1332,12 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
             const uint32_t shares = fair > 0.0 ? (uint32_t)std::min(8.0, std::ceil(top / fair)) : 1u;
             g->hub_layout[3] = shares >= 2 ? h : 0;
             g->hub_layout[4] = shares >= 2 ? shares : 1;
+            // k = 3 alone: staging is most of a root's work and sharing repeats it, so only roots
+            // above kShareWork3 (some 400 slots) as well are shared.  R-MAT 2^12, three ranges:
+            // 291 us, 347 with the line of k = 4, 364 without sharing.
+            h = 0;
+            while (h < hub_keys.size() && h < 4096 && (double)(~hub_keys[h]) > std::max(fair, kShareWork3)) h++;
+            g->hub_split3 = shares >= 2 ? h : 0;
         }
     }
     const unsigned long long max_s2 = tot[0];
@@ -1391,7 +1401,6 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.out4 = (unsigned long long*)out4;
     a.stats = g->stats;
     a.k3 = k3;
-    a.k4 = k4;
     a.rank_lo = rank_lo;
     a.rank_hi = rank_hi;
     // the compact rows come first, then the workgroups' scratch
@@ -1402,13 +1411,15 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.wg_words = g->hub_layout[0];
     a.s2cap = (uint32_t)g->hub_layout[1];
     const unsigned wgs = (unsigned)g->hub_layout[5];
-    a.split_roots = (uint32_t)g->hub_layout[3];   // the heaviest hub roots, shared (set at binning)
+    // the heaviest hub roots, shared (set at binning)
+    a.split_roots = (uint32_t)(k4 ? g->hub_layout[3] : g->hub_split3);
     a.shares = (uint32_t)std::max<size_t>(1, g->hub_layout[4]);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, g->hub_queue, 16);
     if (a.cmp) launch_fill_u64((uint64_t*)a.cmp, g->hub_layout[7] / 8, 0, st);
     // around[0] and around[1] bracket the hub path, around[2] marks the end of k_hub
     if (around) VDMC_HIP(hipEventRecord(around[0], st));
-    hipLaunchKernelGGL(k_hub, dim3(wgs), dim3(HT), 0, st, a);
+    if (k4) hipLaunchKernelGGL((k_hub<true>), dim3(wgs), dim3(HT), 0, st, a);
+    else hipLaunchKernelGGL((k_hub<false>), dim3(wgs), dim3(HT), 0, st, a);
     VDMC_HIP(hipGetLastError());
     if (around) VDMC_HIP(hipEventRecord(around[2], st));
     if (a.cmp) {

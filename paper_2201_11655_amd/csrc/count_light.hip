@@ -12,8 +12,8 @@
 //   * the slots' and r's credits are summed in LDS; a depth-2 vertex takes one memory-side
 //     atomic per class and parent, an end vertex of (1,1,1) one per set.
 // What bounds it: the latency of the few dependent loads per root at small sizes, the
-// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 126 us a call, 665 with the per-set
-// kernel; G(150, 0.027), k = 4: 45 us, 258.
+// memory-side atomics (2.4e10/s) at large ones.  G(1000, 0.005), k = 3 and 4: 126 us a call,
+// 665 with the per-set kernel; G(150, 0.027), k = 4: 45 us, 258.
 //
 // A root's depth-2 entries must fit the hash; three sizes are built (light_tier), chosen by
 // the number of slots and of entries in their rows above r.  Larger roots take the hub path
@@ -26,13 +26,13 @@ namespace {
 
 constexpr uint32_t kSlotMark = 0x80000000u;
 
-template <uint32_t DM, uint32_t CAP>
+template <uint32_t DM, uint32_t CAP, bool K4>
 struct LightLds {
     uint32_t P[DM];                 // slots: (rank << 2) | arc bits r -> slot
     uint32_t PP[DM];                // their original ids
     uint32_t X0[DM], X1[DM];        // arc bits of a slot to the slots, a plane each
     uint32_t CH[DM][3];             // depth-2 entries of a slot by code
-    uint32_t SC[DM][kCmpRow];       // compact counters of a slot (k = 4)
+    uint32_t SC[K4 ? DM : 1][kCmpRow];   // compact counters of a slot (k = 4)
     uint32_t S3[DM][kClasses3];     // k = 3 counters of a slot
     uint32_t R4[kClasses4];
     uint32_t R3[kClasses3];
@@ -71,7 +71,7 @@ __device__ __forceinline__ uint32_t sum8(uint32_t v) {
 
 template <int BS, uint32_t DM, uint32_t CAP, bool K3, bool K4>
 __device__ void light_root(const GraphView& gv, const uint8_t* t3, const uint8_t* t4, const uint8_t* cmp_of,
-                           const uint8_t* cmp_cls, uint32_t r, LightLds<DM, CAP>& S, unsigned long long* shp) {
+                           const uint8_t* cmp_cls, uint32_t r, LightLds<DM, CAP, K4>& S, unsigned long long* shp) {
     const uint32_t tid = threadIdx.x % BS;
     const uint32_t s = gv.split[r], d = min(gv.off[r + 1] - s, DM);
     const uint32_t pr = gv.perm[r];
@@ -359,7 +359,7 @@ __device__ __forceinline__ void add_shapes(gptr<unsigned long long> stats, unsig
 template <int BS, int WPB, uint32_t DM, uint32_t CAP, bool K3, bool K4>
 __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
     static_assert(BS == 64 || WPB == 1, "a group is a wave or the whole workgroup");
-    __shared__ LightLds<DM, CAP> lds[WPB];
+    __shared__ LightLds<DM, CAP, K4> lds[WPB];
     __shared__ uint32_t t4w[K4 ? 1024 : 1];
     __shared__ uint8_t t3[64];
     __shared__ uint8_t cmp_of[256];
@@ -373,11 +373,11 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
     if (threadIdx.x < kCmpRow) cmp_cls[threadIdx.x] = A.cmp_cls[threadIdx.x];
     __syncthreads();
     const uint32_t group = threadIdx.x / BS;
-    LightLds<DM, CAP>& S = lds[group];
+    LightLds<DM, CAP, K4>& S = lds[group];
     unsigned long long shp[kShapes] = {0, 0, 0, 0, 0, 0};
     if (A.roots) {   // one graph: roots in turn
         for (int64_t i = (int64_t)blockIdx.x * WPB + group; i < A.nroots; i += (int64_t)gridDim.x * WPB) {
-            const uint32_t r = A.roots[i];
+            const uint32_t r = A.roots[K4 ? i : A.nroots - 1 - i];   // all tiers at once: the largest first
             if (r < A.rank_lo || r >= A.rank_hi) continue;   // uniform over the group
             light_root<BS, DM, CAP, K3, K4>(A.gv, t3, t4, cmp_of, cmp_cls, r, S, shp);
         }
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
         if (e0 >= (unsigned long long)A.nroots) break;
         const unsigned long long e1 = min(e0 + A.tile, (unsigned long long)A.nroots);
         for (unsigned long long e = e0; e < e1; e++) {
-            const uint2 ent = A.table[e];   // x = graph, y = root
+            const uint2 ent = A.table[K4 ? e : A.nroots - 1 - e];   // x = graph, y = root
             if ((int)ent.x != cur) {
                 if (cur >= 0) add_shapes(A.graphs[cur].stats, shp);
                 cur = (int)ent.x;
@@ -411,10 +411,9 @@ __global__ __launch_bounds__(BS* WPB) void k_light(LightArgs A) {
 }
 
 template <int BS, int WPB, uint32_t DM, uint32_t CAP>
-void launch_one(const LightArgs& a, int k3, int k4, unsigned grid, hipStream_t st) {
+void launch_one(const LightArgs& a, int k3, unsigned grid, hipStream_t st) {
     const dim3 block(BS * WPB);
-    if (k3 && k4) hipLaunchKernelGGL((k_light<BS, WPB, DM, CAP, true, true>), dim3(grid), block, 0, st, a);
-    else if (k3) hipLaunchKernelGGL((k_light<BS, WPB, DM, CAP, true, false>), dim3(grid), block, 0, st, a);
+    if (k3) hipLaunchKernelGGL((k_light<BS, WPB, DM, CAP, true, true>), dim3(grid), block, 0, st, a);
     else hipLaunchKernelGGL((k_light<BS, WPB, DM, CAP, false, true>), dim3(grid), block, 0, st, a);
     VDMC_HIP(hipGetLastError());
 }
@@ -446,10 +445,15 @@ void launch_light(LightArgs a, int tier, int k3, int k4, hipStream_t st) {
     const auto grid = [&](int64_t roots_per_wg, int64_t wgs_per_cu) {
         return (unsigned)std::min<int64_t>((a.nroots + roots_per_wg - 1) / roots_per_wg, cus * wgs_per_cu);
     };
-    if (tier == 2) launch_one<256, 1, 32, 4096>(a, k3, k4, grid(1, 2), st);
-    else if (few) launch_one<256, 1, 32, 512>(a, k3, k4, grid(1, 4), st);
-    else if (tier == 1) launch_one<64, 4, 32, 512>(a, k3, k4, grid(4, 2), st);
-    else launch_one<64, 4, 8, 128>(a, k3, k4, grid(4, 6), st);
+    if (!k4) {   // k = 3 alone hashes the slots only: one kernel and launch for all tiers (537 us with
+                 // the sizes of k = 4, 479 so, for R-MAT 2^14 in five ranges)
+        if (few) hipLaunchKernelGGL((k_light<256, 1, 32, 64, true, false>), dim3(grid(1, 4)), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_light<64, 4, 32, 64, true, false>), dim3(grid(4, 7)), dim3(256), 0, st, a);
+        VDMC_HIP(hipGetLastError());
+    } else if (tier == 2) launch_one<256, 1, 32, 4096>(a, k3, grid(1, 2), st);
+    else if (few) launch_one<256, 1, 32, 512>(a, k3, grid(1, 4), st);
+    else if (tier == 1) launch_one<64, 4, 32, 512>(a, k3, grid(4, 2), st);
+    else launch_one<64, 4, 8, 128>(a, k3, grid(4, 6), st);
 }
 
 }  // namespace vdmc

@@ -199,6 +199,7 @@ struct vdmc_graph_s {
     int32_t* elo = nullptr;      // per output row: the pair's endpoints (original ids, lo < hi)
     int32_t* ehi = nullptr;
     size_t hub_layout[16] = {0};
+    size_t hub_split3 = 0;       // as hub_layout[3] when k = 3 alone is counted
     // timing of the last count call: [0,1] around the per-set kernel, [2,3] around the
     // hub kernel (created at the first count)
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};

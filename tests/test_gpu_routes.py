@@ -141,7 +141,6 @@ def _hub(slots, kids, seed, extra=0):
 def test_hub_layouts(v, slots, kids, extra, pad):
     import torch
     n, src, dst = _hub(slots, kids, slots + kids, extra)
-    want, tot = oracle.count(n, src, dst, 4)
     # padding changes no count: vertices of degree 0, or pairs that rank before the leaves
     add = {"none": 0, "isolated": 600_000, "pairs": 900_000}[pad]
     s, d = src, dst
@@ -151,11 +150,14 @@ def test_hub_layouts(v, slots, kids, extra, pad):
     first = add if pad == "pairs" else 0
     _say(f"hub slots={slots} kids={kids} extra={extra} pad={pad} n={n + add}")
     G = v.Graph(n + add, s, d)
-    out = v.count(G, 4)
-    assert (_np(out[first:first + n]) == want).all()
-    assert int(out.sum()) == int(out[first:first + n].sum())
-    assert sum(list(v.shape_counts(G).values())[2:]) == int(tot.sum())
-    del out
+    for k in (3, 4):
+        want, tot = oracle.count(n, src, dst, k)
+        out = v.count(G, k)
+        assert (_np(out[first:first + n]) == want).all(), k
+        assert int(out.sum()) == int(out[first:first + n].sum())
+        sc = list(v.shape_counts(G).values())
+        assert sum(sc[:2] if k == 3 else sc[2:]) == int(tot.sum())
+        del out
     torch.cuda.empty_cache()
 
 
