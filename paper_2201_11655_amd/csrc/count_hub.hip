@@ -1269,13 +1269,18 @@ void ensure_edge_hash(vdmc_graph_s* g, hipStream_t st) {
     uint32_t eb = 10;   // load <= 1/4
     while (((size_t)1 << eb) < 4 * (size_t)std::max<int64_t>(g->pairs, 1)) eb++;
     const size_t eh_bytes = ((size_t)1 << eb) * sizeof(unsigned long long);
-    VDMC_HIP(hipMalloc(&g->ehash, eh_bytes));
-    VDMC_HIP(hipMemsetAsync(g->ehash, 0, eh_bytes, st));
+    struct Table {   // the graph's once it is filled
+        unsigned long long* p = nullptr;
+        ~Table() { (void)hipFree(p); }
+    } t;
+    VDMC_HIP(hipMalloc(&t.p, eh_bytes));
+    VDMC_HIP(hipMemsetAsync(t.p, 0, eh_bytes, st));
     const unsigned blocks = (unsigned)std::min<int64_t>((g->n + BT - 1) / BT, 65536);
     if (blocks > 0)
-        hipLaunchKernelGGL(k_edge_hash, dim3(blocks), dim3(BT), 0, st, g->off, g->split, g->adj, g->n, g->ehash, eb);
+        hipLaunchKernelGGL(k_edge_hash, dim3(blocks), dim3(BT), 0, st, g->off, g->split, g->adj, g->n, t.p, eb);
     VDMC_HIP(hipGetLastError());
     VDMC_HIP(hipStreamSynchronize(st));
+    std::swap(g->ehash, t.p);
     g->ehash_bits = eb;
 }
 

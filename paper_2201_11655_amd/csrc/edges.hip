@@ -431,68 +431,72 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
 
 }  // namespace
 
+// The index is the graph's only once it is complete: a failure on the way leaves the graph
+// without one, and the next call builds it.
 void ensure_edge_index(vdmc_graph_s* g, hipStream_t st) {
     if (g->epid) return;
     ensure_edge_hash(g, st);
     const int64_t n = g->n, P = g->pairs;
-    std::vector<void*> tmp;
-    auto alloc = [&](size_t bytes) {
-        void* p = nullptr;
-        VDMC_HIP(hipMalloc(&p, bytes ? bytes : 16));
-        tmp.push_back(p);
-        return p;
-    };
-    struct Free {
-        std::vector<void*>& v;
-        ~Free() {
+    struct Owner {
+        std::vector<void*> v;
+        void* alloc(size_t bytes) {
+            void* p = nullptr;
+            VDMC_HIP(hipMalloc(&p, bytes ? bytes : 16));
+            v.push_back(p);
+            return p;
+        }
+        ~Owner() {
             for (void* p : v) (void)hipFree(p);
         }
-    } guard{tmp};
-    uint32_t* epid = nullptr;
-    int32_t *elo = nullptr, *ehi = nullptr;
-    VDMC_HIP(hipMalloc(&epid, ((size_t)1 << g->ehash_bits) * sizeof(uint32_t)));
-    VDMC_HIP(hipMalloc(&elo, std::max<int64_t>(P, 1) * sizeof(int32_t)));
-    VDMC_HIP(hipMalloc(&ehi, std::max<int64_t>(P, 1) * sizeof(int32_t)));
-    // CSR entry -> row, upper entry -> root, and the scratch of k_edge_sets
+    } tmp, kept;
+    auto* epid = (uint32_t*)kept.alloc(((size_t)1 << g->ehash_bits) * sizeof(uint32_t));
+    auto* elo = (int32_t*)kept.alloc(P * sizeof(int32_t));
+    auto* ehi = (int32_t*)kept.alloc(P * sizeof(int32_t));
     uint32_t* work = nullptr;
-    const size_t words = (size_t)6 * P + (1 + kRootRow) * (n + 1);
-    if (n <= kEdgeSetsMaxN && hipMalloc(&work, words * sizeof(uint32_t)) != hipSuccess) {
-        (void)hipGetLastError();   // the per-set kernel needs none of it
-        work = nullptr;
+    if (n > 0 && P > 0) {
+        uint32_t* cnt = (uint32_t*)tmp.alloc((n + 1) * sizeof(uint32_t));
+        uint32_t* uoff = (uint32_t*)tmp.alloc((n + 1) * sizeof(uint32_t));
+        auto* keys = (unsigned long long*)tmp.alloc(P * sizeof(unsigned long long));
+        auto* keys_s = (unsigned long long*)tmp.alloc(P * sizeof(unsigned long long));
+        uint32_t* vals = (uint32_t*)tmp.alloc(P * sizeof(uint32_t));
+        uint32_t* vals_s = (uint32_t*)tmp.alloc(P * sizeof(uint32_t));
+        uint32_t* row_of = (uint32_t*)tmp.alloc(P * sizeof(uint32_t));
+        size_t tb = 0, sb = 0;
+        VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, uoff, (int)n, st));
+        VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sb, keys, keys_s, vals, vals_s, (int)P, 0, 64, st));
+        void* t1 = tmp.alloc(std::max(tb, sb));   // the sort follows the scan on the stream
+        // CSR entry -> row, upper entry -> root, and the scratch of k_edge_sets, where there is memory
+        // beside what the index needs (the per-set kernel does without)
+        const size_t words = (size_t)6 * P + (1 + kRootRow) * (n + 1);
+        if (n <= kEdgeSetsMaxN) {
+            if (hipMalloc(&work, words * sizeof(uint32_t)) == hipSuccess) {
+                kept.v.push_back(work);
+            } else {
+                (void)hipGetLastError();
+                work = nullptr;
+            }
+        }
+        hipLaunchKernelGGL(k_upper_counts, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, n, cnt);
+        VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(t1, tb, cnt, uoff, (int)n, st));
+        hipLaunchKernelGGL(k_pair_keys, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, g->adj, g->perm, n,
+                           uoff, keys, vals);
+        VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(t1, sb, keys, keys_s, vals, vals_s, (int)P, 0, 64, st));
+        hipLaunchKernelGGL(k_rows, dim3(blocks_of(P)), dim3(ET), 0, st, keys_s, vals_s, P, row_of, elo, ehi);
+        hipLaunchKernelGGL(k_slot_rows, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff, row_of,
+                           g->ehash, g->ehash_bits, epid);
+        if (work) {
+            VDMC_HIP(hipMemcpyAsync(work + 6 * P, uoff, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+            hipLaunchKernelGGL(k_entry_rows, dim3(blocks_of(n * 64)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff,
+                               g->ehash, g->ehash_bits, epid, work, work + 2 * P);
+        }
+        VDMC_HIP(hipGetLastError());
+        VDMC_HIP(hipStreamSynchronize(st));
     }
-    g->epid = epid;   // owned by the graph from here on
+    kept.v.clear();   // the graph's from here on
+    g->epid = epid;
     g->elo = elo;
     g->ehi = ehi;
     g->ework = work;
-    if (n == 0 || P == 0) return;
-    uint32_t* cnt = (uint32_t*)alloc((n + 1) * sizeof(uint32_t));
-    uint32_t* uoff = (uint32_t*)alloc((n + 1) * sizeof(uint32_t));
-    auto* keys = (unsigned long long*)alloc(P * sizeof(unsigned long long));
-    auto* keys_s = (unsigned long long*)alloc(P * sizeof(unsigned long long));
-    uint32_t* vals = (uint32_t*)alloc(P * sizeof(uint32_t));
-    uint32_t* vals_s = (uint32_t*)alloc(P * sizeof(uint32_t));
-    uint32_t* row_of = (uint32_t*)alloc(P * sizeof(uint32_t));
-    hipLaunchKernelGGL(k_upper_counts, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, n, cnt);
-    size_t tb = 0;
-    VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, uoff, (int)n, st));
-    void* t1 = alloc(tb);
-    VDMC_HIP(hipcub::DeviceScan::ExclusiveSum(t1, tb, cnt, uoff, (int)n, st));
-    hipLaunchKernelGGL(k_pair_keys, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, g->adj, g->perm, n,
-                       uoff, keys, vals);
-    size_t sb = 0;
-    VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sb, keys, keys_s, vals, vals_s, (int)P, 0, 64, st));
-    void* t2 = alloc(sb);
-    VDMC_HIP(hipcub::DeviceRadixSort::SortPairs(t2, sb, keys, keys_s, vals, vals_s, (int)P, 0, 64, st));
-    hipLaunchKernelGGL(k_rows, dim3(blocks_of(P)), dim3(ET), 0, st, keys_s, vals_s, P, row_of, elo, ehi);
-    hipLaunchKernelGGL(k_slot_rows, dim3(blocks_of(n)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff, row_of,
-                       g->ehash, g->ehash_bits, epid);
-    if (work) {
-        VDMC_HIP(hipMemcpyAsync(work + 6 * P, uoff, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
-        hipLaunchKernelGGL(k_entry_rows, dim3(blocks_of(n * 64)), dim3(ET), 0, st, g->off, g->split, g->adj, n, uoff,
-                           g->ehash, g->ehash_bits, epid, work, work + 2 * P);
-    }
-    VDMC_HIP(hipGetLastError());
-    VDMC_HIP(hipStreamSynchronize(st));
 }
 
 void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {
