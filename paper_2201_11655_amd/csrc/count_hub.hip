@@ -1150,14 +1150,15 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     }
 }
 
-// the compact rows of the hub path added to the output (48 lanes per vertex; one writer per cell)
+// the compact rows of the hub path added to the output (48 lanes per vertex), atomically: two
+// graphs' accumulated ranges may add to one output from two streams
 __global__ __launch_bounds__(192) void k_expand(const void* cmp, int wide, int64_t n, const int32_t* __restrict__ perm,
                                                 const uint8_t* __restrict__ cmp_cls, unsigned long long* out4) {
     const uint32_t s = threadIdx.x % kCmpRow, cls = cmp_cls[s];
     for (int64_t v = blockIdx.x * 4ll + threadIdx.x / kCmpRow; v < n; v += gridDim.x * 4ll) {
         const size_t at = (size_t)v * kCmpRow + s;
         const unsigned long long x = wide ? ((const unsigned long long*)cmp)[at] : ((const uint32_t*)cmp)[at];
-        if (x) out4[(size_t)perm[v] * kClasses4 + cls] += x;
+        if (x) gadd64(&out4[(size_t)perm[v] * kClasses4 + cls], x);
     }
 }
 
