@@ -39,6 +39,13 @@ constexpr uint32_t DMAX = kHubMaxDegree;   // largest |N+(r)| (and largest degre
 constexpr uint32_t CW = DMAX / 16;         // words of a 2-bit code row over the slots
 constexpr uint32_t SHASH = 4096;           // slot hash entries (u16 slot + 1), load <= 1/2
 constexpr uint32_t NSTAR = 10;             // star classes
+// LARGE: phase G credits end vertices path by path where the rows of a root's depth-2 vertices hold
+// less than 1 / kEndsDiv of the graph's entries, else each end once, from its own row, all of which it
+// then reads.  G(n, p) of 1e5 vertices of degree 40, every root one way 58 ms, the other 157; R-MAT
+// 2^17 314 and 203.  With 4, 8 and 16: R-MAT 2^17 215, 203 and 204 ms, Chung-Lu 1e6 1.80, 1.85 and 1.91 s,
+// G(n, p) of degree 120 1.57, 1.56 and 1.80 s.
+constexpr unsigned long long kEndsDiv = 8;
+constexpr int64_t kHubSmallN = 65536;      // LARGE above it: Chung-Lu 1e5 38.0 -> 34.7 ms, R-MAT 2^15 23.9 -> 25.2
 constexpr unsigned long long INV3 = 0xAAAAAAAAAAAAAAABull;      // 3 * INV3 = 1 mod 2^64
 
 struct HubArgs {
@@ -65,6 +72,7 @@ struct HubArgs {
     size_t wg_words;
     uint32_t s2cap;
     uint32_t n;                  // vertices
+    uint32_t hash_below;         // LARGE: roots with fewer entries index their depth-2 vertices by a hash
     void* cmp;                   // compact rows (n x kCmpRow counters, zeroed), or nullptr
     int cmp_wide;                // 64-bit counters instead of 32-bit
     uint32_t split_roots;        // the first split_roots hub roots (the heaviest) ...
@@ -129,44 +137,121 @@ __device__ __forceinline__ void cmp_line(const HubArgs& A, uint32_t v, uint32_t 
     }
 }
 
-// The depth-2 vertices of a root: bitmap B over ranks, P[w] = how many lie before word w (for
-// words that hold one), in LDS or in the workgroup's scratch.
+// n sets to counter s of vertex v's compact row, by one lane
+__device__ __forceinline__ void cmp_add(const HubArgs& A, uint32_t v, uint32_t s, uint32_t n) {
+    const size_t at = (size_t)v * kCmpRow + s;
+    if (A.cmp == nullptr) gadd(A.out4, A.perm, kClasses4, v, A.cmp_cls[s], n);
+    else if (A.cmp_wide) atomicAdd((unsigned long long*)A.cmp + at, (unsigned long long)n);
+    else atomicAdd((uint32_t*)A.cmp + at, n);
+}
+
+// the count of code s (0..8) in a depth-2 vertex's parents by code
+__device__ __forceinline__ uint32_t parents_of(ulonglong2 pc, uint32_t s) {
+    return (uint32_t)(s < 5u ? pc.x >> (12u * s) : pc.y >> (12u * (s - 5u))) & 0xFFFu;
+}
+
+// The depth-2 vertices of a root, numbered: a bitmap B over ranks and P[w] = how many lie before
+// word w (for words that hold one), or, LARGE, a hash of them, in LDS or in the workgroup's scratch.
+// The bitmap costs a root n / 32 words whatever it reaches, the hash 3/2 of its entries: 5000 trees of
+// 40 x 4 vertices in 2^22 vertices 27.4 ms with the bitmap, 1.2 with the hash.  A find in the hash costs
+// more, which phase E, where most of them are, does without.
+template <bool LARGE>
 struct Index2 {
-    bool in_lds;
-    lptr<uint32_t> lb, lp;
-    gptr<uint32_t> gb, gp;
-    __device__ __forceinline__ Index2(bool lds, uint32_t* l, uint32_t* g, uint32_t nbw)
-        : in_lds(lds), lb(l), lp(l + nbw), gb(g), gp(g + nbw) {}
-    __device__ __forceinline__ uint32_t word(uint32_t w) const { return in_lds ? lb[w] : gb[w]; }
-    __device__ __forceinline__ uint32_t before(uint32_t w) const { return in_lds ? lp[w] : gp[w]; }
-    __device__ __forceinline__ void mark(uint32_t e) const {
-        const uint32_t bit = 1u << (e & 31u);
-        if (in_lds) __hip_atomic_fetch_or((lb + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else __hip_atomic_fetch_or((gb + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    static constexpr uint32_t kTag = 0xFFC00000u;   // hash slot: 10 bits of the product, number + 1; 0 = empty
+    bool in_lds, hashed;
+    lptr<uint32_t> l;
+    gptr<uint32_t> g;
+    uint32_t w;                  // words of the bitmap, or slots of the hash
+    gptr<const uint32_t> ids;    // number -> vertex
+    __device__ __forceinline__ Index2(bool lds, bool hash, uint32_t* lp, uint32_t* gp, uint32_t words,
+                                      const uint32_t* v)
+        : in_lds(!LARGE || lds), hashed(LARGE && hash), l(lp), g(gp), w(words), ids((uint32_t*)v) {}
+    // words of the index for a root with `entries` entries above it in its slots' rows
+    static __host__ __device__ __forceinline__ uint32_t slots(uint32_t entries) { return entries + entries / 2u + 1u; }
+    __device__ __forceinline__ uint32_t word(uint32_t i) const { return in_lds ? l[i] : g[i]; }
+    __device__ __forceinline__ uint32_t before(uint32_t i) const { return in_lds ? l[w + i] : g[w + i]; }
+    __device__ __forceinline__ void set(uint32_t i, uint32_t x) const {
+        if (in_lds) l[i] = x;
+        else g[i] = x;
     }
-    __device__ __forceinline__ void set_before(uint32_t w, uint32_t j) const {
-        if (in_lds) lp[w] = j;
-        else gp[w] = j;
-    }
-    __device__ __forceinline__ void clear(uint32_t nbw) const {
+    __device__ __forceinline__ void set_before(uint32_t i, uint32_t j) const { set(w + i, j); }
+    __device__ __forceinline__ uint32_t cas(uint32_t i, uint32_t x) const {   // 0 -> x; what it was
+        uint32_t old = 0;
         if (in_lds)
-            for (uint32_t i = threadIdx.x; i < nbw; i += HT) lb[i] = 0u;
+            __hip_atomic_compare_exchange_strong((l + i), &old, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
         else
-            for (uint32_t i = threadIdx.x; i < nbw; i += HT) gb[i] = 0u;
+            __hip_atomic_compare_exchange_strong((g + i), &old, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        return old;
     }
-    // index of vertex e among the depth-2 vertices, or ~0
+    __device__ __forceinline__ uint32_t next(uint32_t h) const { return h + 1u < w ? h + 1u : 0u; }
+    // marks vertex e; a hash holds e + 1 until number() is called
+    __device__ __forceinline__ void mark(uint32_t e) const {
+        if (hashed) {
+            for (uint32_t h = __umulhi(e * 0x9E3779B1u, w);; h = next(h)) {
+                uint32_t k = word(h);
+                if (k == 0u) k = cas(h, e + 1u);
+                if (k == 0u || k == e + 1u) return;
+            }
+        }
+        const uint32_t bit = 1u << (e & 31u);
+        if (in_lds) __hip_atomic_fetch_or((l + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_fetch_or((g + (e >> 5)), bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // a hash of marks numbered in any order (every thread; *ctr = 0 before, their number after)
+    __device__ __forceinline__ void number(uint32_t* ctr, uint32_t* cids) const {
+        for (uint32_t i0 = wave_id() * 64u; i0 < w; i0 += HT) {
+            const uint32_t i = i0 + lane_id();
+            uint32_t k = 0;
+            if (i < w) k = in_lds ? l[i] : __hip_atomic_load((g + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long m = __ballot(k != 0u);
+            if (m == 0ull) continue;
+            uint32_t j = 0;
+            if (lane_id() == 0) j = atomicAdd(ctr, (uint32_t)__popcll(m));
+            j = (uint32_t)__builtin_amdgcn_readfirstlane((int)j) + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull));
+            if (k) {
+                cids[j] = k - 1u;
+                set(i, (((k - 1u) * 0x9E3779B1u) << 22) | (j + 1u));
+            }
+        }
+    }
+    __device__ __forceinline__ void clear() const {
+        if (in_lds)
+            for (uint32_t i = threadIdx.x; i < w; i += HT) l[i] = 0u;
+        else
+            for (uint32_t i = threadIdx.x; i < w; i += HT) g[i] = 0u;
+    }
+    // number of vertex e among the depth-2 vertices, or ~0: from the bitmap; from either
+    __device__ __forceinline__ uint32_t find_bit(uint32_t e) const {
+        const uint32_t b = word(e >> 5), bit = 1u << (e & 31u);
+        return (b & bit) ? before(e >> 5) + (uint32_t)__popc(b & (bit - 1u)) : ~0u;
+    }
     __device__ __forceinline__ uint32_t find(uint32_t e) const {
-        const uint32_t w = word(e >> 5), bit = 1u << (e & 31u);
-        return (w & bit) ? before(e >> 5) + (uint32_t)__popc(w & (bit - 1u)) : ~0u;
+        if (hashed) {
+            const uint32_t x = e * 0x9E3779B1u;
+            for (uint32_t h = __umulhi(x, w);; h = next(h)) {
+                const uint32_t s = word(h);
+                if (s == 0u) return ~0u;
+                if ((s & kTag) == (x << 22) && ids[(s & ~kTag) - 1u] == e) return (s & ~kTag) - 1u;
+            }
+        }
+        return find_bit(e);
     }
-    // from the ascending list of the depth-2 vertices (every thread of the workgroup)
-    __device__ __forceinline__ void fill(uint32_t nbw, const uint32_t* cids, uint32_t nc) const {
-        clear(nbw);
+    // from the list of the depth-2 vertices, ascending for the bitmap (every thread of the workgroup)
+    __device__ __forceinline__ void fill(uint32_t nc) const {
+        clear();
         __syncthreads();
         for (uint32_t j = threadIdx.x; j < nc; j += HT) {
-            const uint32_t c = cids[j];
+            const uint32_t c = ids[j];
+            if (hashed) {
+                const uint32_t x = c * 0x9E3779B1u;
+                uint32_t h = __umulhi(x, w);
+                while (cas(h, (x << 22) | (j + 1u))) h = next(h);
+                continue;
+            }
             mark(c);
-            if (j == 0u || (cids[j - 1u] >> 5) != (c >> 5)) set_before(c >> 5, j);
+            if (j == 0u || (ids[j - 1u] >> 5) != (c >> 5)) set_before(c >> 5, j);
         }
     }
 };
@@ -260,6 +345,23 @@ __device__ uint32_t block_scan(uint32_t* a, uint32_t len, uint32_t* part) {
 
 constexpr uint32_t U_WORDS = 34000;   // the phase-dependent region (133 KiB)
 
+// the fixed part of it in phases E and G
+constexpr uint32_t E_GW = 96;   // words per 16-lane group: 3 lines, 9 + 36 pair counts
+constexpr uint32_t E_AW = 200;  // words per wave: a's classes
+constexpr uint32_t E_FIX = (HT / 16) * E_GW + NW * E_AW + NW * CW + SHASH / 2;
+constexpr uint32_t G_EB = 4;    // end vertices per group between two flushes
+constexpr uint32_t G_FIX = (HT / 16) * 16 * G_EB + NW * CW + SHASH / 2 + 32;
+constexpr uint32_t G_WIN = 4096;   // least words of a window of ranks
+
+// whether an index of iw words fits LDS for every root of up to D slots: in phases B and G (a hash);
+// in phase E too (a bitmap)
+bool hash_fits(size_t D, size_t iw) {
+    return SHASH / 2 + HT + D * kClasses3 + iw <= U_WORDS && G_FIX + iw + G_WIN <= U_WORDS;
+}
+bool bitmap_fits(size_t D, size_t iw) {
+    return hash_fits(D, iw) && D * 5 + 2 + E_FIX + iw + NW * (FILTER_BITS / 32) <= U_WORDS;
+}
+
 struct HubLds {
     uint32_t P[DMAX];                  // slots: (rank << 2) | arc bits r -> slot
     uint16_t locn[DMAX];               // local neighbours per slot
@@ -271,6 +373,7 @@ struct HubLds {
     uint8_t maps[768];
     uint32_t ctr[8];
     uint32_t seg[2];                   // first slot with arc code 2, 3 to r
+    unsigned long long ends;           // entries in the rows of the depth-2 vertices (LARGE)
     alignas(16) uint32_t U[U_WORDS];
 };
 static_assert(sizeof(HubLds) + 16 <= 163840, "one workgroup's LDS");
@@ -291,7 +394,10 @@ __device__ __forceinline__ void build_row(uint32_t* row, const uint32_t* locnbr,
 
 // K4 = false (k = 3 alone): phases A, B and C3 only.  A kernel of its own (54 registers), as
 // the other's spill, which a launch of some 40 us feels: R-MAT 2^10, five ranges, 271 -> 250 us.
-template <bool K4>
+// LARGE (graphs whose bitmap of the depth-2 vertices is not in LDS for every root, or of more than
+// kHubSmallN vertices): no part of a root's cost grows with n unless its entries do, see Index2 and
+// kEndsDiv.  The other index and way of crediting end vertices take 9 registers more to spill.
+template <bool K4, bool LARGE>
 __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     __shared__ HubLds L;
     __shared__ uint32_t sRoot;
@@ -314,7 +420,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     // word, four in the second, and above them the mask of the non-zero ones
     ulonglong2* pcount = (ulonglong2*)(S + ((DMAX + 2 + 4 * (size_t)A.s2cap + 3) & ~(size_t)3));
     uint32_t* place = (uint32_t*)pcount;
-    uint32_t* gbits = (uint32_t*)(pcount + A.s2cap);             // 2 x nbw: B2 and P2 when LDS has no room
+    uint32_t* gidx = (uint32_t*)(pcount + A.s2cap);              // the index of the depth-2 vertices when
+                                                                 // LDS has no room (LARGE)
     const uint32_t nbw = (A.n + 31u) >> 5;
     unsigned long long shp[kShapes] = {0, 0, 0, 0, 0, 0};
 
@@ -380,16 +487,19 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         if (tid == 0) locoff[D] = 0u;
         __syncthreads();
         uint32_t* part = L.U + SHASH / 2;   // HT words after the slot hash
-        block_scan(locoff, D + 1, part);
+        const uint32_t entries = block_scan(locoff, D + 1, part);
         // ---- phase B: rows of the slots: local lists, depth-2 entries, k = 3 (1,2)
         uint32_t* R3 = L.U + SHASH / 2 + HT;   // D x 13 k = 3 counters of the slots
         if (A.k3)
             for (uint32_t i = tid; i < D * kClasses3; i += HT) R3[i] = 0u;
-        // the depth-2 vertices in a bitmap over ranks, in LDS where it fits
+        // the index of the depth-2 vertices, in LDS where it fits
         const uint32_t used = SHASH / 2 + HT + (A.k3 ? D * kClasses3 : 0u);
-        const bool kept = used + 2u * nbw > U_WORDS;   // in scratch: phases E and G find it there
-        const Index2 X2(!kept, L.U + used, gbits, nbw);
-        if (K4) X2.clear(nbw);
+        const bool hashed = LARGE && entries < A.hash_below;
+        const uint32_t iw = hashed ? Index2<LARGE>::slots(entries) : 2u * nbw;   // its words
+        const uint32_t isz = hashed ? iw : nbw;
+        const bool kept = LARGE && used + iw > U_WORDS;   // in scratch: phases E and G find it there
+        const Index2<LARGE> X2(!kept, hashed, L.U + used, gidx, isz, cids);
+        if (K4) X2.clear();
         __syncthreads();
         for (;;) {
             const uint32_t x = wave_task(&L.ctr[0]);
@@ -445,16 +555,22 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
             }
         }
         __syncthreads();
-        // the depth-2 vertices numbered in rank order (cids), their parents gathered:
+        // the depth-2 vertices numbered (cids; by the bitmap in rank order), their parents gathered:
         // A(c_j) = parents[poff[j] .. poff[j + 1])
         uint32_t ngroups = 0;
         if (K4) {
-            for (uint32_t i = tid; i < nbw; i += HT) X2.set_before(i, (uint32_t)__popc(X2.word(i)));
-            __syncthreads();
-            ngroups = kept ? block_scan(gbits + nbw, nbw, part) : block_scan(L.U + used + nbw, nbw, part);
-            for (uint32_t i = tid; i < nbw; i += HT) {
-                uint32_t at = X2.before(i);
-                for (uint32_t w = X2.word(i); w; w &= w - 1u) cids[at++] = (i << 5) + (uint32_t)__ffs((int)w) - 1u;
+            if (hashed) {
+                X2.number(&L.ctr[1], cids);
+                __syncthreads();
+                ngroups = L.ctr[1];
+            } else {
+                for (uint32_t i = tid; i < nbw; i += HT) X2.set_before(i, (uint32_t)__popc(X2.word(i)));
+                __syncthreads();
+                ngroups = kept ? block_scan(gidx + nbw, nbw, part) : block_scan(L.U + used + nbw, nbw, part);
+                for (uint32_t i = tid; i < nbw; i += HT) {
+                    uint32_t at = X2.before(i);
+                    for (uint32_t w = X2.word(i); w; w &= w - 1u) cids[at++] = (i << 5) + (uint32_t)__ffs((int)w) - 1u;
+                }
             }
             for (uint32_t j = tid; j <= ngroups; j += HT) poff[j] = 0u;
             __syncthreads();
@@ -742,6 +858,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 }
         }
         __syncthreads();
+        if (!LARGE || ngroups > 0u) {   // LARGE: no depth-2 vertex, no more sets
         // ---- phase D: per slot x, the other slots by their codes to r and to x (NX), and x's
         // (2,1,0) sets as the second slot y: below every other slot x' and its children, by
         // code, as if none were adjacent to y (the children that x and x' share are taken out
@@ -819,30 +936,28 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // them); a's and r's are summed in LDS.
         const uint32_t gl = lane & 15u;
         {
-            constexpr uint32_t GW = 96;            // words per 16-lane group: 3 lines, 9 + 36 pair counts
-            constexpr uint32_t AW = 200;           // words per wave: a's classes
-            constexpr uint32_t FW = FILTER_BITS / 32;
-            constexpr uint32_t FIX = (HT / 16) * GW + NW * AW + NW * CW + SHASH / 2;
+            constexpr uint32_t GW = E_GW, AW = E_AW, FW = FILTER_BITS / 32, FIX = E_FIX;
             // a's children as a bitmap a plane over the depth-2 vertices (their arc codes), where
-            // LDS holds that for every wave beside B2 and P2; else as a filter over hashed ranks
-            // in front of a search of a's row (hubs with very many depth-2 vertices)
+            // LDS holds that for every wave beside the index; else as a filter over hashed ranks
+            // in front of a search of a's row (hubs with very many depth-2 vertices, and those with
+            // few, whose hash is not needed here then)
             const uint32_t jw = (ngroups + 31u) >> 5;
-            const bool coded = nxw + FIX + 2u * nbw + 2u * NW * jw <= U_WORDS;
+            const bool coded = !hashed && nxw + FIX + iw + 2u * NW * jw <= U_WORDS;
             const uint32_t mw = coded ? 2u * jw : FW;               // words per wave
-            const bool in_lds = nxw + FIX + 2u * nbw + NW * mw <= U_WORDS;
+            const bool in_lds = nxw + FIX + iw + NW * mw <= U_WORDS;
             uint32_t* GC = L.U + nxw + (tid >> 4) * GW;
             uint32_t* AC = L.U + nxw + (HT / 16) * GW + wid * AW;
             uint32_t* BX = L.U + nxw + (HT / 16) * GW + NW * AW + wid * CW;   // per wave: a's code row
             uint16_t* H2 = (uint16_t*)(L.U + nxw + (HT / 16) * GW + NW * AW + NW * CW);
             uint32_t* M0 = L.U + nxw + FIX + wid * mw;              // children with arc bit 0, or the filter
             uint32_t* M1 = M0 + jw;                                 // children with arc bit 1
-            const Index2 X2(in_lds, L.U + nxw + FIX + NW * mw, gbits, nbw);
+            const Index2<LARGE> X2(in_lds, false, L.U + nxw + FIX + NW * mw, gidx, isz, cids);
             for (uint32_t i = nxw + tid; i < nxw + FIX; i += HT) L.U[i] = 0u;
             for (uint32_t i = lane; i < mw; i += 64) M0[i] = 0u;
             if (tid == 0) L.ctr[6] = 0u;
             __syncthreads();
             for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
-            if (in_lds || !kept) X2.fill(nbw, cids, ngroups);
+            if (!hashed && (!LARGE || in_lds || !kept)) X2.fill(ngroups);
             __syncthreads();
             auto add_r = [&](uint32_t cls, uint32_t n) {
                 atomicAdd(&L.root4[cls], (unsigned long long)(long long)(int32_t)n);
@@ -891,7 +1006,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                 for (uint32_t i0 = 0; i0 < m; i0 += 4u) {
                     const uint32_t i = i0 + (lane >> 4);
                     const bool on = i < m;
-                    const uint32_t j = ent >> 2, ac = ent & 3u, na = f1 - f0;
+                    const uint32_t ac = ent & 3u, na = f1 - f0;
                     const uint32_t cn = cids[ent1 >> 2], f0n = poff[ent1 >> 2], f1n = poff[(ent1 >> 2) + 1u];
                     const uint32_t ent2 = entry(i + 8u);
                     if (on && na > 1u)   // the other parents of c by codes, those above a in the high half
@@ -909,25 +1024,34 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                         if (e <= r || slot_find(H2, L.P, e) >= 0) continue;
                         if (ce == 3u) e3++;
                         else e12 += ce == 1u ? 1u : 1u << 16;
-                        uint32_t ae = 0, j2 = 0;   // e another child of a: its code
+                        uint32_t ae = 0;   // e another child of a: its code
                         if (coded) {
-                            j2 = X2.find(e);
-                            if (j2 == ~0u) continue;
-                            ae = ((M0[j2 >> 5] >> (j2 & 31u)) & 1u) | (((M1[j2 >> 5] >> (j2 & 31u)) & 1u) << 1);
+                            const uint32_t j = X2.find_bit(e);
+                            if (j == ~0u) continue;
+                            ae = ((M0[j >> 5] >> (j & 31u)) & 1u) | (((M1[j >> 5] >> (j & 31u)) & 1u) << 1);
                         } else {
                             const uint32_t b = filter_bit(e);
                             if (!((M0[b >> 5] >> (b & 31u)) & 1u)) continue;
-                            j2 = X2.find(e);
-                            if (j2 == ~0u) continue;
                             uint32_t lo = 0, hi = m;
-                            while (lo + 1u < hi) {
-                                const uint32_t mid = (lo + hi) >> 1;
-                                if ((locnbr[end - 1u - mid] >> 2) <= j2) lo = mid; else hi = mid;
+                            if (!hashed) {   // a's row is in the order of the bitmap's numbers
+                                const uint32_t j = X2.find_bit(e);
+                                if (j == ~0u) continue;
+                                while (lo + 1u < hi) {
+                                    const uint32_t mid = (lo + hi) >> 1;
+                                    if ((locnbr[end - 1u - mid] >> 2) <= j) lo = mid; else hi = mid;
+                                }
+                                const uint32_t x = locnbr[end - 1u - lo];
+                                ae = (x >> 2) == j ? x & 3u : 0u;
+                            } else {
+                                while (lo + 1u < hi) {
+                                    const uint32_t mid = (lo + hi) >> 1;
+                                    if (cids[locnbr[end - 1u - mid] >> 2] <= e) lo = mid; else hi = mid;
+                                }
+                                const uint32_t x = locnbr[end - 1u - lo];
+                                ae = cids[x >> 2] == e ? x & 3u : 0u;
                             }
-                            const uint32_t ent2 = locnbr[end - 1u - lo];
-                            ae = (ent2 >> 2) == j2 ? ent2 & 3u : 0u;
                         }
-                        if (ae) atomicAdd(&GC[48u + (ae - 1u) * 3u + ce - 1u], j2 > j ? 0x10001u : 1u);
+                        if (ae) atomicAdd(&GC[48u + (ae - 1u) * 3u + ce - 1u], e > c ? 0x10001u : 1u);
                     }
                     const uint32_t x0n = q0n < q1n ? A.adj[q0n] : 0u;
                     e12 = row16_sum(e12);
@@ -1046,23 +1170,54 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // its paths, parents adjacent to e included (phase E took those out).  Credited path by
         // path instead, the ends alone would take a memory-side atomic per (1,1,1) set.
         {
-            constexpr uint32_t EB = 4;          // end vertices per group between two flushes
-            constexpr uint32_t GW = 16 * EB;    // words per 16-lane group: 16 path counters each
-            constexpr uint32_t FIX = (HT / 16) * GW + NW * CW + SHASH / 2 + 32;
-            const bool in_lds = FIX + 2u * nbw + 4096u <= U_WORDS;
+            constexpr uint32_t EB = G_EB, GW = 16 * EB, FIX = G_FIX;   // a group: 16 path counters per end vertex
+            const bool in_lds = FIX + iw + G_WIN <= U_WORDS;
             uint32_t* GC = L.U + (tid >> 4) * GW;
             uint16_t* LST = (uint16_t*)(L.U + (HT / 16) * GW + wid * CW);   // per wave: 256 marked vertices
             uint16_t* H2 = (uint16_t*)(L.U + (HT / 16) * GW + NW * CW);
             uint32_t* KS = L.U + FIX - 32;   // path counter of the codes ((r -> a, a -> c) - 1) * 3 + (c -> e) - 1
-            const Index2 X2(in_lds, L.U + FIX, gbits, nbw);
-            uint32_t* BM = L.U + FIX + (in_lds ? 2u * nbw : 0u);
+            const Index2<LARGE> X2(in_lds, hashed, L.U + FIX, gidx, isz, cids);
+            uint32_t* BM = L.U + FIX + (in_lds ? iw : 0u);
             const uint32_t win = min(nbw, U_WORDS - (uint32_t)(BM - L.U));   // words of a window
             for (uint32_t i = tid; i < FIX - 32; i += HT) L.U[i] = 0u;
             if (tid < 27u)
                 KS[tid] = cmp_of[L.t4[motif_index4(tid / 9u + 1u, 0u, 0u, tid % 9u / 3u + 1u, 0u, tid % 3u + 1u)]];
             __syncthreads();
             for (uint32_t i = tid; i < D; i += HT) slot_insert(H2, L.P[i] >> 2, i);
-            if (in_lds || !kept) X2.fill(nbw, cids, ngroups);
+            bool direct = false;
+            if (LARGE) {
+                unsigned long long sum = 0;
+                if (tid == 0) L.ends = 0ull;
+                if (tid < 2) L.ctr[6 + tid] = 0u;
+                __syncthreads();
+                for (uint32_t j = tid; j < ngroups; j += HT) {
+                    const uint32_t c = cids[j];
+                    if (c % G == share) sum += A.off[c + 1] - A.off[c];
+                }
+                if (sum) atomicAdd(&L.ends, sum);
+                __syncthreads();
+                direct = L.ends * kEndsDiv < (unsigned long long)A.off[A.n];
+            }
+            if (direct) {
+                for (;;) {   // 16 lanes per depth-2 vertex c
+                    const uint32_t t = wave_task(&L.ctr[6]);
+                    if (t * 4u >= ngroups) break;
+                    const uint32_t j = t * 4u + (lane >> 4);
+                    const uint32_t c = j < ngroups ? cids[j] : 0u;
+                    const bool own = j < ngroups && c % G == share;
+                    const ulonglong2 pc = own ? pcount[j] : make_ulonglong2(0ull, 0ull);
+                    const uint32_t q1 = own ? A.off[c + 1] : 0u;
+                    for (uint32_t q = (own ? A.off[c] : 0u) + gl; q < q1; q += 16u) {
+                        const uint32_t ee = A.adj[q], e = ee >> 2, ce = (ee & 3u) - 1u;
+                        if (e <= r || slot_find(H2, L.P, e) >= 0) continue;
+                        for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {
+                            const uint32_t s = (uint32_t)__ffs((int)mk) - 1u;
+                            cmp_add(A, e, KS[s * 3u + ce], parents_of(pc, s));
+                        }
+                    }
+                }
+            } else {
+            if (!LARGE || in_lds || !kept) X2.fill(ngroups);
             for (uint32_t w0 = (r + 1u) >> 5; w0 < nbw; w0 += win) {
                 const uint32_t wn = min(win, nbw - w0), e0 = w0 << 5;
                 __syncthreads();
@@ -1116,9 +1271,7 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                                 const ulonglong2 pc = pcount[j];
                                 for (uint32_t mk = (uint32_t)(pc.y >> 48); mk; mk &= mk - 1u) {
                                     const uint32_t s = (uint32_t)__ffs((int)mk) - 1u;
-                                    const unsigned long long f = s < 5u ? pc.x >> (12u * s) : pc.y >> (12u * (s - 5u));
-                                    const uint32_t n = (uint32_t)f & 0xFFFu;
-                                    atomicAdd(&GC[eb * 16u + KS[s * 3u + ce]], n);
+                                    atomicAdd(&GC[eb * 16u + KS[s * 3u + ce]], parents_of(pc, s));
                                 }
                             }
                             q0 = q0n;
@@ -1137,6 +1290,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
                     }
                 }
             }
+            }
+        }
         }
         __syncthreads();
         for (uint32_t i = tid; i < kClasses4; i += HT)
@@ -1359,8 +1514,22 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     if (nhub > 0) {
         const int wgs = hub_workgroups();
         const size_t s2cap = (size_t)max_s2 + 64;
-        const size_t words = (DMAX + 2) + 8 * s2cap + 4 + 2 * (((size_t)g->n + 31) / 32);
-        const size_t wg_words = (words + 63) & ~(size_t)63;
+        const size_t nbw = ((size_t)g->n + 31) / 32, base = (DMAX + 2) + 8 * s2cap + 4;
+        // The index of the depth-2 vertices (see Index2): a bitmap for roots with nbw / 2 entries or more
+        // (R-MAT 2^19 0.88 s, from nbw on 0.91), none if no root has nbw: bitmaps in scratch leave
+        // workgroups out where nbw is large against the roots' rows (G(n, p) of 1e6 vertices of degree
+        // 40, a bitmap from nbw / 16 on, 24 workgroups: 2.5 s, 0.71 without).
+        const bool fits = bitmap_fits((size_t)maxhi, 2 * nbw);
+        const bool large = !fits || g->n > kHubSmallN;
+        const size_t hash_below = max_s2 < nbw ? (size_t)0xFFFFFFFFu : nbw / 2;
+        const size_t most = std::min<size_t>(max_s2, hash_below);   // entries of a root with a hash
+        size_t index = 0;                                           // scratch for it, where LDS may not hold it
+        if (!fits && max_s2 >= nbw) index = 2 * nbw;
+        if (large && !hash_fits((size_t)maxhi, Index2<true>::slots((uint32_t)most)))
+            index = std::max<size_t>(index, Index2<true>::slots((uint32_t)most));
+        const size_t wg_words = (base + index + 63) & ~(size_t)63;
+        g->hub_large = large;
+        g->hub_hash_below = (uint32_t)hash_below;
         g->hub_layout[0] = wg_words;
         g->hub_layout[1] = s2cap;
         // Workgroups (hub_layout[5]): one per compute unit, no more than there are roots and
@@ -1368,14 +1537,15 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
         // class of a vertex has at most 2 max_deg^3 paths or stars in a call, which 32 bits hold
         // up to degree 1290.  Together they stay within the scratch of one workgroup per
         // compute unit; graphs whose rows would take more than half of that go without.
-        const size_t wg_bytes = wg_words * sizeof(uint32_t), room = wg_bytes * (size_t)wgs;
+        const size_t wg_bytes = wg_words * sizeof(uint32_t);
+        const size_t room = ((base + 60 + 63) & ~(size_t)63) * sizeof(uint32_t) * (size_t)wgs;
         const double dm = (double)g->max_deg;
         const int wide = 2.0 * dm * dm * dm >= 4294967296.0 ? 1 : 0;
         const size_t rows = (((size_t)g->n * kCmpRow * (wide ? 8 : 4)) + 255) & ~(size_t)255;
         const bool use_rows = rows <= room / 2;
         const size_t parts = (size_t)nhub + g->hub_layout[3] * (std::max<size_t>(1, g->hub_layout[4]) - 1);
         size_t nwg = std::min<size_t>((size_t)wgs, parts);
-        if (use_rows) nwg = std::max<size_t>(1, std::min(nwg, (room - rows) / wg_bytes));
+        nwg = std::max<size_t>(1, std::min(nwg, (use_rows ? room - rows : room) / wg_bytes));
         g->hub_layout[5] = nwg;
         g->hub_layout[6] = use_rows ? 1 + wide : 0;
         g->hub_layout[7] = use_rows ? rows : 0;
@@ -1411,6 +1581,7 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.rank_hi = rank_hi;
     // the compact rows come first, then the workgroups' scratch
     a.n = (uint32_t)g->n;
+    a.hash_below = g->hub_hash_below;
     a.cmp = k4 && g->hub_layout[6] ? g->hub_scratch : nullptr;
     a.cmp_wide = g->hub_layout[6] == 2;
     a.scratch = (uint32_t*)((char*)g->hub_scratch + g->hub_layout[7]);
@@ -1424,8 +1595,9 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     if (a.cmp) launch_fill_u64((uint64_t*)a.cmp, g->hub_layout[7] / 8, 0, st);
     // around[0] and around[1] bracket the hub path, around[2] marks the end of k_hub
     if (around) VDMC_HIP(hipEventRecord(around[0], st));
-    if (k4) hipLaunchKernelGGL((k_hub<true>), dim3(wgs), dim3(HT), 0, st, a);
-    else hipLaunchKernelGGL((k_hub<false>), dim3(wgs), dim3(HT), 0, st, a);
+    if (!k4) hipLaunchKernelGGL((k_hub<false, false>), dim3(wgs), dim3(HT), 0, st, a);
+    else if (g->hub_large) hipLaunchKernelGGL((k_hub<true, true>), dim3(wgs), dim3(HT), 0, st, a);
+    else hipLaunchKernelGGL((k_hub<true, false>), dim3(wgs), dim3(HT), 0, st, a);
     VDMC_HIP(hipGetLastError());
     if (around) VDMC_HIP(hipEventRecord(around[2], st));
     if (a.cmp) {

@@ -200,6 +200,8 @@ struct vdmc_graph_s {
     int32_t* ehi = nullptr;
     size_t hub_layout[16] = {0};
     size_t hub_split3 = 0;       // as hub_layout[3] when k = 3 alone is counted
+    bool hub_large = false;      // k = 4 takes the kernel whose cost does not grow with n
+    uint32_t hub_hash_below = 0; // its roots with fewer entries index depth-2 vertices by a hash
     // timing of the last count call: [0,1] around the per-set kernel, [2,3] around the
     // hub kernel (created at the first count)
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
