@@ -496,8 +496,7 @@ void launch_count(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out
         VDMC_HIP(hipEventRecord(g->ev[1], st));
         g->timed_light = true;
     }
-    launch_hub(g, k3, k4, out3, out4, st, lo, hi, g->ev + 2);
-    g->timed_hub = g->nhub > 0;
+    g->timed_hub = launch_hub(g, k3, k4, out3, out4, st, lo, hi, g->ev + 2);
 }
 
 void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {

@@ -1336,17 +1336,26 @@ __global__ void k_edge_hash(const uint32_t* __restrict__ off, const uint32_t* __
     }
 }
 
+// part of the ranks that holds rank r
+__host__ __device__ inline uint32_t rank_part(uint32_t r, uint32_t n) {
+    return (uint32_t)((unsigned long long)r * kRankParts / n);
+}
+
 // Per root, 16 lanes: the entries s2 of its slots' rows above it, its bin and sort key.  Hub
 // roots come first, largest estimated work first, then the light tiers.  tot: [0] largest s2
-// of a hub root, [1] largest |N+(r)| of all roots, [2..6] roots per bin (hubs, tiers 0..3).
+// of a hub root, [1] largest |N+(r)| of all roots, [2..6] roots per bin (hubs, tiers 0..3); by_rank:
+// s2 + 1 of the hub roots by kRankParts equal parts of the ranks, the sums, then the largest.
 __global__ __launch_bounds__(256) void k_root_work(const uint32_t* __restrict__ off, const uint32_t* __restrict__ adj,
                                                    const uint32_t* __restrict__ split,
                                                    const uint32_t* __restrict__ roots, int64_t nroots,
                                                    uint32_t hub_min, uint32_t hub_ok, uint32_t light_ok,
                                                    unsigned long long* __restrict__ wkey,
-                                                   unsigned long long* __restrict__ tot) {
+                                                   unsigned long long* __restrict__ tot,
+                                                   unsigned long long* __restrict__ by_rank, uint32_t n) {
     __shared__ unsigned long long sh[8];
+    __shared__ unsigned long long part[kRankParts], most[kRankParts];
     if (threadIdx.x < 8) sh[threadIdx.x] = 0ull;
+    part[threadIdx.x] = most[threadIdx.x] = 0ull;
     __syncthreads();
     const uint32_t gl = threadIdx.x & 15u;
     for (int64_t i = blockIdx.x * 16ll + threadIdx.x / 16; i < nroots; i += gridDim.x * 16ll) {
@@ -1365,10 +1374,18 @@ __global__ __launch_bounds__(256) void k_root_work(const uint32_t* __restrict__ 
         const unsigned long long dd = d;
         wkey[i] = hub ? ~(dd * (dd - 1) * (dd - 2) / 100 + 150 * s2 + 4) : ~0ull - 3ull + (unsigned long long)tier;
         atomicMax(&sh[1], dd);
-        if (hub) atomicMax(&sh[0], s2);
+        if (hub) {
+            atomicMax(&sh[0], s2);
+            atomicAdd(&part[rank_part(r, n)], s2 + 1ull);
+            atomicMax(&most[rank_part(r, n)], s2 + 1ull);
+        }
         atomicAdd(&sh[hub ? 2 : 3 + tier], 1ull);
     }
     __syncthreads();
+    if (part[threadIdx.x]) {
+        atomicAdd(&by_rank[threadIdx.x], part[threadIdx.x]);
+        atomicMax(&by_rank[kRankParts + threadIdx.x], most[threadIdx.x]);
+    }
     if (threadIdx.x < 2) atomicMax(&tot[threadIdx.x], sh[threadIdx.x]);
     else if (threadIdx.x < 7 && sh[threadIdx.x]) atomicAdd(&tot[threadIdx.x], sh[threadIdx.x]);
 }
@@ -1452,17 +1469,17 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     const uint32_t light_ok = g->max_deg < kLightMaxDegree ? 1u : 0u;
     unsigned long long* wkey = tmp.alloc<unsigned long long>(nr + 1);
     unsigned long long* wkey_s = tmp.alloc<unsigned long long>(nr + 1);
-    unsigned long long* d_tot = tmp.alloc<unsigned long long>(8);
+    unsigned long long* d_tot = tmp.alloc<unsigned long long>(8 + 2 * kRankParts);
     unsigned long long tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t nhub = 0;
     std::vector<unsigned long long> hub_keys;   // sorted work keys of the hub roots (~work)
     VDMC_HIP(hipMalloc(&g->hub_queue, 64 + (nr + 1) * sizeof(uint32_t)));   // the cursors, then the binned roots
     g->hubs = (uint32_t*)g->hub_queue + 16;
     if (nr > 0) {
-        launch_fill_u64((uint64_t*)d_tot, 8, 0, st);
+        launch_fill_u64((uint64_t*)d_tot, 8 + 2 * kRankParts, 0, st);
         const unsigned blocks = (unsigned)std::min<int64_t>((nr + 15) / 16, 16384);
         hipLaunchKernelGGL(k_root_work, dim3(blocks), dim3(256), 0, st, g->off, g->adj, g->split, g->roots, nr,
-                           (uint32_t)hub_min, hub_ok, light_ok, wkey, d_tot);
+                           (uint32_t)hub_min, hub_ok, light_ok, wkey, d_tot, d_tot + 8, (uint32_t)g->n);
         VDMC_HIP(hipGetLastError());
         // hub roots by work, then the tiers, each in rank order
         size_t sb = 0;
@@ -1477,6 +1494,7 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
             hub_keys.resize((size_t)nhub);
             VDMC_HIP(hipMemcpyAsync(hub_keys.data(), wkey_s, nhub * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                                     st));
+            VDMC_HIP(hipMemcpyAsync(g->hub_parts, d_tot + 8, sizeof(g->hub_parts), hipMemcpyDeviceToHost, st));
             VDMC_HIP(hipStreamSynchronize(st));
         }
         // Hub roots whose estimated work exceeds a fair share of the device (the total over
@@ -1554,9 +1572,22 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     g->bins_hub_min = hub_min;
 }
 
-void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t st,
+bool launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t st,
                 uint32_t rank_lo, uint32_t rank_hi, const hipEvent_t* around) {
-    if (g->nhub == 0) return;
+    if (g->nhub == 0) return false;
+    // s2 + 1 of the hub roots in the range, those of its first and last part by their share of its ranks
+    double work = 0.0;
+    unsigned long long most = 0;   // the largest of a root there
+    const uint32_t n = (uint32_t)g->n;
+    rank_hi = std::min(rank_hi, n);
+    for (uint64_t lo = rank_lo, hi; lo < rank_hi; lo = hi) {
+        const uint64_t p = rank_part((uint32_t)lo, n);
+        const uint64_t p0 = (p * n + kRankParts - 1) / kRankParts, p1 = ((p + 1) * n + kRankParts - 1) / kRankParts;
+        hi = std::min<uint64_t>(rank_hi, p1);
+        work += (double)g->hub_parts[p] * (double)(hi - lo) / (double)(p1 - p0);
+        most = std::max(most, g->hub_parts[kRankParts + p]);
+    }
+    if (work == 0.0) return false;
     ensure_hub_scratch(g);
     const ClassTables& t = class_tables();
     HubArgs a;
@@ -1580,9 +1611,13 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.rank_lo = rank_lo;
     a.rank_hi = rank_hi;
     // the compact rows come first, then the workgroups' scratch
-    a.n = (uint32_t)g->n;
+    a.n = n;
     a.hash_below = g->hub_hash_below;
-    a.cmp = k4 && g->hub_layout[6] ? g->hub_scratch : nullptr;
+    // rows are cleared and read for every vertex: not for a few small roots (Chung-Lu 1e6, 100 roots from
+    // rank 10000 on, 0.4 n entries: 1.71 ms with rows, 1.65 without; 500 roots, 2 n entries: 3.79 and
+    // 4.19; the root of rank 0 alone, 0.45 n entries: 515 and 532)
+    const bool rows = 2.0 * work >= (double)n || 16ull * most >= n;
+    a.cmp = k4 && g->hub_layout[6] && rows ? g->hub_scratch : nullptr;
     a.cmp_wide = g->hub_layout[6] == 2;
     a.scratch = (uint32_t*)((char*)g->hub_scratch + g->hub_layout[7]);
     a.wg_words = g->hub_layout[0];
@@ -1608,6 +1643,7 @@ void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
         VDMC_HIP(hipGetLastError());
     }
     if (around) VDMC_HIP(hipEventRecord(around[1], st));
+    return true;
 }
 
 }  // namespace vdmc

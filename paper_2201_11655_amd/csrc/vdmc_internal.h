@@ -155,6 +155,7 @@ struct DeviceScratch {
     size_t bytes = 0;
 };
 struct DoneEvent;
+constexpr int kRankParts = 256;   // parts of the ranks for which the hub roots' work is known on the host
 
 }  // namespace vdmc
 
@@ -200,6 +201,7 @@ struct vdmc_graph_s {
     int32_t* ehi = nullptr;
     size_t hub_layout[16] = {0};
     size_t hub_split3 = 0;       // as hub_layout[3] when k = 3 alone is counted
+    unsigned long long hub_parts[2 * vdmc::kRankParts] = {0};   // entries of hub roots by part of the ranks: sum, largest
     bool hub_large = false;      // k = 4 takes the kernel whose cost does not grow with n
     uint32_t hub_hash_below = 0; // its roots with fewer entries index depth-2 vertices by a hash
     // timing of the last count call: [0,1] around the per-set kernel, [2,3] around the
@@ -398,7 +400,8 @@ void ensure_edge_index(vdmc_graph_s* g, hipStream_t stream);   // edges.hip
 constexpr int64_t kEdgeSetsMaxN = 65536;   // bit planes of four waves in one workgroup's LDS
 void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // edges.hip
 void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // count.hip
-void launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t stream,
+// false: no hub root in the range, nothing launched
+bool launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4, hipStream_t stream,
                 uint32_t rank_lo = 0, uint32_t rank_hi = 0xFFFFFFFFu, const hipEvent_t* around = nullptr);
 void free_hub(vdmc_graph_s* g);
 // 5-vertex motifs (count5.hip)

@@ -115,3 +115,31 @@ def test_hub_scratch_does_not_grow_with_n(v):
     want = oracle.count(300 * 41, src, dst, 3)[0]
     assert (_np(out[:300 * 41]) == want).all()
     srv.close()
+
+
+def test_ranges_without_hub_roots(v):
+    """A range of ranks that holds no hub root launches no hub path (vdmc_kernel_times: -1), and ranges
+    of a few roots, a part of the ranks or none add up to the whole count."""
+    import torch
+    n, src, dst = _hub(100, 20, 1, 5)
+    for lone in (0, 100_000):
+        G = v.Graph(n + lone, src, dst)
+        want = v.count(G, 4)
+        off, adj, _ = G.export()
+        deg = np.diff(off)
+        hubs = [r for r in np.nonzero(deg >= 32)[0] if np.count_nonzero(adj[off[r]:off[r + 1]] >> 2 > r) >= 32]
+        assert hubs and want[:n].any()
+        out = torch.zeros_like(want)
+        first = 600                                  # past every hub root and its part of the ranks
+        assert max(hubs) < first - (n + lone) // 256
+        cuts = sorted([0, hubs[0] + 1, hubs[0] + 2, hubs[-1] + 1, first, first, n // 2, n + lone])
+        for lo, hi in zip(cuts[:-1], cuts[1:]):
+            v.count_range(G, 4, out, lo, hi, accumulate=True)
+            torch.cuda.synchronize()
+            ran = v.kernel_times(G)[1] >= 0
+            print(f"range {lo}..{hi} hub path {ran}", flush=True)
+            if lo >= first:
+                assert not ran, (lo, hi)
+            if any(lo <= h < hi for h in hubs):
+                assert ran, (lo, hi)
+        assert torch.equal(out, want), lone
