@@ -507,7 +507,13 @@ void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {
     if (g->pairs == 0) return;
     launch_fill_u64(out, (size_t)g->pairs * C, 0, st);
     if (g->nroots == 0) return;
-    if (g->ework) {   // up to kEdgeSetsMaxN vertices, and memory for it
+    // up to kEdgeSetsMaxN vertices, and memory for it.  Triples of a graph without larger rows are few:
+    // the per-set kernel is one launch for three (k = 3, G(n, p): 3000 vertices of degree 2, 46 us and 54;
+    // 65536 of degree 6, 1009 and 1078; 1e4 of degree 8, row of 21 entries, 221 and 223; 3e4 of degree
+    // 16, 1181 and 821).  So are the sets of a graph with many vertices of degree 0 or 1 (k = 4, 65536
+    // vertices of degree 1.2, 314 and 336 us; of degree 2, 666 and 664).
+    const bool few = g->max_deg <= 24 && (k == 3 || 4 * g->pairs < 3 * g->n);
+    if (g->ework && !few) {
         launch_edge_sets(g, k, out, st);
         g->timed_light = g->timed_hub = false;
         return;

@@ -9,12 +9,13 @@
 // does for vertices: by arc codes as if the members had only the arcs that the shape implies,
 // and then each set that has another arc is corrected.  The pair (r, a) takes the part of
 // the slot a there, (a, c) that of the child c, (c, e) that of the end vertex of a path; a
-// further pair gets only the corrected sets.  The arcs of r and of a are two bit planes in LDS
-// (2 n bytes a workgroup), so that testing an entry of c's row costs two LDS reads.
+// further pair gets only the corrected sets.  The arcs of r and of a are in LDS, as bit planes or
+// a hash (see Arcs), so that testing an entry of c's row costs two LDS reads.
 // What bounds it: the memory-side atomics on the pairs (a, c) and (c, e) (2.4e10 a second);
 // the pair (r, a) is summed in LDS.  Power-law graph of 3001 vertices, 20 k pairs, 25 M sets,
 // k = 4: 0.55 ms a call, 16.1 with the per-set kernel (count.hip, EdgeSink), which remains for
-// graphs of more vertices than the bit planes hold (kEdgeSetsMaxN).
+// graphs of more vertices (kEdgeSetsMaxN: what the planes' LDS and the cells' 16 bits hold) and for
+// k = 3 in graphs of small rows.
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
@@ -26,6 +27,7 @@ namespace vdmc {
 namespace {
 
 constexpr int ET = 256;
+constexpr int64_t kPlanesN = 8192;   // up to here the planes leave room for the 16 waves that registers allow
 
 unsigned blocks_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + ET - 1) / ET, 65536)); }
 
@@ -186,17 +188,47 @@ __device__ __forceinline__ void epair(uint32_t i, uint32_t& k, uint32_t& l) {
     k = i < 3u ? 1u : (i < 5u ? 2u : 3u);
     l = i < 3u ? i + 1u : (i < 5u ? i - 1u : 3u);
 }
-__device__ __forceinline__ uint32_t plane_bits(const uint2* p, uint32_t v) {
-    const uint2 w = p[v >> 5];
-    return ((w.x >> (v & 31u)) & 1u) | (((w.y >> (v & 31u)) & 1u) << 1);
-}
-__device__ __forceinline__ void plane_set(uint2* p, uint32_t ent) {
-    const uint32_t v = ent >> 2, bit = 1u << (v & 31u);
-    if (ent & 1u) atomicOr(&p[v >> 5].x, bit);
-    if (ent & 2u) atomicOr(&p[v >> 5].y, bit);
-}
+// The arcs of a pair's member to other vertices: two bit planes of n bits, or, HASH, cells of the
+// entries (epoch of the pair << 18 | vertex << 2 | code; a cell of another epoch is empty).  Planes are
+// one read a test, but at n = 65536 they leave a CU one workgroup, which is too few for rows of some
+// entries: G(n, p) of degree 2, k = 4, 769 us with planes, 664 with the hash; of degree 6 2007 and 1447;
+// Chung-Lu 3e4 16.1 and 15.3 ms.  (Epochs: a wave takes a pair in 8192 x 4, and rows that the hash
+// takes have fewer than 3072 entries, so at most 3073 of 16384.)
+template <bool HASH>
+struct Arcs {
+    uint2* planes;
+    uint32_t* cells;
+    uint32_t mask, epoch;
+    __device__ __forceinline__ uint32_t bits(uint32_t v) const {
+        if (HASH) {
+            for (uint32_t h = v * 2654435761u >> 15;; h++) {
+                const uint32_t x = cells[h & mask];
+                if ((x >> 18) != epoch) return 0u;
+                if (((x >> 2) & 0xFFFFu) == v) return x & 3u;
+            }
+        }
+        const uint2 w = planes[v >> 5];
+        return ((w.x >> (v & 31u)) & 1u) | (((w.y >> (v & 31u)) & 1u) << 1);
+    }
+    __device__ __forceinline__ void set(uint32_t ent) const {
+        const uint32_t v = ent >> 2;
+        if (HASH) {
+            for (uint32_t h = v * 2654435761u >> 15;; h++) {
+                uint32_t x = cells[h & mask];
+                while ((x >> 18) != epoch) {
+                    const uint32_t got = atomicCAS(&cells[h & mask], x, (epoch << 18) | ent);
+                    if (got == x) return;
+                    x = got;
+                }
+            }
+        }
+        const uint32_t bit = 1u << (v & 31u);
+        if (ent & 1u) atomicOr(&planes[v >> 5].x, bit);
+        if (ent & 2u) atomicOr(&planes[v >> 5].y, bit);
+    }
+};
 // A wave per upper entry (r, a), from the roots of the largest degrees on.
-template <bool K4>
+template <bool K4, bool HASH>
 __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
     constexpr uint32_t C = K4 ? (uint32_t)kClasses4 : (uint32_t)kClasses3;
     constexpr uint32_t NWV = ET / 64;
@@ -205,10 +237,15 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
     __shared__ unsigned long long rows[NWV][K4 ? 3 : 1][C];   // classes of (r, a); of a triangle's (r, b), (a, b)
     __shared__ uint8_t tab[K4 ? 4096 : 64];
     const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u, gl = tid & 7u;
-    uint2* PR = dyn + wid * 2u * A.words;   // arcs of r to its slots
-    uint2* PA = PR + A.words;               // arcs of a to the vertices above r
+    // per wave: arcs of r to its slots; k = 4: arcs of a to the vertices above r
+    constexpr uint32_t NT = K4 ? 2u : 1u;
+    uint2* const my = dyn + wid * NT * A.words;
+    Arcs<HASH> PR{my, (uint32_t*)my, 2u * A.words - 1u, 0u}, PA{my + A.words, (uint32_t*)(my + A.words), 2u * A.words - 1u, 0u};
     unsigned long long(&RA)[C] = rows[wid][0];
     for (uint32_t i = tid; i < (K4 ? 4096u : 64u); i += ET) tab[i] = A.tab[i];
+    // the planes are zero between two pairs: cleared here, then where a pair has set them
+    for (uint32_t i = lane; i < NT * A.words; i += 64) my[i] = make_uint2(0u, 0u);
+    for (uint32_t i = lane; i < C * (K4 ? 3u : 1u); i += 64) RA[i] = 0ull;
     __syncthreads();
     auto add = [&](uint32_t row, uint32_t cls, unsigned long long n) { gadd64(&A.out[(size_t)row * C + cls], n); };
     auto move = [&](uint32_t row, uint32_t was, uint32_t is) {
@@ -227,15 +264,14 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
     for (uint32_t u = blockIdx.x * NWV + wid; u < A.pairs; u += gridDim.x * NWV) {
         const uint32_t r = A.root_of[u], lo = A.split[r], rend = A.off[r + 1], t = lo + (u - A.uoff[r]);
         const uint32_t ent = A.adj[t], a = ent >> 2, ra = ent & 3u, alo = A.off[a], aend = A.off[a + 1];
-        for (uint32_t i = lane; i < A.words; i += 64) PR[i] = PA[i] = make_uint2(0u, 0u);
-        for (uint32_t i = lane; i < C * (K4 ? 3u : 1u); i += 64) RA[i] = 0ull;
+        if (HASH) PA.epoch = ++PR.epoch;
         wave_fence();
-        for (uint32_t i = lo + lane; i < rend; i += 64) plane_set(PR, A.adj[i]);
+        for (uint32_t i = lo + lane; i < rend; i += 64) PR.set(A.adj[i]);
         uint32_t abeg = aend;   // a's first entry above r
         for (bool more = true; more && abeg > alo;) {
             const uint32_t x = lane < abeg - alo ? A.adj[abeg - 1u - lane] : 0u;
             const bool in = (x >> 2) > r;
-            if (in) plane_set(PA, x);
+            if (K4 && in) PA.set(x);
             const uint32_t cnt = (uint32_t)__popcll(__ballot(in));
             abeg -= cnt;
             more = cnt == 64u;
@@ -280,7 +316,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
         // ---- a's row above r: children c, 8 lanes each; for k = 3 a lane per entry
         if (!K4) {
             for (uint32_t i = abeg + lane; i < aend; i += 64) {
-                const uint32_t x = A.adj[i], c = x >> 2, ac = x & 3u, rc = plane_bits(PR, c);
+                const uint32_t x = A.adj[i], c = x >> 2, ac = x & 3u, rc = PR.bits(c);
                 if (!rc) {
                     add(A.eid[i], tab[motif_index3(ra, 0u, ac)], 1ull);
                 } else if (c > a) {
@@ -294,7 +330,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
             for (uint32_t i0 = abeg; i0 < aend; i0 += 8) {
                 const uint32_t i = i0 + (lane >> 3);
                 const uint32_t x = i < aend ? A.adj[i] : 0u, c = x >> 2, ac = x & 3u;
-                const bool on = i < aend && !plane_bits(PR, c);
+                const bool on = i < aend && !PR.bits(c);
                 const uint32_t eac = on ? A.eid[i] : 0u, clo = on ? A.off[c] : 0u;
                 uint32_t e1 = 0, e2 = 0, e3 = 0;   // paths by their last arc
                 for (uint32_t q = on ? A.off[c + 1] : 0u; q > clo; q -= min(8u, q - clo)) {
@@ -302,7 +338,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
                     const uint32_t y = in ? A.adj[q - 1u - gl] : 0u, ece = in ? A.eid[q - 1u - gl] : 0u;
                     const uint32_t e = y >> 2, ce = y & 3u;
                     if (e > r && e != a) {
-                        const uint32_t re = plane_bits(PR, e), ae = plane_bits(PA, e);
+                        const uint32_t re = PR.bits(e), ae = PA.bits(e);
                         if (re) {          // (2,1,0) with the second slot e: from the lower parent of c
                             const uint32_t was = idx4(ra, re, 0u, 0u, ac, 0u), ere = row_of(r, e);
                             atomicAdd(&RA[was], kLess);
@@ -357,16 +393,16 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
             unsigned long long* AB = rows[wid][K4 ? 2 : 0];
             for (uint32_t i0 = abeg; i0 < aend; i0 += 64) {
                 const uint32_t x = i0 + lane < aend ? A.adj[i0 + lane] : 0u;
-                unsigned long long todo = __ballot((x >> 2) > a && plane_bits(PR, x >> 2));
+                unsigned long long todo = __ballot((x >> 2) > a && PR.bits(x >> 2));
                 for (; todo; todo &= todo - 1ull) {
                     const int src = __ffsll((long long)todo) - 1;
                     const uint32_t y = (uint32_t)__shfl((int)x, src, 64), b = y >> 2, ab = y & 3u;
-                    const uint32_t rb = plane_bits(PR, b);
+                    const uint32_t rb = PR.bits(b);
                     wave_fence();
                     for (uint32_t j = lo + lane; j < rend; j += 64) {
                         const uint32_t z = A.adj[j], c = z >> 2, rc = z & 3u;
                         if (c == a || c == b) continue;
-                        const uint32_t xa = plane_bits(PA, c);
+                        const uint32_t xa = PA.bits(c);
                         if (xa && c < b) continue;
                         const uint32_t xb = edge_code(A.table, A.bits, b, c);
                         if (xb && c < a) continue;
@@ -380,7 +416,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
                     }
                     for (uint32_t j = abeg + lane; j < aend; j += 64) {
                         const uint32_t z = A.adj[j], c = z >> 2, ac = z & 3u;
-                        if (plane_bits(PR, c) || edge_code(A.table, A.bits, b, c)) continue;
+                        if (PR.bits(c) || edge_code(A.table, A.bits, b, c)) continue;
                         const uint32_t was = idx4(ra, rb, 0u, 0u, ac, 0u), is = idx4(ra, rb, 0u, ab, ac, 0u);
                         lmove(RA, was, is);
                         lmove(RB, was, is);
@@ -390,7 +426,7 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
                     const uint32_t blo = A.off[b];
                     for (uint32_t j = A.off[b + 1]; j > blo; j -= min(64u, j - blo)) {
                         const uint32_t z = j - blo > lane ? A.adj[j - 1u - lane] : 0u, c = z >> 2, bc = z & 3u;
-                        if (c > r && !plane_bits(PR, c) && !plane_bits(PA, c)) {
+                        if (c > r && !PR.bits(c) && !PA.bits(c)) {
                             const uint32_t was = idx4(rb, ra, 0u, 0u, bc, 0u);
                             const uint32_t is = idx4(rb, ra, 0u, swap_arc_bits(ab), bc, 0u);
                             lmove(RA, was, is);
@@ -413,8 +449,16 @@ __global__ __launch_bounds__(ET) void k_edge_sets(EdgeArgs A) {
         }
         wave_fence();
         const uint32_t era = A.eid[t];
-        for (uint32_t k = lane; k < C; k += 64)
-            if (RA[k]) add(era, k, RA[k]);
+        for (uint32_t k = lane; k < C; k += 64) {
+            if (!RA[k]) continue;
+            add(era, k, RA[k]);
+            RA[k] = 0ull;
+        }
+        if (!HASH) {
+            for (uint32_t i = lo + lane; i < rend; i += 64) PR.planes[A.adj[i] >> 7] = make_uint2(0u, 0u);
+            if (K4)
+                for (uint32_t i = abeg + lane; i < aend; i += 64) PA.planes[A.adj[i] >> 7] = make_uint2(0u, 0u);
+        }
         wave_fence();
     }
     if (!K4) return;
@@ -520,10 +564,16 @@ void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t st) {
     a.tab = k == 3 ? t.t3 : t.t4;
     a.out = (unsigned long long*)out;
     a.stats = g->stats;
-    const size_t lds = (size_t)(ET / 64) * 2 * a.words * sizeof(uint2);
+    // cells for the longest row, three quarters full at most: two in the place of a plane's two words
+    uint32_t pairs_of_cells = 32;
+    while (3 * pairs_of_cells < 2 * (uint32_t)g->max_deg) pairs_of_cells <<= 1;
+    const bool hash = pairs_of_cells < a.words && n > kPlanesN;
+    if (hash) a.words = pairs_of_cells;
+    const size_t lds = (size_t)(ET / 64) * (k == 3 ? 1 : 2) * a.words * sizeof(uint2);
     const unsigned blocks = (unsigned)std::min<int64_t>((P + ET / 64 - 1) / (ET / 64), 8192);
     hipLaunchKernelGGL(k_edge_kids, dim3(blocks_of(P * 8)), dim3(ET), 0, st, a);
-    void (*kern)(EdgeArgs) = k == 3 ? k_edge_sets<false> : k_edge_sets<true>;
+    void (*kern)(EdgeArgs) = k == 3 ? (hash ? k_edge_sets<false, true> : k_edge_sets<false, false>)
+                                    : (hash ? k_edge_sets<true, true> : k_edge_sets<true, false>);
     VDMC_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (k == 3) hipLaunchKernelGGL((k_edge_roots<false>), dim3(blocks_of(n * 64)), dim3(ET), 0, st, a);
     else hipLaunchKernelGGL((k_edge_roots<true>), dim3(blocks_of(n * 64)), dim3(ET), 0, st, a);

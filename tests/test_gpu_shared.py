@@ -47,3 +47,42 @@ def test_two_handles_accumulate_into_one_output(v):
         v.count_range(B, 4, out, cut, n, accumulate=True, stream=sb)
         torch.cuda.synchronize()
         assert torch.equal(out, want), rep
+
+
+@pytest.mark.parametrize("n,deg,cap", [(8192, 1.5, 400), (8193, 1.5, 400), (8193, 1, 3), (20_000, 2, 40), (65_536, 1, 900),
+                                       (65_536, 1, 1500), (65_536, 0.6, 4)])
+def test_edge_layouts(v, n, deg, cap):
+    """Per-edge counts around the number of vertices from which a pair's arcs are held in a hash, with
+    rows that the hash or only the planes hold, and k = 3 around the row from which pairs are counted
+    in groups, against the oracle and the counts of the same graph."""
+    import oracle
+    _, src, dst = _fat(n, deg, cap, n + cap)
+    rng = np.random.default_rng(cap)
+    if cap <= 4:
+        src, dst = (rng.integers(0, n, int(n * deg)).astype(np.int32) for _ in range(2))
+    keep = rng.random(len(src)) < (0.15 if cap >= 900 else 1.0)    # the oracle's time
+    src, dst = src[keep], dst[keep]
+    G = v.Graph(n, src, dst)
+    lo, hi = v.edge_list(G)
+    for k in (3, 4):
+        print(f"edges n={n} deg={deg} cap={cap} k={k} max_deg={G.max_deg}", flush=True)
+        olo, ohi, want = oracle.count_edges(n, src, dst, k)
+        assert (lo == olo).all() and (hi == ohi).all()
+        import torch
+        got = v.count_edges(G, k)
+        torch.cuda.synchronize()
+        assert (got.cpu().numpy().view(np.uint64) == want).all(), k
+
+
+def test_edge_planes_of_the_largest_graph(v):
+    """A star of 1600 leaves in 65536 vertices: rows too long for the hash, bit planes of every vertex."""
+    import torch
+    n, d = 65_536, 1600
+    ids = np.random.default_rng(1).permutation(n)[:d + 1].astype(np.int32)
+    G = v.Graph(n, np.full(d, ids[0], np.int32), ids[1:])
+    for k, sets in ((3, d - 1), (4, (d - 1) * (d - 2) // 2)):
+        out = v.count_edges(G, k)
+        torch.cuda.synchronize()
+        rows = out.cpu().numpy()
+        col = np.flatnonzero(rows.any(axis=0))
+        assert len(col) == 1 and (rows[:, col[0]] == sets).all(), k
