@@ -179,7 +179,8 @@ vdmc_status vdmc_free_graph(vdmc_graph g);
  * k in {3, 4, 5}, other k INVALID_ARG.  k = 5 (n x 9364 output; n < 229,338): along the
  * eight BFS layer shapes of five vertices (vdmc_profile_counters).  Graphs of at most
  * 16384 vertices and 2^24 pairs count sets in groups; their first 5-vertex count builds an
- * item table of 8 (pairs + 2) bytes.  Larger ones go set by set, and their first 5-vertex
+ * item table of 8 (pairs + 2) bytes.  Larger ones, and those of more than 512 vertices with
+ * no degree above 4 that are paths and cycles or have 20000 pairs, go set by set; their first 5-vertex
  * count builds the graph's edge hash (2^ceil(log2(4 pairs)) 8-byte slots) and an
  * (n + 2) x 8-byte item table, synchronising `stream` once.  Both are kept with the
  * graph.  The first 5-vertex count on a device builds 4 MiB of class tables.  A graph
@@ -250,9 +251,9 @@ vdmc_status vdmc_kernel_times(vdmc_graph g, float* ms_out, int32_t n);
  * persistent launch whose work tiles come from a device-side cursor; the launch is
  * captured in a HIP graph the first time a batch signature (same graphs, same
  * outputs, same k) is seen and replayed afterwards.  Asynchronous on `stream`.
- * k = 5: every graph must satisfy vdmc_count_supported (else UNSUPPORTED).  Graphs of at
- * most 16384 vertices and 2^24 pairs are counted by one launch (those up to 512 vertices and the
- * rest by one each), larger ones one by one after it; not captured.
+ * k = 5: every graph must satisfy vdmc_count_supported (else UNSUPPORTED).  Graphs that
+ * vdmc_count counts in groups are counted by one launch (those up to 512 vertices and the
+ * rest by one each), the others one by one after it; not captured.
  */
 vdmc_status vdmc_count_batch(const vdmc_graph* gs, int32_t num, int32_t k,
                              uint64_t* const* outs, void* stream);

@@ -821,10 +821,12 @@ __global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
         if (tid == 0) sNext = atomicAdd(cursor, 1u);
         __syncthreads();
         uint32_t cur_r = kNone, cur_a = kNone;
+        bool any = false;
         for (;;) {
             const uint32_t item = sNext;
             const bool full = sUsed > hn / 8u * 5u;
             if (item >= nitems) break;
+            any = true;
             const uint2 it = A.items[G.first + item];
             const uint32_t r = it.x, r1 = G.off[r + 1], deg = r1 - G.off[r];
             const uint32_t t1 = min(r1, it.y + item_step(r1 - G.split[r], deg));
@@ -879,6 +881,7 @@ __global__ __launch_bounds__(BS) void k_five_sets(SetsArgs A, uint32_t hbits) {
             }
             __syncthreads();
         }
+        if (!any) continue;   // the graph's items were gone: no counters to give
         // the slot's counters to the graph's output
         __syncthreads();
         empty_hash();
@@ -1032,8 +1035,16 @@ struct FivePlan {
 std::mutex g_five_mu;
 std::vector<FivePlan*> g_five_plans;
 
-// whether k_five_sets takes the graph
-bool takes_sets(const vdmc_graph_s* g) { return g->n <= kFiveSetsMaxN && g->pairs <= kFiveSetsMaxPairs; }
+// whether k_five_sets takes the graph.  An item costs it some 30 ns (256 workgroups) however few sets
+// hang on it, the search set by set the time of its longest item, which grows with the degrees.  So
+// graphs of more than kDenseMaxN vertices go set by set if they are paths and cycles, and if no
+// degree is above 4 from 20000 pairs on (us set by set and in groups: path of 600 54 and 64, of 5000 114
+// and 276; binary tree of 16384 585 and 527; ladder of 16000, 24000 pairs, 461 and 1015; 128 x 128 grid
+// 1006 and 1784).
+bool takes_sets(const vdmc_graph_s* g) {
+    if (g->n > kFiveSetsMaxN || g->pairs > kFiveSetsMaxPairs) return false;
+    return g->n <= kDenseMaxN || g->max_deg > 4 || (g->max_deg > 2 && g->pairs < 20000);
+}
 
 // 5-vertex counts set by set over the graph in device memory: every workgroup of the grid takes
 // sub-items from one cursor and credits the caller's output with device-scope atomics.

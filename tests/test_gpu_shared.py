@@ -86,3 +86,37 @@ def test_edge_planes_of_the_largest_graph(v):
         rows = out.cpu().numpy()
         col = np.flatnonzero(rows.any(axis=0))
         assert len(col) == 1 and (rows[:, col[0]] == sets).all(), k
+
+
+@pytest.mark.parametrize("n,width,legs", [(512, 1, 0), (513, 1, 0), (5000, 1, 0), (13_000, 2, 0), (14_000, 2, 0),
+                                          (10_000, 100, 0), (10_200, 100, 0), (6000, 1, 1)])
+def test_five_low_degrees(v, n, width, legs):
+    """5-vertex counts of paths, ladders, grids and combs on both sides of the number of pairs from which
+    they are counted set by set, alone and beside another graph in a batch, against the oracle."""
+    import torch
+    import oracle
+    rng = np.random.default_rng(n)
+    i = np.arange(n - n % (width * (1 + legs)))
+    if legs:      # a comb: a path with a leg at every vertex
+        path, leg = i[i % 2 == 0], i[i % 2 == 1]
+        e = np.concatenate([np.stack([path[:-1], path[1:]], 1), np.stack([path, leg], 1)])
+    else:         # rows of `width` vertices
+        down = i[:-width]
+        e = np.stack([down, down + width], 1)
+        if width > 1:
+            right = i[i % width < width - 1]
+            e = np.concatenate([e, np.stack([right, right + 1], 1)])
+    flip = rng.random(len(e)) < 0.5
+    e[flip] = e[flip][:, ::-1]
+    e = np.concatenate([e, e[rng.random(len(e)) < 0.2][:, ::-1]]).astype(np.int32)
+    src, dst = e[:, 0].copy(), e[:, 1].copy()
+    want, tot = oracle.count(n, src, dst, 5)
+    G = v.Graph(n, src, dst)
+    H = v.Graph(60, rng.integers(0, 60, 200), rng.integers(0, 60, 200))
+    hb = v.count(H, 5).clone()
+    print(f"five low degrees n={n} width={width} legs={legs} pairs={G.pairs} max_deg={G.max_deg}", flush=True)
+    for outs in ([v.count(G, 5), hb], v.count_batch([G, H], 5)):
+        torch.cuda.synchronize()
+        assert (outs[0].cpu().numpy().view(np.uint64) == want).all()
+        assert sum(v.shape_counts5(G).values()) == int(tot.sum())
+        assert torch.equal(outs[1], hb)
