@@ -440,8 +440,10 @@ void launch_light(LightArgs a, int tier, int k3, int k4, hipStream_t st) {
     a.cmp_of = t.maps4 + 512;
     a.cmp_cls = t.cmp_cls;
     const int64_t cus = light_cus();
-    // few roots: four waves each, latency is what counts; many: a wave each
+    // few roots (a workgroup each in one go): four waves each, latency is what counts; many: a wave each
     const bool few = a.roots && a.nroots <= 4 * cus;
+    // as many workgroups as registers and LDS hold at once (8-slot kernel, 112 registers: four a compute
+    // unit; path of 2^20 vertices 1.78 ms with six, whose last two run alone, 1.43 with four)
     const auto grid = [&](int64_t roots_per_wg, int64_t wgs_per_cu) {
         return (unsigned)std::min<int64_t>((a.nroots + roots_per_wg - 1) / roots_per_wg, cus * wgs_per_cu);
     };
@@ -453,7 +455,7 @@ void launch_light(LightArgs a, int tier, int k3, int k4, hipStream_t st) {
     } else if (tier == 2) launch_one<256, 1, 32, 4096>(a, k3, grid(1, 2), st);
     else if (few) launch_one<256, 1, 32, 512>(a, k3, grid(1, 4), st);
     else if (tier == 1) launch_one<64, 4, 32, 512>(a, k3, grid(4, 2), st);
-    else launch_one<64, 4, 8, 128>(a, k3, grid(4, 6), st);
+    else launch_one<64, 4, 8, 128>(a, k3, grid(4, 4), st);
 }
 
 }  // namespace vdmc
