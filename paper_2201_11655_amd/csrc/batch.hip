@@ -46,7 +46,6 @@ struct Plan {
     unsigned small_grid = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipStream_t captured_for = nullptr;
     ~Plan() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
@@ -76,6 +75,17 @@ int num_cu() {
         g_num_cu = prop.multiProcessorCount;
     }
     return g_num_cu;
+}
+
+// the stream on which launches are captured, one per device, kept for the life of the process
+// (g_plan_mu is held)
+hipStream_t capture_stream() {
+    static std::map<int, hipStream_t> streams;
+    int dev = 0;
+    VDMC_HIP(hipGetDevice(&dev));
+    hipStream_t& s = streams[dev];
+    if (!s) VDMC_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+    return s;
 }
 
 BatchKey key_of(const vdmc_graph* gs, int num, int k) {
@@ -235,34 +245,28 @@ void run_plan(Plan& p, hipStream_t st, bool use_graph) {
     const int num = (int)p.graphs.size();
     GraphUse use(p.graphs, st);   // ordered after earlier work on these graphs
     const SmallArgs sa = small_args_of(p);
-    auto launch = [&] {
+    auto launch = [&](hipStream_t s) {
         launch_batch(args_of(p), &sa, p.small_grid, p.small_lds, p.cfg.small_variant, p.cfg.variant, k3, k4, num,
-                     p.cfg.wgs_per_cu, st);
+                     p.cfg.wgs_per_cu, s);
     };
     if (!use_graph || st == nullptr) {
-        launch();
+        launch(st);
     } else {
-        if (!p.exec || p.captured_for != st) {
-            if (p.exec) {
-                (void)hipGraphExecDestroy(p.exec);
-                p.exec = nullptr;
-            }
-            if (p.graph) {
-                (void)hipGraphDestroy(p.graph);
-                p.graph = nullptr;
-            }
-            VDMC_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
+        if (!p.exec) {
+            // captured on a stream of the library's own: while the caller's is in capture, no other
+            // stream may wait for an event recorded on it, as calls on this batch's graphs do
+            const hipStream_t cs = capture_stream();
+            VDMC_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
             try {
-                launch();
+                launch(cs);
             } catch (...) {
                 hipGraph_t g = nullptr;
-                (void)hipStreamEndCapture(st, &g);
+                (void)hipStreamEndCapture(cs, &g);
                 if (g) (void)hipGraphDestroy(g);
                 throw;
             }
-            VDMC_HIP(hipStreamEndCapture(st, &p.graph));
+            VDMC_HIP(hipStreamEndCapture(cs, &p.graph));
             VDMC_HIP(hipGraphInstantiate(&p.exec, p.graph, nullptr, nullptr, 0));
-            p.captured_for = st;
         }
         VDMC_HIP(hipGraphLaunch(p.exec, st));
     }

@@ -120,3 +120,99 @@ def test_five_low_degrees(v, n, width, legs):
         assert (outs[0].cpu().numpy().view(np.uint64) == want).all()
         assert sum(v.shape_counts5(G).values()) == int(tot.sum())
         assert torch.equal(outs[1], hb)
+
+
+def test_threads_with_graphs_of_different_sizes(v):
+    """Kernels whose LDS is sized for the graph, launched from several threads for different graphs at
+    once: every call succeeds and every count is that of the call alone."""
+    import threading
+    import torch
+    rng = np.random.default_rng(11)
+    jobs = []
+    for n, deg in ((300, 3.0), (7000, 1.5), (60, 4.0), (450, 6.0), (2500, 2.0), (700, 0.8)):
+        G = v.Graph(n, rng.integers(0, n, int(n * deg)), rng.integers(0, n, int(n * deg)))
+        jobs.append((G, lambda G, s: v.count_edges(G, 4, stream=s)))
+        jobs.append((G, lambda G, s: v.count_edges(G, 3, stream=s)))
+        if n <= 700:
+            jobs.append((G, lambda G, s: v.count_batch([G], 4, stream=s)[0]))
+            jobs.append((G, lambda G, s: v.count(G, 5, stream=s)))
+    want = []
+    for G, f in jobs:
+        want.append(f(G, None).clone())
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(t):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for rep in range(60):
+                i = (t * 5 + rep * (2 * t + 1)) % len(jobs)
+                try:
+                    got = f_run(i, s)
+                    s.synchronize()
+                    if not torch.equal(got, want[i]):
+                        bad.append((t, i, "counts differ"))
+                except v.VdmcError as e:
+                    bad.append((t, i, str(e)))
+
+    def f_run(i, s):
+        G, f = jobs[i]
+        return f(G, s)
+
+    ts = [threading.Thread(target=work, args=(t,)) for t in range(6)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad, bad[:5]
+
+
+def test_first_batches_beside_other_calls(v):
+    """A batch's first call captures its launches; calls on other streams for graphs whose last call was
+    on the batch's stream go on meanwhile."""
+    import threading
+    import torch
+    rng = np.random.default_rng(12)
+    G = v.Graph(200, rng.integers(0, 200, 600), rng.integers(0, 200, 600))
+    Hs = [v.Graph(300, rng.integers(0, 300, 900), rng.integers(0, 300, 900)) for _ in range(16)]
+    want_g, want_h = v.count(G, 4).clone(), [v.count(H, 3).clone() for H in Hs]
+    outs = [torch.empty_like(want_g) for _ in range(300)]
+    first = [torch.empty_like(w) for w in want_h]
+    torch.cuda.synchronize()
+    bad, done = [], threading.Event()
+
+    def batches():
+        s = torch.cuda.Stream()
+        try:
+            for o in outs:   # another output: another batch to capture
+                for H, f in zip(Hs, first):
+                    v.count(H, 3, f, stream=s)
+                v.count_batch([G], 4, outs=[o], stream=s)
+        except v.VdmcError as e:
+            bad.append(str(e))
+        done.set()
+
+    def others(part):
+        s = torch.cuda.Stream()
+        got = [torch.empty_like(w) for w in want_h]
+        torch.cuda.synchronize()
+        try:
+            while not done.is_set():
+                for i in list(part) * 8:
+                    v.count(Hs[i], 3, got[i], stream=s)
+                s.synchronize()
+            for i in part:
+                if not torch.equal(got[i], want_h[i]):
+                    bad.append(f"counts of graph {i} differ")
+        except v.VdmcError as e:
+            bad.append(str(e))
+
+    ts = [threading.Thread(target=batches)] + [threading.Thread(target=others, args=(range(k, 16, 3),)) for k in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    assert not bad, bad[:3]
+    for o in outs:
+        assert torch.equal(o, want_g)
