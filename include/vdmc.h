@@ -280,9 +280,10 @@ vdmc_status vdmc_init(void);
 vdmc_status vdmc_count_batch_noalloc(const vdmc_graph* gs, int32_t num, int32_t k, uint64_t* const* outs,
                                      void* stream);
 
-/* Picks the batch launch parameters (workgroup size of the whole-graph kernel; threads
- * per root, workgroups per CU and roots per cursor step of the root table) by timing
- * every candidate on the given batch (median of 3 runs).  The choice is kept for batches
+/* Picks the batch launch parameters (workgroup size of the whole-graph kernel; roots per
+ * cursor step of the root tables; threads per root and workgroups per CU of the per-set
+ * kernel) by timing every candidate that the batch's launches depend on (median of 3 runs);
+ * the others keep their defaults.  The choice is kept for batches
  * of the same shape (k, number of graphs, total vertices, total pairs) in this process
  * and appended to cache_path (NULL: memory only); a later process reads such a file when
  * VDMC_TUNE_CACHE names it.  Synchronous.  Results are bit-identical for every choice. */
@@ -290,8 +291,8 @@ vdmc_status vdmc_tune(const vdmc_graph* gs, int32_t num, int32_t k, const char* 
 
 /* The launch parameters vdmc_count_batch uses for a batch of this shape: choice_out[0] =
  * 1 if they come from the tuner (else the defaults), [1] threads per workgroup of the
- * whole-graph kernel, [2] threads per root, [3] workgroups per CU, [4] roots per cursor
- * step.  choice_out: 5 host int32.  Synchronous, no device work. */
+ * whole-graph kernel, [2] threads per root and [3] workgroups per CU of the per-set kernel,
+ * [4] roots per cursor step.  choice_out: 5 host int32.  Synchronous, no device work. */
 vdmc_status vdmc_tuned_choice(const vdmc_graph* gs, int32_t num, int32_t k, int32_t* choice_out);
 
 /*

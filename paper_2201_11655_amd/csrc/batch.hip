@@ -407,22 +407,30 @@ vdmc_status vdmc_tune(const vdmc_graph* gs, int32_t num, int32_t k, const char* 
         hipEvent_t e0, e1;
         VDMC_HIP(hipEventCreate(&e0));
         VDMC_HIP(hipEventCreate(&e1));
-        bool any_generic = false, any_small = false;
+        // what the batch has: graphs that one workgroup counts whole, roots in tables, among them roots
+        // of the per-set kernel (the light-root kernel's launches depend on the tile alone)
+        bool any_generic = false, any_small = false, any_set = false;
         for (int i = 0; i < num; i++) {
-            const bool sm = vdmc::small_eligible(gs[i]->n, 2 * gs[i]->pairs, k);
-            any_small |= sm;
-            any_generic |= !sm;
+            if (vdmc::small_eligible(gs[i]->n, 2 * gs[i]->pairs, k)) {
+                any_small = true;
+                continue;
+            }
+            std::lock_guard<std::mutex> lock(gs[i]->mu);
+            vdmc::ensure_bins(gs[i], st);
+            any_generic |= gs[i]->nlight > 0;
+            any_set |= gs[i]->ntier[3] > 0;
         }
-        // candidates: workgroup size of the whole-graph kernel; for the root table, threads
-        // per root, workgroups per CU and roots per cursor step (the median of 3 timed runs)
+        // candidates: workgroup size of the whole-graph kernel; roots per cursor step; threads per
+        // root and workgroups per CU of the per-set kernel (the median of 3 timed runs)
+        const vdmc::TuneChoice def;
         std::vector<vdmc::TuneChoice> cands;
         for (int sv = 0; sv < (any_small ? 3 : 1); sv++)
-            for (int variant = 0; variant < (any_generic ? vdmc::kBatchVariants : 1); variant++)
-                for (int wgs : any_generic ? std::vector<int>{2, 4, 8, 16} : std::vector<int>{8})
-                    for (unsigned tile : any_generic ? std::vector<unsigned>{1u, 4u, 16u} : std::vector<unsigned>{4u}) {
+            for (int variant = 0; variant < (any_set ? vdmc::kBatchVariants : 1); variant++)
+                for (int wgs : any_set ? std::vector<int>{2, 4, 8, 16} : std::vector<int>{def.wgs_per_cu})
+                    for (unsigned tile : any_generic ? std::vector<unsigned>{1u, 4u, 16u} : std::vector<unsigned>{def.tile}) {
                         vdmc::TuneChoice c;
-                        c.small_variant = any_small ? sv : 2;
-                        c.variant = variant;
+                        c.small_variant = any_small ? sv : def.small_variant;
+                        c.variant = any_set ? variant : def.variant;
                         c.wgs_per_cu = wgs;
                         c.tile = tile;
                         cands.push_back(c);

@@ -216,3 +216,29 @@ def test_first_batches_beside_other_calls(v):
     assert not bad, bad[:3]
     for o in outs:
         assert torch.equal(o, want_g)
+
+
+def test_tuner_leaves_what_no_launch_uses(v):
+    """Threads per root and workgroups per CU are the per-set kernel's: a batch without roots of its
+    keeps their defaults, and is counted as before tuning; one with such roots is tuned over all."""
+    import torch
+    rng = np.random.default_rng(13)
+    Gs = [v.Graph(n, rng.integers(0, n, 3 * n), rng.integers(0, n, 3 * n)) for n in (60, 1500, 1800)]
+    want = [o.clone() for o in v.count_batch(Gs, 3)]
+    before = v.tuned_choice(Gs, 3)
+    v.tune(Gs, 3)
+    after = v.tuned_choice(Gs, 3)
+    print(f"tuned {before} -> {after}", flush=True)
+    assert after["tuned"] and not before["tuned"]
+    for key in ("threads_per_root", "workgroups_per_cu"):
+        assert after[key] == before[key], key
+    star = v.Graph(1500, np.zeros(60, np.int32), np.arange(1, 61, dtype=np.int32))
+    v.set_hub_threshold(star, 1 << 30)      # 60 higher neighbours: neither the hub nor the light-root kernel's
+    with_star = Gs + [star]
+    want.append(v.count(star, 3).clone())
+    v.tune(with_star, 3)
+    for batch in (Gs, with_star):
+        got = v.count_batch(batch, 3)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
