@@ -207,7 +207,7 @@ const ClassTables& class_tables() {
     if (it != g_tables.end()) return *it->second;
     auto* t = new ClassTables();
     uint8_t* d = nullptr;
-    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 768 + 16 + 32 + kCmpRow));
+    VDMC_HIP(hipMalloc(&d, 64 + 4096 + 256 + 64 + 512 + 16 + kCmpRow));
     build_one<3>(d, t->host3, t->codes3);
     build_one<4>(d + 64, t->host4, t->codes4);
     t->t3 = d;
@@ -215,7 +215,7 @@ const ClassTables& class_tables() {
     // compact slots: classes of 4-sets whose G_U is a tree; with the set ordered
     // (v0, v1, v2, v3) and arc bits p_ij, a path v0-v1-v2-v3 has p01, p12, p23 != 0 and a
     // star centred at v1 has p01, p12, p13 != 0 (every other pair empty)
-    std::vector<uint8_t> slot(256, 0xFF), slotcls, star_of(256, 0xFF), path_of(256, 0xFF), star_cls, path_cls;
+    std::vector<uint8_t> slot(256, 0xFF), slotcls, star_of(256, 0xFF), star_cls;
     auto idx4 = [](unsigned p01, unsigned p02, unsigned p03, unsigned p12, unsigned p13, unsigned p23) {
         return ((p01 & 1u) << 11) | ((p01 >> 1) << 8) | ((p02 & 1u) << 10) | ((p02 >> 1) << 5) |
                ((p03 & 1u) << 9) | ((p03 >> 1) << 2) | ((p12 & 1u) << 7) | ((p12 >> 1) << 4) |
@@ -239,14 +239,6 @@ const ClassTables& class_tables() {
         star_of[stars[i]] = (uint8_t)i;
         star_cls.push_back((uint8_t)stars[i]);
     }
-    for (size_t i = 0; i < paths.size(); i++) {
-        path_of[paths[i]] = (uint8_t)i;
-        path_cls.push_back((uint8_t)paths[i]);
-    }
-    for (size_t i = 0; i < cycles.size(); i++) {   // the 4-cycle classes follow the path slots
-        path_of[cycles[i]] = (uint8_t)(paths.size() + i);
-        path_cls.push_back((uint8_t)cycles[i]);
-    }
     tree_classes = stars;
     tree_classes.insert(tree_classes.end(), paths.begin(), paths.end());
     std::sort(tree_classes.begin(), tree_classes.end());
@@ -269,21 +261,18 @@ const ClassTables& class_tables() {
     for (size_t i = 0; i < cycles.size(); i++) cmp_of[cycles[i]] = (uint8_t)(32 + i);
     for (int c = 0; c < 256; c++)
         if (cmp_of[c] != 0xFF) cmp_cls[cmp_of[c]] = (uint8_t)c;
-    // class -> star slot | path or 4-cycle slot | compact counter, then the inverse maps
+    // class -> star slot | compact counter, then the inverse maps
     std::vector<uint8_t> maps(star_of);
-    maps.insert(maps.end(), path_of.begin(), path_of.end());
     maps.insert(maps.end(), cmp_of.begin(), cmp_of.end());
     star_cls.resize(16, 0);
-    path_cls.resize(32, 0);
     maps.insert(maps.end(), star_cls.begin(), star_cls.end());
-    maps.insert(maps.end(), path_cls.begin(), path_cls.end());
     maps.insert(maps.end(), cmp_cls.begin(), cmp_cls.end());
     uint8_t* dm = d + 64 + 4096 + 256 + 64;
     VDMC_HIP(hipMemcpy(dm, maps.data(), maps.size(), hipMemcpyHostToDevice));
     t->maps4 = dm;
-    t->star_cls = dm + 768;
-    t->path_cls = dm + 784;
-    t->cmp_cls = dm + 816;
+    t->cmp_of = dm + 256;
+    t->star_cls = dm + 512;
+    t->cmp_cls = dm + 528;
     g_tables[dev] = t;   // kept for the life of the process
     return *t;
 }

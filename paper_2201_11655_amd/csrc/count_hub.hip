@@ -58,10 +58,8 @@ struct HubArgs {
     unsigned* cursor;            // root cursor
     const uint8_t* t3;
     const uint8_t* t4;
-    const uint8_t* maps;         // [0,256) class -> star slot, [256,512) class -> path or 4-cycle
-                                 // slot, [512,768) class -> compact counter (0xFF = none)
+    const uint8_t* maps;         // [0,256) class -> star slot, [256,512) class -> compact counter (0xFF = none)
     const uint8_t* star_cls;     // star slot -> class
-    const uint8_t* path_cls;     // path or 4-cycle slot -> class
     const uint8_t* cmp_cls;      // compact counter -> class
     unsigned long long* out3;
     unsigned long long* out4;
@@ -370,7 +368,7 @@ struct HubLds {
     unsigned long long root4[kClasses4];
     uint8_t t4[4096];
     uint8_t t3[64];
-    uint8_t maps[768];
+    uint8_t maps[512];
     uint32_t ctr[8];
     uint32_t seg[2];                   // first slot with arc code 2, 3 to r
     unsigned long long ends;           // entries in the rows of the depth-2 vertices (LARGE)
@@ -404,9 +402,9 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wid = wave_id();
     for (uint32_t i = tid; K4 && i < 4096; i += HT) L.t4[i] = A.t4[i];
     for (uint32_t i = tid; i < 64; i += HT) L.t3[i] = A.t3[i];
-    for (uint32_t i = tid; K4 && i < 768; i += HT) L.maps[i] = A.maps[i];
+    for (uint32_t i = tid; K4 && i < 512; i += HT) L.maps[i] = A.maps[i];
     const uint8_t* star_of = L.maps;
-    const uint8_t* cmp_of = L.maps + 512;
+    const uint8_t* cmp_of = L.maps + 256;
     uint32_t* S = A.scratch + (size_t)blockIdx.x * A.wg_words;
     uint32_t* locoff = S;                                        // DMAX + 2
     // rows: slot x has the words [locoff[x], locoff[x + 1]): its local entries from the
@@ -1345,6 +1343,7 @@ __host__ __device__ inline uint32_t rank_part(uint32_t r, uint32_t n) {
 // roots come first, largest estimated work first, then the light tiers.  tot: [0] largest s2
 // of a hub root, [1] largest |N+(r)| of all roots, [2..6] roots per bin (hubs, tiers 0..3); by_rank:
 // s2 + 1 of the hub roots by kRankParts equal parts of the ranks, the sums, then the largest.
+static_assert(kRankParts == 256, "a thread of k_root_work per part of the ranks");
 __global__ __launch_bounds__(256) void k_root_work(const uint32_t* __restrict__ off, const uint32_t* __restrict__ adj,
                                                    const uint32_t* __restrict__ split,
                                                    const uint32_t* __restrict__ roots, int64_t nroots,
@@ -1415,7 +1414,6 @@ void free_hub_scratch(vdmc_graph_s* g) {
     wait_graph(g);
     (void)hipFree(g->hub_scratch);
     g->hub_scratch = nullptr;
-    g->hub_scratch_bytes = 0;
 }
 
 void free_hub(vdmc_graph_s* g) {
@@ -1434,7 +1432,6 @@ size_t hub_scratch_need(const vdmc_graph_s* g) { return g->nhub > 0 ? g->hub_scr
 void ensure_hub_scratch(vdmc_graph_s* g) {
     if (g->nhub == 0 || g->hub_scratch) return;
     VDMC_HIP(hipMalloc(&g->hub_scratch, g->hub_scratch_need));
-    g->hub_scratch_bytes = g->hub_scratch_need;
 }
 
 void ensure_edge_hash(vdmc_graph_s* g, hipStream_t st) {
@@ -1461,10 +1458,12 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     const int hub_min = g->hub_min;
     if (g->bins_hub_min == hub_min) return;
     free_hub(g);   // waits for running work on the old bins
+    HubPlan& hub = g->hub = HubPlan();
     const int64_t nr = g->nroots;
     DeviceTemps tmp((size_t)nr * 40 + (1u << 20));
-    // the hub path needs every degree <= DMAX (a slot's children fit the LDS lists) and
-    // ranks below 2^26 (per-wave child hash keys)
+    // The hub path needs every degree <= DMAX (slot arrays; parents of a depth-2 vertex counted in
+    // 12 bits, pairs below a slot in 16; numbers of depth-2 vertices in 22) and ranks below 2^26 (its
+    // bitmap of them, at most 16 MiB a workgroup)
     const uint32_t hub_ok = (g->max_deg <= (int32_t)DMAX && g->n < ((int64_t)1 << 26)) ? 1u : 0u;
     const uint32_t light_ok = g->max_deg < kLightMaxDegree ? 1u : 0u;
     unsigned long long* wkey = tmp.alloc<unsigned long long>(nr + 1);
@@ -1494,13 +1493,13 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
             hub_keys.resize((size_t)nhub);
             VDMC_HIP(hipMemcpyAsync(hub_keys.data(), wkey_s, nhub * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                                     st));
-            VDMC_HIP(hipMemcpyAsync(g->hub_parts, d_tot + 8, sizeof(g->hub_parts), hipMemcpyDeviceToHost, st));
+            VDMC_HIP(hipMemcpyAsync(g->hub.parts, d_tot + 8, sizeof(g->hub.parts), hipMemcpyDeviceToHost, st));
             VDMC_HIP(hipStreamSynchronize(st));
         }
         // Hub roots whose estimated work exceeds a fair share of the device (the total over
         // twice the workgroups) would each be the critical path on one workgroup: the
         // leading ones of the queue (largest first) are shared by G workgroups, G from the
-        // heaviest root's excess, at most 8.  hub_layout[3] = how many, hub_layout[4] = G.
+        // heaviest root's excess, at most 8.
         if (nhub > 0) {
             double total = 0.0;
             for (unsigned long long k : hub_keys) total += (double)(~k);
@@ -1509,14 +1508,14 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
             while (h < hub_keys.size() && h < 4096 && (double)(~hub_keys[h]) > fair) h++;
             const double top = (double)(~hub_keys[0]);
             const uint32_t shares = fair > 0.0 ? (uint32_t)std::min(8.0, std::ceil(top / fair)) : 1u;
-            g->hub_layout[3] = shares >= 2 ? h : 0;
-            g->hub_layout[4] = shares >= 2 ? shares : 1;
+            hub.split_roots = shares >= 2 ? (uint32_t)h : 0u;
+            hub.shares = std::max(1u, shares);
             // k = 3 alone: staging is most of a root's work and sharing repeats it, so only roots
             // above kShareWork3 (some 400 slots) as well are shared.  R-MAT 2^12, three ranges:
             // 291 us, 347 with the line of k = 4, 364 without sharing.
             h = 0;
             while (h < hub_keys.size() && h < 4096 && (double)(~hub_keys[h]) > std::max(fair, kShareWork3)) h++;
-            g->hub_split3 = shares >= 2 ? h : 0;
+            hub.split_roots3 = shares >= 2 ? (uint32_t)h : 0u;
         }
     }
     const unsigned long long max_s2 = tot[0];
@@ -1525,8 +1524,6 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
     g->light = g->hubs + nhub;
     g->nlight = nr - nhub;
     for (int t = 0; t < 4; t++) g->ntier[t] = (int64_t)tot[3 + t];
-    g->max_scan2 = (int64_t)max_s2;
-    g->max_hi = maxhi;
     // light roots: fewer than hub_min higher neighbours (every root when the hub path is off)
     g->light_max_d = hub_ok ? std::min<int32_t>(maxhi, hub_min - 1) : maxhi;
     if (nhub > 0) {
@@ -1546,28 +1543,28 @@ void ensure_bins(vdmc_graph_s* g, hipStream_t st) {
         if (large && !hash_fits((size_t)maxhi, Index2<true>::slots((uint32_t)most)))
             index = std::max<size_t>(index, Index2<true>::slots((uint32_t)most));
         const size_t wg_words = (base + index + 63) & ~(size_t)63;
-        g->hub_large = large;
-        g->hub_hash_below = (uint32_t)hash_below;
-        g->hub_layout[0] = wg_words;
-        g->hub_layout[1] = s2cap;
-        // Workgroups (hub_layout[5]): one per compute unit, no more than there are roots and
-        // shares of roots.  Compact rows (hub_layout[6]: 0 none, 1 32-bit, 2 64-bit counters): a
-        // class of a vertex has at most 2 max_deg^3 paths or stars in a call, which 32 bits hold
-        // up to degree 1290.  Together they stay within the scratch of one workgroup per
-        // compute unit; graphs whose rows would take more than half of that go without.
+        hub.large = large;
+        hub.hash_below = (uint32_t)hash_below;
+        hub.wg_words = wg_words;
+        hub.s2cap = (uint32_t)s2cap;
+        // Workgroups: one per compute unit, no more than there are roots and shares of roots.
+        // Compact rows: a class of a vertex has at most 2 max_deg^3 paths or stars in a call, which
+        // 32 bits hold up to degree 1290.  Together they stay within the scratch of one workgroup
+        // per compute unit with its index in LDS; graphs whose rows would take more than half of that
+        // go without.
         const size_t wg_bytes = wg_words * sizeof(uint32_t);
         const size_t room = ((base + 60 + 63) & ~(size_t)63) * sizeof(uint32_t) * (size_t)wgs;
         const double dm = (double)g->max_deg;
         const int wide = 2.0 * dm * dm * dm >= 4294967296.0 ? 1 : 0;
         const size_t rows = (((size_t)g->n * kCmpRow * (wide ? 8 : 4)) + 255) & ~(size_t)255;
         const bool use_rows = rows <= room / 2;
-        const size_t parts = (size_t)nhub + g->hub_layout[3] * (std::max<size_t>(1, g->hub_layout[4]) - 1);
+        const size_t parts = (size_t)nhub + (size_t)hub.split_roots * (hub.shares - 1u);
         size_t nwg = std::min<size_t>((size_t)wgs, parts);
         nwg = std::max<size_t>(1, std::min(nwg, (use_rows ? room - rows : room) / wg_bytes));
-        g->hub_layout[5] = nwg;
-        g->hub_layout[6] = use_rows ? 1 + wide : 0;
-        g->hub_layout[7] = use_rows ? rows : 0;
-        g->hub_scratch_need = g->hub_layout[7] + wg_bytes * nwg;
+        hub.wgs = (uint32_t)nwg;
+        hub.row_bytes = use_rows ? rows : 0;
+        hub.row_wide = wide != 0;
+        g->hub_scratch_need = hub.row_bytes + wg_bytes * nwg;
     }
     g->bins_hub_min = hub_min;
 }
@@ -1584,8 +1581,8 @@ bool launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
         const uint64_t p = rank_part((uint32_t)lo, n);
         const uint64_t p0 = (p * n + kRankParts - 1) / kRankParts, p1 = ((p + 1) * n + kRankParts - 1) / kRankParts;
         hi = std::min<uint64_t>(rank_hi, p1);
-        work += (double)g->hub_parts[p] * (double)(hi - lo) / (double)(p1 - p0);
-        most = std::max(most, g->hub_parts[kRankParts + p]);
+        work += (double)g->hub.parts[p] * (double)(hi - lo) / (double)(p1 - p0);
+        most = std::max(most, g->hub.parts[kRankParts + p]);
     }
     if (work == 0.0) return false;
     ensure_hub_scratch(g);
@@ -1602,7 +1599,6 @@ bool launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.t4 = t.t4;
     a.maps = t.maps4;
     a.star_cls = t.star_cls;
-    a.path_cls = t.path_cls;
     a.cmp_cls = t.cmp_cls;
     a.out3 = (unsigned long long*)out3;
     a.out4 = (unsigned long long*)out4;
@@ -1612,26 +1608,26 @@ bool launch_hub(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out4,
     a.rank_hi = rank_hi;
     // the compact rows come first, then the workgroups' scratch
     a.n = n;
-    a.hash_below = g->hub_hash_below;
+    a.hash_below = g->hub.hash_below;
     // rows are cleared and read for every vertex: not for a few small roots (Chung-Lu 1e6, 100 roots from
     // rank 10000 on, 0.4 n entries: 1.71 ms with rows, 1.65 without; 500 roots, 2 n entries: 3.79 and
     // 4.19; the root of rank 0 alone, 0.45 n entries: 515 and 532)
     const bool rows = 2.0 * work >= (double)n || 16ull * most >= n;
-    a.cmp = k4 && g->hub_layout[6] && rows ? g->hub_scratch : nullptr;
-    a.cmp_wide = g->hub_layout[6] == 2;
-    a.scratch = (uint32_t*)((char*)g->hub_scratch + g->hub_layout[7]);
-    a.wg_words = g->hub_layout[0];
-    a.s2cap = (uint32_t)g->hub_layout[1];
-    const unsigned wgs = (unsigned)g->hub_layout[5];
+    a.cmp = k4 && g->hub.row_bytes && rows ? g->hub_scratch : nullptr;
+    a.cmp_wide = g->hub.row_wide;
+    a.scratch = (uint32_t*)((char*)g->hub_scratch + g->hub.row_bytes);
+    a.wg_words = g->hub.wg_words;
+    a.s2cap = g->hub.s2cap;
+    const unsigned wgs = g->hub.wgs;
     // the heaviest hub roots, shared (set at binning)
-    a.split_roots = (uint32_t)(k4 ? g->hub_layout[3] : g->hub_split3);
-    a.shares = (uint32_t)std::max<size_t>(1, g->hub_layout[4]);
+    a.split_roots = k4 ? g->hub.split_roots : g->hub.split_roots3;
+    a.shares = g->hub.shares;
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, g->hub_queue, 16);
-    if (a.cmp) launch_fill_u64((uint64_t*)a.cmp, g->hub_layout[7] / 8, 0, st);
+    if (a.cmp) launch_fill_u64((uint64_t*)a.cmp, g->hub.row_bytes / 8, 0, st);
     // around[0] and around[1] bracket the hub path, around[2] marks the end of k_hub
     if (around) VDMC_HIP(hipEventRecord(around[0], st));
     if (!k4) hipLaunchKernelGGL((k_hub<false, false>), dim3(wgs), dim3(HT), 0, st, a);
-    else if (g->hub_large) hipLaunchKernelGGL((k_hub<true, true>), dim3(wgs), dim3(HT), 0, st, a);
+    else if (g->hub.large) hipLaunchKernelGGL((k_hub<true, true>), dim3(wgs), dim3(HT), 0, st, a);
     else hipLaunchKernelGGL((k_hub<true, false>), dim3(wgs), dim3(HT), 0, st, a);
     VDMC_HIP(hipGetLastError());
     if (around) VDMC_HIP(hipEventRecord(around[2], st));

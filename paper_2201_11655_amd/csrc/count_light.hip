@@ -437,7 +437,7 @@ void launch_light(LightArgs a, int tier, int k3, int k4, hipStream_t st) {
     const ClassTables& t = class_tables();
     a.t3 = t.t3;
     a.t4 = t.t4;
-    a.cmp_of = t.maps4 + 512;
+    a.cmp_of = t.cmp_of;
     a.cmp_cls = t.cmp_cls;
     const int64_t cus = light_cus();
     // few roots (a workgroup each in one go): four waves each, latency is what counts; many: a wave each

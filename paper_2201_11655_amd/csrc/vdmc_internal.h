@@ -98,10 +98,9 @@ struct ClassTables {
     const uint8_t* t4;   // 4096 entries
     const uint8_t* slot4;     // 199 entries: class -> compact slot or 0xFF
     const uint8_t* slotcls;   // kCompact4 entries: compact slot -> class
-    const uint8_t* maps4;     // 768 entries: class -> star slot (10), path or 4-cycle slot (15 + 15), compact
-                              // counter; 0xFF none
+    const uint8_t* maps4;     // 512 entries: class -> star slot (10), then cmp_of; 0xFF none
+    const uint8_t* cmp_of;    // 256 entries: class -> compact counter
     const uint8_t* star_cls;  // 10 entries: star slot -> class
-    const uint8_t* path_cls;  // 30 entries: path or 4-cycle slot -> class
     const uint8_t* cmp_cls;   // kCmpRow entries: compact counter -> class
     std::vector<uint8_t> host3, host4;
     std::vector<uint16_t> codes3, codes4;
@@ -150,12 +149,23 @@ struct DeviceTemps {
     }
 };
 
-struct DeviceScratch {
-    void* ptr = nullptr;
-    size_t bytes = 0;
-};
 struct DoneEvent;
 constexpr int kRankParts = 256;   // parts of the ranks for which the hub roots' work is known on the host
+
+// How the hub path runs on a graph, set when its roots are binned
+struct HubPlan {
+    size_t wg_words = 0;           // scratch of a workgroup, in words
+    uint32_t s2cap = 0;            // entries of a root that it holds
+    uint32_t wgs = 0;              // workgroups
+    uint32_t split_roots = 0;      // the first roots of the queue ...
+    uint32_t split_roots3 = 0;     // ... and how many if k = 3 alone is counted ...
+    uint32_t shares = 1;           // ... are taken by this many workgroups each
+    size_t row_bytes = 0;          // compact rows, in front of the scratch; 0: none
+    bool row_wide = false;         // of 64-bit counters
+    bool large = false;            // k = 4 takes the kernel whose cost does not grow with n
+    uint32_t hash_below = 0;       // its roots with fewer entries index depth-2 vertices by a hash
+    unsigned long long parts[2 * kRankParts] = {0};   // entries of hub roots by part of the ranks: sum, largest
+};
 
 }  // namespace vdmc
 
@@ -185,12 +195,9 @@ struct vdmc_graph_s {
     int64_t ntier[4] = {0, 0, 0, 0};   // light-root kernel (three sizes), per-set kernel
     uint32_t* hubs = nullptr;    // roots handled by the hub kernel, largest work first
     int64_t nhub = 0;
-    int64_t max_scan2 = 0;       // largest depth-2 scan over hub roots (scratch sizing)
-    int32_t max_hi = 0;          // largest |N+(r)|
     int32_t light_max_d = 0;     // largest |N+(r)| among the light roots
     // hub-path scratch (per workgroup slices), sized for this graph
     void* hub_scratch = nullptr;
-    size_t hub_scratch_bytes = 0;
     unsigned* hub_queue = nullptr;   // root cursor
     size_t hub_scratch_need = 0;     // bytes of hub_scratch for the current bins
     unsigned long long* ehash = nullptr;   // edge hash: every pair of the graph, 2^ehash_bits slots
@@ -199,11 +206,7 @@ struct vdmc_graph_s {
     uint32_t* ework = nullptr;   // CSR entry -> row, scratch of k_edge_sets (up to kEdgeSetsMaxN vertices)
     int32_t* elo = nullptr;      // per output row: the pair's endpoints (original ids, lo < hi)
     int32_t* ehi = nullptr;
-    size_t hub_layout[16] = {0};
-    size_t hub_split3 = 0;       // as hub_layout[3] when k = 3 alone is counted
-    unsigned long long hub_parts[2 * vdmc::kRankParts] = {0};   // entries of hub roots by part of the ranks: sum, largest
-    bool hub_large = false;      // k = 4 takes the kernel whose cost does not grow with n
-    uint32_t hub_hash_below = 0; // its roots with fewer entries index depth-2 vertices by a hash
+    vdmc::HubPlan hub;               // how the hub path runs, for the current bins
     // timing of the last count call: [0,1] around the per-set kernel, [2,3] around the
     // hub kernel (created at the first count)
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};

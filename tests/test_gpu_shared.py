@@ -242,3 +242,30 @@ def test_tuner_leaves_what_no_launch_uses(v):
         torch.cuda.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("threshold", [32, 1 << 20])
+def test_every_graph_of_a_mixed_batch(v, threshold):
+    """Batches whose root tables hold roots of every size from several graphs: the counts and the shape
+    counters of each, also where a workgroup goes from one graph to the next and back, against the
+    oracle."""
+    import oracle
+    import torch
+    import test_gpu_routes as routes
+    roots = [routes._root(d, total - d, 7 * d + total) for d, total in
+             ((1, 3), (8, 96), (9, 60), (31, 384), (31, 385), (32, 3072), (33, 400))]
+    graphs = [_fat(1500, 3, 60, 1), routes._join(roots), routes._er(1100, 4, 2), routes._join(roots[::-1]),
+              _fat(2300, 2, 40, 3), routes._er(90, 3, 4)]
+    Gs = [v.Graph(*g) for g in graphs]
+    for G in Gs:
+        v.set_hub_threshold(G, threshold)
+    for k in (3, 4):
+        print(f"mixed batch k={k} threshold={threshold}", flush=True)
+        for rep in range(2):   # captured, then replayed
+            outs = v.count_batch(Gs, k) if rep == 0 else v.count_batch(Gs, k, outs=outs)
+            torch.cuda.synchronize()
+            for i, (g, G, o) in enumerate(zip(graphs, Gs, outs)):
+                want, tot = oracle.count(*g, k)
+                assert (o.cpu().numpy().view(np.uint64) == want).all(), (k, rep, i)
+                sc = list(v.shape_counts(G).values())
+                assert sum(sc[:2] if k == 3 else sc[2:]) == int(tot.sum()), (k, rep, i)
