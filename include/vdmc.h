@@ -5,8 +5,7 @@
  * 4 or 5, the number of connected k-vertex induced subgraphs ("k-motifs") that
  * contain v, split over the isomorphism classes of k-vertex weakly connected
  * digraphs (13 classes for k = 3, 199 for k = 4, 9364 for k = 5; 5-vertex motifs
- * are the extension Sec. 11 names, counted for graphs held whole in one
- * workgroup's LDS).
+ * are the extension Sec. 11 names).
  *
  * Definitions (paper: Levinas, Scherz, Louzoun, "BFS based distributed algorithm
  * for parallel local directed sub-graph enumeration"):
@@ -35,7 +34,8 @@
  *     count_range, count_undirected, count_edges, count_batch, served requests) is
  *     ordered after the previous call's on that graph, whatever its stream, so each
  *     output is that of the call alone.  Calls on different graphs overlap freely.
- *     Output buffers of calls in flight must not alias.
+ *     Output buffers of calls in flight must not alias (vdmc_count_range: unless all of
+ *     them accumulate).
  */
 #ifndef VDMC_H
 #define VDMC_H
@@ -158,8 +158,9 @@ vdmc_status vdmc_count_undirected(vdmc_graph g, int32_t k, uint64_t* out, void* 
  *     a graph builds the edge index (an edge hash of 2^ceil(log2(4 pairs)) 8-byte slots
  *     plus a 4-byte row per slot; up to 65536 vertices also 24 bytes per pair and 52 per
  *     vertex, if there is memory for them; kept with the graph) and synchronises
- *     `stream`.  Graphs with the latter count sets in groups, a wave per pair; others
- *     go through the per-set kernel, which credits the joined pairs of each set.
+ *     `stream`.  Graphs with the latter count sets in groups, a wave per pair; others, and
+ *     those with few sets (no degree above 24, and k = 3 or fewer than 3 n / 4 pairs), go
+ *     through the per-set kernel, which credits the joined pairs of each set.
  */
 vdmc_status vdmc_edge_list(vdmc_graph g, int32_t* lo, int32_t* hi);
 vdmc_status vdmc_count_edges(vdmc_graph g, int32_t k, uint64_t* out, void* stream);
@@ -206,8 +207,10 @@ int32_t vdmc_count_supported(vdmc_graph g, int32_t k);
  * independent; they are the unit the paper proposes for spreading the work over devices,
  * Sec. 11).  Without VDMC_ACCUMULATE, out is zeroed first; with it, the range's counts
  * are added to out, so consecutive ranges covering [0, n) give exactly vdmc_count's
- * result.  Ranks are those of the graph's degree order (vdmc_graph_export's perm maps
- * them to ids).  Asynchronous on `stream`. */
+ * result.  Every addition to out is atomic, so ranges counted through several handles of
+ * one graph may accumulate into one out from several streams.  Ranks are those of the
+ * graph's degree order (vdmc_graph_export's perm maps them to ids).  Asynchronous on
+ * `stream`. */
 vdmc_status vdmc_count_range(vdmc_graph g, int32_t k, uint64_t* out, int64_t rank_begin, int64_t rank_end,
                              uint32_t flags, void* stream);
 

@@ -455,7 +455,9 @@ void launch_count(vdmc_graph_s* g, int k3, int k4, uint64_t* out3, uint64_t* out
         l.rank_lo = lo;
         l.rank_hi = hi;
         l.roots = g->light;
-        // few roots in all: the first two tiers in one launch
+        // few roots in all: the first two tiers in one launch, with a workgroup per root (G(n, p) of 150
+        // vertices of degree 4, 43 us and 61 in two launches; of 1000 and degree 10, 109 and 121; 2000
+        // vertices of degree 10, whose roots are too many for a workgroup each, 209 and 195)
         const bool merge = g->ntier[0] + g->ntier[1] <= 1024;
         for (int t = !k4 ? 2 : (merge ? 1 : 0); t < 3; t++) {   // k = 3 alone: all three
             l.nroots = !k4 ? g->ntier[0] + g->ntier[1] + g->ntier[2]

@@ -51,7 +51,7 @@
 namespace vdmc {
 namespace {
 
-constexpr int64_t kFiveSetsMaxN = 16384;                       // bit planes of 3 + members in LDS (24 KiB)
+constexpr int64_t kFiveSetsMaxN = 16384;                       // bit planes of 9 members in LDS (36 KiB)
 constexpr int64_t kFiveSetsMaxPairs = (int64_t)1 << 24;        // item table of at most 128 MiB
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 // LDS counter slots per vertex: the 27 classes of 5-sets whose induced subgraph is a tree

@@ -10,20 +10,21 @@
 //
 //   * one workgroup (16 waves) per root; N+(r) (the "slots") is staged in LDS with a
 //     hash from rank to slot; each slot's neighbours among the slots become a short
-//     list; its entries above r outside N+(r) mark the depth-2 vertices in a bitmap,
-//     which numbers them in rank order, and the parents A(c) = N(c) n N+(r) of each are
-//     gathered into one run;
+//     list; its entries above r outside N+(r) mark the depth-2 vertices in an index (a
+//     bitmap over ranks or a hash) that numbers them, and the parents A(c) = N(c) n N+(r)
+//     of each are gathered into one run;
 //   * (3,0,0): 2-bit code rows over the slots, 32 slots a word; the group sizes are
 //     popcounts of two slots' rows (phase C4);
 //   * (2,1,0), (1,2,0) and (1,1,1): per slot a and child c of a, from the counts of the
 //     slots by code, of the other parents of c and of the vertices in c's row (phases D, E);
 //   * the end vertices of the (1,1,1) paths lie anywhere in the graph: each one that a
-//     root reaches is visited once, from its own row (phase G).
+//     root reaches is visited once, from its own row, or, where that would read much more
+//     than the paths, credited from the rows of the depth-2 vertices (phase G).
 // Credits of slots and of r are summed in LDS.  The others go to compact rows (kCmpRow
 // counters per vertex) a 64-byte line at a time, because the memory-side atomics (2.4e10
 // lines/s whatever the lanes add within a line) are what bounded a kernel that credited
 // set by set; k_expand adds the rows to the output.  Measured (one MI355X): Chung-Lu
-// n = 1e5, k = 3 and 4, 1.87e10 sets: 145 ms set by set, 43 ms in groups; R-MAT
+// n = 1e5, k = 3 and 4, 1.87e10 sets: 145 ms set by set, 37 ms in groups; R-MAT
 // n = 2^15, 1.6e10 sets: 212 ms and 25 ms.
 #include "motif_device.h"
 #include "vdmc_internal.h"
@@ -66,7 +67,7 @@ struct HubArgs {
     unsigned long long* stats;
     int k3;
     uint32_t rank_lo, rank_hi;   // only roots with rank in [rank_lo, rank_hi)
-    uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | pcount | bitmap
+    uint32_t* scratch;           // per workgroup: locoff | rows | parents | poff | cids | pcount | index
     size_t wg_words;
     uint32_t s2cap;
     uint32_t n;                  // vertices
@@ -394,7 +395,7 @@ __device__ __forceinline__ void build_row(uint32_t* row, const uint32_t* locnbr,
 // the other's spill, which a launch of some 40 us feels: R-MAT 2^10, five ranges, 271 -> 250 us.
 // LARGE (graphs whose bitmap of the depth-2 vertices is not in LDS for every root, or of more than
 // kHubSmallN vertices): no part of a root's cost grows with n unless its entries do, see Index2 and
-// kEndsDiv.  The other index and way of crediting end vertices take 9 registers more to spill.
+// kEndsDiv.  The other index and way of crediting end vertices take 6 registers more to spill.
 template <bool K4, bool LARGE>
 __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
     __shared__ HubLds L;
@@ -1166,7 +1167,8 @@ __global__ __launch_bounds__(HT) void k_hub(HubArgs A) {
         // ranks: marked in a bitmap from the rows of the depth-2 vertices, then 16 lanes per
         // end e walk e's row: its depth-2 neighbours c and their parents (pcount, by codes) are
         // its paths, parents adjacent to e included (phase E took those out).  Credited path by
-        // path instead, the ends alone would take a memory-side atomic per (1,1,1) set.
+        // path instead, the ends alone would take a memory-side atomic per (1,1,1) set.  LARGE, roots
+        // with few of them (kEndsDiv): from c's row, an atomic per e and code of c's parents.
         {
             constexpr uint32_t EB = G_EB, GW = 16 * EB, FIX = G_FIX;   // a group: 16 path counters per end vertex
             const bool in_lds = FIX + iw + G_WIN <= U_WORDS;
@@ -1370,6 +1372,9 @@ __global__ __launch_bounds__(256) void k_root_work(const uint32_t* __restrict__ 
         int tier = light_ok ? light_tier(d, s2) : 3;
         // hub path: from hub_min higher neighbours on, and roots too large for the light kernel
         const bool hub = hub_ok && d <= DMAX && (d >= hub_min || (tier == 3 && d <= 32u));
+        // work of a hub root, for the queue's order and for sharing: its triples of slots against its
+        // entries (these weighed 50 and 500: R-MAT 2^15 24.9 and 23.6 ms, Chung-Lu 1e5 36.8 and 36.5, now
+        // 24.8 and 36.6; the triples ten times as much: R-MAT 2^13 5.1 and 4.5 ms, Chung-Lu 1e5 38.8)
         const unsigned long long dd = d;
         wkey[i] = hub ? ~(dd * (dd - 1) * (dd - 2) / 100 + 150 * s2 + 4) : ~0ull - 3ull + (unsigned long long)tier;
         atomicMax(&sh[1], dd);

@@ -400,7 +400,7 @@ void ensure_hub_scratch(vdmc_graph_s* g);                 // caller holds g->mu
 void free_hub_scratch(vdmc_graph_s* g);                   // caller holds g->mu; waits for the graph's work
 void ensure_edge_hash(vdmc_graph_s* g, hipStream_t stream);    // count_hub.hip
 void ensure_edge_index(vdmc_graph_s* g, hipStream_t stream);   // edges.hip
-constexpr int64_t kEdgeSetsMaxN = 65536;   // bit planes of four waves in one workgroup's LDS
+constexpr int64_t kEdgeSetsMaxN = 65536;   // bit planes of four waves in one workgroup's LDS; 16-bit ids in its hash
 void launch_edge_sets(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // edges.hip
 void launch_count_edges(vdmc_graph_s* g, int k, uint64_t* out, hipStream_t stream);   // count.hip
 // false: no hub root in the range, nothing launched
